@@ -130,12 +130,26 @@ static int64_t decode_slots(const Geom& g, int64_t total) {
 }
 static int64_t decode_slots_max() { return device_cu_count() * (int64_t)4; }
 
+// Splits of a flat plan of the fp32 kernel: enough for one workgroup (eight wavefronts
+// that share the split's keys) per CU of an MI355X, and never more than
+// 4096 / (B Hq ceil(q / 64)), which bounds the per-split pairs a call keeps.
+static int64_t f32_splits_max(const Geom& g, int64_t q_len) {
+  const int64_t rows = (int64_t)g.G * q_len;
+  const int64_t tiles = (int64_t)g.B * g.Hkv * ceil_div(rows, f32_phase2_rows_per_workgroup(rows));
+  const int64_t fill = ceil_div(256, tiles), bound = ceil_div(4096, (int64_t)g.B * g.Hq * ceil_div(q_len, 64));
+  return fill < bound ? fill : bound;
+}
+constexpr int64_t F32_SPLIT_MIN = 128;     // keys: one 16-key unit for each of the eight wavefronts
+// Up to here one workgroup walks all keys of its rows and there is nothing to merge.
+constexpr int64_t F32_DIRECT_BYTES = 1 << 20;
+
 // Split plan for a phase-2 call with q_len new tokens that can see `total`
 // cache rows.  Decode-sized calls (G * q_len rows fit one 16-column MFMA tile)
 // stream the cache: without per-part outputs the keys of each (batch, KV head)
 // are cut into equal splits, one per resident workgroup; with per-part outputs
 // the splits respect block boundaries.  Larger calls are compute-bound and use
-// as few splits as still fill the GPU.
+// as few splits as still fill the GPU; fp32 calls ditto, in equal runs of keys when
+// no per-part outputs are asked for.
 static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bool want_parts,
                       SplitPlan* p) {
   Geom g = make_geom(s);
@@ -162,24 +176,34 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     p->s_total = (int32_t)ceil_div(total, split_len);
     return true;
   }
+  if (s->dtype == STAR_ATTN_F32 && !want_parts) {
+    int64_t splits = f32_splits_max(g, q_len);
+    if (splits > ceil_div(total, F32_SPLIT_MIN)) splits = ceil_div(total, F32_SPLIT_MIN);
+    if (total * g.d * 8 <= F32_DIRECT_BYTES) splits = 1;
+    p->flat = 1;
+    p->split_len = round_up(ceil_div(total, splits), 32);
+    p->spb = 0;
+    p->st = 0;
+    p->s_total = (int32_t)ceil_div(total, p->split_len);
+    return true;
+  }
   if (p->decode) {
     int64_t key_heads = g.cap * g.B * g.Hkv;
     int64_t want = ceil_div(key_heads, 2048);
     split_len = 256;
     while (split_len < want && split_len < 4096) split_len *= 2;
   } else {
-    int64_t wgs;   // workgroups per split
+    int64_t want, min_len;   // splits over all blocks that fill the GPU; keys worth a split
     if (s->dtype == STAR_ATTN_F32) {
-      wgs = (int64_t)g.B * g.Hq * ceil_div(q_len, 64);
+      want = f32_splits_max(g, q_len);
+      min_len = F32_SPLIT_MIN;
     } else {
-      wgs = (int64_t)g.B * g.Hkv * (g.G / flash_heads_per_workgroup(g.G)) *
-            ceil_div(q_len, flash_tokens_per_workgroup(g.G));
+      const int64_t wgs = (int64_t)g.B * g.Hkv * (g.G / flash_heads_per_workgroup(g.G)) *
+                          ceil_div(q_len, flash_tokens_per_workgroup(g.G));   // per split
+      want = ceil_div(256, wgs);                     // one workgroup per CU
+      min_len = 256;
     }
-    // one thread walks a whole split in the fp32 kernel, so short calls are cut
-    // much finer there (down to one 32-key LDS tile per split)
-    const int64_t min_len = s->dtype == STAR_ATTN_F32 ? 32 : 256;
-    const int64_t want_wgs = s->dtype == STAR_ATTN_F32 ? 4096 : 256;   // bf16: one workgroup per CU
-    int64_t spb = ceil_div(want_wgs, wgs * n);
+    int64_t spb = ceil_div(want, n);
     int64_t spb_max = bmax / min_len > 1 ? bmax / min_len : 1;
     if (spb > spb_max) spb = spb_max;
     if (spb < 1) spb = 1;
@@ -239,7 +263,9 @@ extern "C" {
 size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len) {
   if (validate_shape(shape) != STAR_ATTN_OK || max_q_len <= 0) return 0;
   // The plan depends on q_len only through the number of row tiles, so the
-  // largest requirement is found at tile boundaries and at max_q_len itself.
+  // largest requirement is found at tile boundaries and at max_q_len itself.  The
+  // fp32 kernel's tiles hold 32 / G tokens, which need not be a whole number: every
+  // q_len is looked at there, up to where one split per part fills the GPU.
   size_t best = 0;
   auto consider = [&](int64_t q) {
     if (q < 1 || q > max_q_len) return;
@@ -247,9 +273,10 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
       SplitPlan p;
       // the number of splits never exceeds what the full cache needs
       if (!make_plan(shape, q, shape->cache_capacity, parts != 0, &p)) continue;
-      if (p.flat) {   // a shorter cache may need one split more than the full one; bound it
+      if (p.flat) {   // a shorter cache may need more splits than the full one; bound them
         int64_t pairs = (int64_t)shape->batch * shape->n_kv_heads;
-        int64_t s0 = decode_slots_max() / pairs > 1 ? decode_slots_max() / pairs : 1;
+        int64_t s0 = p.decode ? (decode_slots_max() / pairs > 1 ? decode_slots_max() / pairs : 1)
+                              : f32_splits_max(make_geom(shape), q);
         if (p.s_total < s0) p.s_total = (int32_t)s0;
       }
       size_t b = plan_bytes(shape, p, q);
@@ -257,7 +284,11 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
     }
   };
   for (int64_t q = 1; q <= max_q_len && q <= 64; ++q) consider(q);
-  for (int64_t q = 64; q <= max_q_len; q += 32) { consider(q); consider(q + 1); }
+  if (shape->dtype == STAR_ATTN_F32) {
+    for (int64_t q = 65; q <= max_q_len && q <= 256 * 32; ++q) consider(q);
+  } else {
+    for (int64_t q = 64; q <= max_q_len; q += 32) { consider(q); consider(q + 1); }
+  }
   consider(max_q_len);
   return best;
 }
@@ -293,14 +324,14 @@ static int phase1_impl(const star_attn_shape* shape, int anchor_mode, const Rope
   const bool ext = (anchor_mode == STAR_ATTN_ANCHOR_EXTERNAL ||
                     anchor_mode == STAR_ATTN_ANCHOR_PER_BLOCK ||
                     anchor_mode == STAR_ATTN_ANCHOR_ALL_BLOCKS) && shape->anchor > 0;
-  // the fp32 kernel reads a head-major copy of the external anchor (workspace);
-  // the bf16 kernel reads the caller's tensors directly
-  const bool ext_copy = ext && shape->dtype == STAR_ATTN_F32;
+  // separately given anchors are read where the caller left them; the fp32 workspace
+  // stays a requirement of the call (star_attn_phase1_workspace_bytes) all the same
+  const bool ext_workspace = ext && shape->dtype == STAR_ATTN_F32;
   if (ext) {
     if (!K_anchor || !V_anchor) return STAR_ATTN_ERR_NULL_POINTER;
     if (misaligned(K_anchor) || misaligned(V_anchor)) return STAR_ATTN_ERR_MISALIGNED;
   }
-  if (ext_copy) {
+  if (ext_workspace) {
     if (!workspace) return STAR_ATTN_ERR_NULL_POINTER;
     if ((uintptr_t)workspace & 255u) return STAR_ATTN_ERR_MISALIGNED;
     if (workspace_bytes < 2 * anchor_copy_bytes(shape, anchor_mode))
@@ -342,40 +373,21 @@ static int phase1_impl(const star_attn_shape* shape, int anchor_mode, const Rope
     }
   } slot_release{ds, slot, st};
   // Algorithm 1: keep the K/V of every block once (anchor copies never exist here).
-  // The bf16 attention kernel reads plain inputs where they are and files them in
-  // the caches itself; rotated keys and the fp32 kernel go through the caches.
-  const bool fused_cache_write = shape->dtype == STAR_ATTN_BF16 && !rope;
-  if (fused_cache_write) {
-    // nothing to launch here
-  } else if (rope) {
-    if (launch_rope_rotate(shape->dtype, g.B, g.L, g.Hq, g.d, rope->pos0, rope->theta, Q, Q, st) !=
-            hipSuccess ||
-        launch_rope_cache_write(g, shape->dtype, K, K_cache, g.L, 0, rope->pos0, rope->theta, st) !=
-            hipSuccess ||
-        launch_cache_write(g, shape->dtype, nullptr, V, K_cache, V_cache, g.L, 0, st) != hipSuccess)
-      return STAR_ATTN_ERR_LAUNCH_FAILED;
-  } else if (launch_cache_write(g, shape->dtype, K, V, K_cache, V_cache, g.L, 0, st) != hipSuccess) {
+  // The attention kernels read plain inputs where they are and file them in the
+  // caches themselves; rotated keys go through the caches.
+  if (rope && (launch_rope_rotate(shape->dtype, g.B, g.L, g.Hq, g.d, rope->pos0, rope->theta, Q, Q, st) !=
+                   hipSuccess ||
+               launch_rope_cache_write(g, shape->dtype, K, K_cache, g.L, 0, rope->pos0, rope->theta, st) !=
+                   hipSuccess ||
+               launch_cache_write(g, shape->dtype, nullptr, V, K_cache, V_cache, g.L, 0, st) != hipSuccess))
     return STAR_ATTN_ERR_LAUNCH_FAILED;
-  }
   Phase1Args a;
   a.g = g; a.Q = Q; a.O = O_ctx; a.LSE = LSE_ctx; a.Kc = K_cache; a.Vc = V_cache;
   a.anchor_mode = anchor_mode; a.Ka = K_anchor; a.Va = V_anchor;
-  a.Kin = fused_cache_write ? K : nullptr;
-  a.Vin = fused_cache_write ? V : nullptr;
+  a.Kin = rope ? nullptr : K;
+  a.Vin = rope ? nullptr : V;
   a.tickets = tickets;
   a.n_cu = ds ? ds->n_cu : 0;
-  if (ext_copy) {
-    // the separately given anchors, head-major like the caches: [B, Hkv, n_anchor * a, d]
-    // (the [B, n_anchor, a, Hkv, d] input is [B, n_anchor * a, Hkv, d] token-major)
-    const int64_t rows = (anchor_mode == STAR_ATTN_ANCHOR_PER_BLOCK ? ceil_div(g.L, g.b) : 1) * g.a;
-    Geom ga = g;
-    ga.cap = rows;
-    char* wk = (char*)workspace;
-    char* wv = wk + anchor_copy_bytes(shape, anchor_mode);
-    if (launch_cache_write(ga, shape->dtype, K_anchor, V_anchor, wk, wv, rows, 0, st) != hipSuccess)
-      return STAR_ATTN_ERR_LAUNCH_FAILED;
-    a.Ka = wk; a.Va = wv;
-  }
   hipError_t e = shape->dtype == STAR_ATTN_F32 ? launch_phase1_f32(a, st) : launch_phase1_bf16(a, st);
   return e == hipSuccess ? STAR_ATTN_OK : STAR_ATTN_ERR_LAUNCH_FAILED;
 }
@@ -466,11 +478,10 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   hipStream_t st = (hipStream_t)hip_stream;
 
   // Algorithm 2: the new tokens' K/V join the cache before they attend.  The
-  // streaming decode kernel appends them itself (it reads the new rows from
-  // Kq/Vq and writes them to the cache); the other paths use the cache writer.
-  // Unrotated keys cannot take the fused route (the decode kernel moves rows with
-  // DMAs): they are rotated into the cache first.
-  const bool fused_append = append && shape->dtype == STAR_ATTN_BF16 && plan.decode && !rope;
+  // streaming decode kernel and the fp32 kernel append them themselves (they read the
+  // new rows from Kq/Vq and write them to the cache); the bf16 row-tiled kernel uses
+  // the cache writer.  Unrotated keys are rotated into the cache first.
+  const bool fused_append = append && !rope && (plan.decode || shape->dtype == STAR_ATTN_F32);
   if (!append) {
     // a context host's share: the cache is read as it is
   } else if (rope) {
@@ -496,11 +507,16 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   a.Vn = fused_append ? Vq : nullptr;
   a.O_sub = (float*)workspace;
   a.LSE_sub = (float*)workspace + rows * g.d;
+  const bool direct = shape->dtype == STAR_ATTN_F32 && plan.flat && plan.s_total == 1;
+  a.O = direct && !pair ? O : nullptr;
+  a.A = direct && pair ? A : nullptr;
+  a.LSE = direct && pair ? LSE : nullptr;
   hipError_t e;
   if (shape->dtype == STAR_ATTN_F32) e = launch_phase2_f32(a, st);
   else if (plan.decode) e = launch_phase2_decode_bf16(a, st);
   else e = launch_phase2_rows_bf16(a, st);
   if (e != hipSuccess) return STAR_ATTN_ERR_LAUNCH_FAILED;
+  if (direct) return STAR_ATTN_OK;
 
   MergeArgs m;
   m.g = g; m.plan = plan; m.q_len = (int32_t)q_len; m.out_bf16 = shape->dtype == STAR_ATTN_BF16;

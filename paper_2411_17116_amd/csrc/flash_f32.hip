@@ -1,227 +1,498 @@
-// fp32 path (head_dim 64 or 128): one thread owns one query row.
+// fp32 path (head_dim 64 or 128): row-tiled attention on the fp32 matrix
+// instructions, fp32 storage, products, sums and softmax throughout, so the result
+// stays within 1e-5 of an fp64 evaluation at the sizes this path is meant for.
 //
-// The row's query and output accumulator live in registers, K/V tiles of the
-// row tile's key ranges are staged through LDS and read as broadcasts, and the
-// online softmax (running maximum + rescaled sum) runs per thread with no
-// cross-lane traffic.  The same row routine serves phase 1 (Section 2.1: key
-// ranges = anchor + own block up to the row) and the phase-2 partial attention
-// of one split (Eq. 1-2: key range = the split, limited to the keys the token
-// may see).  Arithmetic is fp32 throughout so the result stays within 1e-5 of
-// an fp64 evaluation at the sizes this path is meant for.
+// What bounds it: the fp32 MFMA rate (157 TFLOP/s, 32 cycles for the 2048 flops of
+// v_mfma_f32_16x16x4_f32) for long key ranges, latency for short ones.  Both are
+// served by the same split:
+//   * A workgroup owns a tile of 16 NB query rows of one KV group, and its KW
+//     wavefronts share the tile's KEYS: wavefront w takes the 16-key units
+//     w, w + KW, ...  Nothing crosses wavefronts until the end, so there is no LDS
+//     and no barrier in the key loop, and a tile of few rows still has KW
+//     wavefronts' worth of loads and MFMAs in flight.
+//   * Rows are packed over the heads of a KV group (row = token * G + head in
+//     group), so that a K/V unit is read once for all of them.
+//   * S^T = K Q^T: lane (col = lane % 16, j4 = lane / 16) supplies K[col][16 t + 4 j4 + e]
+//     straight from a 16-byte global load (any assignment of d to (MFMA step, lane
+//     group) works as long as Q uses the same one) and receives keys 4 j4 + v of
+//     query row col.  Those are exactly the lanes that have to supply P^T in MFMA
+//     step v of O^T += V^T P^T, whose four keys are 4 j4 + v; V is loaded as
+//     256-byte row pieces, element e of a lane's 16 bytes being output row
+//     d = 64 h + 4 (lane % 16) + e of MFMA e.  So neither K, V nor P moves between lanes.
+//   * K of the next unit is requested once the scores of this one are done, V once
+//     its products are done: each load has half a unit of MFMAs (2048 cycles at
+//     NB = 2, d = 128) to arrive.
+//   * The KW partial results (O, m, l) of a row meet in LDS once, at the end.
+// Phase 1 reads K and V where the caller left them and files its own tokens' rows in
+// the caches; phase 2 reads the new tokens from the call's Kq / Vq and appends them.
+// Measured, whole calls, against a kernel of one thread per row: 8 / 2 heads, d = 128,
+// L = 4099, b = 1024, a = 512: 3390 -> 170 us (89 TFLOP/s); 1 head, d = 64, L = 1024,
+// b = a = 256: 274 -> 11.4 us.
 #include "star_internal.h"
 
 namespace star {
 
 namespace {
 
-constexpr int ROWS = 64;   // rows (threads) per workgroup
-constexpr int TK = 32;     // keys per LDS tile
-constexpr int CH = 8;      // keys per softmax update
-
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-template <int D>
-struct RowState {
-  float q[D];
-  float o[D];
-  float m;   // running maximum of the log2-domain logits
-  float l;   // running sum of 2^(logit - m)
+constexpr int UNIT = 16;   // keys per step of a wavefront
+constexpr float LOG2E = 1.4426950408889634f;
+constexpr float LN2 = 0.6931471805599453f;
+
+__device__ __forceinline__ float xor16(float x) {
+  return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401F));
+}
+__device__ __forceinline__ float xor32_max(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float xor32_sum(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// The keys a row tile walks: rows [a_lo, a_hi) of Ka / Va, visible to every row of
+// the tile, then keys [l_lo, l_hi), of which a row sees those below its own bound;
+// key k of the second range is row k - l_off of Kl / Vl.  Consecutive rows are
+// a_stride / l_stride floats apart.
+struct KeySeq {
+  const float* Ka;
+  const float* Va;
+  const float* Kl;
+  const float* Vl;
+  int64_t a_stride, l_stride;
+  int a_lo, a_hi, l_lo, l_hi, l_off;
+  int n_a, n_units;
+  __device__ __forceinline__ void count() {
+    n_a = (a_hi - a_lo + UNIT - 1) / UNIT;
+    n_units = n_a + (l_hi - l_lo + UNIT - 1) / UNIT;
+  }
 };
 
-// Attend the workgroup's rows to keys [lo, hi) of one KV head.  `limit` is this
-// thread's exclusive key bound (a key is visible iff key < limit).
-template <int D>
-__device__ __forceinline__ void attend_range(RowState<D>& st, const float* __restrict__ Kb,
-                                             const float* __restrict__ Vb, int64_t lo, int64_t hi,
-                                             int64_t limit, float* Ks, float* Vs) {
-  const int tid = threadIdx.x;
-  for (int64_t k0 = lo; k0 < hi; k0 += TK) {
-    __syncthreads();
-    // cooperative tile load, 16 bytes per thread per step; rows past `hi` are
-    // clamped to the last valid key (they are masked below)
-    constexpr int VPR = D / 4;
-    for (int v = tid; v < TK * VPR; v += ROWS) {
-      int r = v / VPR, c = v - r * VPR;
-      int64_t key = k0 + r < hi ? k0 + r : hi - 1;
-      ((f32x4*)Ks)[v] = *(const f32x4*)(Kb + key * D + c * 4);
-      ((f32x4*)Vs)[v] = *(const f32x4*)(Vb + key * D + c * 4);
-    }
-    __syncthreads();
-    for (int c0 = 0; c0 < TK; c0 += CH) {
-      if (k0 + c0 >= hi) break;
-      // two partial sums per logit, added at the end: chains of d/2 terms keep the
-      // rounding of a large logit (a planted pair reaches 25 in log2 units) down
-      float s[CH], s2[CH];
-#pragma unroll
-      for (int kk = 0; kk < CH; ++kk) s[kk] = s2[kk] = 0.f;
-#pragma unroll
-      for (int dd = 0; dd < D; dd += 4) {
-#pragma unroll
-        for (int kk = 0; kk < CH; ++kk) {
-          f32x4 kv = *(const f32x4*)(Ks + (c0 + kk) * D + dd);
-          s[kk] = __builtin_fmaf(st.q[dd], kv[0], s[kk]);
-          s2[kk] = __builtin_fmaf(st.q[dd + 1], kv[1], s2[kk]);
-          s[kk] = __builtin_fmaf(st.q[dd + 2], kv[2], s[kk]);
-          s2[kk] = __builtin_fmaf(st.q[dd + 3], kv[3], s2[kk]);
-        }
-      }
-#pragma unroll
-      for (int kk = 0; kk < CH; ++kk) s[kk] += s2[kk];
-      float cmax = -INFINITY;
-#pragma unroll
-      for (int kk = 0; kk < CH; ++kk) {
-        int64_t key = k0 + c0 + kk;
-        bool vis = key < hi && key < limit;
-        s[kk] = vis ? s[kk] : -INFINITY;
-        cmax = fmaxf(cmax, s[kk]);
-      }
-      float m_new = fmaxf(st.m, cmax);
-      if (m_new == -INFINITY) continue;            // nothing visible yet for this row
-      float alpha = exp2f(st.m - m_new);           // 0 when st.m == -inf
-      float p[CH];
-      float psum = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < CH; ++kk) {
-        p[kk] = exp2f(s[kk] - m_new);              // 0 for masked keys
-        psum += p[kk];
-      }
-      st.l = st.l * alpha + psum;
-      st.m = m_new;
-#pragma unroll
-      for (int dd = 0; dd < D; dd += 4) {
-        f32x4 acc = {st.o[dd] * alpha, st.o[dd + 1] * alpha, st.o[dd + 2] * alpha,
-                     st.o[dd + 3] * alpha};
-#pragma unroll
-        for (int kk = 0; kk < CH; ++kk) {
-          f32x4 vv = *(const f32x4*)(Vs + (c0 + kk) * D + dd);
-          acc[0] = __builtin_fmaf(p[kk], vv[0], acc[0]);
-          acc[1] = __builtin_fmaf(p[kk], vv[1], acc[1]);
-          acc[2] = __builtin_fmaf(p[kk], vv[2], acc[2]);
-          acc[3] = __builtin_fmaf(p[kk], vv[3], acc[3]);
-        }
-        st.o[dd] = acc[0]; st.o[dd + 1] = acc[1]; st.o[dd + 2] = acc[2]; st.o[dd + 3] = acc[3];
-      }
-    }
-  }
-}
+// A wavefront's state.  Lane (col, j4) belongs to row col of each of NB 16-row blocks.
+template <int D, int NB>
+struct RowState {
+  f32x4 q[NB][D / 16];        // q[.][t][e] = Q[row][16 t + 4 j4 + e] * scale * log2(e)
+  f32x4 o[NB][D / 64][4];     // o[.][h][e][w] = O[row][64 h + 16 j4 + 4 w + e]
+  float m[NB], l[NB];         // running maximum (log2 units; uniform over a row's four lanes) and
+                              // this lane's share of the sum of 2^(s - m)
+};
 
 template <int D>
-__device__ __forceinline__ void load_row(RowState<D>& st, const float* q, bool active, float qk_scale) {
-#pragma unroll
-  for (int dd = 0; dd < D; dd += 4) {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (active) v = *(const f32x4*)(q + dd);
-    st.q[dd] = v[0] * qk_scale; st.q[dd + 1] = v[1] * qk_scale;
-    st.q[dd + 2] = v[2] * qk_scale; st.q[dd + 3] = v[3] * qk_scale;
-    st.o[dd] = st.o[dd + 1] = st.o[dd + 2] = st.o[dd + 3] = 0.f;
-  }
-  st.m = -INFINITY;
-  st.l = 0.f;
-}
+struct Unit {
+  f32x4 k[D / 16];
+  f32x4 v[4][D / 64];
+};
 
-template <int D>
-__device__ __forceinline__ void store_row(const RowState<D>& st, float* o, float* lse) {
-  float inv = st.l > 0.f ? 1.f / st.l : 0.f;
-#pragma unroll
-  for (int dd = 0; dd < D; dd += 4) {
-    f32x4 v = {st.o[dd] * inv, st.o[dd + 1] * inv, st.o[dd + 2] * inv, st.o[dd + 3] * inv};
-    *(f32x4*)(o + dd) = v;
-  }
-  if (lse) *lse = st.l > 0.f ? (st.m + log2f(st.l)) * 0.6931471805599453f : -INFINITY;
-}
-
-constexpr float LOG2E = 1.4426950408889634f;
-
-// grid: x = block index * tiles_per_block + tile in block, y = query head, z = batch
-template <int D>
-__global__ __launch_bounds__(ROWS) void phase1_f32_kernel(Phase1Args a, int tiles_per_block) {
-  __shared__ __attribute__((aligned(16))) float Ks[TK * D];
-  __shared__ __attribute__((aligned(16))) float Vs[TK * D];
-  const Geom& g = a.g;
-  int i = blockIdx.x / tiles_per_block, t = blockIdx.x % tiles_per_block;
-  int h = blockIdx.y, beta = blockIdx.z;
-  int64_t s = (int64_t)i * g.b;
-  int64_t e = s + g.b < g.L ? s + g.b : g.L;
-  int64_t row0 = s + (int64_t)t * ROWS;
-  if (row0 >= e) return;                              // tile beyond a short last block
-  int64_t p = row0 + threadIdx.x;
-  bool active = p < e;
-  int kvh = h / g.G;
-  const float* Kb = (const float*)a.Kc + ((int64_t)beta * g.Hkv + kvh) * g.cap * D;
-  const float* Vb = (const float*)a.Vc + ((int64_t)beta * g.Hkv + kvh) * g.cap * D;
-  RowState<D> st;
-  load_row<D>(st, (const float*)a.Q + (((int64_t)beta * g.L + (active ? p : row0)) * g.Hq + h) * D,
-              active, g.scale * LOG2E);
-  int64_t limit = active ? p + 1 : 0;
-  int64_t last = row0 + ROWS < e ? row0 + ROWS : e;   // exclusive bound of the tile's rows
-  int64_t a_lo, a_hi;                                              // anchor: fully visible
-  if (anchor_range(g, a.anchor_mode, i, &a_lo, &a_hi)) {
-    const int64_t anchor_rows = (a.anchor_mode == ANCHOR_PER_BLOCK ? (g.L + g.b - 1) / g.b : 1) * g.a;
-    const float* Kab = (const float*)a.Ka + ((int64_t)beta * g.Hkv + kvh) * anchor_rows * D;
-    const float* Vab = (const float*)a.Va + ((int64_t)beta * g.Hkv + kvh) * anchor_rows * D;
-    // rows of the anchor buffer are not positions: every one is visible
-    attend_range<D>(st, Kab, Vab, a_lo, a_hi, active ? a_hi : 0, Ks, Vs);
+// Where unit u starts: its first row's address offset, and how many of its rows exist.
+struct UnitAt {
+  const float* K;
+  const float* V;
+  int64_t stride;
+  int row0, n_rows;           // rows row0 .. row0 + min(16, n_rows) - 1 of K / V
+  int key0;
+  bool local;
+};
+__device__ __forceinline__ UnitAt unit_at(const KeySeq& seq, int u) {
+  UnitAt x;
+  x.local = u >= seq.n_a;
+  if (!x.local) {
+    x.key0 = seq.a_lo + u * UNIT;
+    x.row0 = x.key0;
+    x.n_rows = seq.a_hi - x.key0;
+    x.K = seq.Ka; x.V = seq.Va; x.stride = seq.a_stride;
   } else {
-    attend_range<D>(st, Kb, Vb, a_lo, a_hi, limit, Ks, Vs);
+    x.key0 = seq.l_lo + (u - seq.n_a) * UNIT;
+    x.row0 = x.key0 - seq.l_off;
+    x.n_rows = seq.l_hi - x.key0;
+    x.K = seq.Kl; x.V = seq.Vl; x.stride = seq.l_stride;
   }
-  attend_range<D>(st, Kb, Vb, s, last, limit, Ks, Vs);             // own block, causal
-  if (active) {
-    float* o = (float*)a.O + (((int64_t)beta * g.L + p) * g.Hq + h) * D;
-    float* lse = a.LSE ? a.LSE + ((int64_t)beta * g.Hq + h) * g.L + p : nullptr;
-    store_row<D>(st, o, lse);
+  return x;
+}
+
+// Rows past the range's end re-read its last row (their scores are masked).
+template <int D>
+__device__ __forceinline__ void load_k(Unit<D>& r, const UnitAt& x, int lane) {
+  int i = lane & 15;
+  i = i < x.n_rows ? i : x.n_rows - 1;
+  const float* p = x.K + (int64_t)(x.row0 + i) * x.stride + 4 * (lane >> 4);
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t) r.k[t] = *(const f32x4*)(p + 16 * t);
+}
+template <int D>
+__device__ __forceinline__ void load_v(Unit<D>& r, const UnitAt& x, int lane) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    int i = 4 * (lane >> 4) + v;
+    i = i < x.n_rows ? i : x.n_rows - 1;
+    const float* p = x.V + (int64_t)(x.row0 + i) * x.stride + 4 * (lane & 15);
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h) r.v[v][h] = *(const f32x4*)(p + 64 * h);
   }
 }
 
-// grid: x = (batch * s_total + split) * row_tiles + row tile, y = query head
-template <int D>
-__global__ __launch_bounds__(ROWS) void phase2_f32_kernel(Phase2Args a, int row_tiles) {
-  __shared__ __attribute__((aligned(16))) float Ks[TK * D];
-  __shared__ __attribute__((aligned(16))) float Vs[TK * D];
-  const Geom& g = a.g;
-  int h = blockIdx.y;
-  int bs = blockIdx.x / row_tiles;
-  int beta = bs / a.plan.s_total, s = bs % a.plan.s_total;
-  int j = (blockIdx.x % row_tiles) * ROWS + threadIdx.x;
-  bool active = j < a.q_len;
-  int64_t total = visible_total(a);
-  int64_t lo, hi;
-  split_range(a.plan, g.L, g.b, total, s, &lo, &hi);
-  int kvh = h / g.G;
-  const float* Kb = (const float*)a.Kc + ((int64_t)beta * g.Hkv + kvh) * g.cap * D;
-  const float* Vb = (const float*)a.Vc + ((int64_t)beta * g.Hkv + kvh) * g.cap * D;
-  RowState<D> st;
-  load_row<D>(st, (const float*)a.Qq + (((int64_t)beta * a.q_len + (active ? j : 0)) * g.Hq + h) * D,
-              active, g.scale * LOG2E);
-  int64_t limit = active ? visible_limit(a, j) : 0;
-  attend_range<D>(st, Kb, Vb, lo, hi, limit, Ks, Vs);
-  if (active) {
-    int64_t r = (((int64_t)beta * a.plan.s_total + s) * g.Hq + h) * a.q_len + j;
-    store_row<D>(st, a.O_sub + r * D, a.LSE_sub + r);
+// Attend the wavefront's rows to units first, first + step, ... of the sequence.
+//   row_lim   this lane's exclusive bound on keys of the second range, per row block
+//   wave_lim  smallest bound of the wavefront's live rows
+template <int D, int NB>
+__device__ __forceinline__ void attend(RowState<D, NB>& w, const KeySeq& seq, int first, int step,
+                                       const int (&row_lim)[NB], int wave_lim, int lane) {
+  if (first >= seq.n_units) return;
+  const int j4 = lane >> 4;
+  Unit<D> r;
+  UnitAt cur = unit_at(seq, first);
+  load_k<D>(r, cur, lane);
+  load_v<D>(r, cur, lane);
+  for (int u = first;;) {
+    const int un = u + step;
+    const bool more = un < seq.n_units;
+    const UnitAt nxt = unit_at(seq, more ? un : u);
+    // two chains per score tile (d split by parity): half the rounding of one chain of d terms
+    f32x4 s[NB];
+    {
+      f32x4 s0[NB], s1[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) s0[b] = s1[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < D / 16; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) {
+            s0[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][e], w.q[b][t][e], s0[b], 0, 0, 0);
+            s1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][e + 1], w.q[b][t][e + 1], s1[b], 0, 0, 0);
+          }
+#pragma unroll
+      for (int b = 0; b < NB; ++b) s[b] = s0[b] + s1[b];
+    }
+    if (more) load_k<D>(r, nxt, lane);
+    if (cur.n_rows < UNIT || (cur.local && cur.key0 + UNIT > wave_lim)) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int room = row_lim[b] - cur.key0;
+        const int n = (cur.local && room < cur.n_rows ? room : cur.n_rows) - 4 * j4;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s[b][v] = v < n ? s[b][v] : -INFINITY;
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      float t = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
+      t = xor32_max(fmaxf(t, xor16(t)));
+      if (__builtin_amdgcn_ballot_w64(t > w.m[b]) != 0) {      // some row's maximum moved
+        const float m_new = fmaxf(w.m[b], t);
+        const float mm = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(w.m[b] - mm);   // 0 while nothing was visible
+        w.m[b] = m_new;
+        w.l[b] *= alpha;
+#pragma unroll
+        for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w.o[b][h][e] *= alpha;
+      }
+      const float mm = w.m[b] == -INFINITY ? 0.f : w.m[b];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s[b][v] = __builtin_amdgcn_exp2f(s[b][v] - mm);
+      w.l[b] += (s[b][0] + s[b][1]) + (s[b][2] + s[b][3]);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+            w.o[b][h][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.v[v][h][e], s[b][v], w.o[b][h][e], 0, 0, 0);
+    if (!more) break;
+    load_v<D>(r, nxt, lane);
+    cur = nxt;
+    u = un;
   }
+}
+
+// Query rows of a tile: `ptr` of row block b's lane row (null: no such row).
+template <int D, int NB>
+__device__ __forceinline__ void load_row(RowState<D, NB>& w, int b, const float* q, float qk_scale, int j4) {
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t)
+    w.q[b][t] = q ? *(const f32x4*)(q + 16 * t + 4 * j4) * qk_scale : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w.o[b][h][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  w.m[b] = -INFINITY;
+  w.l[b] = 0.f;
+}
+
+// LDS in which the KW wavefronts' results of a tile meet, 64 columns of d at a time.
+// The pitch of 68 floats spreads the 16 rows of a 16-byte write over all banks.
+template <int NB, int KW>
+struct Meet {
+  float o[KW][16 * NB][68];
+  float m[KW][16 * NB], l[KW][16 * NB];
+  float scale[KW][16 * NB];
+};
+
+// Fold the wavefronts' partial results; `store(row, col, f32x4)` takes the normalised
+// output of tile row `row`, columns col .. col + 3, and `store_lse(row, lse)` its
+// natural-log denominator (-inf, output 0, for a row that saw no key).
+template <int D, int NB, int KW, typename Store, typename StoreLse>
+__device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<NB, KW>& x, Store store, StoreLse store_lse) {
+  constexpr int ROWS = 16 * NB;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, j4 = lane >> 4;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    float l = w.l[b] + xor16(w.l[b]);
+    l = xor32_sum(l);
+    if (j4 == 0) { x.m[wave][16 * b + col] = w.m[b]; x.l[wave][16 * b + col] = l; }
+  }
+  __syncthreads();
+  for (int i = tid; i < KW * ROWS; i += 64 * KW) {
+    const int k = i / ROWS, row = i % ROWS;
+    float m = -INFINITY;
+#pragma unroll
+    for (int n = 0; n < KW; ++n) m = fmaxf(m, x.m[n][row]);
+    const float mm = m == -INFINITY ? 0.f : m;
+    float l = 0.f;
+#pragma unroll
+    for (int n = 0; n < KW; ++n) l += x.l[n][row] * __builtin_amdgcn_exp2f(x.m[n][row] - mm);
+    x.scale[k][row] = l > 0.f ? __builtin_amdgcn_exp2f(x.m[k][row] - mm) * (1.f / l) : 0.f;
+    if (k == 0) store_lse(row, l > 0.f ? (m + log2f(l)) * LN2 : -INFINITY);
+  }
+#pragma unroll
+  for (int h = 0; h < D / 64; ++h) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        *(f32x4*)&x.o[wave][16 * b + col][16 * j4 + 4 * c] =
+            f32x4{w.o[b][h][0][c], w.o[b][h][1][c], w.o[b][h][2][c], w.o[b][h][3][c]};
+    __syncthreads();
+    for (int i = tid; i < ROWS * 16; i += 64 * KW) {
+      const int row = i >> 4, c = 4 * (i & 15);
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < KW; ++k) acc += *(const f32x4*)&x.o[k][row][c] * x.scale[k][row];
+      store(row, 64 * h + c, acc);
+    }
+    if (h + 1 < D / 64) __syncthreads();
+  }
+}
+
+// Copy `n` rows of d floats (K and V) into cache rows: 16 bytes per thread and step.
+template <int D>
+__device__ __forceinline__ void file_rows(const float* K, const float* V, int64_t stride, float* Kc, float* Vc,
+                                          int n, int n_threads) {
+  for (int i = threadIdx.x; i < n * (D / 4); i += n_threads) {
+    const int row = i / (D / 4), c = 4 * (i % (D / 4));
+    const f32x4 k = *(const f32x4*)(K + row * stride + c), v = *(const f32x4*)(V + row * stride + c);
+    *(f32x4*)(Kc + (int64_t)row * D + c) = k;
+    *(f32x4*)(Vc + (int64_t)row * D + c) = v;
+  }
+}
+
+// ------------------------------------------------------------------ phase 1
+// grid.x numbers (kv head fastest, batch, tile in block -- late, i.e. heavy, first --,
+// block -- block 0, which has no anchor, last).
+template <int D, int NB, int KW>
+__global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, int tiles_per_block) {
+  __shared__ Meet<NB, KW> x;
+  constexpr int ROWS = 16 * NB;
+  const Geom& g = a.g;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
+  int id = blockIdx.x;
+  const int kvh = id % g.Hkv; id /= g.Hkv;
+  const int beta = id % g.B; id /= g.B;
+  const int t = tiles_per_block - 1 - id % tiles_per_block; id /= tiles_per_block;
+  const int n = (int)((g.L + g.b - 1) / g.b);
+  const int i = id + 1 == n ? 0 : id + 1;
+  const int s = (int)(i * g.b);
+  const int e = (int)(s + g.b < g.L ? s + g.b : g.L);
+  const int64_t r0 = (int64_t)t * ROWS, n_rows = (int64_t)(e - s) * g.G;    // rows of this block
+  if (r0 >= n_rows) return;                           // tile beyond a short block
+  const int live_rows = (int)(n_rows - r0 < ROWS ? n_rows - r0 : ROWS);
+
+  // K / V rows from the token-major inputs when they are handed over as they are
+  // (then this kernel also files them in the caches), else from the filled caches
+  const bool from_input = a.Kin != nullptr;
+  const int64_t stride = from_input ? (int64_t)g.Hkv * D : D;
+  const int64_t in0 = ((int64_t)beta * g.L * g.Hkv + kvh) * D, cache0 = ((int64_t)beta * g.Hkv + kvh) * g.cap * D;
+  const float* Kb = from_input ? (const float*)a.Kin + in0 : (const float*)a.Kc + cache0;
+  const float* Vb = from_input ? (const float*)a.Vin + in0 : (const float*)a.Vc + cache0;
+
+  RowState<D, NB> w;
+  int row_lim[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int rr = 16 * b + col;
+    const int64_t r = r0 + (rr < live_rows ? rr : 0);
+    const int tok = s + (int)(r / g.G), head = kvh * g.G + (int)(r % g.G);
+    row_lim[b] = tok + 1;
+    load_row<D, NB>(w, b, rr < live_rows ? (const float*)a.Q + (((int64_t)beta * g.L + tok) * g.Hq + head) * D : nullptr,
+                    g.scale * LOG2E, j4);
+  }
+  const int wave_lim = s + (int)(r0 / g.G) + 1;       // the tile's first row sees least
+
+  KeySeq seq;
+  int64_t a_lo, a_hi;
+  const bool ext = anchor_range(g, a.anchor_mode, i, &a_lo, &a_hi);
+  seq.a_lo = (int)a_lo; seq.a_hi = (int)a_hi;
+  // separately given anchors: token-major, n_anchor * a rows per batch
+  const int64_t anchor_rows = (int64_t)(a.anchor_mode == ANCHOR_PER_BLOCK ? n : 1) * g.a;
+  seq.Ka = ext ? (const float*)a.Ka + ((int64_t)beta * anchor_rows * g.Hkv + kvh) * D : Kb;
+  seq.Va = ext ? (const float*)a.Va + ((int64_t)beta * anchor_rows * g.Hkv + kvh) * D : Vb;
+  seq.a_stride = ext ? (int64_t)g.Hkv * D : stride;
+  seq.Kl = Kb; seq.Vl = Vb; seq.l_stride = stride; seq.l_off = 0;
+  seq.l_lo = s;
+  seq.l_hi = s + (int)((r0 + live_rows - 1) / g.G) + 1;
+  seq.count();
+  attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, lane);
+
+  meet<D, NB, KW>(w, x,
+      [&](int row, int c, f32x4 v) {
+        if (row >= live_rows) return;
+        const int64_t r = r0 + row;
+        const int tok = s + (int)(r / g.G), head = kvh * g.G + (int)(r % g.G);
+        *(f32x4*)((float*)a.O + (((int64_t)beta * g.L + tok) * g.Hq + head) * D + c) = v;
+      },
+      [&](int row, float lse) {
+        if (row >= live_rows || !a.LSE) return;
+        const int64_t r = r0 + row;
+        const int tok = s + (int)(r / g.G), head = kvh * g.G + (int)(r % g.G);
+        a.LSE[((int64_t)beta * g.Hq + head) * g.L + tok] = lse;
+      });
+
+  // Algorithm 1, "keep the block's K/V": a token is filed by the tile that holds its first row
+  if (from_input) {
+    const int t0 = s + (int)((r0 + g.G - 1) / g.G), t1 = s + (int)((r0 + live_rows + g.G - 1) / g.G);
+    file_rows<D>(Kb + (int64_t)t0 * stride, Vb + (int64_t)t0 * stride, stride,
+                 (float*)a.Kc + cache0 + (int64_t)t0 * D, (float*)a.Vc + cache0 + (int64_t)t0 * D, t1 - t0, 64 * KW);
+  }
+}
+
+// ------------------------------------------------------------------ phase 2
+// grid.x numbers (kv head fastest, row tile, split, batch).
+template <int D, int NB, int KW>
+__global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, int row_tiles) {
+  __shared__ Meet<NB, KW> x;
+  constexpr int ROWS = 16 * NB;
+  const Geom& g = a.g;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
+  int id = blockIdx.x;
+  const int kvh = id % g.Hkv; id /= g.Hkv;
+  const int tile = id % row_tiles; id /= row_tiles;
+  const int sp = id % a.plan.s_total;
+  const int beta = id / a.plan.s_total;
+  const int r0 = tile * ROWS, n_rows = g.G * a.q_len;  // row = token * G + head in group
+  const int live_rows = n_rows - r0 < ROWS ? n_rows - r0 : ROWS;
+
+  const int total = (int)visible_total(a), cache_len = (int)a.cache_len;
+  int64_t lo, hi;
+  split_range(a.plan, g.L, g.b, total, sp, &lo, &hi);
+
+  RowState<D, NB> w;
+  int row_lim[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int rr = 16 * b + col, r = r0 + (rr < live_rows ? rr : 0);
+    const int j = r / g.G, head = kvh * g.G + r % g.G;
+    row_lim[b] = (int)visible_limit(a, j);
+    load_row<D, NB>(w, b, rr < live_rows ? (const float*)a.Qq + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D : nullptr,
+                    g.scale * LOG2E, j4);
+  }
+  const int wave_lim = (int)visible_limit(a, r0 / g.G);
+
+  // rows below cache_len are cached and visible to every token; the rest are the
+  // call's own tokens, read where the caller left them (or from the caches, if a
+  // preceding kernel has put them there)
+  const int64_t cache0 = ((int64_t)beta * g.Hkv + kvh) * g.cap * D;
+  const bool fused_append = a.Kn != nullptr;
+  KeySeq seq;
+  seq.Ka = (const float*)a.Kc + cache0; seq.Va = (const float*)a.Vc + cache0; seq.a_stride = D;
+  seq.a_lo = (int)lo;
+  seq.a_hi = (int)(hi < cache_len ? hi : cache_len);
+  if (seq.a_hi < seq.a_lo) seq.a_hi = seq.a_lo;
+  seq.l_lo = lo > cache_len ? (int)lo : cache_len;
+  seq.l_hi = (int)hi;
+  if (seq.l_hi < seq.l_lo) seq.l_hi = seq.l_lo;
+  const int64_t new0 = ((int64_t)beta * a.q_len * g.Hkv + kvh) * D;
+  seq.Kl = fused_append ? (const float*)a.Kn + new0 : seq.Ka;
+  seq.Vl = fused_append ? (const float*)a.Vn + new0 : seq.Va;
+  seq.l_stride = fused_append ? (int64_t)g.Hkv * D : D;
+  seq.l_off = fused_append ? cache_len : 0;
+  seq.count();
+  attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, lane);
+
+  const bool direct = a.O != nullptr || a.A != nullptr;      // one split: nothing to merge
+  meet<D, NB, KW>(w, x,
+      [&](int row, int c, f32x4 v) {
+        if (row >= live_rows) return;
+        const int r = r0 + row, j = r / g.G, head = kvh * g.G + r % g.G;
+        float* dst = a.O ? (float*)a.O + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D
+                   : a.A ? a.A + (((int64_t)beta * g.Hq + head) * a.q_len + j) * D
+                         : a.O_sub + ((((int64_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j) * D;
+        *(f32x4*)(dst + c) = v;
+      },
+      [&](int row, float lse) {
+        if (row >= live_rows) return;
+        const int r = r0 + row, j = r / g.G, head = kvh * g.G + r % g.G;
+        if (!direct) a.LSE_sub[(((int64_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j] = lse;
+        else if (a.LSE) a.LSE[((int64_t)beta * g.Hq + head) * a.q_len + j] = lse;
+      });
+
+  // Algorithm 2, append: the split that holds a new token files its row
+  if (fused_append && tile == 0 && seq.l_hi > seq.l_lo) {
+    const int64_t src = (int64_t)(seq.l_lo - cache_len) * seq.l_stride;
+    file_rows<D>(seq.Kl + src, seq.Vl + src, seq.l_stride, (float*)a.Kc + cache0 + (int64_t)seq.l_lo * D,
+                 (float*)a.Vc + cache0 + (int64_t)seq.l_lo * D, seq.l_hi - seq.l_lo, 64 * KW);
+  }
+}
+
+template <int D, int NB, int KW>
+hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
+  const Geom& g = a.g;
+  const int64_t n = (g.L + g.b - 1) / g.b, bmax = g.b < g.L ? g.b : g.L;
+  const int64_t tpb = (bmax * g.G + 16 * NB - 1) / (16 * NB), wgs = n * tpb * g.B * g.Hkv;
+  if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+  phase1_f32_kernel<D, NB, KW><<<dim3((unsigned)wgs), 64 * KW, 0, st>>>(a, (int)tpb);
+  return hipGetLastError();
+}
+
+template <int D, int NB, int KW>
+hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
+  const Geom& g = a.g;
+  const int64_t tiles = ((int64_t)g.G * a.q_len + 16 * NB - 1) / (16 * NB);
+  const int64_t wgs = tiles * g.B * g.Hkv * a.plan.s_total;
+  if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff - 64) return hipErrorInvalidValue;
+  phase2_f32_kernel<D, NB, KW><<<dim3((unsigned)wgs), 64 * KW, 0, st>>>(a, (int)tiles);
+  return hipGetLastError();
 }
 
 }  // namespace
 
+// 32-row tiles shared by four wavefronts (two workgroups per CU) once there are two such
+// tiles per CU: at 8 / 2 heads, d = 128, L = 4099 they take 171 us against 192 (32 rows,
+// eight wavefronts), 191 (16 rows, four) and 215 us (16 rows, eight); d = 64: 99 against
+// 143, 100 and 107.  Fewer rows are bound by the latency of a tile, not by the matrix
+// pipe: 16-row tiles shared by eight wavefronts (1 head, d = 64, L = 1024: 11.5 us against
+// 12.2 with four and 17.9 for 32-row tiles).
 hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   const Geom& g = a.g;
-  int64_t n = (g.L + g.b - 1) / g.b;
-  int64_t bmax = g.b < g.L ? g.b : g.L;
-  int tpb = (int)((bmax + ROWS - 1) / ROWS);
-  if (n * tpb > 0x7fffffff) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(n * tpb), (unsigned)g.Hq, (unsigned)g.B);
-  if (g.d == 64) phase1_f32_kernel<64><<<grid, ROWS, 0, st>>>(a, tpb);
-  else phase1_f32_kernel<128><<<grid, ROWS, 0, st>>>(a, tpb);
-  return hipGetLastError();
+  const int64_t tiles32 = (g.L * g.G + 31) / 32 * g.Hkv * g.B;
+  if (tiles32 >= 512)
+    return g.d == 64 ? launch_phase1<64, 2, 4>(a, st) : launch_phase1<128, 2, 4>(a, st);
+  return g.d == 64 ? launch_phase1<64, 1, 8>(a, st) : launch_phase1<128, 1, 8>(a, st);
 }
+
+int f32_phase2_rows_per_workgroup(int64_t rows) { return rows > 16 ? 32 : 16; }
 
 hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st) {
   const Geom& g = a.g;
-  int row_tiles = (a.q_len + ROWS - 1) / ROWS;
-  if ((int64_t)g.B * a.plan.s_total * row_tiles > 0x7fffffff) return hipErrorInvalidValue;
-  dim3 grid((unsigned)((int64_t)g.B * a.plan.s_total * row_tiles), (unsigned)g.Hq, 1);
-  if (g.d == 64) phase2_f32_kernel<64><<<grid, ROWS, 0, st>>>(a, row_tiles);
-  else phase2_f32_kernel<128><<<grid, ROWS, 0, st>>>(a, row_tiles);
-  return hipGetLastError();
+  if (f32_phase2_rows_per_workgroup((int64_t)g.G * a.q_len) == 32)
+    return g.d == 64 ? launch_phase2<64, 2, 8>(a, st) : launch_phase2<128, 2, 8>(a, st);
+  return g.d == 64 ? launch_phase2<64, 1, 8>(a, st) : launch_phase2<128, 1, 8>(a, st);
 }
 
 }  // namespace star

@@ -16,11 +16,13 @@ namespace star {
 // indices from n_blocks * spb on are pieces of the tail.
 // ---------------------------------------------------------------------------
 //
-// A "flat" plan ignores part boundaries: with S = s_total splits, split s is the
-// comb of 32-key steps s, s + S, s + 2S, ... of everything the call may see
-// (split_len only sizes S).  It is used by decode-sized calls that do not ask
-// for per-part outputs, where equal splits (one per resident workgroup) that
-// sweep the cache together matter more than part boundaries.
+// A "flat" plan ignores part boundaries; it is used by calls that do not ask for
+// per-part outputs, where equal splits matter more than part boundaries.  For the
+// streaming decode kernel, with S = s_total splits, split s is the comb of 32-key
+// steps s, s + S, s + 2S, ... of everything the call may see (split_len only sizes
+// S), so that one split per resident workgroup sweeps the cache together with the
+// others.  For the fp32 kernel split s is the run [s, s + 1) * split_len; with one
+// split the kernel writes the call's results itself and nothing is merged.
 struct SplitPlan {
   int64_t split_len;   // keys per split (multiple of 32)
   int32_t spb;         // splits per context block
@@ -54,10 +56,9 @@ struct Phase1Args {
   const void* Vc;
   int32_t anchor_mode;  // AnchorMode
   const void* Ka;       // ANCHOR_EXTERNAL / ALL_BLOCKS / PER_BLOCK: anchor keys / values of n_anchor
-  const void* Va;       // = 1 / 1 / n anchors; head-major [B, Hkv, n_anchor * a, d] for the fp32
-                        // kernel, token-major [B, n_anchor, a, Hkv, d] for the bf16 one
-  const void* Kin;      // bf16 kernel: the token-major inputs [B, L, Hkv, d] to read keys /
-  const void* Vin;      // values from (and to file in the caches); null: read the caches
+  const void* Va;       // = 1 / 1 / n anchors, token-major [B, n_anchor, a, Hkv, d]
+  const void* Kin;      // the token-major inputs [B, L, Hkv, d] to read keys / values from (and to
+  const void* Vin;      // file in the caches); null: read the caches
   unsigned int* tickets;  // bf16 kernel: this launch's eight work-queue counters (device memory)
   int32_t n_cu;           // bf16 kernel: compute units of the device the call runs on
 };
@@ -83,12 +84,15 @@ struct Phase2Args {
   int32_t causal;       // 1: the new tokens are appended and token j sees rows [0, cache_len + j];
                         // 0: nothing is appended and every token sees rows [0, cache_len)
   const void* Qq;       // [B, q_len, Hq, d]
-  const void* Kn;       // new tokens' K, V [B, q_len, Hkv, d]; null: the caches already
-  const void* Vn;       // hold them (decode kernel: nothing to append, read the caches)
-  void* Kc;             // caches; the new tokens are already appended unless the
-  void* Vc;             // kernel appends them itself (decode path)
+  const void* Kn;       // new tokens' K, V [B, q_len, Hkv, d], which the kernel appends; null: the
+  const void* Vn;       // caches already hold them, or there are none
+  void* Kc;
+  void* Vc;
   float* O_sub;         // [B, s_total, Hq, q_len, d]   per-split local attention
   float* LSE_sub;       // [B, s_total, Hq, q_len]      per-split log-sum-exp
+  void* O;              // fp32 kernel, flat plan of one split: the call's own results (MergeArgs'
+  float* A;             // O, A, LSE) instead of O_sub / LSE_sub; else all null
+  float* LSE;
 };
 
 // Cache rows a phase-2 call may see in all, and new token j's exclusive bound.
@@ -128,10 +132,16 @@ __host__ __device__ inline bool decode_cache_resident(const Geom& g, int64_t tot
 }
 inline int decode_workgroups_per_cu(bool resident) { return resident ? 4 : 3; }
 
-// Key range [lo, hi) of split s of a plan that is not flat (hi clipped to what
-// exists for this call).
+// Key range [lo, hi) of split s of a plan other than the decode kernel's flat one (hi
+// clipped to what exists for this call).
 __host__ __device__ inline void split_range(const SplitPlan& p, int64_t L, int64_t b,
                                             int64_t total_keys, int s, int64_t* lo, int64_t* hi) {
+  if (p.flat) {
+    int64_t x = (int64_t)s * p.split_len, y = x + p.split_len;
+    *lo = x < total_keys ? x : total_keys;
+    *hi = y < total_keys ? y : total_keys;
+    return;
+  }
   int n_ctx = p.n_blocks * p.spb;
   if (s < n_ctx) {
     int64_t m = s / p.spb, piece = s % p.spb;
@@ -152,6 +162,9 @@ __host__ __device__ inline void split_range(const SplitPlan& p, int64_t L, int64
 // workgroup, and tokens per workgroup (the split plan sizes its grids with them).
 int flash_heads_per_workgroup(int G);
 int flash_tokens_per_workgroup(int G);
+
+// Rows (heads of a KV group x tokens) of a workgroup of the fp32 phase-2 kernel.
+int f32_phase2_rows_per_workgroup(int64_t rows);
 
 // Compute units of the current device (cached per device; 0 if the runtime refuses).
 int device_cu_count();

@@ -1,0 +1,60 @@
+"""The fp32 kernels at the edges of their tiling: 16- and 32-row tiles packed over the
+heads of a KV group (groups that do and do not divide a tile), 16-key units dealt to
+the wavefronts of a workgroup (fewer units than wavefronts, ragged last units), calls
+of one workgroup per row tile that write their results themselves and calls whose
+splits are merged, with and without per-part outputs."""
+import pytest
+import torch
+
+import paper_2411_17116_amd as sa
+import workloads
+from tests import parity_harness as ph
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,b,a,lq,nd", [
+    (1, 1, 1, 64, 15, 16, 16, 1, 2),        # one ragged unit, one row tile
+    (1, 3, 1, 128, 129, 17, 9, 11, 2),      # G = 3: tokens straddle row tiles; 33 rows: two tiles
+    (2, 5, 1, 64, 257, 64, 33, 13, 2),      # G = 5
+    (1, 40, 2, 64, 100, 50, 25, 2, 1),      # G = 20: one token's heads in two tiles
+    (1, 2, 2, 128, 1023, 200, 16, 17, 2),   # at the edge of one workgroup per row tile (1 MiB of K and V)
+    (1, 2, 2, 128, 1100, 200, 16, 17, 2),   # beyond it: splits and a merge
+    (1, 4, 2, 64, 2500, 700, 1, 33, 2),     # 16-row and 32-row tiles, several splits
+])
+def test_fp32_tile_edges(B, Hq, Hkv, d, L, b, a, lq, nd):
+    cfg = workloads.StarConfig("f32tiles", "fp32", B, Hq, Hkv, d, L, b, a, lq, nd, seed=L + Hq, n_planted=2)
+    print(f"[{cfg}]", flush=True)
+    rep = ph.run_parity(cfg, all_rows=True)
+    assert rep.ok, rep.detail
+    # the same query call without per-part outputs: other splits (or none), each within
+    # the fp32 bound of the oracle, so within twice the bound of each other
+    inp = workloads.make_inputs(cfg, "cuda")
+    one, two = ph.HipRun(cfg, inp, "cuda"), ph.HipRun(cfg, inp, "cuda")
+    one.phase1()
+    two.phase1()
+    want, _, _ = one.phase2(inp.Qq, inp.Kq, inp.Vq, want_parts=True)
+    got, _, _ = two.phase2(inp.Qq, inp.Kq, inp.Vq, want_parts=False)
+    torch.cuda.synchronize()
+    assert (want - got).abs().max().item() <= 2 * ph.TOL["fp32"]["o"]
+    assert torch.equal(one.Kc, two.Kc) and torch.equal(one.Vc, two.Vc)
+
+
+def test_fp32_many_rows():
+    """Enough rows for the kernel set-up of long prefills (32-row tiles)."""
+    cfg = workloads.StarConfig("f32many", "fp32", 2, 6, 2, 128, 3001, 500, 301, 100, 1, seed=5, n_planted=2)
+    rep = ph.run_parity(cfg)
+    assert rep.ok, rep.detail
+
+
+def test_fp32_workspace_covers_every_shorter_call():
+    """Whatever a query call of at most max_q tokens plans must fit what
+    star_attn_workspace_bytes asked for (tiles hold 32 / G tokens: not a whole number)."""
+    for Hq, Hkv in ((4, 1), (3, 1), (20, 1), (8, 8)):
+        shape = sa.StarShape.make("fp32", 1, Hq, Hkv, 64, 3000, 700, 100, 3400)
+        for max_q in (75, 130, 400):
+            have = sa.workspace_bytes(shape, max_q)
+            for q in range(1, max_q + 1):
+                for parts in (False, True):
+                    for cached in (3000, 3400 - q):
+                        assert sa.phase2_plan(shape, cached, q, parts).workspace_bytes <= have, (Hq, q, parts)
