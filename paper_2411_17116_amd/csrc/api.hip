@@ -140,8 +140,10 @@ static int64_t f32_splits_max(const Geom& g, int64_t q_len) {
   return fill < bound ? fill : bound;
 }
 constexpr int64_t F32_SPLIT_MIN = 128;     // keys: one 16-key unit for each of the eight wavefronts
-// Up to here one workgroup walks all keys of its rows and there is nothing to merge.
-constexpr int64_t F32_DIRECT_BYTES = 1 << 20;
+// Up to these bytes of K and V per KV head one workgroup walks all keys of its rows and
+// there is nothing to merge: with the matrix pipe of one CU it takes 9.3 us at 250 KiB and
+// 13.9 at 530 (one row, d = 64), splits and their merge 11.7 us at either.
+constexpr int64_t F32_DIRECT_BYTES = 256 << 10;
 
 // Split plan for a phase-2 call with q_len new tokens that can see `total`
 // cache rows.  Decode-sized calls (G * q_len rows fit one 16-column MFMA tile)

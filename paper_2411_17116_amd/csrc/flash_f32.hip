@@ -26,8 +26,9 @@
 // Phase 1 reads K and V where the caller left them and files its own tokens' rows in
 // the caches; phase 2 reads the new tokens from the call's Kq / Vq and appends them.
 // Measured, whole calls, against a kernel of one thread per row: 8 / 2 heads, d = 128,
-// L = 4099, b = 1024, a = 512: 3390 -> 170 us (89 TFLOP/s); 1 head, d = 64, L = 1024,
-// b = a = 256: 274 -> 11.4 us.
+// L = 4099, b = 1024, a = 512: 3390 -> 151 us (100 TFLOP/s; 119 at 8192 tokens in blocks of
+// 2048, where a library fp32 matrix product reaches 152); 1 head, d = 64, L = 1024,
+// b = a = 256: 274 -> 9.9 us.
 #include "star_internal.h"
 
 namespace star {
@@ -35,6 +36,9 @@ namespace star {
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+typedef const __attribute__((address_space(1))) f32x4* GlobalVec;
 
 constexpr int UNIT = 16;   // keys per step of a wavefront
 constexpr float LOG2E = 1.4426950408889634f;
@@ -55,13 +59,12 @@ __device__ __forceinline__ float xor32_sum(float x) {
 // The keys a row tile walks: rows [a_lo, a_hi) of Ka / Va, visible to every row of
 // the tile, then keys [l_lo, l_hi), of which a row sees those below its own bound;
 // key k of the second range is row k - l_off of Kl / Vl.  Consecutive rows are
-// a_stride / l_stride floats apart.
+// a_stride / l_stride bytes apart.
+// Everything here is uniform over a wavefront, so that a unit's address is a scalar
+// base plus a 32-bit offset per lane.
 struct KeySeq {
-  const float* Ka;
-  const float* Va;
-  const float* Kl;
-  const float* Vl;
-  int64_t a_stride, l_stride;
+  GlobalBytes Ka, Va, Kl, Vl;
+  unsigned a_stride, l_stride;
   int a_lo, a_hi, l_lo, l_hi, l_off;
   int n_a, n_units;
   __device__ __forceinline__ void count() {
@@ -85,29 +88,28 @@ struct Unit {
   f32x4 v[4][D / 64];
 };
 
-// Where unit u starts: its first row's address offset, and how many of its rows exist.
+// Unit u: its first row in K / V, how many rows of the range are left from there on,
+// and its first key.
 struct UnitAt {
-  const float* K;
-  const float* V;
-  int64_t stride;
-  int row0, n_rows;           // rows row0 .. row0 + min(16, n_rows) - 1 of K / V
+  GlobalBytes K, V;
+  unsigned stride;
+  int n_rows;
   int key0;
   bool local;
 };
 __device__ __forceinline__ UnitAt unit_at(const KeySeq& seq, int u) {
+  // the four bases as scalars of their own: chosen between as struct members, the
+  // compiler would keep the struct in scratch memory and index it
+  GlobalBytes Ka = seq.Ka, Va = seq.Va, Kl = seq.Kl, Vl = seq.Vl;
+  asm("" : "+s"(Ka), "+s"(Va), "+s"(Kl), "+s"(Vl));
   UnitAt x;
   x.local = u >= seq.n_a;
-  if (!x.local) {
-    x.key0 = seq.a_lo + u * UNIT;
-    x.row0 = x.key0;
-    x.n_rows = seq.a_hi - x.key0;
-    x.K = seq.Ka; x.V = seq.Va; x.stride = seq.a_stride;
-  } else {
-    x.key0 = seq.l_lo + (u - seq.n_a) * UNIT;
-    x.row0 = x.key0 - seq.l_off;
-    x.n_rows = seq.l_hi - x.key0;
-    x.K = seq.Kl; x.V = seq.Vl; x.stride = seq.l_stride;
-  }
+  x.key0 = x.local ? seq.l_lo + (u - seq.n_a) * UNIT : seq.a_lo + u * UNIT;
+  x.n_rows = (x.local ? seq.l_hi : seq.a_hi) - x.key0;
+  x.stride = x.local ? seq.l_stride : seq.a_stride;
+  const size_t off = (size_t)(x.local ? x.key0 - seq.l_off : x.key0) * x.stride;
+  x.K = (x.local ? Kl : Ka) + off;
+  x.V = (x.local ? Vl : Va) + off;
   return x;
 }
 
@@ -115,21 +117,106 @@ __device__ __forceinline__ UnitAt unit_at(const KeySeq& seq, int u) {
 template <int D>
 __device__ __forceinline__ void load_k(Unit<D>& r, const UnitAt& x, int lane) {
   int i = lane & 15;
-  i = i < x.n_rows ? i : x.n_rows - 1;
-  const float* p = x.K + (int64_t)(x.row0 + i) * x.stride + 4 * (lane >> 4);
+  if (x.n_rows < UNIT) i = i < x.n_rows ? i : x.n_rows - 1;
+  const unsigned off = (unsigned)i * x.stride + 16 * (lane >> 4);
 #pragma unroll
-  for (int t = 0; t < D / 16; ++t) r.k[t] = *(const f32x4*)(p + 16 * t);
+  for (int t = 0; t < D / 16; ++t) r.k[t] = *(GlobalVec)(x.K + off + 64 * t);
 }
 template <int D>
 __device__ __forceinline__ void load_v(Unit<D>& r, const UnitAt& x, int lane) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     int i = 4 * (lane >> 4) + v;
-    i = i < x.n_rows ? i : x.n_rows - 1;
-    const float* p = x.V + (int64_t)(x.row0 + i) * x.stride + 4 * (lane & 15);
+    if (x.n_rows < UNIT) i = i < x.n_rows ? i : x.n_rows - 1;
+    const unsigned off = (unsigned)i * x.stride + 16 * (lane & 15);
 #pragma unroll
-    for (int h = 0; h < D / 64; ++h) r.v[v][h] = *(const f32x4*)(p + 64 * h);
+    for (int h = 0; h < D / 64; ++h) r.v[v][h] = *(GlobalVec)(x.V + off + 256 * h);
   }
+}
+
+// One unit: scores, softmax, products.  MORE: K and V of unit `nxt` are requested as soon
+// as this unit's are used up -- without a branch, so that the compiler's waits for V
+// need not include them.
+template <int D, int NB, bool MORE>
+__device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, const UnitAt& cur, const UnitAt& nxt,
+                                            const int (&row_lim)[NB], int wave_lim, int lane) {
+  const int j4 = lane >> 4;
+  // two chains per score tile (d split by parity): half the rounding of one chain of d terms
+  f32x4 s[NB], s1[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) s[b] = s1[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; e += 2)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        s[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][e], w.q[b][t][e], s[b], 0, 0, 0);
+        s1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][e + 1], w.q[b][t][e + 1], s1[b], 0, 0, 0);
+      }
+  if (MORE) load_k<D>(r, nxt, lane);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) s[b] += s1[b];
+  if (cur.n_rows < UNIT || (cur.local && cur.key0 + UNIT > wave_lim)) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int room = row_lim[b] - cur.key0;
+      const int n = (cur.local && room < cur.n_rows ? room : cur.n_rows) - 4 * j4;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s[b][v] = v < n ? s[b][v] : -INFINITY;
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    float t = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
+    t = xor32_max(fmaxf(t, xor16(t)));
+    if (__builtin_amdgcn_ballot_w64(t > w.m[b]) != 0) {      // some row's maximum moved
+      const float m_new = fmaxf(w.m[b], t);
+      const float mm = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(w.m[b] - mm);   // 0 while nothing was visible
+      w.m[b] = m_new;
+      w.l[b] *= alpha;
+#pragma unroll
+      for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w.o[b][h][e] *= alpha;
+    }
+    const float mm = w.m[b] == -INFINITY ? 0.f : w.m[b];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s[b][v] = __builtin_amdgcn_exp2f(s[b][v] - mm);
+    w.l[b] += (s[b][0] + s[b][1]) + (s[b][2] + s[b][3]);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          w.o[b][h][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.v[v][h][e], s[b][v], w.o[b][h][e], 0, 0, 0);
+  if (MORE) load_v<D>(r, nxt, lane);
+}
+
+// The lane's query row of row block b, as it is in memory (scale_rows() follows once the
+// first keys have been requested, so that both round trips overlap).
+template <int D, int NB>
+__device__ __forceinline__ void load_row(RowState<D, NB>& w, int b, const float* q, int j4) {
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t) w.q[b][t] = *(const f32x4*)(q + 16 * t + 4 * j4);
+#pragma unroll
+  for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w.o[b][h][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  w.m[b] = -INFINITY;
+  w.l[b] = 0.f;
+}
+template <int D, int NB>
+__device__ __forceinline__ void scale_rows(RowState<D, NB>& w, float qk_scale) {
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) w.q[b][t] *= qk_scale;
 }
 
 // Attend the wavefront's rows to units first, first + step, ... of the sequence.
@@ -137,93 +224,19 @@ __device__ __forceinline__ void load_v(Unit<D>& r, const UnitAt& x, int lane) {
 //   wave_lim  smallest bound of the wavefront's live rows
 template <int D, int NB>
 __device__ __forceinline__ void attend(RowState<D, NB>& w, const KeySeq& seq, int first, int step,
-                                       const int (&row_lim)[NB], int wave_lim, int lane) {
+                                       const int (&row_lim)[NB], int wave_lim, float qk_scale, int lane) {
   if (first >= seq.n_units) return;
-  const int j4 = lane >> 4;
   Unit<D> r;
   UnitAt cur = unit_at(seq, first);
   load_k<D>(r, cur, lane);
   load_v<D>(r, cur, lane);
-  for (int u = first;;) {
-    const int un = u + step;
-    const bool more = un < seq.n_units;
-    const UnitAt nxt = unit_at(seq, more ? un : u);
-    // two chains per score tile (d split by parity): half the rounding of one chain of d terms
-    f32x4 s[NB];
-    {
-      f32x4 s0[NB], s1[NB];
-#pragma unroll
-      for (int b = 0; b < NB; ++b) s0[b] = s1[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < D / 16; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; e += 2)
-#pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            s0[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][e], w.q[b][t][e], s0[b], 0, 0, 0);
-            s1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][e + 1], w.q[b][t][e + 1], s1[b], 0, 0, 0);
-          }
-#pragma unroll
-      for (int b = 0; b < NB; ++b) s[b] = s0[b] + s1[b];
-    }
-    if (more) load_k<D>(r, nxt, lane);
-    if (cur.n_rows < UNIT || (cur.local && cur.key0 + UNIT > wave_lim)) {
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int room = row_lim[b] - cur.key0;
-        const int n = (cur.local && room < cur.n_rows ? room : cur.n_rows) - 4 * j4;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) s[b][v] = v < n ? s[b][v] : -INFINITY;
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      float t = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
-      t = xor32_max(fmaxf(t, xor16(t)));
-      if (__builtin_amdgcn_ballot_w64(t > w.m[b]) != 0) {      // some row's maximum moved
-        const float m_new = fmaxf(w.m[b], t);
-        const float mm = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f(w.m[b] - mm);   // 0 while nothing was visible
-        w.m[b] = m_new;
-        w.l[b] *= alpha;
-#pragma unroll
-        for (int h = 0; h < D / 64; ++h)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w.o[b][h][e] *= alpha;
-      }
-      const float mm = w.m[b] == -INFINITY ? 0.f : w.m[b];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) s[b][v] = __builtin_amdgcn_exp2f(s[b][v] - mm);
-      w.l[b] += (s[b][0] + s[b][1]) + (s[b][2] + s[b][3]);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int h = 0; h < D / 64; ++h)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int b = 0; b < NB; ++b)
-            w.o[b][h][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.v[v][h][e], s[b][v], w.o[b][h][e], 0, 0, 0);
-    if (!more) break;
-    load_v<D>(r, nxt, lane);
+  scale_rows<D, NB>(w, qk_scale);
+  for (int u = first + step; u < seq.n_units; u += step) {
+    const UnitAt nxt = unit_at(seq, u);
+    attend_unit<D, NB, true>(w, r, cur, nxt, row_lim, wave_lim, lane);
     cur = nxt;
-    u = un;
   }
-}
-
-// Query rows of a tile: `ptr` of row block b's lane row (null: no such row).
-template <int D, int NB>
-__device__ __forceinline__ void load_row(RowState<D, NB>& w, int b, const float* q, float qk_scale, int j4) {
-#pragma unroll
-  for (int t = 0; t < D / 16; ++t)
-    w.q[b][t] = q ? *(const f32x4*)(q + 16 * t + 4 * j4) * qk_scale : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int h = 0; h < D / 64; ++h)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) w.o[b][h][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-  w.m[b] = -INFINITY;
-  w.l[b] = 0.f;
+  attend_unit<D, NB, false>(w, r, cur, cur, row_lim, wave_lim, lane);
 }
 
 // LDS in which the KW wavefronts' results of a tile meet, 64 columns of d at a time.
@@ -294,30 +307,36 @@ __device__ __forceinline__ void file_rows(const float* K, const float* V, int64_
 }
 
 // ------------------------------------------------------------------ phase 1
-// grid.x numbers (kv head fastest, batch, tile in block -- late, i.e. heavy, first --,
-// block -- block 0, which has no anchor, last).
+// grid.x numbers (kv head fastest, batch, block in group -- block 0, which has no anchor,
+// last --, tile in block -- late, i.e. heavy, first --, group of blocks).  Inside a group
+// the tiles come in descending weight, so that those that share a CU, or come last,
+// even out.
 template <int D, int NB, int KW>
-__global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, int tiles_per_block) {
+__global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, int group,
+                                                                   int tiles_per_block) {
   __shared__ Meet<NB, KW> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
   int id = blockIdx.x;
   const int kvh = id % g.Hkv; id /= g.Hkv;
   const int beta = id % g.B; id /= g.B;
-  const int t = tiles_per_block - 1 - id % tiles_per_block; id /= tiles_per_block;
-  const int n = (int)((g.L + g.b - 1) / g.b);
-  const int i = id + 1 == n ? 0 : id + 1;
+  const int n = (int)((g.L + g.b - 1) / g.b), first = id / (group * tiles_per_block) * group;
+  id -= first * tiles_per_block;
+  const int in_group = n - first < group ? n - first : group;
+  const int i = first + id % in_group + 1 == n ? 0 : first + id % in_group + 1;
+  const int t = tiles_per_block - 1 - id / in_group;
   const int s = (int)(i * g.b);
   const int e = (int)(s + g.b < g.L ? s + g.b : g.L);
-  const int64_t r0 = (int64_t)t * ROWS, n_rows = (int64_t)(e - s) * g.G;    // rows of this block
+  const int r0 = t * ROWS, n_rows = (e - s) * g.G;    // rows of this block
   if (r0 >= n_rows) return;                           // tile beyond a short block
-  const int live_rows = (int)(n_rows - r0 < ROWS ? n_rows - r0 : ROWS);
+  const int live_rows = n_rows - r0 < ROWS ? n_rows - r0 : ROWS;
+  const int tok0 = s + r0 / g.G, head0 = r0 % g.G;    // the tile's first row; row rr is rr rows on
 
   // K / V rows from the token-major inputs when they are handed over as they are
   // (then this kernel also files them in the caches), else from the filled caches
   const bool from_input = a.Kin != nullptr;
-  const int64_t stride = from_input ? (int64_t)g.Hkv * D : D;
+  const int64_t stride = from_input ? (int64_t)g.Hkv * D : D;      // floats between rows
   const int64_t in0 = ((int64_t)beta * g.L * g.Hkv + kvh) * D, cache0 = ((int64_t)beta * g.Hkv + kvh) * g.cap * D;
   const float* Kb = from_input ? (const float*)a.Kin + in0 : (const float*)a.Kc + cache0;
   const float* Vb = from_input ? (const float*)a.Vin + in0 : (const float*)a.Vc + cache0;
@@ -327,13 +346,12 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, in
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int rr = 16 * b + col;
-    const int64_t r = r0 + (rr < live_rows ? rr : 0);
-    const int tok = s + (int)(r / g.G), head = kvh * g.G + (int)(r % g.G);
+    const unsigned r = head0 + (rr < live_rows ? rr : 0);     // rows past the block repeat the first
+    const int tok = tok0 + (int)(r / (unsigned)g.G), head = kvh * g.G + (int)(r % (unsigned)g.G);
     row_lim[b] = tok + 1;
-    load_row<D, NB>(w, b, rr < live_rows ? (const float*)a.Q + (((int64_t)beta * g.L + tok) * g.Hq + head) * D : nullptr,
-                    g.scale * LOG2E, j4);
+    load_row<D, NB>(w, b, (const float*)a.Q + (((int64_t)beta * g.L + tok) * g.Hq + head) * D, j4);
   }
-  const int wave_lim = s + (int)(r0 / g.G) + 1;       // the tile's first row sees least
+  const int wave_lim = tok0 + 1;                      // the tile's first row sees least
 
   KeySeq seq;
   int64_t a_lo, a_hi;
@@ -341,32 +359,33 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, in
   seq.a_lo = (int)a_lo; seq.a_hi = (int)a_hi;
   // separately given anchors: token-major, n_anchor * a rows per batch
   const int64_t anchor_rows = (int64_t)(a.anchor_mode == ANCHOR_PER_BLOCK ? n : 1) * g.a;
-  seq.Ka = ext ? (const float*)a.Ka + ((int64_t)beta * anchor_rows * g.Hkv + kvh) * D : Kb;
-  seq.Va = ext ? (const float*)a.Va + ((int64_t)beta * anchor_rows * g.Hkv + kvh) * D : Vb;
-  seq.a_stride = ext ? (int64_t)g.Hkv * D : stride;
-  seq.Kl = Kb; seq.Vl = Vb; seq.l_stride = stride; seq.l_off = 0;
+  const int64_t anchor0 = ((int64_t)beta * anchor_rows * g.Hkv + kvh) * D;
+  seq.Ka = (GlobalBytes)(ext ? (const float*)a.Ka + anchor0 : Kb);
+  seq.Va = (GlobalBytes)(ext ? (const float*)a.Va + anchor0 : Vb);
+  seq.a_stride = (unsigned)(ext ? (int64_t)g.Hkv * D : stride) * 4;
+  seq.Kl = (GlobalBytes)Kb; seq.Vl = (GlobalBytes)Vb; seq.l_stride = (unsigned)stride * 4; seq.l_off = 0;
   seq.l_lo = s;
-  seq.l_hi = s + (int)((r0 + live_rows - 1) / g.G) + 1;
+  seq.l_hi = tok0 + (head0 + live_rows - 1) / g.G + 1;
   seq.count();
-  attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, lane);
+  attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, g.scale * LOG2E, lane);
 
   meet<D, NB, KW>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
-        const int64_t r = r0 + row;
-        const int tok = s + (int)(r / g.G), head = kvh * g.G + (int)(r % g.G);
+        const unsigned r = head0 + row;
+        const int tok = tok0 + (int)(r / (unsigned)g.G), head = kvh * g.G + (int)(r % (unsigned)g.G);
         *(f32x4*)((float*)a.O + (((int64_t)beta * g.L + tok) * g.Hq + head) * D + c) = v;
       },
       [&](int row, float lse) {
         if (row >= live_rows || !a.LSE) return;
-        const int64_t r = r0 + row;
-        const int tok = s + (int)(r / g.G), head = kvh * g.G + (int)(r % g.G);
+        const unsigned r = head0 + row;
+        const int tok = tok0 + (int)(r / (unsigned)g.G), head = kvh * g.G + (int)(r % (unsigned)g.G);
         a.LSE[((int64_t)beta * g.Hq + head) * g.L + tok] = lse;
       });
 
   // Algorithm 1, "keep the block's K/V": a token is filed by the tile that holds its first row
   if (from_input) {
-    const int t0 = s + (int)((r0 + g.G - 1) / g.G), t1 = s + (int)((r0 + live_rows + g.G - 1) / g.G);
+    const int t0 = tok0 + (head0 + g.G - 1) / g.G, t1 = tok0 + (head0 + live_rows + g.G - 1) / g.G;
     file_rows<D>(Kb + (int64_t)t0 * stride, Vb + (int64_t)t0 * stride, stride,
                  (float*)a.Kc + cache0 + (int64_t)t0 * D, (float*)a.Vc + cache0 + (int64_t)t0 * D, t1 - t0, 64 * KW);
   }
@@ -379,7 +398,7 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
   __shared__ Meet<NB, KW> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
   int id = blockIdx.x;
   const int kvh = id % g.Hkv; id /= g.Hkv;
   const int tile = id % row_tiles; id /= row_tiles;
@@ -396,11 +415,10 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
   int row_lim[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int rr = 16 * b + col, r = r0 + (rr < live_rows ? rr : 0);
+    const int rr = 16 * b + col, r = r0 + (rr < live_rows ? rr : 0);   // rows past the last repeat the first
     const int j = r / g.G, head = kvh * g.G + r % g.G;
     row_lim[b] = (int)visible_limit(a, j);
-    load_row<D, NB>(w, b, rr < live_rows ? (const float*)a.Qq + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D : nullptr,
-                    g.scale * LOG2E, j4);
+    load_row<D, NB>(w, b, (const float*)a.Qq + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D, j4);
   }
   const int wave_lim = (int)visible_limit(a, r0 / g.G);
 
@@ -410,7 +428,9 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
   const int64_t cache0 = ((int64_t)beta * g.Hkv + kvh) * g.cap * D;
   const bool fused_append = a.Kn != nullptr;
   KeySeq seq;
-  seq.Ka = (const float*)a.Kc + cache0; seq.Va = (const float*)a.Vc + cache0; seq.a_stride = D;
+  const float* Kb = (const float*)a.Kc + cache0;
+  const float* Vb = (const float*)a.Vc + cache0;
+  seq.Ka = (GlobalBytes)Kb; seq.Va = (GlobalBytes)Vb; seq.a_stride = 4 * D;
   seq.a_lo = (int)lo;
   seq.a_hi = (int)(hi < cache_len ? hi : cache_len);
   if (seq.a_hi < seq.a_lo) seq.a_hi = seq.a_lo;
@@ -418,12 +438,13 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
   seq.l_hi = (int)hi;
   if (seq.l_hi < seq.l_lo) seq.l_hi = seq.l_lo;
   const int64_t new0 = ((int64_t)beta * a.q_len * g.Hkv + kvh) * D;
-  seq.Kl = fused_append ? (const float*)a.Kn + new0 : seq.Ka;
-  seq.Vl = fused_append ? (const float*)a.Vn + new0 : seq.Va;
-  seq.l_stride = fused_append ? (int64_t)g.Hkv * D : D;
+  const float* Kl = fused_append ? (const float*)a.Kn + new0 : Kb;
+  const float* Vl = fused_append ? (const float*)a.Vn + new0 : Vb;
+  seq.Kl = (GlobalBytes)Kl; seq.Vl = (GlobalBytes)Vl;
+  seq.l_stride = (unsigned)(fused_append ? g.Hkv * D : D) * 4;
   seq.l_off = fused_append ? cache_len : 0;
   seq.count();
-  attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, lane);
+  attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, g.scale * LOG2E, lane);
 
   const bool direct = a.O != nullptr || a.A != nullptr;      // one split: nothing to merge
   meet<D, NB, KW>(w, x,
@@ -444,8 +465,8 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
 
   // Algorithm 2, append: the split that holds a new token files its row
   if (fused_append && tile == 0 && seq.l_hi > seq.l_lo) {
-    const int64_t src = (int64_t)(seq.l_lo - cache_len) * seq.l_stride;
-    file_rows<D>(seq.Kl + src, seq.Vl + src, seq.l_stride, (float*)a.Kc + cache0 + (int64_t)seq.l_lo * D,
+    const int64_t stride = (int64_t)g.Hkv * D, src = (int64_t)(seq.l_lo - cache_len) * stride;
+    file_rows<D>(Kl + src, Vl + src, stride, (float*)a.Kc + cache0 + (int64_t)seq.l_lo * D,
                  (float*)a.Vc + cache0 + (int64_t)seq.l_lo * D, seq.l_hi - seq.l_lo, 64 * KW);
   }
 }
@@ -455,8 +476,14 @@ hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   const Geom& g = a.g;
   const int64_t n = (g.L + g.b - 1) / g.b, bmax = g.b < g.L ? g.b : g.L;
   const int64_t tpb = (bmax * g.G + 16 * NB - 1) / (16 * NB), wgs = n * tpb * g.B * g.Hkv;
-  if (wgs > 0x7fffffff) return hipErrorInvalidValue;
-  phase1_f32_kernel<D, NB, KW><<<dim3((unsigned)wgs), 64 * KW, 0, st>>>(a, (int)tpb);
+  // (a block of 2^31 rows would be 550 GB of queries)
+  if (wgs > 0x7fffffff || bmax * g.G > 0x7fffffff - 64) return hipErrorInvalidValue;
+  // All blocks in one group, unless the keys in use at a time would then not fit the 4 MiB
+  // L2 cache of an XCD: K and V of a KV head beyond 6 MiB go block by block.  8 / 2 heads,
+  // d = 128: blocks of 2048 of 8192 tokens 816 us in one group, 705 block by block; blocks
+  // of 1024 of 4099 tokens 151 and 155 us, of 256 of 1024 tokens 24 and 27 us.
+  const int64_t group = g.L * g.d * 8 <= ((int64_t)6 << 20) ? n : 1;
+  phase1_f32_kernel<D, NB, KW><<<dim3((unsigned)wgs), 64 * KW, 0, st>>>(a, (int)group, (int)tpb);
   return hipGetLastError();
 }
 
@@ -472,17 +499,20 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
 
 }  // namespace
 
-// 32-row tiles shared by four wavefronts (two workgroups per CU) once there are two such
-// tiles per CU: at 8 / 2 heads, d = 128, L = 4099 they take 171 us against 192 (32 rows,
-// eight wavefronts), 191 (16 rows, four) and 215 us (16 rows, eight); d = 64: 99 against
-// 143, 100 and 107.  Fewer rows are bound by the latency of a tile, not by the matrix
-// pipe: 16-row tiles shared by eight wavefronts (1 head, d = 64, L = 1024: 11.5 us against
-// 12.2 with four and 17.9 for 32-row tiles).
+// 32-row tiles shared by four wavefronts (two workgroups per CU) once there are four such
+// tiles per CU; down to one 16-row tile per CU, 16-row tiles shared by four (three per CU);
+// fewer rows than that are bound by the latency of a tile: eight wavefronts share it.
+// Measured (32 x 4 / 16 x 4 / 16 x 8, us; 8 / 2 heads except the last): d = 128: L = 8192
+// (2048 32-row tiles) 705 / 740 / 819, L = 4099 (1025) 151 / 156 / 193, L = 1024 (256)
+// 26.3 / 23.7 / 29.2; d = 64: L = 8192 369 / 375 / 395, L = 2048 (512) 39.0 / 37.3 / 39.4;
+// 1 head, d = 64, L = 1024 (32) 16.0 / 10.0 / 9.9.
 hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   const Geom& g = a.g;
-  const int64_t tiles32 = (g.L * g.G + 31) / 32 * g.Hkv * g.B;
-  if (tiles32 >= 512)
+  const int64_t rows = g.L * g.G * g.Hkv * g.B;
+  if (rows >= 1024 * 32)
     return g.d == 64 ? launch_phase1<64, 2, 4>(a, st) : launch_phase1<128, 2, 4>(a, st);
+  if (rows >= 256 * 16)
+    return g.d == 64 ? launch_phase1<64, 1, 4>(a, st) : launch_phase1<128, 1, 4>(a, st);
   return g.d == 64 ? launch_phase1<64, 1, 8>(a, st) : launch_phase1<128, 1, 8>(a, st);
 }
 

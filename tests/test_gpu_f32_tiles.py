@@ -18,8 +18,8 @@ pytestmark = pytest.mark.gpu
     (1, 3, 1, 128, 129, 17, 9, 11, 2),      # G = 3: tokens straddle row tiles; 33 rows: two tiles
     (2, 5, 1, 64, 257, 64, 33, 13, 2),      # G = 5
     (1, 40, 2, 64, 100, 50, 25, 2, 1),      # G = 20: one token's heads in two tiles
-    (1, 2, 2, 128, 1023, 200, 16, 17, 2),   # at the edge of one workgroup per row tile (1 MiB of K and V)
-    (1, 2, 2, 128, 1100, 200, 16, 17, 2),   # beyond it: splits and a merge
+    (1, 2, 2, 128, 239, 100, 16, 17, 2),    # query call: 256 KiB of K and V, one workgroup per row tile
+    (1, 2, 2, 128, 240, 100, 16, 17, 2),    # beyond that: splits and a merge
     (1, 4, 2, 64, 2500, 700, 1, 33, 2),     # 16-row and 32-row tiles, several splits
 ])
 def test_fp32_tile_edges(B, Hq, Hkv, d, L, b, a, lq, nd):
@@ -40,9 +40,14 @@ def test_fp32_tile_edges(B, Hq, Hkv, d, L, b, a, lq, nd):
     assert torch.equal(one.Kc, two.Kc) and torch.equal(one.Vc, two.Vc)
 
 
-def test_fp32_many_rows():
-    """Enough rows for the kernel set-up of long prefills (32-row tiles)."""
-    cfg = workloads.StarConfig("f32many", "fp32", 2, 6, 2, 128, 3001, 500, 301, 100, 1, seed=5, n_planted=2)
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,b,a", [
+    (2, 6, 2, 128, 3001, 500, 301),         # 32-row tiles, all blocks in one group
+    (1, 4, 1, 64, 13000, 3000, 99),         # 32-row tiles, block by block
+    (1, 4, 2, 128, 1100, 256, 256),         # 16-row tiles, four wavefronts
+])
+def test_fp32_many_rows(B, Hq, Hkv, d, L, b, a):
+    """Enough rows for the kernel set-ups of longer prefills."""
+    cfg = workloads.StarConfig("f32many", "fp32", B, Hq, Hkv, d, L, b, a, 100, 1, seed=5, n_planted=2)
     rep = ph.run_parity(cfg)
     assert rep.ok, rep.detail
 
