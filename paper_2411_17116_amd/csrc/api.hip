@@ -377,11 +377,8 @@ static int phase1_impl(const star_attn_shape* shape, int anchor_mode, const Rope
   // Algorithm 1: keep the K/V of every block once (anchor copies never exist here).
   // The attention kernels read plain inputs where they are and file them in the
   // caches themselves; rotated keys go through the caches.
-  if (rope && (launch_rope_rotate(shape->dtype, g.B, g.L, g.Hq, g.d, rope->pos0, rope->theta, Q, Q, st) !=
-                   hipSuccess ||
-               launch_rope_cache_write(g, shape->dtype, K, K_cache, g.L, 0, rope->pos0, rope->theta, st) !=
-                   hipSuccess ||
-               launch_cache_write(g, shape->dtype, nullptr, V, K_cache, V_cache, g.L, 0, st) != hipSuccess))
+  if (rope && launch_rope(shape->dtype, g, g.Hq, Q, Q, K, V, K_cache, V_cache, g.L, 0, rope->pos0, rope->theta,
+                          tickets, st) != hipSuccess)
     return STAR_ATTN_ERR_LAUNCH_FAILED;
   Phase1Args a;
   a.g = g; a.Q = Q; a.O = O_ctx; a.LSE = LSE_ctx; a.Kc = K_cache; a.Vc = V_cache;
@@ -389,6 +386,7 @@ static int phase1_impl(const star_attn_shape* shape, int anchor_mode, const Rope
   a.Kin = rope ? nullptr : K;
   a.Vin = rope ? nullptr : V;
   a.tickets = tickets;
+  a.tickets_clear = rope ? 1 : 0;
   a.n_cu = ds ? ds->n_cu : 0;
   hipError_t e = shape->dtype == STAR_ATTN_F32 ? launch_phase1_f32(a, st) : launch_phase1_bf16(a, st);
   return e == hipSuccess ? STAR_ATTN_OK : STAR_ATTN_ERR_LAUNCH_FAILED;
@@ -430,8 +428,8 @@ int star_attn_rope(const star_attn_shape* shape, int32_t n_heads, int64_t n_toke
   if (n_heads <= 0 || n_tokens <= 0) return STAR_ATTN_ERR_INVALID_SHAPE;
   if (!X || !Y) return STAR_ATTN_ERR_NULL_POINTER;
   if (misaligned(X) || misaligned(Y)) return STAR_ATTN_ERR_MISALIGNED;
-  hipError_t e = launch_rope_rotate(shape->dtype, shape->batch, n_tokens, n_heads, shape->head_dim,
-                                    pos0, rope_theta, X, Y, (hipStream_t)hip_stream);
+  hipError_t e = launch_rope(shape->dtype, make_geom(shape), n_heads, X, Y, nullptr, nullptr, nullptr, nullptr,
+                             n_tokens, 0, pos0, rope_theta, nullptr, (hipStream_t)hip_stream);
   return e == hipSuccess ? STAR_ATTN_OK : STAR_ATTN_ERR_LAUNCH_FAILED;
 }
 
@@ -487,13 +485,8 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   if (!append) {
     // a context host's share: the cache is read as it is
   } else if (rope) {
-    const int64_t pos = rope->pos0 + cache_len;
-    if (launch_rope_rotate(shape->dtype, g.B, q_len, g.Hq, g.d, pos, rope->theta, Qq, Qq, st) !=
-            hipSuccess ||
-        launch_rope_cache_write(g, shape->dtype, Kq, K_cache, q_len, cache_len, pos, rope->theta,
-                                st) != hipSuccess ||
-        launch_cache_write(g, shape->dtype, nullptr, Vq, K_cache, V_cache, q_len, cache_len, st) !=
-            hipSuccess)
+    if (launch_rope(shape->dtype, g, g.Hq, Qq, Qq, Kq, Vq, K_cache, V_cache, q_len, cache_len,
+                    rope->pos0 + cache_len, rope->theta, nullptr, st) != hipSuccess)
       return STAR_ATTN_ERR_LAUNCH_FAILED;
   } else if (!fused_append && launch_cache_write(g, shape->dtype, Kq, Vq, K_cache, V_cache, q_len,
                                                  cache_len, st) != hipSuccess) {

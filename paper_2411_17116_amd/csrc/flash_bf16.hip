@@ -666,8 +666,8 @@ __device__ __forceinline__ void load_q(WaveState& w, int rb, const char* qrow, i
 // XCDs of one chip differ by a few per cent in clock under the power limit, and
 // with a fixed share each the launch would last as long as the slowest needs.
 // The eight counters belong to the launch (the caller's workspace, or a set of
-// the library's own that no launch in flight holds); a one-workgroup kernel in
-// front of the launch clears them.
+// the library's own that no launch in flight holds); the kernel that rotates a call's
+// projections, or a one-workgroup kernel in front of the launch, clears them.
 __global__ void phase1_tickets_reset_kernel(unsigned int* tickets) {
   if (threadIdx.x < 8) tickets[threadIdx.x] = 0u;
 }
@@ -938,8 +938,10 @@ hipError_t launch_phase1_bf16(const Phase1Args& a, hipStream_t st) {
   if (NW == 4) n_cu *= 2;
   const unsigned resident = (unsigned)(wgs < n_cu ? wgs : n_cu);
   if (resident == 0) return hipSuccess;
-  phase1_tickets_reset_kernel<<<1, 64, 0, st>>>(a.tickets);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (!a.tickets_clear) {
+    phase1_tickets_reset_kernel<<<1, 64, 0, st>>>(a.tickets);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   phase1_bf16_kernel<<<dim3(resident), NT, 4 * TILEB, st>>>(a, hpw, tpb, n_hs, (unsigned)wgs);
   return hipGetLastError();
 }

@@ -7,21 +7,26 @@
 // Llama family the paper evaluates: dimension i < d/2 pairs with i + d/2 and the
 // pair is turned by pos * theta^(-2i/d).
 //
-// Two kernels, both pure HBM streams (16 bytes per access):
-//   * rope_rotate_kernel      X [B, T, H, d] -> Y [B, T, H, d] (Y may be X),
-//   * rope_cache_write_kernel K [B, T, Hkv, d] -> K cache [B, Hkv, cap, d]: the
-//     layout change of the cache writer with the rotation applied on the way.
-// A thread owns one (token, group of 16-byte chunk pairs): it evaluates the
-// angles once -- in double precision, because pos * frequency reaches 1e6 rad
-// and fp32 cannot hold its fractional turn -- and reuses the sines and cosines
-// for every head of the token.
+// One kernel does everything a call needs before it can attend: Q is rotated (in
+// place, or X -> Y for the rotation alone), K is rotated on its way from
+// [B, T, Hkv, d] into the head-major cache [B, Hkv, cap, d], and V goes there as it
+// is.  It is bound by HBM for a prefill and by latency for a decode step:
+//   * A workgroup owns TT tokens.  Their d/2 angles each are evaluated once into LDS
+//     (a thread's angles share the frequency) -- in double precision, because
+//     pos * frequency reaches 1e6 rad and fp32 cannot hold its fractional turn -- and
+//     serve all heads.
+//   * Then every thread keeps one (token, pair of 16-byte chunks) and walks the
+//     token's rows (query heads, key heads, value heads), BATCH rows requested before
+//     the first is stored: rows rotated in place would otherwise be a chain of round
+//     trips (nothing may be loaded ahead of a store that could alias it).
+// Measured: a decode token of the 32 / 8-head shape (48 rows) 2.6 us, where two kernels
+// that walked the heads in turn and a copy took 15 + 6 + 2.8 (and two more launch gaps).
 #include "star_internal.h"
 
 namespace star {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 
@@ -29,111 +34,159 @@ template <typename T> struct Chunk;
 template <> struct Chunk<float> {
   static constexpr int N = 4;
   typedef f32x4 vec;
-  static __device__ __forceinline__ void load(const void* p, float (&x)[4]) {
-    f32x4 v = *(const f32x4*)p;
-    x[0] = v[0]; x[1] = v[1]; x[2] = v[2]; x[3] = v[3];
-  }
-  static __device__ __forceinline__ void store(void* p, const float (&x)[4]) {
-    *(f32x4*)p = f32x4{x[0], x[1], x[2], x[3]};
-  }
+  static __device__ __forceinline__ vec pack(const float (&x)[4]) { return f32x4{x[0], x[1], x[2], x[3]}; }
 };
 template <> struct Chunk<__bf16> {
   static constexpr int N = 8;
-  static __device__ __forceinline__ void load(const void* p, float (&x)[8]) {
-    bf16x8 v = *(const bf16x8*)p;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = (float)v[e];
-  }
-  static __device__ __forceinline__ void store(void* p, const float (&x)[8]) {
+  typedef bf16x8 vec;
+  static __device__ __forceinline__ vec pack(const float (&x)[8]) {
     bf16x8 v;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = (__bf16)x[e];      // round to nearest even
-    *(bf16x8*)p = v;
+    return v;
   }
 };
 
-// cos and sin of pos * theta^(-2i/d), i = i0 .. i0 + N - 1
-template <int N>
-__device__ __forceinline__ void angles(int64_t pos, int i0, int d, double log2_theta,
-                                       float (&cs)[N], float (&sn)[N]) {
+constexpr int THREADS = 256;
+constexpr int BATCH = 3;
+
+struct RopeArgs {
+  const void* X;          // [B, T, H, d] -> Y, same layout (Y may be X)
+  void* Y;
+  const void* K;          // [B, T, Hkv, d] -> rows [dst_row, dst_row + T) of Kc [B, Hkv, cap, d],
+  const void* V;          // rotated, and V -> Vc as it is (Hkv = 0: neither)
+  void* Kc;
+  void* Vc;
+  int32_t H, Hkv;
+  uint32_t n_tokens, total;   // T, B T
+  int64_t cap, dst_row, pos0;
+  double log2_theta;
+  unsigned int* clear;    // eight counters to zero for the launch behind this one, or null
+};
+
+// theta^(-2i/d), and cos and sin of pos times that
+__device__ __forceinline__ double frequency(int i, int d, double log2_theta) {
+  return exp2(-2.0 * (double)i / (double)d * log2_theta);
+}
+__device__ __forceinline__ void angle(int64_t pos, double inv_freq, float* cs, float* sn) {
   const double TWO_PI = 6.283185307179586476925, INV_TWO_PI = 0.1591549430918953357689;
-#pragma unroll
-  for (int e = 0; e < N; ++e) {
-    double inv_freq = exp2(-2.0 * (double)(i0 + e) / (double)d * log2_theta);
-    double ang = (double)pos * inv_freq;
-    double r = fma(-rint(ang * INV_TWO_PI), TWO_PI, ang);     // |r| <= pi
-    double s, c;
-    sincos(r, &s, &c);
-    cs[e] = (float)c;
-    sn[e] = (float)s;
-  }
+  double ang = (double)pos * inv_freq;
+  double r = fma(-rint(ang * INV_TWO_PI), TWO_PI, ang);     // |r| <= pi
+  double s, c;
+  sincos(r, &s, &c);
+  *cs = (float)c;
+  *sn = (float)s;
 }
 
-// Rows are [batch, token, head, d]; dst_row_stride / dst_head_stride describe
-// where (batch, token, head) lands in the destination, in elements.
-template <typename T>
-__global__ __launch_bounds__(256) void rope_kernel(const T* X, T* Y, int64_t n_tokens,
-                                                   int H, int d, int64_t pos0, double log2_theta,
-                                                   int64_t dst_batch_stride, int64_t dst_token_stride,
-                                                   int64_t dst_head_stride, int64_t n_threads) {
+template <typename T, int half, int TT>
+__global__ __launch_bounds__(THREADS) void rope_kernel(RopeArgs a) {
   constexpr int N = Chunk<T>::N;
-  const int cpr = d / 2 / N;                       // chunk pairs per row
-  int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= n_threads) return;
-  int c = (int)(id % cpr);
-  int64_t bt = id / cpr;
-  int64_t t = bt % n_tokens, beta = bt / n_tokens;
-  float cs[N], sn[N];
-  angles<N>(pos0 + t, c * N, d, log2_theta, cs, sn);
-  const T* src = X + (bt * H) * (int64_t)d + c * N;
-  T* dst = Y + beta * dst_batch_stride + t * dst_token_stride + c * N;
-  for (int h = 0; h < H; ++h) {
-    float lo[N], hi[N], ylo[N], yhi[N];
-    Chunk<T>::load(src + (int64_t)h * d, lo);
-    Chunk<T>::load(src + (int64_t)h * d + d / 2, hi);
+  typedef typename Chunk<T>::vec vec;
+  __shared__ float cs_all[TT][half], sn_all[TT][half];
+  const int tid = threadIdx.x;
+  const uint32_t tok0 = blockIdx.x * TT;
+  if (a.clear && blockIdx.x == 0 && tid < 8) a.clear[tid] = 0u;
+  {
+    static_assert(THREADS % half == 0, "a thread's angles share their frequency");
+    const int i = tid % half;
+    const double inv_freq = frequency(i, 2 * half, a.log2_theta);
 #pragma unroll
-    for (int e = 0; e < N; ++e) {
-      ylo[e] = lo[e] * cs[e] - hi[e] * sn[e];
-      yhi[e] = hi[e] * cs[e] + lo[e] * sn[e];
+    for (int k0 = 0; k0 < TT; k0 += THREADS / half) {
+      const int k = k0 + tid / half;
+      if (k < TT)                                  // tokens past the last: angles nobody reads
+        angle(a.pos0 + (tok0 + k) % a.n_tokens, inv_freq, &cs_all[k][i], &sn_all[k][i]);
     }
-    Chunk<T>::store(dst + h * dst_head_stride, ylo);
-    Chunk<T>::store(dst + h * dst_head_stride + d / 2, yhi);
+  }
+  __syncthreads();
+
+  constexpr int cpr = half / N;                    // chunk pairs per row: 8 or 16
+  const int c = (tid % cpr) * N, k = (tid / cpr) % TT, slot = tid / (cpr * TT), n_slots = THREADS / (cpr * TT);
+  const uint32_t tok = tok0 + k;
+  if (tok >= a.total) return;
+  float cs[N], sn[N];
+#pragma unroll
+  for (int e = 0; e < N; ++e) { cs[e] = cs_all[k][c + e]; sn[e] = sn_all[k][c + e]; }
+  const uint32_t beta = tok / a.n_tokens, t = tok % a.n_tokens;
+  constexpr size_t d = 2 * half;
+  const size_t cache0 = ((size_t)beta * a.Hkv * a.cap + a.dst_row + t) * d + c;
+  const int n_rows = a.H + 2 * a.Hkv;
+  for (int h0 = slot; h0 < n_rows; h0 += BATCH * n_slots) {
+    vec lo[BATCH], hi[BATCH];
+    T* dst[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      int h = h0 + u * n_slots;
+      if (h >= n_rows) h = h0;                     // past the last: row h0 again, not stored
+      const T* src;
+      if (h < a.H) {
+        src = (const T*)a.X + ((size_t)tok * a.H + h) * d + c;
+        dst[u] = (T*)a.Y + ((size_t)tok * a.H + h) * d + c;
+      } else {
+        const bool v = h >= a.H + a.Hkv;
+        const int g = h - a.H - (v ? a.Hkv : 0);
+        src = (const T*)(v ? a.V : a.K) + ((size_t)tok * a.Hkv + g) * d + c;
+        dst[u] = (T*)(v ? a.Vc : a.Kc) + cache0 + (size_t)g * a.cap * d;
+      }
+      lo[u] = *(const vec*)src;
+      hi[u] = *(const vec*)(src + half);
+    }
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const int h = h0 + u * n_slots;
+      if (h >= n_rows) break;
+      if (h < a.H + a.Hkv) {
+        float ylo[N], yhi[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+          const float x = (float)lo[u][e], y = (float)hi[u][e];
+          ylo[e] = x * cs[e] - y * sn[e];
+          yhi[e] = y * cs[e] + x * sn[e];
+        }
+        lo[u] = Chunk<T>::pack(ylo);
+        hi[u] = Chunk<T>::pack(yhi);
+      }
+      *(vec*)dst[u] = lo[u];
+      *(vec*)(dst[u] + half) = hi[u];
+    }
   }
 }
 
-template <typename T>
-hipError_t launch(const void* X, void* Y, int B, int64_t n_tokens, int H, int d, int64_t pos0,
-                  double theta, int64_t sb, int64_t st_, int64_t sh, hipStream_t st) {
-  int cpr = d / 2 / Chunk<T>::N;
-  int64_t n_threads = (int64_t)B * n_tokens * cpr;
-  if (n_threads == 0) return hipSuccess;
-  int64_t blocks = (n_threads + 255) / 256;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  rope_kernel<T><<<dim3((unsigned)blocks), 256, 0, st>>>((const T*)X, (T*)Y, n_tokens, H, d, pos0,
-                                                         log2(theta), sb, st_, sh, n_threads);
+template <typename T, int half, int TT>
+hipError_t launch(const RopeArgs& a, hipStream_t st) {
+  rope_kernel<T, half, TT><<<dim3((a.total + TT - 1) / TT), THREADS, 0, st>>>(a);
   return hipGetLastError();
+}
+
+// Tokens per workgroup.  One where a token's rows keep 256 threads busy, or where there
+// are too few tokens to fill the GPU otherwise; four for fewer rows; sixteen where the
+// angles outweigh the rows.  Measured on 131072 tokens, d = 128, bf16, us with 1 / 4 / 16
+// tokens (a kernel that gave a thread all heads of its chunk, before): 32 rows 376 / 390 /
+// 413 (469), 16 rows 177 / 190 / 212 (240), 8 rows 92 / 76 / 81 (86), 4 rows 87 / 50 / 41
+// (44), 1 row 79 / 40 / 30 (35); 4000 tokens of 8 rows 8.6 / 7.5 / 7.6 (8.8).
+template <typename T, int half>
+hipError_t launch(const RopeArgs& a, hipStream_t st) {
+  const int64_t rows = (int64_t)a.H + 2 * a.Hkv;
+  if (rows >= 16 || a.total < 1024) return launch<T, half, 1>(a, st);
+  if (rows > 4 || a.total < 4096) return launch<T, half, 4>(a, st);
+  return launch<T, half, 16>(a, st);
 }
 
 }  // namespace
 
-// X [B, n_tokens, H, d] -> Y, same layout (Y may alias X), token t at pos0 + t.
-hipError_t launch_rope_rotate(int dtype, int B, int64_t n_tokens, int H, int d, int64_t pos0,
-                              double theta, const void* X, void* Y, hipStream_t st) {
-  int64_t sh = d, stk = (int64_t)H * d, sb = n_tokens * stk;
-  return dtype == 0 ? launch<float>(X, Y, B, n_tokens, H, d, pos0, theta, sb, stk, sh, st)
-                    : launch<__bf16>(X, Y, B, n_tokens, H, d, pos0, theta, sb, stk, sh, st);
-}
-
-// K [B, n_tokens, Hkv, d] -> rows [dst_row, dst_row + n_tokens) of the head-major
-// cache [B, Hkv, cap, d], token t rotated at pos0 + t.
-hipError_t launch_rope_cache_write(const Geom& g, int dtype, const void* K, void* Kc,
-                                   int64_t n_tokens, int64_t dst_row, int64_t pos0, double theta,
-                                   hipStream_t st) {
-  int64_t sh = g.cap * g.d, stk = g.d, sb = (int64_t)g.Hkv * g.cap * g.d;
-  size_t es = dtype == 0 ? 4 : 2;
-  void* dst = (char*)Kc + (size_t)dst_row * g.d * es;
-  return dtype == 0 ? launch<float>(K, dst, g.B, n_tokens, g.Hkv, g.d, pos0, theta, sb, stk, sh, st)
-                    : launch<__bf16>(K, dst, g.B, n_tokens, g.Hkv, g.d, pos0, theta, sb, stk, sh, st);
+hipError_t launch_rope(int dtype, const Geom& g, int H, const void* X, void* Y, const void* K, const void* V,
+                       void* Kc, void* Vc, int64_t n_tokens, int64_t dst_row, int64_t pos0, double theta,
+                       unsigned int* clear, hipStream_t st) {
+  const int64_t total = (int64_t)g.B * n_tokens;
+  if (total == 0) return hipSuccess;
+  if (total > 0x7fffffff) return hipErrorInvalidValue;      // (550 GB and more of one tensor)
+  RopeArgs a;
+  a.X = X; a.Y = Y; a.K = K; a.V = V; a.Kc = Kc; a.Vc = Vc;
+  a.H = H; a.Hkv = K ? g.Hkv : 0;
+  a.n_tokens = (uint32_t)n_tokens; a.total = (uint32_t)total;
+  a.cap = g.cap; a.dst_row = dst_row; a.pos0 = pos0; a.log2_theta = log2(theta);
+  a.clear = clear;
+  if (dtype != 0) return launch<__bf16, 64>(a, st);
+  return g.d == 64 ? launch<float, 32>(a, st) : launch<float, 64>(a, st);
 }
 
 }  // namespace star

@@ -60,6 +60,7 @@ struct Phase1Args {
   const void* Kin;      // the token-major inputs [B, L, Hkv, d] to read keys / values from (and to
   const void* Vin;      // file in the caches); null: read the caches
   unsigned int* tickets;  // bf16 kernel: this launch's eight work-queue counters (device memory)
+  int32_t tickets_clear;  // bf16 kernel: a preceding kernel of the call has zeroed them
   int32_t n_cu;           // bf16 kernel: compute units of the device the call runs on
 };
 
@@ -174,11 +175,12 @@ int device_cu_count();
 hipError_t launch_cache_write(const Geom& g, int dtype, const void* K, const void* V,
                               void* Kc, void* Vc, int64_t n_tokens, int64_t dst_row,
                               hipStream_t st);
-hipError_t launch_rope_rotate(int dtype, int B, int64_t n_tokens, int H, int d, int64_t pos0,
-                              double theta, const void* X, void* Y, hipStream_t st);
-hipError_t launch_rope_cache_write(const Geom& g, int dtype, const void* K, void* Kc,
-                                   int64_t n_tokens, int64_t dst_row, int64_t pos0, double theta,
-                                   hipStream_t st);
+// X [B, n_tokens, H, d] rotated into Y (same layout; Y may be X), token t at pos0 + t; with
+// K and V (null: neither) [B, n_tokens, Hkv, d], rotated K and V as it is into cache rows
+// [dst_row, dst_row + n_tokens).  `clear`: eight counters to zero on the way, or null.
+hipError_t launch_rope(int dtype, const Geom& g, int H, const void* X, void* Y, const void* K, const void* V,
+                       void* Kc, void* Vc, int64_t n_tokens, int64_t dst_row, int64_t pos0, double theta,
+                       unsigned int* clear, hipStream_t st);
 hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st);
 hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st);
 hipError_t launch_phase1_bf16(const Phase1Args& a, hipStream_t st);

@@ -205,3 +205,22 @@ def test_config2_shape_unrotated_inputs_sampled():
     triples = workloads.phase1_sample(cfg, inp.planted_ctx, n_random=64)
     del inp
     _rope_path(cfg, 500000.0, 0, triples=triples, heads=[0, 3, 31], decode_steps=[0, cfg.nd - 1])
+
+
+@pytest.mark.parametrize("dtype,d,B,T,H", [
+    ("bf16", 128, 2, 513, 3),        # few rows, few tokens
+    ("bf16", 128, 1, 4099, 2),       # few rows, many tokens, not a multiple of a workgroup's
+    ("bf16", 128, 3, 1367, 7),       # tokens of two sequences in one workgroup
+    ("bf16", 128, 1, 1030, 33),      # many rows
+    ("fp32", 64, 2, 2051, 1),
+    ("fp32", 128, 1, 1027, 9),
+])
+def test_rotation_workgroup_shapes(dtype, d, B, T, H):
+    """Every tokens-per-workgroup set-up of the rotation, ragged."""
+    gen = torch.Generator().manual_seed(T + H)
+    X = torch.randn((B, T, H, d), generator=gen).to(torch.float32 if dtype == "fp32" else torch.bfloat16).cuda()
+    shape = sa.StarShape.make(dtype, B, H, H, d, T, T, T, T)
+    want = so.rope_rotate(X.float().cpu().numpy(), 77 + np.arange(T), 500000.0)
+    sa.rope(shape, X, X, 500000.0, pos0=77)
+    torch.cuda.synchronize()
+    assert _storage_close(X, want, dtype)
