@@ -145,6 +145,46 @@ constexpr int64_t F32_SPLIT_MIN = 128;     // keys: one 16-key unit for each of 
 // 13.9 at 530 (one row, d = 64), splits and their merge 11.7 us at either.
 constexpr int64_t F32_DIRECT_BYTES = 256 << 10;
 
+// ---- bf16 row-tiled kernel: one workgroup per CU is resident (256 of them).
+constexpr int64_t ROW_WGS = 256;
+
+// Workgroups of one split.
+static int64_t rows_wgs(const Geom& g, int64_t q_len) {
+  const int64_t rows = (int64_t)g.G * q_len;
+  return (int64_t)g.B * g.Hkv * ceil_div(rows, flash_phase2_rows_per_workgroup(rows));
+}
+// Time of `splits` splits of `len` keys, in the time of one key tile: rounds of resident
+// workgroups, each of them its key tiles (64 keys; 128 where the halves of a workgroup
+// share them) and some 6 tiles' time (10 us) to start, fill the pipeline and store.
+static int64_t rows_cost(const Geom& g, int64_t q_len, int64_t splits, int64_t len) {
+  const int64_t tile = flash_phase2_rows_per_workgroup((int64_t)g.G * q_len) == 128 ? 128 : 64;
+  return ceil_div(splits * rows_wgs(g, q_len), ROW_WGS) * (ceil_div(len, tile) + 6);
+}
+// Largest number of splits whose per-split pairs a call may keep: what
+// star_attn_phase2_static's scratch holds, and at least `aligned`.
+static int64_t rows_splits_cap(const Geom& g, int64_t q_len, int64_t aligned) {
+  const int64_t pair = (int64_t)g.B * g.Hq * q_len * (g.d + 1) * 4;
+  const int64_t fit = STAR_ATTN_STATIC_SCRATCH_BYTES / pair;
+  return fit > aligned ? fit : aligned;
+}
+// Equal runs of keys for a call without per-part outputs: the number of splits that fills
+// the resident workgroups once, or, where a split's workgroups do not divide them, up to
+// four times.
+static int64_t rows_flat_splits(const Geom& g, int64_t q_len, int64_t total, int64_t cap) {
+  const int64_t wgs = rows_wgs(g, q_len);
+  int64_t best = 1, cost = rows_cost(g, q_len, 1, total);
+  for (int64_t k = 1; k <= 4; ++k) {
+    int64_t s = k * ROW_WGS / wgs;
+    if (s > ceil_div(total, 256)) s = ceil_div(total, 256);     // keys worth a split
+    if (s > cap) s = cap;
+    if (s < 1) continue;
+    const int64_t len = round_up(ceil_div(total, s), 64);
+    const int64_t c = rows_cost(g, q_len, ceil_div(total, len), len);
+    if (c < cost) { cost = c; best = s; }
+  }
+  return best;
+}
+
 // Split plan for a phase-2 call with q_len new tokens that can see `total`
 // cache rows.  Decode-sized calls (G * q_len rows fit one 16-column MFMA tile)
 // stream the cache: without per-part outputs the keys of each (batch, KV head)
@@ -201,8 +241,8 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
       min_len = F32_SPLIT_MIN;
     } else {
       const int64_t wgs = (int64_t)g.B * g.Hkv * (g.G / flash_heads_per_workgroup(g.G)) *
-                          ceil_div(q_len, flash_tokens_per_workgroup(g.G));   // per split
-      want = ceil_div(256, wgs);                     // one workgroup per CU
+                          ceil_div(q_len, flash_tokens_per_workgroup(g.G));
+      want = ceil_div(ROW_WGS, wgs);
       min_len = 256;
     }
     int64_t spb = ceil_div(want, n);
@@ -215,6 +255,19 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   int64_t st = tail_cap > 0 ? ceil_div(tail_cap, split_len) : 1;
   int64_t s_total = n * spb + st;
   if (s_total > (1 << 24)) return false;
+  if (s->dtype == STAR_ATTN_BF16 && !p->decode && !want_parts) {
+    // equal runs of keys instead of splits of every part, if they take less time
+    const int64_t splits = rows_flat_splits(g, q_len, total, rows_splits_cap(g, q_len, s_total));
+    const int64_t len = round_up(ceil_div(total, splits), 64);
+    if (rows_cost(g, q_len, splits, len) < rows_cost(g, q_len, s_total, split_len)) {
+      p->flat = 1;
+      p->split_len = len;
+      p->spb = 0;
+      p->st = 0;
+      p->s_total = (int32_t)ceil_div(total, len);
+      return true;
+    }
+  }
   p->split_len = split_len;
   p->spb = (int32_t)spb;
   p->st = (int32_t)st;
@@ -264,32 +317,53 @@ extern "C" {
 
 size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len) {
   if (validate_shape(shape) != STAR_ATTN_OK || max_q_len <= 0) return 0;
-  // The plan depends on q_len only through the number of row tiles, so the
-  // largest requirement is found at tile boundaries and at max_q_len itself.  The
-  // fp32 kernel's tiles hold 32 / G tokens, which need not be a whole number: every
-  // q_len is looked at there, up to where one split per part fills the GPU.
+  // The plan depends on q_len only through the number of row tiles, so the largest
+  // requirement is found at tile boundaries and at max_q_len itself.
+  const Geom g = make_geom(shape);
   size_t best = 0;
+  auto need = [&](int64_t splits, int64_t q) {
+    SplitPlan p = {};
+    p.s_total = (int32_t)splits;
+    size_t b = plan_bytes(shape, p, q);
+    if (b > best) best = b;
+  };
   auto consider = [&](int64_t q) {
     if (q < 1 || q > max_q_len) return;
-    for (int parts = 0; parts < 2; ++parts) {
-      SplitPlan p;
-      // the number of splits never exceeds what the full cache needs
-      if (!make_plan(shape, q, shape->cache_capacity, parts != 0, &p)) continue;
-      if (p.flat) {   // a shorter cache may need more splits than the full one; bound them
-        int64_t pairs = (int64_t)shape->batch * shape->n_kv_heads;
-        int64_t s0 = p.decode ? (decode_slots_max() / pairs > 1 ? decode_slots_max() / pairs : 1)
-                              : f32_splits_max(make_geom(shape), q);
-        if (p.s_total < s0) p.s_total = (int32_t)s0;
-      }
-      size_t b = plan_bytes(shape, p, q);
-      if (b > best) best = b;
+    SplitPlan p;
+    // the number of part-aligned splits never exceeds what the full cache needs
+    const bool ok = make_plan(shape, q, shape->cache_capacity, true, &p);
+    const int64_t aligned = ok ? p.s_total : 0;
+    need(aligned, q);
+    // a shorter cache may be cut into more equal runs than the full one; bound them
+    if (p.decode) {
+      int64_t pairs = (int64_t)g.B * g.Hkv;
+      int64_t s0 = decode_slots_max() / pairs > 1 ? decode_slots_max() / pairs : 1;
+      SplitPlan f;
+      if (make_plan(shape, q, shape->cache_capacity, false, &f)) need(f.s_total > s0 ? f.s_total : s0, q);
+    } else if (shape->dtype == STAR_ATTN_F32) {
+      need(f32_splits_max(g, q), q);
+    } else if (ok) {
+      int64_t most = 4 * ROW_WGS / rows_wgs(g, q), worth = ceil_div(g.cap, 256);
+      if (most > worth) most = worth;
+      if (most < 1) most = 1;
+      SplitPlan f = {};
+      f.s_total = (int32_t)most;
+      if (plan_bytes(shape, f, q) <= STAR_ATTN_STATIC_SCRATCH_BYTES) need(most, q);
+      else if (best < STAR_ATTN_STATIC_SCRATCH_BYTES) best = STAR_ATTN_STATIC_SCRATCH_BYTES;   // rows_splits_cap
+      need(1, q);
     }
   };
   for (int64_t q = 1; q <= max_q_len && q <= 64; ++q) consider(q);
   if (shape->dtype == STAR_ATTN_F32) {
+    // tiles hold 32 / G tokens, not a whole number: every q_len up to where one split
+    // per part fills the GPU
     for (int64_t q = 65; q <= max_q_len && q <= 256 * 32; ++q) consider(q);
   } else {
     for (int64_t q = 64; q <= max_q_len; q += 32) { consider(q); consider(q + 1); }
+    // the equal runs' tiles end elsewhere (256 / G or 128 / G tokens)
+    for (int64_t q = 65; q < max_q_len && q <= 4096; ++q)
+      if (rows_wgs(g, q + 1) != rows_wgs(g, q)) consider(q);
+    if (max_q_len > 4096 && best < STAR_ATTN_STATIC_SCRATCH_BYTES) best = STAR_ATTN_STATIC_SCRATCH_BYTES;
   }
   consider(max_q_len);
   return best;
@@ -478,20 +552,13 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   hipStream_t st = (hipStream_t)hip_stream;
 
   // Algorithm 2: the new tokens' K/V join the cache before they attend.  The
-  // streaming decode kernel and the fp32 kernel append them themselves (they read the
-  // new rows from Kq/Vq and write them to the cache); the bf16 row-tiled kernel uses
-  // the cache writer.  Unrotated keys are rotated into the cache first.
-  const bool fused_append = append && !rope && (plan.decode || shape->dtype == STAR_ATTN_F32);
-  if (!append) {
-    // a context host's share: the cache is read as it is
-  } else if (rope) {
-    if (launch_rope(shape->dtype, g, g.Hq, Qq, Qq, Kq, Vq, K_cache, V_cache, q_len, cache_len,
-                    rope->pos0 + cache_len, rope->theta, nullptr, st) != hipSuccess)
-      return STAR_ATTN_ERR_LAUNCH_FAILED;
-  } else if (!fused_append && launch_cache_write(g, shape->dtype, Kq, Vq, K_cache, V_cache, q_len,
-                                                 cache_len, st) != hipSuccess) {
+  // attention kernels append them themselves (they read the new rows from Kq/Vq and
+  // write them to the cache).  Unrotated keys are rotated into the cache first.
+  const bool fused_append = append && !rope;
+  if (append && rope &&
+      launch_rope(shape->dtype, g, g.Hq, Qq, Qq, Kq, Vq, K_cache, V_cache, q_len, cache_len,
+                  rope->pos0 + cache_len, rope->theta, nullptr, st) != hipSuccess)
     return STAR_ATTN_ERR_LAUNCH_FAILED;
-  }
 
   size_t rows = (size_t)g.B * plan.s_total * g.Hq * (size_t)q_len;
   Phase2Args a;

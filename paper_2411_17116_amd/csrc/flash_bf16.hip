@@ -73,16 +73,16 @@ constexpr int TILEB = TKEYS * ROWB;        // 16 KiB
 constexpr int LDS_K0 = 0, LDS_K1 = TILEB, LDS_V0 = 2 * TILEB, LDS_V1 = 3 * TILEB;
 // Wavefronts per workgroup.  All of them walk the same K/V tiles, so the L2 -> LDS
 // traffic per flop falls with NW; 8 wavefronts of <= 256 registers are two per SIMD.
-#ifndef STAR_FLASH_WAVES
-#define STAR_FLASH_WAVES 8
-#endif
-constexpr int NW = STAR_FLASH_WAVES;
+constexpr int NW = 8;
 constexpr int NT = 64 * NW;                // threads per workgroup
 constexpr int RB = 2;                      // 16-row blocks per wavefront
 constexpr int WG_BLOCKS = NW * RB;         // 16-row blocks per workgroup
-constexpr int DMA_ROWS = NT / 16;          // key rows one DMA instruction of the workgroup moves
-constexpr int DMA_ITERS = TKEYS / DMA_ROWS;
-static_assert(NW == 4 || NW == 8, "tile DMA is written for 4 or 8 wavefronts");
+static_assert(NW == 8, "the row-tiled kernels are written for 8 wavefronts");
+// W wavefronts share a ring of tiles (and walk its tiles together): all eight of a
+// workgroup, or the four of either half, each half with a ring and tiles of its own.
+// One DMA instruction of each of them moves DMA_ROWS key rows.
+template <int W> constexpr int DMA_ROWS = 64 * W / 16;
+template <int W> constexpr int DMA_ITERS = TKEYS / DMA_ROWS<W>;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -129,16 +129,18 @@ __device__ __forceinline__ float quad_sum(float x) {
 // to the compiler, which would drop a builtin s_waitcnt it believes redundant.
 __device__ __forceinline__ void wait_vmcnt0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // all but the two most recent tile DMAs (DMA_ITERS instructions each) have landed
+template <int W>
 __device__ __forceinline__ void wait_vmcnt_2tiles() {
-  if (DMA_ITERS == 4) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  if (DMA_ITERS<W> == 4) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
 }
 
 // Sequence of key tiles a workgroup walks: first the tiles of the anchor rows
-// [a_lo, a_hi) of Ka / Va (n_a of them), then the tiles of rows [loc_lo, loc_hi)
-// of Kl / Vl.  All four are bases of one (batch, KV head); consecutive key rows
+// [a_lo, a_hi) of Ka / Va (n_a of them; phase 2: the rows cached before the call), then
+// the tiles of rows [loc_lo, loc_hi) of Kl / Vl (phase 2: the call's own).  All four are bases of one (batch, KV head); consecutive key rows
 // are a_stride / l_stride bytes apart (ROWB in a head-major cache, Hkv * ROWB in
-// a token-major input tensor).
+// a token-major input tensor).  The two halves of a workgroup (W = 4) take its tiles in
+// turn: n_tiles counts the half's own, and the idx-th of them is tile 2 idx + half.
 struct TileSeq {
   int n_a;
   int n_tiles;
@@ -152,13 +154,17 @@ struct TileSeq {
   const char* Vl;
   int a_stride;
   int l_stride;
-  __device__ __forceinline__ int stride(int idx) const { return idx < n_a ? a_stride : l_stride; }
-  __device__ __forceinline__ void tile(int idx, int* key0, int* hi) const {
-    if (idx < n_a) { *key0 = a_lo + idx * TKEYS; *hi = a_hi; }
-    else { *key0 = loc_lo + (idx - n_a) * TKEYS; *hi = loc_hi; }
+  int half;             // W = 4 only
+  template <int W> __device__ __forceinline__ int at(int idx) const { return W == NW ? idx : 2 * idx + half; }
+  template <int W> __device__ __forceinline__ bool anchor(int idx) const { return at<W>(idx) < n_a; }
+  template <int W> __device__ __forceinline__ int stride(int idx) const { return anchor<W>(idx) ? a_stride : l_stride; }
+  template <int W> __device__ __forceinline__ void tile(int idx, int* key0, int* hi) const {
+    const int i = at<W>(idx);
+    if (i < n_a) { *key0 = a_lo + i * TKEYS; *hi = a_hi; }
+    else { *key0 = loc_lo + (i - n_a) * TKEYS; *hi = loc_hi; }
   }
-  __device__ __forceinline__ const char* kbase(int idx) const { return idx < n_a ? Ka : Kl; }
-  __device__ __forceinline__ const char* vbase(int idx) const { return idx < n_a ? Va : Vl; }
+  template <int W> __device__ __forceinline__ const char* kbase(int idx) const { return anchor<W>(idx) ? Ka : Kl; }
+  template <int W> __device__ __forceinline__ const char* vbase(int idx) const { return anchor<W>(idx) ? Va : Vl; }
 };
 
 // A wavefront's state.  Lane (col = lane % 16, j4 = lane / 16) belongs to query
@@ -180,7 +186,7 @@ struct LaneAddr {
   unsigned k[4];       // K operand: row col, chunk 4 j4 + t (swizzled)
   unsigned v[8];       // V^T operand: see lane_addr()
   unsigned dma;        // byte offset of this thread's 16-byte unit inside its key row
-  int tid;
+  int tid;             // among the W wavefronts that share a ring
   int j4;
   bool upper;          // wave-uniform: the second of the two wavefronts that share a SIMD
 };
@@ -189,6 +195,7 @@ struct LaneAddr {
 // `tid` moves the 16-byte unit (row it*DMA_ROWS + tid/16, slot tid%16) for each it;
 // rows at or past `hi` re-read the last valid row (they are masked in the score
 // tile, and finite values keep 0 * V finite).
+template <int W>
 __device__ __forceinline__ void issue_tile(const char* base, int stride, int key0, int hi,
                                            unsigned lds, const LaneAddr& la) {
   unsigned wave_base = __builtin_amdgcn_readfirstlane((la.tid & ~63) * 16);
@@ -196,15 +203,15 @@ __device__ __forceinline__ void issue_tile(const char* base, int stride, int key
     const char* sb = base + (size_t)key0 * stride;
     const unsigned voff = (unsigned)(la.tid >> 4) * stride + la.dma;
 #pragma unroll
-    for (int it = 0; it < DMA_ITERS; ++it)
-      dma16(sb + (size_t)(it * DMA_ROWS) * stride, voff, lds + it * DMA_ROWS * ROWB + wave_base);
+    for (int it = 0; it < DMA_ITERS<W>; ++it)
+      dma16(sb + (size_t)(it * DMA_ROWS<W>) * stride, voff, lds + it * DMA_ROWS<W> * ROWB + wave_base);
   } else {                             // ragged tile: clamp each lane's row below hi
     const char* sb = base + (size_t)key0 * stride;
 #pragma unroll
-    for (int it = 0; it < DMA_ITERS; ++it) {
-      int row = it * DMA_ROWS + (la.tid >> 4);
+    for (int it = 0; it < DMA_ITERS<W>; ++it) {
+      int row = it * DMA_ROWS<W> + (la.tid >> 4);
       row = key0 + row < hi ? row : hi - 1 - key0;
-      dma16(sb, (unsigned)row * (unsigned)stride + la.dma, lds + it * DMA_ROWS * ROWB + wave_base);
+      dma16(sb, (unsigned)row * (unsigned)stride + la.dma, lds + it * DMA_ROWS<W> * ROWB + wave_base);
     }
   }
 }
@@ -465,7 +472,7 @@ struct LoopRegs {
   bf16x8 pA[RB], pB[RB];      // their exponentials (bf16)
 };
 
-template <bool SAFE, bool MORE, int KN, int VC, int KF, int VF>
+template <int W, bool SAFE, bool MORE, int KN, int VC, int KF, int VF>
 __device__ __forceinline__ void tile_step(WaveState& w, const LaneAddr& la, const TileSeq& seq,
                                           int t, const int (&row_lim)[RB], int wave_lo, float c,
                                           unsigned lds0, LoopRegs& r) {
@@ -476,15 +483,15 @@ __device__ __forceinline__ void tile_step(WaveState& w, const LaneAddr& la, cons
   __builtin_amdgcn_s_barrier();
   if (t + 2 < seq.n_tiles) {
     int k2, h2;
-    seq.tile(t + 2, &k2, &h2);
-    issue_tile(seq.kbase(t + 2), seq.stride(t + 2), k2, h2, lds0 + KF, la);
+    seq.tile<W>(t + 2, &k2, &h2);
+    issue_tile<W>(seq.kbase<W>(t + 2), seq.stride<W>(t + 2), k2, h2, lds0 + KF, la);
   }
   if (MORE) {
     int nk0, nhi;
-    seq.tile(t + 1, &nk0, &nhi);
-    issue_tile(seq.vbase(t + 1), seq.stride(t + 1), nk0, nhi, lds0 + VF, la);
+    seq.tile<W>(t + 1, &nk0, &nhi);
+    issue_tile<W>(seq.vbase<W>(t + 1), seq.stride<W>(t + 1), nk0, nhi, lds0 + VF, la);
     // one wave-uniform test per tile: does any of its keys need a mask for this wavefront?
-    const bool anchor_tile = t + 1 < seq.n_a;
+    const bool anchor_tile = seq.anchor<W>(t + 1);
     const int mask_from = anchor_tile ? nhi : (wave_lo < nhi ? wave_lo : nhi);
     const bool need_mask = nk0 + TKEYS > mask_from;
     // The two wavefronts of a SIMD take turns at the higher issue priority, one
@@ -513,7 +520,7 @@ __device__ __forceinline__ void tile_step(WaveState& w, const LaneAddr& la, cons
 //   row_lim     this lane's exclusive causal key bound per row block (0 = inactive row)
 //   wave_lo     smallest row_lim among the wavefront's active rows: key tiles that
 //               end at or below it need no causal mask
-template <bool SAFE>
+template <int W, bool SAFE>
 __device__ __forceinline__ void key_loop(WaveState& w, const LaneAddr& la, const TileSeq& seq,
                                          const int (&row_lim)[RB], int wave_lo, float c,
                                          unsigned lds0) {
@@ -525,22 +532,22 @@ __device__ __forceinline__ void key_loop(WaveState& w, const LaneAddr& la, const
   int key0, hi;
 
   // Prologue: K tile 0, V tile 0 and K tile 1 in flight; scores of tile 0.
-  seq.tile(0, &key0, &hi);
-  issue_tile(seq.kbase(0), seq.stride(0), key0, hi, lds0 + K0, la);
-  issue_tile(seq.vbase(0), seq.stride(0), key0, hi, lds0 + V0, la);
+  seq.tile<W>(0, &key0, &hi);
+  issue_tile<W>(seq.kbase<W>(0), seq.stride<W>(0), key0, hi, lds0 + K0, la);
+  issue_tile<W>(seq.vbase<W>(0), seq.stride<W>(0), key0, hi, lds0 + V0, la);
   if (T > 1) {
     int k1, h1;
-    seq.tile(1, &k1, &h1);
-    issue_tile(seq.kbase(1), seq.stride(1), k1, h1, lds0 + K1, la);
-    wait_vmcnt_2tiles();
+    seq.tile<W>(1, &k1, &h1);
+    issue_tile<W>(seq.kbase<W>(1), seq.stride<W>(1), k1, h1, lds0 + K1, la);
+    wait_vmcnt_2tiles<W>();
   } else {
     wait_vmcnt0();
   }
   __builtin_amdgcn_s_barrier();
   stage<SAFE, true, false, false, K0, 0>(w, la, r.sA, r.sA, r.pA, r.pA, c, alpha, pre);
-  mask_if_needed(r.sA, key0, hi, wave_lo, row_lim, la.j4, seq.n_a > 0);
+  mask_if_needed(r.sA, key0, hi, wave_lo, row_lim, la.j4, seq.anchor<W>(0));
   stage<SAFE, true, false, false, K0 + H, 0>(w, la, r.sB, r.sA, r.pA, r.pA, c, alpha, pre);
-  mask_if_needed(r.sB, key0 + 32, hi, wave_lo, row_lim, la.j4, seq.n_a > 0);
+  mask_if_needed(r.sB, key0 + 32, hi, wave_lo, row_lim, la.j4, seq.anchor<W>(0));
   // first unit: its row maximum becomes the reference (nothing to rescale yet)
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -554,14 +561,14 @@ __device__ __forceinline__ void key_loop(WaveState& w, const LaneAddr& la, const
   // and the accumulators flow through straight-line code.
   int t = 0;
   for (; t + 2 < T; t += 2) {
-    tile_step<SAFE, true, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
-    tile_step<SAFE, true, K0, V1, K1, V0>(w, la, seq, t + 1, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, SAFE, true, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, SAFE, true, K0, V1, K1, V0>(w, la, seq, t + 1, row_lim, wave_lo, c, lds0, r);
   }
   if (T - t == 2) {
-    tile_step<SAFE, true, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
-    tile_step<SAFE, false, K0, V1, K1, V0>(w, la, seq, t + 1, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, SAFE, true, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, SAFE, false, K0, V1, K1, V0>(w, la, seq, t + 1, row_lim, wave_lo, c, lds0, r);
   } else {
-    tile_step<SAFE, false, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, SAFE, false, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
   }
   __builtin_amdgcn_s_setprio(0);
 }
@@ -580,14 +587,15 @@ __device__ __forceinline__ void reset_state(WaveState& w) {
 }
 
 // LDS addresses of the calling lane.
+template <int W>
 __device__ __forceinline__ LaneAddr lane_addr(unsigned lds0) {
   LaneAddr la;
-  la.tid = threadIdx.x;
+  la.tid = W == NW ? threadIdx.x : threadIdx.x & (64 * W - 1);
   const int lane = la.tid & 63;
   const int col = lane & 15;
   la.j4 = lane >> 4;
   // eight wavefronts on four SIMDs: wavefronts w and w + 4 share one
-  la.upper = __builtin_amdgcn_readfirstlane((la.tid >> 8) & 1) != 0;
+  la.upper = __builtin_amdgcn_readfirstlane((threadIdx.x >> 8) & 1) != 0;
   // K operand: in MFMA step t, lane (col, j4) reads row col, chunk 4 j4 + t (any
   // assignment of d-chunks to (t, j4) works as long as Q uses the same one; this
   // one keeps the 16-byte reads of a wavefront free of LDS bank conflicts, the
@@ -604,12 +612,25 @@ __device__ __forceinline__ LaneAddr lane_addr(unsigned lds0) {
   return la;
 }
 
+// The key loop, and the barriers a half with fewer tiles than the other still owes it.
+template <int W, bool SAFE>
+__device__ __forceinline__ void key_loop_in_step(WaveState& w, const LaneAddr& la, const TileSeq& seq,
+                                                 const int (&row_lim)[RB], int wave_lo, float c, unsigned lds0,
+                                                 int most_tiles) {
+  if (W == NW || seq.n_tiles > 0) key_loop<W, SAFE>(w, la, seq, row_lim, wave_lo, c, lds0);
+  if (W != NW)
+    for (int t = seq.n_tiles > 0 ? seq.n_tiles : -1; t < most_tiles; ++t) __builtin_amdgcn_s_barrier();
+}
+
 // Attention of the workgroup's rows over a tile sequence: the fast loop, and the
 // exact loop again if any wavefront's scores left the fast loop's safe range.
+//   lds_wg      base of the workgroup's LDS; lds0 that of the calling wavefront's ring
+//   most_tiles  tiles of the half that has more (W = 4), or seq.n_tiles
+template <int W>
 __device__ __forceinline__ void attend(WaveState& w, const TileSeq& seq, const int (&row_lim)[RB],
-                                       int wave_lo, float c, unsigned lds0) {
-  const LaneAddr la = lane_addr(lds0);
-  if (seq.n_tiles == 0) return;
+                                       int wave_lo, float c, unsigned lds0, unsigned lds_wg, int most_tiles) {
+  const LaneAddr la = lane_addr<W>(lds0);
+  if (most_tiles == 0) return;
   // Consume the Q fragments here so that the compiler places its own wait for
   // their loads before the first DMA is in flight (and none inside the loops).
 #pragma unroll
@@ -620,7 +641,7 @@ __device__ __forceinline__ void attend(WaveState& w, const TileSeq& seq, const i
     const __bf16 o = (la.tid & 15) == 0 ? (__bf16)1.0f : (__bf16)0.0f;
     w.ones = bf16x8{o, o, o, o, o, o, o, o};
   }
-  key_loop<false>(w, la, seq, row_lim, wave_lo, c, lds0);
+  key_loop_in_step<W, false>(w, la, seq, row_lim, wave_lo, c, lds0, most_tiles);
   // row 0 of the ones-row product sits in element 0 of the lanes with j4 == 0: the row's whole sum
   // (quad_sum over the row's four lanes then finds it once); sums that left the safe range show here
 #pragma unroll
@@ -634,8 +655,8 @@ __device__ __forceinline__ void attend(WaveState& w, const TileSeq& seq, const i
   // flag writes, the writes before the reads, and the reads before any new DMA.
   __syncthreads();
   const bool bad = __builtin_amdgcn_ballot_w64(!(w.lmax < LSUM_LIMIT)) != 0;
-  LDS_AS int* flags = (LDS_AS int*)(size_t)lds0;
-  if ((la.tid & 63) == 0) flags[la.tid >> 6] = bad ? 1 : 0;
+  LDS_AS int* flags = (LDS_AS int*)(size_t)lds_wg;
+  if ((la.tid & 63) == 0) flags[threadIdx.x >> 6] = bad ? 1 : 0;
   __syncthreads();
   int any_bad = 0;
 #pragma unroll
@@ -643,7 +664,8 @@ __device__ __forceinline__ void attend(WaveState& w, const TileSeq& seq, const i
   __syncthreads();
   if (__builtin_expect(any_bad != 0, 0)) {
     reset_state(w);
-    key_loop<true>(w, la, seq, row_lim, wave_lo, c, lds0);
+    key_loop_in_step<W, true>(w, la, seq, row_lim, wave_lo, c, lds0, most_tiles);
+    if (W != NW) __syncthreads();    // the rings are free for the halves to meet in
   }
 }
 
@@ -760,7 +782,7 @@ __device__ __forceinline__ void phase1_item(const Phase1Args& a, int hpw, int tp
   seq.n_tiles = seq.n_a + (wg_last - s + TKEYS - 1) / TKEYS;
 
   unsigned lds0 = (unsigned)(size_t)(LDS_AS char*)lds;
-  attend(w, seq, row_lim, wave_lo, g.scale * LOG2E, lds0);
+  attend<NW>(w, seq, row_lim, wave_lo, g.scale * LOG2E, lds0, lds0, seq.n_tiles);
 
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -806,7 +828,7 @@ __device__ __forceinline__ void phase1_item(const Phase1Args& a, int hpw, int tp
   }
 }
 
-__global__ __launch_bounds__(NT, NW == 4 ? 2 : 1) void phase1_bf16_kernel(Phase1Args a, int hpw,
+__global__ __launch_bounds__(NT, 1) void phase1_bf16_kernel(Phase1Args a, int hpw,
                                                                           int tpb, int n_hs,
                                                                           unsigned n_items) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -824,72 +846,131 @@ __global__ __launch_bounds__(NT, NW == 4 ? 2 : 1) void phase1_bf16_kernel(Phase1
 
 // ------------------------------------------------------------------ phase 2
 // Local attention (Eq. 1) and log-sum-exp (log of Eq. 2) of a row tile over one
-// split of the cache.  grid.x = ((batch * s_total + split) * n_hs + hs) * row_tiles + tile,
-// grid.y = kv head.
-__global__ __launch_bounds__(NT, NW == 4 ? 2 : 1) void phase2_rows_bf16_kernel(Phase2Args a, int hpw,
-                                                                               int n_hs,
-                                                                               int row_tiles) {
+// split of the cache.  Rows are numbered token * G + head in group, so that a tile is
+// full whatever G and q_len are.  W = 8: a tile of 256 rows, all wavefronts walk the same
+// key tiles.  W = 4: a tile of 128 rows; the two halves of the workgroup hold the same
+// rows, walk every other key tile and meet in LDS at the end: at no more than 128 rows a
+// key tile then costs half a tile's time of the matrix pipes, and twice as many bytes are
+// in flight (what bounds these calls is the stream of the cache).
+// grid.x numbers (kv head fastest, row tile, split, batch): with Hkv a multiple of 8 an
+// XCD's L2 serves one KV head, and the row tiles of a split read its keys there.
+template <int W>
+__global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, int row_tiles) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const Geom& g = a.g;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int col = lane & 15, j4 = lane >> 4;
-  const int tm = 16 * (WG_BLOCKS / hpw);
+  const int tid = threadIdx.x, wave = (tid >> 6) % W, half = __builtin_amdgcn_readfirstlane((tid >> 6) / W);
+  const int lane = tid & 63, col = lane & 15, j4 = lane >> 4;
 
   int id = blockIdx.x;
-  int tt = id % row_tiles; id /= row_tiles;
-  int hs = id % n_hs; id /= n_hs;
-  int sp = id % a.plan.s_total;
-  int beta = id / a.plan.s_total;
-  int kvh = blockIdx.y;
+  const int kvh = id % g.Hkv; id /= g.Hkv;
+  const int tt = id % row_tiles; id /= row_tiles;
+  const int sp = id % a.plan.s_total;
+  const int beta = id / a.plan.s_total;
 
-  int total = (int)visible_total(a);
+  const int total = (int)visible_total(a), cache_len = (int)a.cache_len;
   int64_t lo64, hi64;
   split_range(a.plan, g.L, g.b, total, sp, &lo64, &hi64);
-  int lo = (int)lo64, hi = (int)hi64;
+  const int lo = (int)lo64, hi = (int)hi64;
 
   const char* Kb = (const char*)a.Kc + ((size_t)beta * g.Hkv + kvh) * (size_t)g.cap * ROWB;
   const char* Vb = (const char*)a.Vc + ((size_t)beta * g.Hkv + kvh) * (size_t)g.cap * ROWB;
   WaveState w;
   int head[RB], jrow[RB], row_lim[RB];
   bool active[RB];
+  const unsigned n_rows = (unsigned)g.G * (unsigned)a.q_len, r0 = (unsigned)tt * (16 * RB * W);
   int wave_lo = 0x7fffffff;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    int gb = wave * RB + rb;
-    head[rb] = kvh * g.G + hs * hpw + gb % hpw;
-    int j0 = tt * tm + 16 * (gb / hpw);
-    jrow[rb] = j0 + col;
-    active[rb] = jrow[rb] < a.q_len;
-    int qj = active[rb] ? jrow[rb] : (j0 < a.q_len ? j0 : a.q_len - 1);
-    load_q(w, rb, (const char*)a.Qq + (((size_t)beta * a.q_len + qj) * g.Hq + head[rb]) * ROWB, j4);
-    row_lim[rb] = active[rb] ? (int)visible_limit(a, jrow[rb]) : 0;
-    int l0 = j0 < a.q_len ? (int)visible_limit(a, j0) : 0;
-    wave_lo = l0 < wave_lo ? l0 : wave_lo;
+    const unsigned rr = r0 + 16 * (wave * RB + rb) + col;
+    active[rb] = rr < n_rows;
+    const unsigned r = active[rb] ? rr : n_rows - 1;     // rows past the last repeat it
+    jrow[rb] = (int)(r / (unsigned)g.G);
+    head[rb] = kvh * g.G + (int)(r % (unsigned)g.G);
+    load_q(w, rb, (const char*)a.Qq + (((size_t)beta * a.q_len + jrow[rb]) * g.Hq + head[rb]) * ROWB, j4);
+    row_lim[rb] = (int)visible_limit(a, jrow[rb]);
+    wave_lo = row_lim[rb] < wave_lo ? row_lim[rb] : wave_lo;
   }
-  wave_lo = __builtin_amdgcn_readfirstlane(wave_lo);   // wave-uniform
+  wave_lo = __builtin_amdgcn_readfirstlane(wave_lo);     // lane 0 holds the smallest row, and with it the bound
   reset_state(w);
 
+  // rows cached before the call are visible to every token; the call's own are read
+  // where the caller left them, or from the caches if a preceding kernel has put them there
+  const bool fused_append = a.Kn != nullptr;
+  const int new_stride = fused_append ? g.Hkv * ROWB : ROWB;
+  const size_t new0 = ((size_t)beta * a.q_len * g.Hkv + kvh) * ROWB;
+  const char* Kn = (const char*)a.Kn + new0;
+  const char* Vn = (const char*)a.Vn + new0;
   TileSeq seq;
-  seq.a_lo = 0; seq.a_hi = 0; seq.n_a = 0; seq.loc_lo = lo; seq.loc_hi = hi;
-  seq.Ka = Kb; seq.Va = Vb; seq.Kl = Kb; seq.Vl = Vb;
-  seq.a_stride = ROWB; seq.l_stride = ROWB;
-  seq.n_tiles = hi > lo ? (hi - lo + TKEYS - 1) / TKEYS : 0;
+  seq.a_lo = lo;
+  seq.a_hi = hi < cache_len ? hi : cache_len;
+  if (seq.a_hi < lo) seq.a_hi = lo;
+  seq.n_a = (seq.a_hi - lo + TKEYS - 1) / TKEYS;
+  seq.loc_lo = lo > cache_len ? lo : cache_len;
+  seq.loc_hi = hi > seq.loc_lo ? hi : seq.loc_lo;
+  seq.Ka = Kb; seq.Va = Vb; seq.a_stride = ROWB;
+  // key k of the call's own is row k - cache_len of Kq / Vq
+  seq.Kl = fused_append ? Kn - (size_t)cache_len * new_stride : Kb;
+  seq.Vl = fused_append ? Vn - (size_t)cache_len * new_stride : Vb;
+  seq.l_stride = new_stride;
+  seq.half = half;
+  const int tiles = seq.n_a + (seq.loc_hi - seq.loc_lo + TKEYS - 1) / TKEYS;
+  seq.n_tiles = W == NW ? tiles : (tiles + 1 - half) / 2;
 
-  unsigned lds0 = (unsigned)(size_t)(LDS_AS char*)lds;
-  attend(w, seq, row_lim, wave_lo, g.scale * LOG2E, lds0);
+  const unsigned lds_wg = (unsigned)(size_t)(LDS_AS char*)lds, lds0 = lds_wg + (W == NW ? 0 : half * 4 * TILEB);
+  const float c = g.scale * LOG2E;
+  attend<W>(w, seq, row_lim, wave_lo, c, lds0, lds_wg, W == NW ? tiles : (tiles + 1) / 2);
 
+  // Algorithm 2, append: the split that holds a new token files its K and V rows
+  if (fused_append && tt == 0) {
+    const int n_units = (seq.loc_hi - seq.loc_lo) * 16;
+    const size_t dst = ((size_t)beta * g.Hkv + kvh) * (size_t)g.cap + seq.loc_lo;
+    for (int u = tid; u < n_units; u += NT) {
+      const size_t from = (size_t)(seq.loc_lo - cache_len + (u >> 4)) * new_stride + (u & 15) * 16;
+      const i32x4 k = *(const i32x4*)(Kn + from), v = *(const i32x4*)(Vn + from);
+      *(i32x4*)((char*)a.Kc + dst * ROWB + (size_t)u * 16) = k;
+      *(i32x4*)((char*)a.Vc + dst * ROWB + (size_t)u * 16) = v;
+    }
+  }
+
+  float l_tot[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) l_tot[rb] = quad_sum(w.l[rb]);
+  if (W != NW) {
+    // The lanes of the second half hand over (O, m, l) to those of the first, register
+    // by register: 1 KiB per wavefront and register, in the ring areas nobody reads any more.
+    LDS_AS char* box = (LDS_AS char*)(size_t)lds_wg + wave * (RB * 9 * 1024) + lane * 16;
+    if (half == 1) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) *(LDS_AS f32x4*)(box + (rb * 9 + dt) * 1024) = w.o[rb][dt];
+        *(LDS_AS f32x4*)(box + (rb * 9 + 8) * 1024) = f32x4{w.m[rb], l_tot[rb], 0.f, 0.f};
+      }
+    }
+    __syncthreads();
+    if (half == 1) return;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const f32x4 ml = *(LDS_AS f32x4*)(box + (rb * 9 + 8) * 1024);
+      const float m = fmaxf(w.m[rb], ml[0]), mm = m == -INFINITY ? 0.f : m;
+      const float s0 = __builtin_amdgcn_exp2f((w.m[rb] - mm) * c), s1 = __builtin_amdgcn_exp2f((ml[0] - mm) * c);
+      l_tot[rb] = l_tot[rb] * s0 + ml[1] * s1;
+      w.m[rb] = m;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt)
+        w.o[rb][dt] = w.o[rb][dt] * s0 + *(LDS_AS f32x4*)(box + (rb * 9 + dt) * 1024) * s1;
+    }
+  }
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    float l_tot = quad_sum(w.l[rb]);
     if (active[rb]) {
-      float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+      float inv = l_tot[rb] > 0.f ? 1.f / l_tot[rb] : 0.f;
       size_t r = (((size_t)beta * a.plan.s_total + sp) * g.Hq + head[rb]) * a.q_len + jrow[rb];
       float* orow = a.O_sub + r * D;
 #pragma unroll
       for (int dt = 0; dt < 8; ++dt) *(f32x4*)(orow + 16 * dt + 4 * j4) = w.o[rb][dt] * inv;
       if (j4 == 0)
-        a.LSE_sub[r] = l_tot > 0.f ? (w.m[rb] * g.scale * LOG2E + __builtin_amdgcn_logf(l_tot)) * LN2
-                                   : -INFINITY;
+        a.LSE_sub[r] = l_tot[rb] > 0.f ? (w.m[rb] * c + __builtin_amdgcn_logf(l_tot[rb])) * LN2 : -INFINITY;
     }
   }
 }
@@ -906,16 +987,23 @@ int flash_heads_per_workgroup(int G) {
 }
 int flash_tokens_per_workgroup(int G) { return 16 * (WG_BLOCKS / flash_heads_per_workgroup(G)); }
 
-// The kernels' 64 KiB tile ring is dynamic LDS; the runtime wants to be told
-// once per kernel and device that a launch may ask for that much.
-enum { ATTR_PHASE1 = 0, ATTR_PHASE2_ROWS = 1 };
+// Rows per workgroup of the phase-2 kernel: 128, two halves of the workgroup sharing the
+// keys, where that leaves fewer rows empty than 256.
+int flash_phase2_rows_per_workgroup(int64_t rows) {
+  return (rows + 127) / 128 < 2 * ((rows + 255) / 256) ? 128 : 256;
+}
+
+// The kernels' 64 KiB tile rings (one, or one per half) are dynamic LDS; the runtime wants
+// to be told once per kernel and device that a launch may ask for that much.
+enum { ATTR_PHASE1 = 0, ATTR_PHASE2_ROWS = 1, ATTR_PHASE2_HALVES = 2 };
 static hipError_t allow_tile_ring(int which, const void* kernel) {
-  static std::atomic<bool> done[2][64];
+  static std::atomic<bool> done[3][64];
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev >= 0 && dev < 64 && done[which][dev].load(std::memory_order_acquire)) return hipSuccess;
-  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * TILEB);
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (which == ATTR_PHASE2_HALVES ? 8 : 4) * TILEB);
   if (e == hipSuccess && dev >= 0 && dev < 64) done[which][dev].store(true, std::memory_order_release);
   return e;
 }
@@ -933,9 +1021,8 @@ hipError_t launch_phase1_bf16(const Phase1Args& a, hipStream_t st) {
   hipError_t e = allow_tile_ring(ATTR_PHASE1, (const void*)phase1_bf16_kernel);
   if (e != hipSuccess) return e;
   // one workgroup per CU (registers and LDS admit no more), never more than items
-  int n_cu = a.n_cu;
+  const int n_cu = a.n_cu;
   if (n_cu <= 0 || !a.tickets) return hipErrorInvalidValue;
-  if (NW == 4) n_cu *= 2;
   const unsigned resident = (unsigned)(wgs < n_cu ? wgs : n_cu);
   if (resident == 0) return hipSuccess;
   if (!a.tickets_clear) {
@@ -946,19 +1033,22 @@ hipError_t launch_phase1_bf16(const Phase1Args& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_phase2_rows_bf16(const Phase2Args& a, hipStream_t st) {
+template <int W>
+static hipError_t launch_phase2_rows(const Phase2Args& a, int which, hipStream_t st) {
   const Geom& g = a.g;
-  int hpw = flash_heads_per_workgroup(g.G);
-  int tm = flash_tokens_per_workgroup(g.G);
-  int n_hs = g.G / hpw;
-  int row_tiles = (a.q_len + tm - 1) / tm;
-  int64_t gx = (int64_t)g.B * a.plan.s_total * n_hs * row_tiles;
-  if (gx > 0x7fffffff || g.Hkv > 65535) return hipErrorInvalidValue;
-  hipError_t e = allow_tile_ring(ATTR_PHASE2_ROWS, (const void*)phase2_rows_bf16_kernel);
+  const int64_t row_tiles = ((int64_t)g.G * a.q_len + 16 * RB * W - 1) / (16 * RB * W);
+  const int64_t wgs = (int64_t)g.B * a.plan.s_total * row_tiles * g.Hkv;
+  if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff) return hipErrorInvalidValue;
+  hipError_t e = allow_tile_ring(which, (const void*)phase2_rows_bf16_kernel<W>);
   if (e != hipSuccess) return e;
-  phase2_rows_bf16_kernel<<<dim3((unsigned)gx, (unsigned)g.Hkv), NT, 4 * TILEB, st>>>(a, hpw, n_hs,
-                                                                                      row_tiles);
+  phase2_rows_bf16_kernel<W><<<dim3((unsigned)wgs), NT, (NW / W) * 4 * TILEB, st>>>(a, (int)row_tiles);
   return hipGetLastError();
+}
+
+hipError_t launch_phase2_rows_bf16(const Phase2Args& a, hipStream_t st) {
+  if (flash_phase2_rows_per_workgroup((int64_t)a.g.G * a.q_len) == 128)
+    return launch_phase2_rows<4>(a, ATTR_PHASE2_HALVES, st);
+  return launch_phase2_rows<NW>(a, ATTR_PHASE2_ROWS, st);
 }
 
 }  // namespace star

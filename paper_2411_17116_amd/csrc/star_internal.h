@@ -21,8 +21,8 @@ namespace star {
 // streaming decode kernel, with S = s_total splits, split s is the comb of 32-key
 // steps s, s + S, s + 2S, ... of everything the call may see (split_len only sizes
 // S), so that one split per resident workgroup sweeps the cache together with the
-// others.  For the fp32 kernel split s is the run [s, s + 1) * split_len; with one
-// split the kernel writes the call's results itself and nothing is merged.
+// others.  For the row-tiled kernels split s is the run [s, s + 1) * split_len; with one
+// split the fp32 kernel writes the call's results itself and nothing is merged.
 struct SplitPlan {
   int64_t split_len;   // keys per split (multiple of 32)
   int32_t spb;         // splits per context block
@@ -159,10 +159,13 @@ __host__ __device__ inline void split_range(const SplitPlan& p, int64_t L, int64
   }
 }
 
-// Row tiling of the bf16 row-tiled kernels: heads of one KV group that share a
-// workgroup, and tokens per workgroup (the split plan sizes its grids with them).
+// Row tiling of the bf16 phase-1 kernel: heads of one KV group that share a workgroup,
+// and tokens per workgroup.
 int flash_heads_per_workgroup(int G);
 int flash_tokens_per_workgroup(int G);
+
+// Rows (heads of a KV group x tokens) of a workgroup of the bf16 row-tiled phase-2 kernel.
+int flash_phase2_rows_per_workgroup(int64_t rows);
 
 // Rows (heads of a KV group x tokens) of a workgroup of the fp32 phase-2 kernel.
 int f32_phase2_rows_per_workgroup(int64_t rows);

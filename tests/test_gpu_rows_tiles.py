@@ -1,0 +1,60 @@
+"""The bf16 row-tiled phase-2 kernel at the edges of its tiling: rows packed over tokens and
+heads (groups that do and do not divide a tile), tiles of 128 rows whose workgroup halves
+share the keys (odd and even numbers of key tiles, a half without any) and tiles of 256,
+splits of equal runs and of parts, new tokens read from the call's tensors and appended by
+the kernel, and the exact fallback of the softmax in both halves."""
+import pytest
+import torch
+
+import paper_2411_17116_amd as sa
+import workloads
+from tests import parity_harness as ph
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,b,a,lq,gamma", [
+    (1, 1, 1, 40, 64, 64, 17, 1.5),        # one ragged tile: the second half has none
+    (1, 1, 1, 64, 64, 64, 65, 1.5),        # cached and new rows in tiles of their own
+    (2, 3, 1, 700, 300, 100, 21, 1.5),     # G = 3: 63 rows, tokens straddle row blocks
+    (1, 5, 1, 1000, 256, 0, 51, 1.5),      # 255 rows: one 256-row tile
+    (1, 4, 2, 1300, 400, 64, 32, 1.5),     # 128 rows: one tile shared by the halves
+    (1, 4, 2, 1300, 400, 64, 33, 1.5),     # 132 rows: one 256-row tile
+    (1, 8, 2, 1300, 1300, 64, 65, 1.5),    # 260 rows: three 128-row tiles
+    (1, 8, 2, 900, 100, 100, 97, 1.5),     # 388 rows: two 256-row tiles
+    (1, 40, 2, 600, 200, 7, 3, 1.5),       # G = 20
+    (1, 8, 2, 6000, 1500, 64, 21, 6.0),    # scores far above the reference: the exact loop
+    (1, 4, 2, 3000, 800, 64, 60, 6.0),     # the same on a 256-row tile
+])
+def test_row_tile_edges(B, Hq, Hkv, L, b, a, lq, gamma):
+    cfg = workloads.StarConfig("rows", "bf16", B, Hq, Hkv, 128, L, b, a, lq, 1, seed=L + lq, n_planted=8,
+                               gamma=gamma)
+    print(f"[{cfg}]", flush=True)
+    rep = ph.run_parity(cfg, all_rows=L < 1500)      # the query call with per-part outputs
+    assert rep.ok, rep.detail
+    # the same call as a serving program makes it, without per-part outputs
+    inp = workloads.make_inputs(cfg, "cuda")
+    run = ph.HipRun(cfg, inp, "cuda")
+    run.phase1()
+    O, _, _ = run.phase2(inp.Qq, inp.Kq, inp.Vq, want_parts=False)
+    torch.cuda.synchronize()
+    heads = list(range(Hq)) if Hq <= 8 else [0, 19, 20, Hq - 1]
+    res = ph.check_phase2(run, inp.Qq, ([inp.Kq], [inp.Vq]), L, O, None, None, heads, tag="flat")
+    assert res["flat_O"] <= ph.TOL["bf16"]["o"], res
+    for g in range(Hkv):
+        assert torch.equal(run.Kc[:, g, L:L + lq], inp.Kq[:, :, g])
+        assert torch.equal(run.Vc[:, g, L:L + lq], inp.Vq[:, :, g])
+        assert not run.Kc[:, g, L + lq:].any()
+
+
+def test_workspace_covers_every_shorter_call():
+    """Whatever a call of at most max_q tokens on a cache of any length plans fits what
+    star_attn_workspace_bytes asked for."""
+    for Hq, Hkv, B in ((4, 1, 1), (3, 1, 2), (20, 1, 1), (64, 8, 2), (12, 4, 1)):
+        shape = sa.StarShape.make("bf16", B, Hq, Hkv, 128, 30000, 7000, 100, 30000 + 5000)
+        for max_q in (7, 75, 300):
+            have = sa.workspace_bytes(shape, max_q)
+            for q in range(1, max_q + 1):
+                for parts in (False, True):
+                    for cached in (30000, 33333, 35000 - q):
+                        assert sa.phase2_plan(shape, cached, q, parts).workspace_bytes <= have, (Hq, q, parts)
