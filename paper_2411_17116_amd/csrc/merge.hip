@@ -14,14 +14,18 @@
 // dtype it can leave the merged pair itself, (A, lse) in fp32 -- what a host
 // sends when its cache is one share of a larger one.
 //
-// merge_kernel: one workgroup per (batch, head, row): GROUPS groups of 32 lanes walk the
-// splits of a part, each lane owning d/32 output elements and each group
-// folding its splits with a running maximum (loads of INFL splits are in flight
-// per group); the partial results are combined through LDS.  A decode step has
-// few rows and 128 to 1024 splits per row (16 groups x 8 in flight: one to
-// eight round trips); a query-encode call has thousands of rows and a few splits per
-// part (8 groups x 4).  Traffic is s_total * (d + 1) floats per row
-// -- negligible next to the cache.
+// Two sets of kernels:
+//   * merge_flat_kernel / merge_flat_rows_kernel for calls of one part (a flat split plan,
+//     pairs gathered from hosts), which is every call of a serving loop.  What bounds them
+//     is latency: a decode step has few rows of 24 to 512 splits, so the rows are spread
+//     over many workgroups (a piece of d each) and the weights of the splits in flight are
+//     taken against their common maximum, with no chain from split to split.
+//   * merge_kernel / merge_rows_kernel for calls with several parts: the per-part pairs are
+//     written out on the way.  merge_kernel: one workgroup per (batch, head, row), 8 groups
+//     of 32 lanes walk the splits of a part, each lane owning d/32 output elements and each
+//     group folding its splits with a running maximum (4 in flight); the partial results
+//     are combined through LDS.
+// Traffic is s_total * (d + 1) floats per row -- negligible next to the cache.
 //
 // The fold over parts keeps a compensation term per accumulator (Kahan
 // summation): a context cut into hundreds of small blocks is hundreds of
@@ -33,6 +37,9 @@ namespace star {
 
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+constexpr float LOG2E = 1.4426950408889634f;
 
 // sum += x with the rounding error of the addition carried in `comp`
 __device__ __forceinline__ void add_compensated(float& sum, float& comp, float x) {
@@ -64,7 +71,7 @@ __global__ __launch_bounds__(32 * GROUPS) void merge_kernel(MergeArgs a) {
   const SplitPlan& p = a.plan;
   const int64_t sub_stride = a.split_stride;                                 // rows between splits
   const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;   // split 0
-  const int n_parts = p.flat ? 1 : p.n_blocks + 1;
+  const int n_parts = p.n_blocks + 1;
 
   float m_g = -INFINITY, l_g = 0.f, l_c = 0.f;
   float acc_g[E], acc_c[E];
@@ -73,8 +80,7 @@ __global__ __launch_bounds__(32 * GROUPS) void merge_kernel(MergeArgs a) {
 
   for (int m = 0; m < n_parts; ++m) {
     int s_lo, s_hi;
-    if (p.flat) { s_lo = 0; s_hi = p.s_total; }
-    else if (m < p.n_blocks) { s_lo = m * p.spb; s_hi = s_lo + p.spb; }
+    if (m < p.n_blocks) { s_lo = m * p.spb; s_hi = s_lo + p.spb; }
     else { s_lo = p.n_blocks * p.spb; s_hi = p.s_total; }
 
     // Each group folds its splits (s_lo + grp, + GROUPS, ...) with a running maximum;
@@ -193,7 +199,7 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(MergeArgs a, int64_t n_
   const int beta = (int)(row / ((int64_t)a.q_len * g.Hq));
   const SplitPlan& p = a.plan;
   const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;
-  const int n_parts = p.flat ? 1 : p.n_blocks + 1;
+  const int n_parts = p.n_blocks + 1;
 
   float m_g = -INFINITY, l_g = 0.f, l_c = 0.f;
   float acc_g[E], acc_c[E];
@@ -201,8 +207,7 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(MergeArgs a, int64_t n_
   for (int e = 0; e < E; ++e) acc_g[e] = acc_c[e] = 0.f;
   for (int m = 0; m < n_parts; ++m) {
     int s_lo, s_hi;
-    if (p.flat) { s_lo = 0; s_hi = p.s_total; }
-    else if (m < p.n_blocks) { s_lo = m * p.spb; s_hi = s_lo + p.spb; }
+    if (m < p.n_blocks) { s_lo = m * p.spb; s_hi = s_lo + p.spb; }
     else { s_lo = p.n_blocks * p.spb; s_hi = p.s_total; }
     float pm = -INFINITY, wsum = 0.f;
     float acc[E];
@@ -273,14 +278,174 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(MergeArgs a, int64_t n_
   if (a.LSE && li == 0) a.LSE[arow] = l_g > 0.f ? m_g + logf(l_g) : -INFINITY;
 }
 
+// ------------------------------------------------------------------ one part
+// exp(x) for the weight of a split, x <= 0.  The rounding of the product is at most
+// |x| 2^-24 of a weight e^x: below 3e-8 of the largest.
+__device__ __forceinline__ float weight(float x) { return __builtin_amdgcn_exp2f(x * LOG2E); }
+
+// What one lane gathers: the weighted sum of its four elements of the splits' outputs, the
+// sum of weights, both relative to exp(m).
+struct Fold {
+  float m, w;
+  f32x4 acc;
+};
+__device__ __forceinline__ Fold empty_fold() { return Fold{-INFINITY, 0.f, f32x4{0.f, 0.f, 0.f, 0.f}}; }
+__device__ __forceinline__ float finite(float m) { return m == -INFINITY ? 0.f : m; }
+
+// N splits at once: `ls` their log-sum-exps (-inf: empty, `v` unset).
+template <int N>
+__device__ __forceinline__ void fold_splits(Fold& f, const float (&ls)[N], const f32x4 (&v)[N]) {
+  float m = f.m;
+#pragma unroll
+  for (int u = 0; u < N; ++u) m = fmaxf(m, ls[u]);
+  const float mm = finite(m), old = weight(f.m - mm);
+  f.w *= old;
+  f.acc *= old;
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const float w = weight(ls[u] - mm);
+    f.w += w;
+    f.acc += ls[u] == -INFINITY ? f32x4{0.f, 0.f, 0.f, 0.f} : v[u] * w;
+  }
+  f.m = m;
+}
+__device__ __forceinline__ void store_merged(const MergeArgs& a, int beta, int h, int64_t j, int d0, const Fold& f) {
+  const Geom& g = a.g;
+  const f32x4 out = f.w > 0.f ? f.acc * (1.f / f.w) : f32x4{0.f, 0.f, 0.f, 0.f};
+  const int64_t orow = ((int64_t)beta * a.q_len + j) * g.Hq + h, arow = ((int64_t)beta * g.Hq + h) * a.q_len + j;
+  if (a.A) *(f32x4*)(a.A + arow * g.d + d0) = out;
+  if (a.O) {
+    if (a.out_bf16) {
+      unsigned short* o = (unsigned short*)a.O + orow * g.d + d0;
+      const uint32_t lo = f32_to_bf16_rne(out[0]) | (uint32_t)f32_to_bf16_rne(out[1]) << 16;
+      const uint32_t hi = f32_to_bf16_rne(out[2]) | (uint32_t)f32_to_bf16_rne(out[3]) << 16;
+      *(uint2*)o = make_uint2(lo, hi);
+    } else {
+      *(f32x4*)((float*)a.O + orow * g.d + d0) = out;
+    }
+  }
+  if (a.LSE && d0 == 0) a.LSE[arow] = f.w > 0.f ? f.m + logf(f.w) : -INFINITY;
+}
+
+// One workgroup per (row, piece of 4 LPS elements of d): LPS lanes per split, the others
+// walk the splits, INFL in flight per lane.  grid: x = token * pieces + piece, y = head,
+// z = batch.
+template <int LPS, int THREADS, int INFL>
+__global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
+  constexpr int GROUPS = THREADS / LPS, WAVES = THREADS / 64;
+  __shared__ float red_m[WAVES], red_w[WAVES];
+  __shared__ f32x4 red_acc[WAVES][LPS];
+  const Geom& g = a.g;
+  const int tid = threadIdx.x, li = tid % LPS, grp = tid / LPS;
+  const int pieces = g.d / (4 * LPS), j = blockIdx.x / pieces, d0 = (blockIdx.x % pieces) * (4 * LPS) + 4 * li;
+  const int h = blockIdx.y, beta = blockIdx.z, S = a.plan.s_total;
+  const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;
+
+  Fold f = empty_fold();
+  for (int s0 = grp; s0 < S; s0 += INFL * GROUPS) {
+    float ls[INFL];
+    f32x4 v[INFL];
+#pragma unroll
+    for (int u = 0; u < INFL; ++u) {
+      const int s = s0 + u * GROUPS;
+      const int64_t r = base + (int64_t)(s < S ? s : s0) * a.split_stride;
+      ls[u] = a.LSE_sub[r];
+      v[u] = *(const f32x4*)(a.O_sub + r * g.d + d0);
+      if (s >= S) ls[u] = -INFINITY;
+    }
+    fold_splits<INFL>(f, ls, v);
+  }
+  // the groups of a wavefront, then the wavefronts
+#pragma unroll
+  for (int x = LPS; x < 64; x <<= 1) {
+    Fold o;
+    o.m = __shfl_xor(f.m, x);
+    o.w = __shfl_xor(f.w, x);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o.acc[e] = __shfl_xor(f.acc[e], x);
+    const float m = fmaxf(f.m, o.m), mm = finite(m), sf = weight(f.m - mm), so = weight(o.m - mm);
+    f.w = f.w * sf + o.w * so;
+    f.acc = f.acc * sf + o.acc * so;
+    f.m = m;
+  }
+  if ((tid & 63) < LPS) {
+    if (li == 0) { red_m[tid >> 6] = f.m; red_w[tid >> 6] = f.w; }
+    red_acc[tid >> 6][li] = f.acc;
+  }
+  __syncthreads();
+  if (tid >= LPS) return;
+  f = empty_fold();
+#pragma unroll
+  for (int k = 0; k < WAVES; ++k) f.m = fmaxf(f.m, red_m[k]);
+  const float mm = finite(f.m);
+#pragma unroll
+  for (int k = 0; k < WAVES; ++k) {
+    const float w = weight(red_m[k] - mm);
+    f.w += red_w[k] * w;
+    f.acc += red_acc[k][li] * w;
+  }
+  store_merged(a, beta, h, j, d0, f);
+}
+
+// Many rows of a few splits each (query encoding, pairs of other hosts): d / 4 lanes own a
+// row, up to eight splits in flight, nothing crosses lanes.
+template <int D>
+__global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, unsigned n_rows) {
+  constexpr int LPR = D / 4, INFL = 8;
+  const Geom& g = a.g;
+  const unsigned row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;      // (beta, h, j), j fastest
+  if (row >= n_rows) return;
+  const int d0 = 4 * (threadIdx.x % LPR), S = a.plan.s_total;
+  const unsigned bh = row / (unsigned)a.q_len, j = row % (unsigned)a.q_len, beta = bh / (unsigned)g.Hq, h = bh % (unsigned)g.Hq;
+  const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;
+  Fold f = empty_fold();
+  for (int s0 = 0; s0 < S; s0 += INFL) {
+    float ls[INFL];
+    f32x4 v[INFL];
+#pragma unroll
+    for (int u = 0; u < INFL; ++u) {
+      const int64_t r = base + (int64_t)(s0 + u < S ? s0 + u : s0) * a.split_stride;
+      ls[u] = a.LSE_sub[r];
+      v[u] = *(const f32x4*)(a.O_sub + r * D + d0);
+      if (s0 + u >= S) ls[u] = -INFINITY;
+    }
+    fold_splits<INFL>(f, ls, v);
+  }
+  store_merged(a, (int)beta, (int)h, j, d0, f);
+}
+
+template <int LPS, int THREADS, int INFL>
+hipError_t launch_flat(const MergeArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)(a.q_len * (a.g.d / (4 * LPS))), (unsigned)a.g.Hq, (unsigned)a.g.B);
+  merge_flat_kernel<LPS, THREADS, INFL><<<grid, THREADS, 0, st>>>(a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
   const int64_t rows = (int64_t)a.g.B * a.g.Hq * a.q_len;
   if (rows > 0x7fffffff) return hipErrorInvalidValue;
   const SplitPlan& p = a.plan;
+  if (p.flat) {
+    const int S = p.s_total;
+    if (S <= 8 && rows >= 64) {
+      const unsigned wgs = a.g.d == 64 ? (unsigned)((rows + 15) / 16) : (unsigned)((rows + 7) / 8);
+      if (a.g.d == 64) merge_flat_rows_kernel<64><<<dim3(wgs), 256, 0, st>>>(a, (unsigned)rows);
+      else merge_flat_rows_kernel<128><<<dim3(wgs), 256, 0, st>>>(a, (unsigned)rows);
+      return hipGetLastError();
+    }
+    // Few rows: pieces of d, so that the row's splits are in flight at once over more
+    // workgroups and wavefronts; many rows fill the GPU as they are.  Measured, us, for
+    // (rows x splits) against the kernel with the chain from split to split and a workgroup
+    // per row: 8 x 384 10.8 -> 4.3, 32 x 128 5.7 -> 3.9, 32 x 96 6.0 -> 4.7, 672 x 29
+    // 7.4 -> 4.0 (pieces of 32: 6.2-8.2), 8 x 32 (d = 64) 8.6 -> 3.3.
+    if (rows < 256) return S > 128 ? launch_flat<8, 512, 2>(a, st) : launch_flat<16, 256, 4>(a, st);
+    if (S > 64) return launch_flat<16, 512, 4>(a, st);
+    return a.g.d == 64 ? launch_flat<16, 256, 4>(a, st) : launch_flat<32, 256, 4>(a, st);
+  }
   // splits the largest part is made of
-  const int per_part = p.flat ? p.s_total : (p.spb > p.st ? p.spb : p.st);
+  const int per_part = p.spb > p.st ? p.spb : p.st;
   if (per_part <= 8 && rows >= 64) {
     // many rows, few splits each: a row per 32 lanes
     const unsigned wgs = (unsigned)((rows + 7) / 8);
@@ -288,9 +453,6 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
     else merge_rows_kernel<128, 4><<<dim3(wgs), 256, 0, st>>>(a, rows);
   } else if (a.g.d == 64) {
     merge_kernel<64, 8, 4><<<dim3((unsigned)rows), 256, 0, st>>>(a);
-  } else if (p.flat != 0 && p.s_total > 32) {
-    // decode: few rows, many splits each
-    merge_kernel<128, 16, 8><<<dim3((unsigned)rows), 512, 0, st>>>(a);
   } else {
     merge_kernel<128, 8, 4><<<dim3((unsigned)rows), 256, 0, st>>>(a);
   }

@@ -1,0 +1,43 @@
+"""star_attn_merge (the kernels behind every call of one part) over numbers of pairs and rows
+at the edges of its set-ups, against Eq. 3-4 in float64: pieces of a row, whole rows, several
+rows per workgroup; empty pairs whose slabs hold NaN; rows that saw nothing at all."""
+import pytest
+import torch
+
+import paper_2411_17116_amd as sa
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("B,H,q,n_parts", [
+    (1, 1, 1, 1), (1, 3, 1, 7), (2, 4, 8, 8), (1, 8, 8, 9), (3, 5, 1, 64), (1, 4, 1, 65), (1, 2, 1, 128),
+    (1, 2, 2, 129), (1, 1, 1, 700), (2, 8, 16, 33), (1, 16, 17, 64), (1, 32, 9, 66),
+])
+def test_merge_against_float64(dtype, d, B, H, q, n_parts):
+    gen = torch.Generator().manual_seed(n_parts * 100 + q)
+    A = torch.randn((n_parts, B, H, q, d), generator=gen)
+    LSE = 3.0 * torch.randn((n_parts, B, H, q), generator=gen) + 9.0
+    empty = torch.rand((n_parts, B, H, q), generator=gen) < 0.2
+    empty[:, 0, 0, 0] = True                                  # a row without any key
+    LSE[empty] = -float("inf")
+    w = torch.softmax(LSE.double(), dim=0).nan_to_num(0.0)
+    want = (w[..., None] * A.double()).sum(dim=0)
+    want_lse = torch.logsumexp(LSE.double(), dim=0)
+    A[empty] = float("nan")                                   # never read for its value
+    shape = sa.StarShape.make(dtype, B, H, H, d, 64, 64, 64, 64 + q)
+    O = torch.empty((B, q, H, d), dtype=torch.float32 if dtype == "fp32" else torch.bfloat16, device="cuda")
+    Am, Lm = torch.empty((B, H, q, d), device="cuda"), torch.empty((B, H, q), device="cuda")
+    print(f"merge {dtype} d={d} B={B} H={H} q={q} parts={n_parts}", flush=True)
+    sa.merge(shape, A.cuda(), LSE.cuda(), O=O, A=Am, LSE=Lm)
+    torch.cuda.synchronize()
+    # fp32 sums of up to 700 weighted values of size 1, weights that sum to 1: 700 roundings of
+    # at most 2^-24 each in the worst order, far fewer in the tree: 2e-6 is eight of them
+    assert (Am.cpu().double() - want).abs().max().item() <= 2e-6
+    seen = torch.isfinite(want_lse)
+    # the log-sum-exps are near 20 (an fp32 step there is 1.9e-6): two steps
+    assert not seen.any() or (Lm.cpu().double() - want_lse)[seen].abs().max().item() <= 4e-6
+    assert torch.isneginf(Lm.cpu()[~seen]).all()
+    got = O.float().cpu().double().transpose(1, 2)
+    step = 2.0 ** -24 if dtype == "fp32" else 2.0 ** -8
+    assert ((got - want).abs() <= want.abs() * step + 2e-6).all()
