@@ -46,11 +46,12 @@
 //     scheduling region whose order is pinned with sched_group_barrier.
 //   * Only tiles that touch a row's causal frontier or a ragged range end take
 //     the masking path.
-//   * Phase 1 is launched with one workgroup per CU; the workgroups draw their
-//     work items (a row tile of one block and KV head) from eight ticket queues,
-//     each XCD from its own first (one KV head per XCD's L2 when Hkv is a
+//   * A long phase 1 is launched with one workgroup per CU; the workgroups draw
+//     their work items (a row tile of one block and KV head) from eight ticket
+//     queues, each XCD from its own first (one KV head per XCD's L2 when Hkv is a
 //     multiple of 8) and from the others once that is empty.  The queue counters
-//     are the launch's own (Phase1Args::tickets).
+//     are the launch's own (Phase1Args::tickets).  A short one is a plain grid of
+//     smaller items (plain_phase1()).
 #include "star_internal.h"
 
 #include <atomic>
@@ -78,9 +79,9 @@ constexpr int NT = 64 * NW;                // threads per workgroup
 constexpr int RB = 2;                      // 16-row blocks per wavefront
 constexpr int WG_BLOCKS = NW * RB;         // 16-row blocks per workgroup
 static_assert(NW == 8, "the row-tiled kernels are written for 8 wavefronts");
-// W wavefronts share a ring of tiles (and walk its tiles together): all eight of a
-// workgroup, or the four of either half, each half with a ring and tiles of its own.
-// One DMA instruction of each of them moves DMA_ROWS key rows.
+// W wavefronts share a ring of tiles (and walk its tiles together), H such groups make a
+// workgroup: eight wavefronts, four, or two halves of four with a ring and tiles each.
+// One DMA instruction of each wavefront of a ring moves DMA_ROWS key rows.
 template <int W> constexpr int DMA_ROWS = 64 * W / 16;
 template <int W> constexpr int DMA_ITERS = TKEYS / DMA_ROWS<W>;
 constexpr float LOG2E = 1.4426950408889634f;
@@ -139,7 +140,7 @@ __device__ __forceinline__ void wait_vmcnt_2tiles() {
 // [a_lo, a_hi) of Ka / Va (n_a of them; phase 2: the rows cached before the call), then
 // the tiles of rows [loc_lo, loc_hi) of Kl / Vl (phase 2: the call's own).  All four are bases of one (batch, KV head); consecutive key rows
 // are a_stride / l_stride bytes apart (ROWB in a head-major cache, Hkv * ROWB in
-// a token-major input tensor).  The two halves of a workgroup (W = 4) take its tiles in
+// a token-major input tensor).  The two halves of a workgroup (H = 2) take its tiles in
 // turn: n_tiles counts the half's own, and the idx-th of them is tile 2 idx + half.
 struct TileSeq {
   int n_a;
@@ -154,17 +155,17 @@ struct TileSeq {
   const char* Vl;
   int a_stride;
   int l_stride;
-  int half;             // W = 4 only
-  template <int W> __device__ __forceinline__ int at(int idx) const { return W == NW ? idx : 2 * idx + half; }
-  template <int W> __device__ __forceinline__ bool anchor(int idx) const { return at<W>(idx) < n_a; }
-  template <int W> __device__ __forceinline__ int stride(int idx) const { return anchor<W>(idx) ? a_stride : l_stride; }
-  template <int W> __device__ __forceinline__ void tile(int idx, int* key0, int* hi) const {
-    const int i = at<W>(idx);
+  int half;             // H = 2 only
+  template <int H> __device__ __forceinline__ int at(int idx) const { return H == 1 ? idx : 2 * idx + half; }
+  template <int H> __device__ __forceinline__ bool anchor(int idx) const { return at<H>(idx) < n_a; }
+  template <int H> __device__ __forceinline__ int stride(int idx) const { return anchor<H>(idx) ? a_stride : l_stride; }
+  template <int H> __device__ __forceinline__ void tile(int idx, int* key0, int* hi) const {
+    const int i = at<H>(idx);
     if (i < n_a) { *key0 = a_lo + i * TKEYS; *hi = a_hi; }
     else { *key0 = loc_lo + (i - n_a) * TKEYS; *hi = loc_hi; }
   }
-  template <int W> __device__ __forceinline__ const char* kbase(int idx) const { return anchor<W>(idx) ? Ka : Kl; }
-  template <int W> __device__ __forceinline__ const char* vbase(int idx) const { return anchor<W>(idx) ? Va : Vl; }
+  template <int H> __device__ __forceinline__ const char* kbase(int idx) const { return anchor<H>(idx) ? Ka : Kl; }
+  template <int H> __device__ __forceinline__ const char* vbase(int idx) const { return anchor<H>(idx) ? Va : Vl; }
 };
 
 // A wavefront's state.  Lane (col = lane % 16, j4 = lane / 16) belongs to query
@@ -472,7 +473,7 @@ struct LoopRegs {
   bf16x8 pA[RB], pB[RB];      // their exponentials (bf16)
 };
 
-template <int W, bool SAFE, bool MORE, int KN, int VC, int KF, int VF>
+template <int W, int H_, bool SAFE, bool MORE, int KN, int VC, int KF, int VF>
 __device__ __forceinline__ void tile_step(WaveState& w, const LaneAddr& la, const TileSeq& seq,
                                           int t, const int (&row_lim)[RB], int wave_lo, float c,
                                           unsigned lds0, LoopRegs& r) {
@@ -483,15 +484,15 @@ __device__ __forceinline__ void tile_step(WaveState& w, const LaneAddr& la, cons
   __builtin_amdgcn_s_barrier();
   if (t + 2 < seq.n_tiles) {
     int k2, h2;
-    seq.tile<W>(t + 2, &k2, &h2);
-    issue_tile<W>(seq.kbase<W>(t + 2), seq.stride<W>(t + 2), k2, h2, lds0 + KF, la);
+    seq.tile<H_>(t + 2, &k2, &h2);
+    issue_tile<W>(seq.kbase<H_>(t + 2), seq.stride<H_>(t + 2), k2, h2, lds0 + KF, la);
   }
   if (MORE) {
     int nk0, nhi;
-    seq.tile<W>(t + 1, &nk0, &nhi);
-    issue_tile<W>(seq.vbase<W>(t + 1), seq.stride<W>(t + 1), nk0, nhi, lds0 + VF, la);
+    seq.tile<H_>(t + 1, &nk0, &nhi);
+    issue_tile<W>(seq.vbase<H_>(t + 1), seq.stride<H_>(t + 1), nk0, nhi, lds0 + VF, la);
     // one wave-uniform test per tile: does any of its keys need a mask for this wavefront?
-    const bool anchor_tile = seq.anchor<W>(t + 1);
+    const bool anchor_tile = seq.anchor<H_>(t + 1);
     const int mask_from = anchor_tile ? nhi : (wave_lo < nhi ? wave_lo : nhi);
     const bool need_mask = nk0 + TKEYS > mask_from;
     // The two wavefronts of a SIMD take turns at the higher issue priority, one
@@ -520,7 +521,7 @@ __device__ __forceinline__ void tile_step(WaveState& w, const LaneAddr& la, cons
 //   row_lim     this lane's exclusive causal key bound per row block (0 = inactive row)
 //   wave_lo     smallest row_lim among the wavefront's active rows: key tiles that
 //               end at or below it need no causal mask
-template <int W, bool SAFE>
+template <int W, int H_, bool SAFE>
 __device__ __forceinline__ void key_loop(WaveState& w, const LaneAddr& la, const TileSeq& seq,
                                          const int (&row_lim)[RB], int wave_lo, float c,
                                          unsigned lds0) {
@@ -532,22 +533,22 @@ __device__ __forceinline__ void key_loop(WaveState& w, const LaneAddr& la, const
   int key0, hi;
 
   // Prologue: K tile 0, V tile 0 and K tile 1 in flight; scores of tile 0.
-  seq.tile<W>(0, &key0, &hi);
-  issue_tile<W>(seq.kbase<W>(0), seq.stride<W>(0), key0, hi, lds0 + K0, la);
-  issue_tile<W>(seq.vbase<W>(0), seq.stride<W>(0), key0, hi, lds0 + V0, la);
+  seq.tile<H_>(0, &key0, &hi);
+  issue_tile<W>(seq.kbase<H_>(0), seq.stride<H_>(0), key0, hi, lds0 + K0, la);
+  issue_tile<W>(seq.vbase<H_>(0), seq.stride<H_>(0), key0, hi, lds0 + V0, la);
   if (T > 1) {
     int k1, h1;
-    seq.tile<W>(1, &k1, &h1);
-    issue_tile<W>(seq.kbase<W>(1), seq.stride<W>(1), k1, h1, lds0 + K1, la);
+    seq.tile<H_>(1, &k1, &h1);
+    issue_tile<W>(seq.kbase<H_>(1), seq.stride<H_>(1), k1, h1, lds0 + K1, la);
     wait_vmcnt_2tiles<W>();
   } else {
     wait_vmcnt0();
   }
   __builtin_amdgcn_s_barrier();
   stage<SAFE, true, false, false, K0, 0>(w, la, r.sA, r.sA, r.pA, r.pA, c, alpha, pre);
-  mask_if_needed(r.sA, key0, hi, wave_lo, row_lim, la.j4, seq.anchor<W>(0));
+  mask_if_needed(r.sA, key0, hi, wave_lo, row_lim, la.j4, seq.anchor<H_>(0));
   stage<SAFE, true, false, false, K0 + H, 0>(w, la, r.sB, r.sA, r.pA, r.pA, c, alpha, pre);
-  mask_if_needed(r.sB, key0 + 32, hi, wave_lo, row_lim, la.j4, seq.anchor<W>(0));
+  mask_if_needed(r.sB, key0 + 32, hi, wave_lo, row_lim, la.j4, seq.anchor<H_>(0));
   // first unit: its row maximum becomes the reference (nothing to rescale yet)
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -561,14 +562,14 @@ __device__ __forceinline__ void key_loop(WaveState& w, const LaneAddr& la, const
   // and the accumulators flow through straight-line code.
   int t = 0;
   for (; t + 2 < T; t += 2) {
-    tile_step<W, SAFE, true, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
-    tile_step<W, SAFE, true, K0, V1, K1, V0>(w, la, seq, t + 1, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, H_, SAFE, true, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, H_, SAFE, true, K0, V1, K1, V0>(w, la, seq, t + 1, row_lim, wave_lo, c, lds0, r);
   }
   if (T - t == 2) {
-    tile_step<W, SAFE, true, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
-    tile_step<W, SAFE, false, K0, V1, K1, V0>(w, la, seq, t + 1, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, H_, SAFE, true, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, H_, SAFE, false, K0, V1, K1, V0>(w, la, seq, t + 1, row_lim, wave_lo, c, lds0, r);
   } else {
-    tile_step<W, SAFE, false, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
+    tile_step<W, H_, SAFE, false, K1, V0, K0, V1>(w, la, seq, t, row_lim, wave_lo, c, lds0, r);
   }
   __builtin_amdgcn_s_setprio(0);
 }
@@ -587,10 +588,10 @@ __device__ __forceinline__ void reset_state(WaveState& w) {
 }
 
 // LDS addresses of the calling lane.
-template <int W>
+template <int W, int H>
 __device__ __forceinline__ LaneAddr lane_addr(unsigned lds0) {
   LaneAddr la;
-  la.tid = W == NW ? threadIdx.x : threadIdx.x & (64 * W - 1);
+  la.tid = H == 1 ? threadIdx.x : threadIdx.x & (64 * W - 1);
   const int lane = la.tid & 63;
   const int col = lane & 15;
   la.j4 = lane >> 4;
@@ -613,23 +614,23 @@ __device__ __forceinline__ LaneAddr lane_addr(unsigned lds0) {
 }
 
 // The key loop, and the barriers a half with fewer tiles than the other still owes it.
-template <int W, bool SAFE>
+template <int W, int H, bool SAFE>
 __device__ __forceinline__ void key_loop_in_step(WaveState& w, const LaneAddr& la, const TileSeq& seq,
                                                  const int (&row_lim)[RB], int wave_lo, float c, unsigned lds0,
                                                  int most_tiles) {
-  if (W == NW || seq.n_tiles > 0) key_loop<W, SAFE>(w, la, seq, row_lim, wave_lo, c, lds0);
-  if (W != NW)
+  if (H == 1 || seq.n_tiles > 0) key_loop<W, H, SAFE>(w, la, seq, row_lim, wave_lo, c, lds0);
+  if (H != 1)
     for (int t = seq.n_tiles > 0 ? seq.n_tiles : -1; t < most_tiles; ++t) __builtin_amdgcn_s_barrier();
 }
 
 // Attention of the workgroup's rows over a tile sequence: the fast loop, and the
 // exact loop again if any wavefront's scores left the fast loop's safe range.
 //   lds_wg      base of the workgroup's LDS; lds0 that of the calling wavefront's ring
-//   most_tiles  tiles of the half that has more (W = 4), or seq.n_tiles
-template <int W>
+//   most_tiles  tiles of the half that has more (H = 2), or seq.n_tiles
+template <int W, int H>
 __device__ __forceinline__ void attend(WaveState& w, const TileSeq& seq, const int (&row_lim)[RB],
                                        int wave_lo, float c, unsigned lds0, unsigned lds_wg, int most_tiles) {
-  const LaneAddr la = lane_addr<W>(lds0);
+  const LaneAddr la = lane_addr<W, H>(lds0);
   if (most_tiles == 0) return;
   // Consume the Q fragments here so that the compiler places its own wait for
   // their loads before the first DMA is in flight (and none inside the loops).
@@ -641,7 +642,7 @@ __device__ __forceinline__ void attend(WaveState& w, const TileSeq& seq, const i
     const __bf16 o = (la.tid & 15) == 0 ? (__bf16)1.0f : (__bf16)0.0f;
     w.ones = bf16x8{o, o, o, o, o, o, o, o};
   }
-  key_loop_in_step<W, false>(w, la, seq, row_lim, wave_lo, c, lds0, most_tiles);
+  key_loop_in_step<W, H, false>(w, la, seq, row_lim, wave_lo, c, lds0, most_tiles);
   // row 0 of the ones-row product sits in element 0 of the lanes with j4 == 0: the row's whole sum
   // (quad_sum over the row's four lanes then finds it once); sums that left the safe range show here
 #pragma unroll
@@ -660,12 +661,44 @@ __device__ __forceinline__ void attend(WaveState& w, const TileSeq& seq, const i
   __syncthreads();
   int any_bad = 0;
 #pragma unroll
-  for (int i = 0; i < NW; ++i) any_bad |= flags[i];
+  for (int i = 0; i < W * H; ++i) any_bad |= flags[i];
   __syncthreads();
   if (__builtin_expect(any_bad != 0, 0)) {
     reset_state(w);
-    key_loop_in_step<W, true>(w, la, seq, row_lim, wave_lo, c, lds0, most_tiles);
-    if (W != NW) __syncthreads();    // the rings are free for the halves to meet in
+    key_loop_in_step<W, H, true>(w, la, seq, row_lim, wave_lo, c, lds0, most_tiles);
+    if (H != 1) __syncthreads();    // the rings are free for the halves to meet in
+  }
+}
+
+// The two halves of a workgroup hold partial results of the same rows.  The lanes of the
+// second hand over (O, m, l) to those of the first, register by register: 1 KiB per
+// wavefront and register, in the ring areas nobody reads any more.  l[.] receives the
+// rows' sums (of both halves, in the first).
+__device__ __forceinline__ void meet_halves(WaveState& w, float (&l)[RB], unsigned lds_wg, int wave, int half, int lane,
+                                            float c) {
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) l[rb] = quad_sum(w.l[rb]);
+  LDS_AS char* box = (LDS_AS char*)(size_t)lds_wg + wave * (RB * 9 * 1024) + lane * 16;
+  if (half == 1) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) *(LDS_AS f32x4*)(box + (rb * 9 + dt) * 1024) = w.o[rb][dt];
+      *(LDS_AS f32x4*)(box + (rb * 9 + 8) * 1024) = f32x4{w.m[rb], l[rb], 0.f, 0.f};
+    }
+  }
+  __syncthreads();
+  if (half == 1) return;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const f32x4 ml = *(LDS_AS f32x4*)(box + (rb * 9 + 8) * 1024);
+    const float m = fmaxf(w.m[rb], ml[0]), mm = m == -INFINITY ? 0.f : m;
+    const float s0 = __builtin_amdgcn_exp2f((w.m[rb] - mm) * c), s1 = __builtin_amdgcn_exp2f((ml[0] - mm) * c);
+    l[rb] = l[rb] * s0 + ml[1] * s1;
+    w.m[rb] = m;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+      w.o[rb][dt] = w.o[rb][dt] * s0 + *(LDS_AS f32x4*)(box + (rb * 9 + dt) * 1024) * s1;
   }
 }
 
@@ -706,21 +739,68 @@ __device__ __forceinline__ int next_item(unsigned int* tickets, int home, unsign
   return -1;
 }
 
-__device__ __forceinline__ void phase1_item(const Phase1Args& a, int hpw, int tpb, int n_hs, int id,
-                                            char* lds) {
+// Prefills that last about a millisecond or less take a plain launch: one item of 128
+// rows per workgroup, no queues (and no kernel that clears them).  What bounds these is what an item
+// costs outside its key loop (10 us, six key tiles' time) and the tail of the launch.
+//   W = 4, H = 1: four wavefronts, two workgroups per CU, so that one's loads and stores
+//   hide behind the other's key loop.  W = 4, H = 2: where there are no more items than
+//   CUs, the halves of an eight-wavefront workgroup share an item's keys instead.
+// Order: kv head fastest, then batch, head sub-group; then, in groups of `group` blocks
+// with the same anchor, tile within block (heavy first) and block; the first block last,
+// if it is the only one without an anchor.  `resident` workgroups start at once; if the
+// rest is no more than that many, it comes lightest first (`turn` of them), so that a CU
+// that starts with a heavy item gets a light one beside it.
+struct PlainGrid {
+  int tpb, n_hs;       // tiles per block, head sub-groups
+  int n_same, group;   // blocks of the same weight, and how many of them are taken together
+  int first;           // the first of them (0 or 1)
+  int resident, turn;  // see above; turn = 0: as they come
+};
+struct Item {
+  int kvh, beta, hs, t, i;
+};
+__device__ __forceinline__ Item plain_item(const Geom& g, const PlainGrid& p, int id) {
+  Item x;
+  if (p.turn > 0 && id >= p.resident) id = p.resident + p.turn - 1 - (id - p.resident);
+  x.kvh = id % g.Hkv; id /= g.Hkv;
+  x.beta = id % g.B; id /= g.B;
+  x.hs = id % p.n_hs; id /= p.n_hs;
+  if (id < p.n_same * p.tpb) {
+    const int lo = id / (p.group * p.tpb) * p.group, in = p.n_same - lo < p.group ? p.n_same - lo : p.group;
+    id -= lo * p.tpb;
+    x.t = p.tpb - 1 - id / in;
+    x.i = p.first + lo + id % in;
+  } else {
+    x.t = p.tpb - 1 - (id - p.n_same * p.tpb);
+    x.i = 0;
+  }
+  return x;
+}
+template <int W, int H>
+__device__ __forceinline__ void phase1_item(const Phase1Args& a, int hpw, int tpb, int n_hs, int id, char* lds,
+                                            const PlainGrid* plain = nullptr) {
+  constexpr int THREADS = 64 * W * H;
   const Geom& g = a.g;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = H == 1 ? tid >> 6 : (tid >> 6) % W, lane = tid & 63;
+  const int half = H == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 6) / W);
   const int col = lane & 15, j4 = lane >> 4;
-  const int tm = 16 * (WG_BLOCKS / hpw);         // tokens per workgroup
+  const int tm = 16 * (W * RB / hpw);            // tokens per workgroup
 
-  // item decode: kv head fastest, then batch, head sub-group, tile within block
-  // (late = heavy first), block (block 0, the lightest, last)
-  int kvh = id % g.Hkv; id /= g.Hkv;
-  int beta = id % g.B; id /= g.B;
-  int hs = id % n_hs; id /= n_hs;
-  int t = tpb - 1 - (id % tpb); id /= tpb;
-  int n = (int)((g.L + g.b - 1) / g.b);
-  int i = id + 1 == n ? 0 : id + 1;
+  int kvh, beta, hs, t, n, i;
+  if constexpr (W == NW) {
+    // item decode of the queues: kv head fastest, then batch, head sub-group, tile within
+    // block (late = heavy first), block (block 0, the lightest, last)
+    kvh = id % g.Hkv; id /= g.Hkv;
+    beta = id % g.B; id /= g.B;
+    hs = id % n_hs; id /= n_hs;
+    t = tpb - 1 - (id % tpb); id /= tpb;
+    n = (int)((g.L + g.b - 1) / g.b);
+    i = id + 1 == n ? 0 : id + 1;
+  } else {
+    const Item x = plain_item(g, *plain, id);
+    kvh = x.kvh; beta = x.beta; hs = x.hs; t = x.t; i = x.i;
+    n = (int)((g.L + g.b - 1) / g.b);
+  }
 
   int s = (int)(i * g.b);
   int e = (int)((int64_t)s + g.b < g.L ? s + g.b : g.L);
@@ -779,15 +859,20 @@ __device__ __forceinline__ void phase1_item(const Phase1Args& a, int hpw, int tp
   seq.n_a = (seq.a_hi - seq.a_lo + TKEYS - 1) / TKEYS;
   seq.loc_lo = s;
   seq.loc_hi = wg_last;
-  seq.n_tiles = seq.n_a + (wg_last - s + TKEYS - 1) / TKEYS;
+  const int tiles = seq.n_a + (wg_last - s + TKEYS - 1) / TKEYS;
+  seq.half = half;
+  seq.n_tiles = H == 1 ? tiles : (tiles + 1 - half) / 2;
 
   unsigned lds0 = (unsigned)(size_t)(LDS_AS char*)lds;
-  attend<NW>(w, seq, row_lim, wave_lo, g.scale * LOG2E, lds0, lds0, seq.n_tiles);
+  attend<W, H>(w, seq, row_lim, wave_lo, g.scale * LOG2E, lds0 + (H == 1 ? 0 : half * 4 * TILEB), lds0,
+               H == 1 ? tiles : (tiles + 1) / 2);
+  float l_half[RB];
+  if (H != 1) meet_halves(w, l_half, lds0, wave, half, lane, g.scale * LOG2E);
 
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    float l_tot = quad_sum(w.l[rb]);
-    if (active[rb]) {
+    float l_tot = H == 1 ? quad_sum(w.l[rb]) : l_half[rb];
+    if (active[rb] && (H == 1 || half == 0)) {
       float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
       char* orow = (char*)a.O + (((size_t)beta * g.L + tok[rb]) * g.Hq + head[rb]) * ROWB;
 #pragma unroll
@@ -811,8 +896,8 @@ __device__ __forceinline__ void phase1_item(const Phase1Args& a, int hpw, int tp
     char* kc = (char*)a.Kc + (((size_t)beta * g.Hkv + kvh) * (size_t)g.cap + row0) * ROWB;
     char* vc = (char*)a.Vc + (((size_t)beta * g.Hkv + kvh) * (size_t)g.cap + row0) * ROWB;
     // two units per thread and pass, all four loads before the stores: one round trip
-    for (int u = tid; u < n_units; u += 2 * NT) {
-      const int u2 = u + NT;
+    for (int u = tid; u < n_units; u += 2 * THREADS) {
+      const int u2 = u + THREADS;
       const bool two = u2 < n_units;
       const size_t s1 = (size_t)(row0 + (u >> 4)) * kv_stride + (u & 15) * 16;
       const size_t s2 = two ? (size_t)(row0 + (u2 >> 4)) * kv_stride + (u2 & 15) * 16 : s1;
@@ -839,9 +924,16 @@ __global__ __launch_bounds__(NT, 1) void phase1_bf16_kernel(Phase1Args a, int hp
     const int id = item;
     __syncthreads();                 // everyone holds it before the next round overwrites it
     if (id < 0) return;              // every queue is empty: uniform over the workgroup
-    phase1_item(a, hpw, tpb, n_hs, id, lds);
+    phase1_item<NW, 1>(a, hpw, tpb, n_hs, id, lds);
     __syncthreads();                 // the item's LDS reads are done before the next item's DMAs
   }
+}
+
+template <int W, int H>
+__global__ __launch_bounds__(64 * W * H, W * H == 4 ? 2 : 1) void phase1_bf16_plain_kernel(Phase1Args a, int hpw,
+                                                                                      PlainGrid p) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  phase1_item<W, H>(a, hpw, p.tpb, p.n_hs, (int)blockIdx.x, lds, &p);
 }
 
 // ------------------------------------------------------------------ phase 2
@@ -918,7 +1010,7 @@ __global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, i
 
   const unsigned lds_wg = (unsigned)(size_t)(LDS_AS char*)lds, lds0 = lds_wg + (W == NW ? 0 : half * 4 * TILEB);
   const float c = g.scale * LOG2E;
-  attend<W>(w, seq, row_lim, wave_lo, c, lds0, lds_wg, W == NW ? tiles : (tiles + 1) / 2);
+  attend<W, NW / W>(w, seq, row_lim, wave_lo, c, lds0, lds_wg, W == NW ? tiles : (tiles + 1) / 2);
 
   // Algorithm 2, append: the split that holds a new token files its K and V rows
   if (fused_append && tt == 0) {
@@ -933,33 +1025,12 @@ __global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, i
   }
 
   float l_tot[RB];
+  if (W == NW) {
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) l_tot[rb] = quad_sum(w.l[rb]);
-  if (W != NW) {
-    // The lanes of the second half hand over (O, m, l) to those of the first, register
-    // by register: 1 KiB per wavefront and register, in the ring areas nobody reads any more.
-    LDS_AS char* box = (LDS_AS char*)(size_t)lds_wg + wave * (RB * 9 * 1024) + lane * 16;
-    if (half == 1) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) *(LDS_AS f32x4*)(box + (rb * 9 + dt) * 1024) = w.o[rb][dt];
-        *(LDS_AS f32x4*)(box + (rb * 9 + 8) * 1024) = f32x4{w.m[rb], l_tot[rb], 0.f, 0.f};
-      }
-    }
-    __syncthreads();
+    for (int rb = 0; rb < RB; ++rb) l_tot[rb] = quad_sum(w.l[rb]);
+  } else {
+    meet_halves(w, l_tot, lds_wg, wave, half, lane, c);
     if (half == 1) return;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const f32x4 ml = *(LDS_AS f32x4*)(box + (rb * 9 + 8) * 1024);
-      const float m = fmaxf(w.m[rb], ml[0]), mm = m == -INFINITY ? 0.f : m;
-      const float s0 = __builtin_amdgcn_exp2f((w.m[rb] - mm) * c), s1 = __builtin_amdgcn_exp2f((ml[0] - mm) * c);
-      l_tot[rb] = l_tot[rb] * s0 + ml[1] * s1;
-      w.m[rb] = m;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
-        w.o[rb][dt] = w.o[rb][dt] * s0 + *(LDS_AS f32x4*)(box + (rb * 9 + dt) * 1024) * s1;
-    }
   }
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -995,21 +1066,75 @@ int flash_phase2_rows_per_workgroup(int64_t rows) {
 
 // The kernels' 64 KiB tile rings (one, or one per half) are dynamic LDS; the runtime wants
 // to be told once per kernel and device that a launch may ask for that much.
-enum { ATTR_PHASE1 = 0, ATTR_PHASE2_ROWS = 1, ATTR_PHASE2_HALVES = 2 };
+enum { ATTR_PHASE1 = 0, ATTR_PHASE2_ROWS, ATTR_PHASE2_HALVES, ATTR_PLAIN, ATTR_PLAIN_HALVES, ATTR_COUNT };
 static hipError_t allow_tile_ring(int which, const void* kernel) {
-  static std::atomic<bool> done[3][64];
+  static std::atomic<bool> done[ATTR_COUNT][64];
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev >= 0 && dev < 64 && done[which][dev].load(std::memory_order_acquire)) return hipSuccess;
   e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (which == ATTR_PHASE2_HALVES ? 8 : 4) * TILEB);
+                          (which == ATTR_PHASE2_HALVES || which == ATTR_PLAIN_HALVES ? 8 : 4) * TILEB);
   if (e == hipSuccess && dev >= 0 && dev < 64) done[which][dev].store(true, std::memory_order_release);
   return e;
 }
 
+template <int H>
+static hipError_t launch_phase1_plain(const Phase1Args& a, int hpw, const PlainGrid& p, int64_t wgs, hipStream_t st) {
+  hipError_t e = allow_tile_ring(H == 1 ? ATTR_PLAIN : ATTR_PLAIN_HALVES, (const void*)phase1_bf16_plain_kernel<4, H>);
+  if (e != hipSuccess) return e;
+  phase1_bf16_plain_kernel<4, H><<<dim3((unsigned)wgs), 256 * H, H * 4 * TILEB, st>>>(a, hpw, p);
+  return hipGetLastError();
+}
+
+// Launches a prefill of up to 600 key tiles (256 rows x 64 keys) per CU, about a
+// millisecond, as a plain grid of 128-row items; false: leave it to the queues.  Beyond
+// that the queues' 256-row items win: half the L2 -> LDS traffic, and no XCD waits for
+// another.  Measured, us, queues / plain (32 / 8 heads, b = a = L / 4, tiles per CU in
+// brackets): L = 300 (0.2) 25.3 / 11.7, 1000 (3) 33.4 / 17.5, 2000 (10) 49.3 / 29.7, 4000
+// (38) 105.9 / 90.9, 8191 (160) 322 / 305, 20000 (954) 1703 / 1719, 40000 6451 / 6740; 16
+// heads, G = 1: 20000 (477) 935 / 926; 64 / 8 heads: 8191 (320) 621 / 605, 20000 (1907)
+// 3337 / 3420; b = 1250, a = 312: 20000 (141) 365 / 347.
+// No more items than CUs, and longer than eight key tiles: the halves of a workgroup share
+// an item (8 / 2 heads, L = 4000: 36 us against 44, L = 2000: 22.5 and 24.5; L = 300, five
+// tiles: 11.8 and 11.0).
+static bool plain_phase1(const Phase1Args& a, hipStream_t st, hipError_t* e) {
+  const Geom& g = a.g;
+  const bool all = g.a == 0 || a.anchor_mode == ANCHOR_ALL_BLOCKS;       // every block alike
+  const int64_t bmax = g.b < g.L ? g.b : g.L, n = (g.L + g.b - 1) / g.b;
+  // key tiles of 256 rows x 64 keys, in rounds of 256 workgroups
+  const double work = (double)g.Hq * g.B * ((double)g.L * bmax / 2 + (double)(all ? g.L : g.L - bmax) * g.a) / (16384.0 * 256);
+  if (work > 600) return false;
+  int hpw = flash_heads_per_workgroup(g.G);      // at most 8, the row blocks of four wavefronts
+  const int tm = 16 * (4 * RB / hpw);
+  PlainGrid p;
+  p.tpb = (int)((bmax + tm - 1) / tm);
+  p.n_hs = g.G / hpw;
+  const int64_t wgs = (int64_t)g.Hkv * g.B * p.n_hs * p.tpb * n;
+  if (wgs > 0x7fffffff) return false;
+  p.first = all || n == 1 ? 0 : 1;
+  p.n_same = (int)n - p.first;
+  const int64_t longest = (g.a + TKEYS - 1) / TKEYS + (bmax + TKEYS - 1) / TKEYS;
+  if (wgs <= a.n_cu && longest > 8) {
+    p.group = 1; p.resident = 0; p.turn = 0;
+    *e = launch_phase1_plain<2>(a, hpw, p, wgs, st);
+    return true;
+  }
+  // all resident at once, two per CU: what matters is which two, as long as the keys of all
+  // blocks fit the L2 caches beside each other
+  const bool pairs = wgs > a.n_cu && wgs <= 2 * a.n_cu && g.L * 2 * ROWB <= (2 << 20);
+  p.group = pairs ? p.n_same : 1;
+  p.resident = a.n_cu;
+  p.turn = pairs ? (int)(wgs - a.n_cu) : 0;
+  *e = launch_phase1_plain<1>(a, hpw, p, wgs, st);
+  return true;
+}
+
 hipError_t launch_phase1_bf16(const Phase1Args& a, hipStream_t st) {
   const Geom& g = a.g;
+  if (a.n_cu <= 0 || !a.tickets) return hipErrorInvalidValue;
+  hipError_t e;
+  if (plain_phase1(a, st, &e)) return e;
   int hpw = flash_heads_per_workgroup(g.G);
   int tm = flash_tokens_per_workgroup(g.G);
   int n_hs = g.G / hpw;
@@ -1018,11 +1143,10 @@ hipError_t launch_phase1_bf16(const Phase1Args& a, hipStream_t st) {
   int tpb = (int)((bmax + tm - 1) / tm);
   int64_t wgs = (int64_t)g.Hkv * g.B * n_hs * tpb * n;
   if (wgs > 0x7fffffff) return hipErrorInvalidValue;
-  hipError_t e = allow_tile_ring(ATTR_PHASE1, (const void*)phase1_bf16_kernel);
+  e = allow_tile_ring(ATTR_PHASE1, (const void*)phase1_bf16_kernel);
   if (e != hipSuccess) return e;
   // one workgroup per CU (registers and LDS admit no more), never more than items
   const int n_cu = a.n_cu;
-  if (n_cu <= 0 || !a.tickets) return hipErrorInvalidValue;
   const unsigned resident = (unsigned)(wgs < n_cu ? wgs : n_cu);
   if (resident == 0) return hipSuccess;
   if (!a.tickets_clear) {
