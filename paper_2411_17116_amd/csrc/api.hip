@@ -148,17 +148,21 @@ constexpr int64_t F32_DIRECT_BYTES = 256 << 10;
 // ---- bf16 row-tiled kernel: one workgroup per CU is resident (256 of them).
 constexpr int64_t ROW_WGS = 256;
 
-// Workgroups of one split.
-static int64_t rows_wgs(const Geom& g, int64_t q_len) {
-  const int64_t rows = (int64_t)g.G * q_len;
-  return (int64_t)g.B * g.Hkv * ceil_div(rows, flash_phase2_rows_per_workgroup(rows));
+// Workgroups of one split with tiles of `tile` rows.
+static int64_t rows_wgs(const Geom& g, int64_t q_len, int tile) {
+  return (int64_t)g.B * g.Hkv * ceil_div((int64_t)g.G * q_len, tile);
 }
-// Time of `splits` splits of `len` keys, in the time of one key tile: rounds of resident
-// workgroups, each of them its key tiles (64 keys; 128 where the halves of a workgroup
-// share them) and some 6 tiles' time (10 us) to start, fill the pipeline and store.
-static int64_t rows_cost(const Geom& g, int64_t q_len, int64_t splits, int64_t len) {
-  const int64_t tile = flash_phase2_rows_per_workgroup((int64_t)g.G * q_len) == 128 ? 128 : 64;
-  return ceil_div(splits * rows_wgs(g, q_len), ROW_WGS) * (ceil_div(len, tile) + 6);
+// Time of `splits` splits of `len` keys, in hundredths of a key tile's time (1.65 us): rounds
+// of resident workgroups, each of them its key tiles -- 64 keys for 256 rows, or 128 keys
+// for 128 rows, whose halves share them, 15 % dearer: twice the L2 -> LDS bytes -- and some
+// 6 tiles' time to start, fill the pipeline and store; then the per-split pairs, written
+// and read back at the rate of a copy (8 MB per tile's time).  Measured (32 / 8 heads, us
+// with 256 / 128 rows): 64 tokens on 1000 keys 24.3 / 20.2, 8000 34.8 / 23.9, 32768 56 /
+// 53, 131072 156 / 166; 33 tokens on 32768 49 / 51; 256 tokens on 131072 487 / 550.
+static int64_t rows_cost(const Geom& g, int64_t q_len, int tile, int64_t splits, int64_t len) {
+  const int64_t keys = tile == 128 ? 115 * ceil_div(len, 128) : 100 * ceil_div(len, 64);
+  const int64_t pairs = splits * g.B * g.Hq * q_len * (g.d + 1) * 8;
+  return ceil_div(splits * rows_wgs(g, q_len, tile), ROW_WGS) * (keys + 600) + pairs / 80000;
 }
 // Largest number of splits whose per-split pairs a call may keep: what
 // star_attn_phase2_static's scratch holds, and at least `aligned`.
@@ -167,21 +171,26 @@ static int64_t rows_splits_cap(const Geom& g, int64_t q_len, int64_t aligned) {
   const int64_t fit = STAR_ATTN_STATIC_SCRATCH_BYTES / pair;
   return fit > aligned ? fit : aligned;
 }
-// Equal runs of keys for a call without per-part outputs: the number of splits that fills
-// the resident workgroups once, or, where a split's workgroups do not divide them, up to
-// four times.
-static int64_t rows_flat_splits(const Geom& g, int64_t q_len, int64_t total, int64_t cap) {
-  const int64_t wgs = rows_wgs(g, q_len);
-  int64_t best = 1, cost = rows_cost(g, q_len, 1, total);
-  for (int64_t k = 1; k <= 4; ++k) {
-    int64_t s = k * ROW_WGS / wgs;
-    if (s > ceil_div(total, 256)) s = ceil_div(total, 256);     // keys worth a split
-    if (s > cap) s = cap;
-    if (s < 1) continue;
-    const int64_t len = round_up(ceil_div(total, s), 64);
-    const int64_t c = rows_cost(g, q_len, ceil_div(total, len), len);
-    if (c < cost) { cost = c; best = s; }
-  }
+// Equal runs of keys for a call without per-part outputs: with either tile, the number of
+// splits that fills the resident workgroups once, or, where a split's workgroups do not
+// divide them, up to four times.
+struct RowsChoice {
+  int tile;
+  int64_t splits, len, cost;
+};
+static RowsChoice rows_flat(const Geom& g, int64_t q_len, int64_t total, int64_t cap) {
+  RowsChoice best = {0, 0, 0, 0};
+  for (int tile = 256; tile >= 128; tile -= 128)
+    for (int64_t k = 0; k <= 4; ++k) {
+      int64_t s = k == 0 ? 1 : k * ROW_WGS / rows_wgs(g, q_len, tile);
+      if (s > ceil_div(total, 256)) s = ceil_div(total, 256);     // keys worth a split
+      if (s > cap) s = cap;
+      if (s < 1) continue;
+      const int64_t len = round_up(ceil_div(total, s), 64);
+      s = ceil_div(total, len);
+      const int64_t cost = rows_cost(g, q_len, tile, s, len);
+      if (best.tile == 0 || cost < best.cost) best = {tile, s, len, cost};
+    }
   return best;
 }
 
@@ -201,6 +210,7 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   int64_t rows = (int64_t)g.G * q_len;
   p->decode = (s->dtype == STAR_ATTN_BF16 && rows <= 16) ? 1 : 0;
   p->flat = 0;
+  p->tile_rows = 0;
   p->n_blocks = (int32_t)n;
   if (n > (1 << 24)) return false;
   int64_t split_len;
@@ -255,17 +265,21 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   int64_t st = tail_cap > 0 ? ceil_div(tail_cap, split_len) : 1;
   int64_t s_total = n * spb + st;
   if (s_total > (1 << 24)) return false;
-  if (s->dtype == STAR_ATTN_BF16 && !p->decode && !want_parts) {
+  if (s->dtype == STAR_ATTN_BF16 && !p->decode) {
+    const int64_t c256 = rows_cost(g, q_len, 256, s_total, split_len), c128 = rows_cost(g, q_len, 128, s_total, split_len);
+    p->tile_rows = c128 < c256 ? 128 : 256;
     // equal runs of keys instead of splits of every part, if they take less time
-    const int64_t splits = rows_flat_splits(g, q_len, total, rows_splits_cap(g, q_len, s_total));
-    const int64_t len = round_up(ceil_div(total, splits), 64);
-    if (rows_cost(g, q_len, splits, len) < rows_cost(g, q_len, s_total, split_len)) {
-      p->flat = 1;
-      p->split_len = len;
-      p->spb = 0;
-      p->st = 0;
-      p->s_total = (int32_t)ceil_div(total, len);
-      return true;
+    if (!want_parts) {
+      const RowsChoice f = rows_flat(g, q_len, total, rows_splits_cap(g, q_len, s_total));
+      if (f.cost < (c128 < c256 ? c128 : c256)) {
+        p->flat = 1;
+        p->tile_rows = f.tile;
+        p->split_len = f.len;
+        p->spb = 0;
+        p->st = 0;
+        p->s_total = (int32_t)f.splits;
+        return true;
+      }
     }
   }
   p->split_len = split_len;
@@ -343,7 +357,7 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
     } else if (shape->dtype == STAR_ATTN_F32) {
       need(f32_splits_max(g, q), q);
     } else if (ok) {
-      int64_t most = 4 * ROW_WGS / rows_wgs(g, q), worth = ceil_div(g.cap, 256);
+      int64_t most = 4 * ROW_WGS / rows_wgs(g, q, 256), worth = ceil_div(g.cap, 256);
       if (most > worth) most = worth;
       if (most < 1) most = 1;
       SplitPlan f = {};
@@ -362,7 +376,7 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
     for (int64_t q = 64; q <= max_q_len; q += 32) { consider(q); consider(q + 1); }
     // the equal runs' tiles end elsewhere (256 / G or 128 / G tokens)
     for (int64_t q = 65; q < max_q_len && q <= 4096; ++q)
-      if (rows_wgs(g, q + 1) != rows_wgs(g, q)) consider(q);
+      if (rows_wgs(g, q + 1, 128) != rows_wgs(g, q, 128)) consider(q);
     if (max_q_len > 4096 && best < STAR_ATTN_STATIC_SCRATCH_BYTES) best = STAR_ATTN_STATIC_SCRATCH_BYTES;
   }
   consider(max_q_len);
@@ -636,7 +650,7 @@ int star_attn_merge(const star_attn_shape* shape, int64_t n_parts, int64_t q_len
   if (rows > (int64_t)0x7fffffff || rows * n_parts > ((int64_t)1 << 40)) return STAR_ATTN_ERR_INVALID_SHAPE;
   MergeArgs m;
   m.g = g;
-  m.plan = SplitPlan{0, 0, 0, 0, (int32_t)n_parts, 0, 1};    // one part made of n_parts splits
+  m.plan = SplitPlan{0, 0, 0, 0, (int32_t)n_parts, 0, 1, 0};    // one part made of n_parts splits
   m.q_len = (int32_t)q_len;
   m.out_bf16 = shape->dtype == STAR_ATTN_BF16;
   m.O_sub = A_parts; m.LSE_sub = LSE_parts;

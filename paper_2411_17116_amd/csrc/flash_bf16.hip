@@ -943,7 +943,9 @@ __global__ __launch_bounds__(64 * W * H, W * H == 4 ? 2 : 1) void phase1_bf16_pl
 // key tiles.  W = 4: a tile of 128 rows; the two halves of the workgroup hold the same
 // rows, walk every other key tile and meet in LDS at the end: at no more than 128 rows a
 // key tile then costs half a tile's time of the matrix pipes, and twice as many bytes are
-// in flight (what bounds these calls is the stream of the cache).
+// in flight (what bounds these calls is the stream of the cache); with more rows it halves
+// the per-split pairs.  The split plan chooses (rows_cost() in api.hip).  A ring of four
+// tiles with three in flight was 2.5 % slower for 256 rows: latency is not what bounds it.
 // grid.x numbers (kv head fastest, row tile, split, batch): with Hkv a multiple of 8 an
 // XCD's L2 serves one KV head, and the row tiles of a split read its keys there.
 template <int W>
@@ -1058,12 +1060,6 @@ int flash_heads_per_workgroup(int G) {
 }
 int flash_tokens_per_workgroup(int G) { return 16 * (WG_BLOCKS / flash_heads_per_workgroup(G)); }
 
-// Rows per workgroup of the phase-2 kernel: 128, two halves of the workgroup sharing the
-// keys, where that leaves fewer rows empty than 256.
-int flash_phase2_rows_per_workgroup(int64_t rows) {
-  return (rows + 127) / 128 < 2 * ((rows + 255) / 256) ? 128 : 256;
-}
-
 // The kernels' 64 KiB tile rings (one, or one per half) are dynamic LDS; the runtime wants
 // to be told once per kernel and device that a launch may ask for that much.
 enum { ATTR_PHASE1 = 0, ATTR_PHASE2_ROWS, ATTR_PHASE2_HALVES, ATTR_PLAIN, ATTR_PLAIN_HALVES, ATTR_COUNT };
@@ -1170,8 +1166,7 @@ static hipError_t launch_phase2_rows(const Phase2Args& a, int which, hipStream_t
 }
 
 hipError_t launch_phase2_rows_bf16(const Phase2Args& a, hipStream_t st) {
-  if (flash_phase2_rows_per_workgroup((int64_t)a.g.G * a.q_len) == 128)
-    return launch_phase2_rows<4>(a, ATTR_PHASE2_HALVES, st);
+  if (a.plan.tile_rows == 128) return launch_phase2_rows<4>(a, ATTR_PHASE2_HALVES, st);
   return launch_phase2_rows<NW>(a, ATTR_PHASE2_ROWS, st);
 }
 
