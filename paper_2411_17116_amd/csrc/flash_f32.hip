@@ -478,11 +478,12 @@ hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   const int64_t tpb = (bmax * g.G + 16 * NB - 1) / (16 * NB), wgs = n * tpb * g.B * g.Hkv;
   // (a block of 2^31 rows would be 550 GB of queries)
   if (wgs > 0x7fffffff || bmax * g.G > 0x7fffffff - 64) return hipErrorInvalidValue;
-  // All blocks in one group, unless the keys in use at a time would then not fit the 4 MiB
-  // L2 cache of an XCD: K and V of a KV head beyond 6 MiB go block by block.  8 / 2 heads,
-  // d = 128: blocks of 2048 of 8192 tokens 816 us in one group, 705 block by block; blocks
-  // of 1024 of 4099 tokens 151 and 155 us, of 256 of 1024 tokens 24 and 27 us.
-  const int64_t group = g.L * g.d * 8 <= ((int64_t)6 << 20) ? n : 1;
+  // All blocks in one group while a few rounds of workgroups are all there is and the keys in
+  // use at a time fit the 4 MiB L2 cache of an XCD (K and V of a KV head up to 6 MiB), else
+  // block by block.  8 / 2 heads, us in one group / block by block: d = 128: blocks of 2048 of
+  // 8192 tokens 816 / 705, of 1024 of 4099 (1025 workgroups) 151 / 155, of 256 of 1024 24 / 27;
+  // d = 64: of 2048 of 8192 (2048 workgroups) 434 / 369, of 1024 of 4099 86 / 90.
+  const int64_t group = wgs <= 1536 && g.L * g.d * 8 <= ((int64_t)6 << 20) ? n : 1;
   phase1_f32_kernel<D, NB, KW><<<dim3((unsigned)wgs), 64 * KW, 0, st>>>(a, (int)group, (int)tpb);
   return hipGetLastError();
 }
