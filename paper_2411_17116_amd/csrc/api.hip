@@ -130,16 +130,25 @@ static int64_t decode_slots(const Geom& g, int64_t total) {
 }
 static int64_t decode_slots_max() { return device_cu_count() * (int64_t)4; }
 
-// Splits of a flat plan of the fp32 kernel: enough for one workgroup (eight wavefronts
-// that share the split's keys) per CU of an MI355X, and never more than
+// ---- fp32 kernel: tiles of 16 rows shared by eight wavefronts (one workgroup per CU), or
+// of 32 rows shared by four (two per CU).
+// Most splits: what the resident workgroups can take at once, and never more than
 // 4096 / (B Hq ceil(q / 64)), which bounds the per-split pairs a call keeps.
-static int64_t f32_splits_max(const Geom& g, int64_t q_len) {
-  const int64_t rows = (int64_t)g.G * q_len;
-  const int64_t tiles = (int64_t)g.B * g.Hkv * ceil_div(rows, f32_phase2_rows_per_workgroup(rows));
-  const int64_t fill = ceil_div(256, tiles), bound = ceil_div(4096, (int64_t)g.B * g.Hq * ceil_div(q_len, 64));
-  return fill < bound ? fill : bound;
+static int64_t f32_splits_max(const Geom& g, int64_t q_len, int tile) {
+  const int64_t tiles = (int64_t)g.B * g.Hkv * ceil_div((int64_t)g.G * q_len, tile);
+  const int64_t fill = (tile == 16 ? 256 : 512) / tiles, bound = ceil_div(4096, (int64_t)g.B * g.Hq * ceil_div(q_len, 64));
+  return fill < 1 ? 1 : fill < bound ? fill : bound;
 }
-constexpr int64_t F32_SPLIT_MIN = 128;     // keys: one 16-key unit for each of the eight wavefronts
+constexpr int64_t F32_SPLIT_MIN = 128;     // keys: one or two 16-key units for each wavefront
+// Rows per tile: 16 while those tiles with splits of that size leave CUs idle or fill them
+// about twice (a unit of 16 keys then takes half as long), 32 beyond.  Measured, us, against
+// 32-row tiles shared by eight wavefronts, one workgroup per CU (8 / 2 heads, d = 128):
+// 33 tokens on 300 keys 18.2 -> 12.6, on 4000 26.0 -> 22.9; 100 on 4000 50.0 -> 32.7, on
+// 16000 124 -> 74.
+static int f32_tile_rows(const Geom& g, int64_t q_len, int64_t total) {
+  const int64_t rows = (int64_t)g.G * q_len, tiles = (int64_t)g.B * g.Hkv * ceil_div(rows, 16);
+  return rows <= 16 || tiles * ceil_div(total, F32_SPLIT_MIN) <= 512 ? 16 : 32;
+}
 // Up to these bytes of K and V per KV head one workgroup walks all keys of its rows and
 // there is nothing to merge: with the matrix pipe of one CU it takes 9.3 us at 250 KiB and
 // 13.9 at 530 (one row, d = 64), splits and their merge 11.7 us at either.
@@ -229,7 +238,8 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     return true;
   }
   if (s->dtype == STAR_ATTN_F32 && !want_parts) {
-    int64_t splits = f32_splits_max(g, q_len);
+    p->tile_rows = f32_tile_rows(g, q_len, total);
+    int64_t splits = f32_splits_max(g, q_len, p->tile_rows);
     if (splits > ceil_div(total, F32_SPLIT_MIN)) splits = ceil_div(total, F32_SPLIT_MIN);
     if (total * g.d * 8 <= F32_DIRECT_BYTES) splits = 1;
     p->flat = 1;
@@ -247,7 +257,8 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   } else {
     int64_t want, min_len;   // splits over all blocks that fill the GPU; keys worth a split
     if (s->dtype == STAR_ATTN_F32) {
-      want = f32_splits_max(g, q_len);
+      p->tile_rows = f32_tile_rows(g, q_len, total);
+      want = f32_splits_max(g, q_len, p->tile_rows);
       min_len = F32_SPLIT_MIN;
     } else {
       const int64_t wgs = (int64_t)g.B * g.Hkv * (g.G / flash_heads_per_workgroup(g.G)) *
@@ -355,7 +366,8 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
       SplitPlan f;
       if (make_plan(shape, q, shape->cache_capacity, false, &f)) need(f.s_total > s0 ? f.s_total : s0, q);
     } else if (shape->dtype == STAR_ATTN_F32) {
-      need(f32_splits_max(g, q), q);
+      need(f32_splits_max(g, q, 16), q);
+      need(f32_splits_max(g, q, 32), q);
     } else if (ok) {
       int64_t most = 4 * ROW_WGS / rows_wgs(g, q, 256), worth = ceil_div(g.cap, 256);
       if (most > worth) most = worth;

@@ -141,22 +141,28 @@ template <int D, int NB, bool MORE>
 __device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, const UnitAt& cur, const UnitAt& nxt,
                                             const int (&row_lim)[NB], int wave_lim, int lane) {
   const int j4 = lane >> 4;
-  // two chains per score tile (d split by parity): half the rounding of one chain of d terms
-  f32x4 s[NB], s1[NB];
+  // four chains per score tile (element e of every 16-byte piece has its own; two where the
+  // registers are used up): a quarter of the terms, and of the partial sums' size, per chain
+  // keeps the rounding of a large logit down
+  constexpr int CH = NB == 2 && D == 128 ? 2 : 4;
+  f32x4 s[NB], part[NB][CH];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) s[b] = s1[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int k = 0; k < CH; ++k) part[b][k] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int t = 0; t < D / 16; ++t)
 #pragma unroll
     for (int e = 0; e < 4; e += 2)
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        s[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][e], w.q[b][t][e], s[b], 0, 0, 0);
-        s1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][e + 1], w.q[b][t][e + 1], s1[b], 0, 0, 0);
-      }
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int k = e; k < e + 2; ++k)
+          part[b][k % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][k], w.q[b][t][k], part[b][k % CH], 0, 0, 0);
   if (MORE) load_k<D>(r, nxt, lane);
 #pragma unroll
-  for (int b = 0; b < NB; ++b) s[b] += s1[b];
+  for (int b = 0; b < NB; ++b)
+    s[b] = CH == 2 ? part[b][0] + part[b][1] : (part[b][0] + part[b][1]) + (part[b][CH - 2] + part[b][CH - 1]);
   if (cur.n_rows < UNIT || (cur.local && cur.key0 + UNIT > wave_lim)) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -517,13 +523,9 @@ hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   return g.d == 64 ? launch_phase1<64, 1, 8>(a, st) : launch_phase1<128, 1, 8>(a, st);
 }
 
-int f32_phase2_rows_per_workgroup(int64_t rows) { return rows > 16 ? 32 : 16; }
-
 hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st) {
-  const Geom& g = a.g;
-  if (f32_phase2_rows_per_workgroup((int64_t)g.G * a.q_len) == 32)
-    return g.d == 64 ? launch_phase2<64, 2, 8>(a, st) : launch_phase2<128, 2, 8>(a, st);
-  return g.d == 64 ? launch_phase2<64, 1, 8>(a, st) : launch_phase2<128, 1, 8>(a, st);
+  if (a.plan.tile_rows == 32) return a.g.d == 64 ? launch_phase2<64, 2, 4>(a, st) : launch_phase2<128, 2, 4>(a, st);
+  return a.g.d == 64 ? launch_phase2<64, 1, 8>(a, st) : launch_phase2<128, 1, 8>(a, st);
 }
 
 }  // namespace star

@@ -31,7 +31,7 @@ struct SplitPlan {
   int32_t s_total;     // n_blocks * spb + st  (flat: number of splits)
   int32_t decode;      // 1: streaming split-KV kernel, 0: row-tiled kernel
   int32_t flat;        // 1: splits ignore part boundaries
-  int32_t tile_rows;   // bf16 row-tiled kernel: rows per workgroup (256 or 128); else 0
+  int32_t tile_rows;   // row-tiled kernels: rows per workgroup (bf16 256 or 128, fp32 32 or 16)
 };
 
 // Geometry every kernel needs.  Strides are in elements.
@@ -164,9 +164,6 @@ __host__ __device__ inline void split_range(const SplitPlan& p, int64_t L, int64
 // and tokens per workgroup.
 int flash_heads_per_workgroup(int G);
 int flash_tokens_per_workgroup(int G);
-
-// Rows (heads of a KV group x tokens) of a workgroup of the fp32 phase-2 kernel.
-int f32_phase2_rows_per_workgroup(int64_t rows);
 
 // Compute units of the current device (cached per device; 0 if the runtime refuses).
 int device_cu_count();

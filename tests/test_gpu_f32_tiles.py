@@ -50,6 +50,16 @@ def test_fp32_many_rows(B, Hq, Hkv, d, L, b, a):
     cfg = workloads.StarConfig("f32many", "fp32", B, Hq, Hkv, d, L, b, a, 100, 1, seed=5, n_planted=2)
     rep = ph.run_parity(cfg)
     assert rep.ok, rep.detail
+    # the query call (100 tokens: 32-row tiles of phase 2 on the longer contexts) in equal runs of keys
+    inp = workloads.make_inputs(cfg, "cuda")
+    one, two = ph.HipRun(cfg, inp, "cuda"), ph.HipRun(cfg, inp, "cuda")
+    one.phase1()
+    two.phase1()
+    want, _, _ = one.phase2(inp.Qq, inp.Kq, inp.Vq, want_parts=True)
+    got, _, _ = two.phase2(inp.Qq, inp.Kq, inp.Vq, want_parts=False)
+    torch.cuda.synchronize()
+    assert (want - got).abs().max().item() <= 2 * ph.TOL["fp32"]["o"]
+    assert torch.equal(one.Kc, two.Kc) and torch.equal(one.Vc, two.Vc)
 
 
 def test_fp32_workspace_covers_every_shorter_call():
