@@ -16,8 +16,8 @@
  * Conventions
  *   - Every pointer is DEVICE memory owned by the caller unless it says "host".
  *     The library never allocates device memory, frees or keeps a pointer
- *     after a call returns.  The bf16 phase-1 kernel draws its row tiles from
- *     eight work-queue counters; they live in the call's workspace.  A caller
+ *     after a call returns.  The bf16 phase-1 kernel draws the row tiles of a long
+ *     prefill from eight work-queue counters; they live in the call's workspace.  A caller
  *     that passes no workspace gets one of 64 sets in the library's static
  *     device memory instead (its only state): a set is handed out again only
  *     when the call that last used it has finished on the device, and a call
@@ -174,9 +174,9 @@ int star_attn_phase1(const star_attn_shape* shape,
  *                 inputs; read only in these modes with a > 0 (else may be NULL)
  *   workspace     at least star_attn_phase1_workspace_bytes(shape, mode) bytes,
  *                 256-byte aligned, scratch.  bf16: the work-queue counters, as in
- *                 star_attn_phase1 (NULL selects the library's own).  fp32:
- *                 a head-major copy of separately given anchors; unused and may be
- *                 NULL / 0 when that size is 0
+ *                 star_attn_phase1 (NULL selects the library's own).  fp32: asked for
+ *                 with separately given anchors (their size; the kernels read them in
+ *                 place, the room is spare); unused and may be NULL / 0 when that size is 0
  *   other arguments as in star_attn_phase1
  * Errors as in star_attn_phase1, plus STAR_ATTN_ERR_INVALID_MODE and
  * STAR_ATTN_ERR_WORKSPACE_TOO_SMALL.
@@ -189,7 +189,7 @@ int star_attn_phase1_anchor(const star_attn_shape* shape, int anchor_mode,
                             void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* Workspace bytes of star_attn_phase1 / _anchor / _rope: 256 for bf16 (the launch's work-queue
- * counters), the anchor copies for separately given anchors in fp32, else 0; 0 for an invalid shape. */
+ * counters), the size of separately given anchors in fp32, else 0; 0 for an invalid shape. */
 size_t star_attn_phase1_workspace_bytes(const star_attn_shape* shape, int anchor_mode);
 
 /*
@@ -280,7 +280,7 @@ int star_attn_phase2_static(const star_attn_shape* shape,
  *   n_parts    number of gathered pairs, >= 1
  *   A_parts    in   [n_parts, B, Hq, q_len, d] fp32 (one contiguous slab per host)
  *   LSE_parts  in   [n_parts, B, Hq, q_len] fp32; -inf marks a host that saw no
- *              key: its slab is not read and it contributes nothing
+ *              key: its slab may hold anything and contributes nothing
  *   O          out  [B, q_len, Hq, d] in the storage dtype; may be NULL if A is given
  *   A, LSE     out  the merged pair in fp32, layouts as above (for merging in
  *              stages); each may be NULL

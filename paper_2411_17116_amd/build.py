@@ -14,7 +14,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstarattn.so")
-SOURCES = ["api.hip", "kv_cache.hip", "rope.hip", "flash_f32.hip", "flash_bf16.hip",
+SOURCES = ["api.hip", "rope.hip", "flash_f32.hip", "flash_bf16.hip",
            "decode_bf16.hip", "merge.hip"]
 # the benchmark's calibration kernels: a library of their own, so that the
 # product library holds nothing but the path

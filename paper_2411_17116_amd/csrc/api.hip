@@ -321,8 +321,8 @@ static int validate_rope(const star_attn_shape* s, double theta, int64_t pos0) {
   return STAR_ATTN_OK;
 }
 
-// Bytes of one head-major copy of the external anchor (K or V), 256-byte padded.
-static size_t anchor_copy_bytes(const star_attn_shape* s, int anchor_mode) {
+// Bytes of the separately given anchors (K or V), 256-byte padded.
+static size_t anchor_bytes(const star_attn_shape* s, int anchor_mode) {
   size_t es = s->dtype == STAR_ATTN_F32 ? 4 : 2;
   size_t anchors = anchor_mode == STAR_ATTN_ANCHOR_PER_BLOCK
                        ? (size_t)((s->ctx_len + s->block - 1) / s->block) : 1;
@@ -401,7 +401,7 @@ size_t star_attn_phase1_workspace_bytes(const star_attn_shape* shape, int anchor
   const bool given = anchor_mode == STAR_ATTN_ANCHOR_EXTERNAL ||
                      anchor_mode == STAR_ATTN_ANCHOR_PER_BLOCK ||
                      anchor_mode == STAR_ATTN_ANCHOR_ALL_BLOCKS;
-  return given ? 2 * anchor_copy_bytes(shape, anchor_mode) : 0;
+  return given ? 2 * anchor_bytes(shape, anchor_mode) : 0;
 }
 
 }  // extern "C"
@@ -436,7 +436,7 @@ static int phase1_impl(const star_attn_shape* shape, int anchor_mode, const Rope
   if (ext_workspace) {
     if (!workspace) return STAR_ATTN_ERR_NULL_POINTER;
     if ((uintptr_t)workspace & 255u) return STAR_ATTN_ERR_MISALIGNED;
-    if (workspace_bytes < 2 * anchor_copy_bytes(shape, anchor_mode))
+    if (workspace_bytes < 2 * anchor_bytes(shape, anchor_mode))
       return STAR_ATTN_ERR_WORKSPACE_TOO_SMALL;
   }
   Geom g = make_geom(shape);

@@ -169,10 +169,6 @@ int flash_tokens_per_workgroup(int G);
 int device_cu_count();
 
 // Host-side launchers (each returns the hipError_t of its launch).
-// K and / or V (a null source is skipped) into rows [dst_row, dst_row + n_tokens).
-hipError_t launch_cache_write(const Geom& g, int dtype, const void* K, const void* V,
-                              void* Kc, void* Vc, int64_t n_tokens, int64_t dst_row,
-                              hipStream_t st);
 // X [B, n_tokens, H, d] rotated into Y (same layout; Y may be X), token t at pos0 + t; with
 // K and V (null: neither) [B, n_tokens, Hkv, d], rotated K and V as it is into cache rows
 // [dst_row, dst_row + n_tokens).  `clear`: eight counters to zero on the way, or null.
