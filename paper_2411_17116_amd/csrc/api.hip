@@ -147,7 +147,7 @@ constexpr int64_t F32_SPLIT_MIN = 128;     // keys: one or two 16-key units for 
 // 16000 124 -> 74.
 static int f32_tile_rows(const Geom& g, int64_t q_len, int64_t total) {
   const int64_t rows = (int64_t)g.G * q_len, tiles = (int64_t)g.B * g.Hkv * ceil_div(rows, 16);
-  return rows <= 16 || tiles * ceil_div(total, F32_SPLIT_MIN) <= 512 ? 16 : 32;
+  return rows <= 16 || (double)tiles * ceil_div(total, F32_SPLIT_MIN) <= 512 ? 16 : 32;
 }
 // Up to these bytes of K and V per KV head one workgroup walks all keys of its rows and
 // there is nothing to merge: with the matrix pipe of one CU it takes 9.3 us at 250 KiB and
@@ -168,10 +168,10 @@ static int64_t rows_wgs(const Geom& g, int64_t q_len, int tile) {
 // and read back at the rate of a copy (8 MB per tile's time).  Measured (32 / 8 heads, us
 // with 256 / 128 rows): 64 tokens on 1000 keys 24.3 / 20.2, 8000 34.8 / 23.9, 32768 56 /
 // 53, 131072 156 / 166; 33 tokens on 32768 49 / 51; 256 tokens on 131072 487 / 550.
-static int64_t rows_cost(const Geom& g, int64_t q_len, int tile, int64_t splits, int64_t len) {
-  const int64_t keys = tile == 128 ? 115 * ceil_div(len, 128) : 100 * ceil_div(len, 64);
-  const int64_t pairs = splits * g.B * g.Hq * q_len * (g.d + 1) * 8;
-  return ceil_div(splits * rows_wgs(g, q_len, tile), ROW_WGS) * (keys + 600) + pairs / 80000;
+static double rows_cost(const Geom& g, int64_t q_len, int tile, int64_t splits, int64_t len) {
+  const double keys = tile == 128 ? 115.0 * ceil_div(len, 128) : 100.0 * ceil_div(len, 64);
+  const double pairs = 8.0 * splits * g.B * g.Hq * q_len * (g.d + 1);
+  return ceil((double)splits * rows_wgs(g, q_len, tile) / ROW_WGS) * (keys + 600) + pairs / 80000;
 }
 // Largest number of splits whose per-split pairs a call may keep: what
 // star_attn_phase2_static's scratch holds, and at least `aligned`.
@@ -185,10 +185,11 @@ static int64_t rows_splits_cap(const Geom& g, int64_t q_len, int64_t aligned) {
 // divide them, up to four times.
 struct RowsChoice {
   int tile;
-  int64_t splits, len, cost;
+  int64_t splits, len;
+  double cost;
 };
 static RowsChoice rows_flat(const Geom& g, int64_t q_len, int64_t total, int64_t cap) {
-  RowsChoice best = {0, 0, 0, 0};
+  RowsChoice best = {0, 0, 0, 0.0};
   for (int tile = 256; tile >= 128; tile -= 128)
     for (int64_t k = 0; k <= 4; ++k) {
       int64_t s = k == 0 ? 1 : k * ROW_WGS / rows_wgs(g, q_len, tile);
@@ -197,7 +198,7 @@ static RowsChoice rows_flat(const Geom& g, int64_t q_len, int64_t total, int64_t
       if (s < 1) continue;
       const int64_t len = round_up(ceil_div(total, s), 64);
       s = ceil_div(total, len);
-      const int64_t cost = rows_cost(g, q_len, tile, s, len);
+      const double cost = rows_cost(g, q_len, tile, s, len);
       if (best.tile == 0 || cost < best.cost) best = {tile, s, len, cost};
     }
   return best;
@@ -277,7 +278,7 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   int64_t s_total = n * spb + st;
   if (s_total > (1 << 24)) return false;
   if (s->dtype == STAR_ATTN_BF16 && !p->decode) {
-    const int64_t c256 = rows_cost(g, q_len, 256, s_total, split_len), c128 = rows_cost(g, q_len, 128, s_total, split_len);
+    const double c256 = rows_cost(g, q_len, 256, s_total, split_len), c128 = rows_cost(g, q_len, 128, s_total, split_len);
     p->tile_rows = c128 < c256 ? 128 : 256;
     // equal runs of keys instead of splits of every part, if they take less time
     if (!want_parts) {
@@ -366,8 +367,11 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
       SplitPlan f;
       if (make_plan(shape, q, shape->cache_capacity, false, &f)) need(f.s_total > s0 ? f.s_total : s0, q);
     } else if (shape->dtype == STAR_ATTN_F32) {
-      need(f32_splits_max(g, q, 16), q);
-      need(f32_splits_max(g, q, 32), q);
+      const int64_t worth = ceil_div(g.cap, F32_SPLIT_MIN);
+      for (int tile = 16; tile <= 32; tile += 16) {
+        const int64_t most = f32_splits_max(g, q, tile);
+        need(most < worth ? most : worth, q);
+      }
     } else if (ok) {
       int64_t most = 4 * ROW_WGS / rows_wgs(g, q, 256), worth = ceil_div(g.cap, 256);
       if (most > worth) most = worth;
