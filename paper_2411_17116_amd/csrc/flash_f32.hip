@@ -313,18 +313,18 @@ __device__ __forceinline__ void file_rows(const float* K, const float* V, int64_
 }
 
 // ------------------------------------------------------------------ phase 1
-// grid.x numbers (kv head fastest, batch, block in group -- block 0, which has no anchor,
+// Workgroups are numbered (kv head fastest, batch, block in group -- block 0, which has no anchor,
 // last --, tile in block -- late, i.e. heavy, first --, group of blocks).  Inside a group
 // the tiles come in descending weight, so that those that share a CU, or come last,
 // even out.
 template <int D, int NB, int KW>
-__global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, int group,
-                                                                   int tiles_per_block) {
+__global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, int group, int tiles_per_block,
+                                                                int first_wg) {
   __shared__ Meet<NB, KW> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
-  int id = blockIdx.x;
+  int id = first_wg + (int)blockIdx.x;
   const int kvh = id % g.Hkv; id /= g.Hkv;
   const int beta = id % g.B; id /= g.B;
   const int n = (int)((g.L + g.b - 1) / g.b), first = id / (group * tiles_per_block) * group;
@@ -398,14 +398,14 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, in
 }
 
 // ------------------------------------------------------------------ phase 2
-// grid.x numbers (kv head fastest, row tile, split, batch).
+// Workgroups are numbered (kv head fastest, row tile, split, batch).
 template <int D, int NB, int KW>
-__global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, int row_tiles) {
+__global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, int row_tiles, int first_wg) {
   __shared__ Meet<NB, KW> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
-  int id = blockIdx.x;
+  int id = first_wg + (int)blockIdx.x;
   const int kvh = id % g.Hkv; id /= g.Hkv;
   const int tile = id % row_tiles; id /= row_tiles;
   const int sp = id % a.plan.s_total;
@@ -490,8 +490,9 @@ hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   // 8192 tokens 816 / 705, of 1024 of 4099 (1025 workgroups) 151 / 155, of 256 of 1024 24 / 27;
   // d = 64: of 2048 of 8192 (2048 workgroups) 434 / 369, of 1024 of 4099 86 / 90.
   const int64_t group = wgs <= 1536 && g.L * g.d * 8 <= ((int64_t)6 << 20) ? n : 1;
-  phase1_f32_kernel<D, NB, KW><<<dim3((unsigned)wgs), 64 * KW, 0, st>>>(a, (int)group, (int)tpb);
-  return hipGetLastError();
+  return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
+    phase1_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, (int)group, (int)tpb, (int)first);
+  });
 }
 
 template <int D, int NB, int KW>
@@ -500,8 +501,9 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
   const int64_t tiles = ((int64_t)g.G * a.q_len + 16 * NB - 1) / (16 * NB);
   const int64_t wgs = tiles * g.B * g.Hkv * a.plan.s_total;
   if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff - 64) return hipErrorInvalidValue;
-  phase2_f32_kernel<D, NB, KW><<<dim3((unsigned)wgs), 64 * KW, 0, st>>>(a, (int)tiles);
-  return hipGetLastError();
+  return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
+    phase2_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, (int)tiles, (int)first);
+  });
 }
 
 }  // namespace

@@ -168,6 +168,20 @@ int flash_tokens_per_workgroup(int G);
 // Compute units of the current device (cached per device; 0 if the runtime refuses).
 int device_cu_count();
 
+// A launch counts work-items in 32 bits, and the runtime keeps the low 32 bits of a larger
+// grid without an error: 8454015 workgroups of 512 threads run as 65407.  More workgroups than
+// fit are therefore launched in pieces; launch(first, n) enqueues workgroups [first, first + n).
+template <typename Launch>
+inline hipError_t launch_in_pieces(int64_t workgroups, int threads, Launch launch) {
+  const int64_t most = (int64_t)0xffffffffu / threads;
+  for (int64_t first = 0; first < workgroups; first += most) {
+    launch((unsigned)first, (unsigned)(workgroups - first < most ? workgroups - first : most));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Host-side launchers (each returns the hipError_t of its launch).
 // X [B, n_tokens, H, d] rotated into Y (same layout; Y may be X), token t at pos0 + t; with
 // K and V (null: neither) [B, n_tokens, Hkv, d], rotated K and V as it is into cache rows
