@@ -930,10 +930,10 @@ __global__ __launch_bounds__(NT, 1) void phase1_bf16_kernel(Phase1Args a, int hp
 }
 
 template <int W, int H>
-__global__ __launch_bounds__(64 * W * H, W * H == 4 ? 2 : 1) void phase1_bf16_plain_kernel(Phase1Args a, int hpw,
-                                                                                      PlainGrid p) {
+__global__ __launch_bounds__(64 * W * H, W * H == 4 ? 2 : 1) void phase1_bf16_plain_kernel(Phase1Args a, int hpw, PlainGrid p,
+                                                                                      int first_wg) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  phase1_item<W, H>(a, hpw, p.tpb, p.n_hs, (int)blockIdx.x, lds, &p);
+  phase1_item<W, H>(a, hpw, p.tpb, p.n_hs, first_wg + (int)blockIdx.x, lds, &p);
 }
 
 // ------------------------------------------------------------------ phase 2
@@ -946,16 +946,16 @@ __global__ __launch_bounds__(64 * W * H, W * H == 4 ? 2 : 1) void phase1_bf16_pl
 // in flight (what bounds these calls is the stream of the cache); with more rows it halves
 // the per-split pairs.  The split plan chooses (rows_cost() in api.hip).  A ring of four
 // tiles with three in flight was 2.5 % slower for 256 rows: latency is not what bounds it.
-// grid.x numbers (kv head fastest, row tile, split, batch): with Hkv a multiple of 8 an
+// Workgroups are numbered (kv head fastest, row tile, split, batch): with Hkv a multiple of 8 an
 // XCD's L2 serves one KV head, and the row tiles of a split read its keys there.
 template <int W>
-__global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, int row_tiles) {
+__global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, int row_tiles, int first_wg) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const Geom& g = a.g;
   const int tid = threadIdx.x, wave = (tid >> 6) % W, half = __builtin_amdgcn_readfirstlane((tid >> 6) / W);
   const int lane = tid & 63, col = lane & 15, j4 = lane >> 4;
 
-  int id = blockIdx.x;
+  int id = first_wg + (int)blockIdx.x;
   const int kvh = id % g.Hkv; id /= g.Hkv;
   const int tt = id % row_tiles; id /= row_tiles;
   const int sp = id % a.plan.s_total;
@@ -1079,8 +1079,9 @@ template <int H>
 static hipError_t launch_phase1_plain(const Phase1Args& a, int hpw, const PlainGrid& p, int64_t wgs, hipStream_t st) {
   hipError_t e = allow_tile_ring(H == 1 ? ATTR_PLAIN : ATTR_PLAIN_HALVES, (const void*)phase1_bf16_plain_kernel<4, H>);
   if (e != hipSuccess) return e;
-  phase1_bf16_plain_kernel<4, H><<<dim3((unsigned)wgs), 256 * H, H * 4 * TILEB, st>>>(a, hpw, p);
-  return hipGetLastError();
+  return launch_in_pieces(wgs, 256 * H, [&](unsigned first, unsigned n_wgs) {
+    phase1_bf16_plain_kernel<4, H><<<dim3(n_wgs), 256 * H, H * 4 * TILEB, st>>>(a, hpw, p, (int)first);
+  });
 }
 
 // Launches a prefill of up to 600 key tiles (256 rows x 64 keys) per CU, about a
@@ -1161,8 +1162,9 @@ static hipError_t launch_phase2_rows(const Phase2Args& a, int which, hipStream_t
   if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff) return hipErrorInvalidValue;
   hipError_t e = allow_tile_ring(which, (const void*)phase2_rows_bf16_kernel<W>);
   if (e != hipSuccess) return e;
-  phase2_rows_bf16_kernel<W><<<dim3((unsigned)wgs), NT, (NW / W) * 4 * TILEB, st>>>(a, (int)row_tiles);
-  return hipGetLastError();
+  return launch_in_pieces(wgs, NT, [&](unsigned first, unsigned n_wgs) {
+    phase2_rows_bf16_kernel<W><<<dim3(n_wgs), NT, (NW / W) * 4 * TILEB, st>>>(a, (int)row_tiles, (int)first);
+  });
 }
 
 hipError_t launch_phase2_rows_bf16(const Phase2Args& a, hipStream_t st) {

@@ -57,3 +57,8 @@ def test_fp32_decode_step():
         w = torch.softmax((Kc[s].double() * q[s, 0, :, None].double()).sum(-1) * d ** -0.5, dim=2)
         want = (w[..., None] * Vc[s].double()).sum(2)
         assert (O[s, 0].double() - want).abs().max().item() <= 1e-5
+
+
+def test_bf16_prefill():
+    # the plain grid: 8 x 2098000 items of four wavefronts
+    _prefill_of_one_token_blocks(torch.bfloat16, 128, 2098000, 8)
