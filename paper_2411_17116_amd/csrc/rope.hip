@@ -59,6 +59,7 @@ struct RopeArgs {
   void* Vc;
   int32_t H, Hkv;
   uint32_t n_tokens, total;   // T, B T
+  uint32_t first;         // first token of the launch
   int64_t cap, dst_row, pos0;
   double log2_theta;
   unsigned int* clear;    // eight counters to zero for the launch behind this one, or null
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(THREADS) void rope_kernel(RopeArgs a) {
   typedef typename Chunk<T>::vec vec;
   __shared__ float cs_all[TT][half], sn_all[TT][half];
   const int tid = threadIdx.x;
-  const uint32_t tok0 = blockIdx.x * TT;
+  const uint32_t tok0 = a.first + blockIdx.x * TT;
   if (a.clear && blockIdx.x == 0 && tid < 8) a.clear[tid] = 0u;
   {
     static_assert(THREADS % half == 0, "a thread's angles share their frequency");
@@ -152,9 +153,12 @@ __global__ __launch_bounds__(THREADS) void rope_kernel(RopeArgs a) {
 }
 
 template <typename T, int half, int TT>
-hipError_t launch(const RopeArgs& a, hipStream_t st) {
-  rope_kernel<T, half, TT><<<dim3((a.total + TT - 1) / TT), THREADS, 0, st>>>(a);
-  return hipGetLastError();
+hipError_t launch(RopeArgs a, hipStream_t st) {
+  return launch_in_pieces(((int64_t)a.total + TT - 1) / TT, THREADS, [&](unsigned first, unsigned n_wgs) {
+    a.first = first * TT;
+    rope_kernel<T, half, TT><<<dim3(n_wgs), THREADS, 0, st>>>(a);
+    a.clear = nullptr;
+  });
 }
 
 // Tokens per workgroup.  One where a token's rows keep 256 threads busy, or where there

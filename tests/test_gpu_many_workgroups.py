@@ -62,3 +62,21 @@ def test_fp32_decode_step():
 def test_bf16_prefill():
     # the plain grid: 8 x 2098000 items of four wavefronts
     _prefill_of_one_token_blocks(torch.bfloat16, 128, 2098000, 8)
+
+
+def test_rope():
+    """Tokens of 16 heads are rotated by a workgroup each, here 2^24 + 1000 of them in place;
+    windows of the result against the rotation of the window alone."""
+    T, H = (1 << 24) + 1000, 16
+    X = torch.empty((1, T, H, 128), dtype=torch.bfloat16, device="cuda")
+    for t in range(0, T, 1 << 20):
+        X[:, t:t + (1 << 20)].normal_()
+    windows = [(0, 64), (1000, 64), (T // 2 - 7, 64), ((1 << 24) - 32, 64), (T - 64, 64)]
+    before = [X[:, s:s + n].clone() for s, n in windows]
+    print("rope", flush=True)
+    sa.rope(sa.StarShape.make("bf16", 1, H, H, 128, T, T, 0, T), X, X, 500000.0)
+    for (s, n), x in zip(windows, before):
+        y = torch.empty_like(x)
+        sa.rope(sa.StarShape.make("bf16", 1, H, H, 128, n, n, 0, n), x, y, 500000.0, pos0=s)
+        torch.cuda.synchronize()
+        assert torch.equal(X[:, s:s + n], y), s
