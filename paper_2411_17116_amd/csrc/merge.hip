@@ -57,14 +57,14 @@ __device__ __forceinline__ unsigned short f32_to_bf16_rne(float f) {
 }
 
 template <int D, int GROUPS, int INFL>
-__global__ __launch_bounds__(32 * GROUPS) void merge_kernel(MergeArgs a) {
+__global__ __launch_bounds__(32 * GROUPS) void merge_kernel(MergeArgs a, unsigned first_wg) {
   constexpr int E = D / 32;                  // output elements per lane
   __shared__ float red_max[GROUPS];
   __shared__ float red_w[GROUPS];
   __shared__ float red_acc[GROUPS][D];
   const Geom& g = a.g;
   const int tid = threadIdx.x, grp = tid >> 5, li = tid & 31;
-  int64_t row = blockIdx.x;                 // (beta, h, j), j fastest
+  int64_t row = first_wg + blockIdx.x;      // (beta, h, j), j fastest
   int j = (int)(row % a.q_len);
   int h = (int)((row / a.q_len) % g.Hq);
   int beta = (int)(row / ((int64_t)a.q_len * g.Hq));
@@ -188,11 +188,11 @@ __global__ __launch_bounds__(32 * GROUPS) void merge_kernel(MergeArgs a) {
 // nothing crosses lanes -- no LDS, no barriers.  A part's splits are folded in
 // index order with INFL loads in flight, the parts in index order after them.
 template <int D, int INFL>
-__global__ __launch_bounds__(256) void merge_rows_kernel(MergeArgs a, int64_t n_rows) {
+__global__ __launch_bounds__(256) void merge_rows_kernel(MergeArgs a, int64_t n_rows, unsigned first_wg) {
   constexpr int E = D / 32;
   const Geom& g = a.g;
   const int li = threadIdx.x & 31;
-  const int64_t row = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);      // (beta, h, j), j fastest
+  const int64_t row = (int64_t)(first_wg + blockIdx.x) * 8 + (threadIdx.x >> 5);      // (beta, h, j), j fastest
   if (row >= n_rows) return;
   const int j = (int)(row % a.q_len);
   const int h = (int)((row / a.q_len) % g.Hq);
@@ -390,10 +390,10 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
 // Many rows of a few splits each (query encoding, pairs of other hosts): d / 4 lanes own a
 // row, up to eight splits in flight, nothing crosses lanes.
 template <int D>
-__global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, unsigned n_rows) {
+__global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, unsigned n_rows, unsigned first_wg) {
   constexpr int LPR = D / 4, INFL = 8;
   const Geom& g = a.g;
-  const unsigned row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;      // (beta, h, j), j fastest
+  const unsigned row = (first_wg + blockIdx.x) * (256 / LPR) + threadIdx.x / LPR;      // (beta, h, j), j fastest
   if (row >= n_rows) return;
   const int d0 = 4 * (threadIdx.x % LPR), S = a.plan.s_total;
   const unsigned bh = row / (unsigned)a.q_len, j = row % (unsigned)a.q_len, beta = bh / (unsigned)g.Hq, h = bh % (unsigned)g.Hq;
@@ -430,10 +430,11 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
   if (p.flat) {
     const int S = p.s_total;
     if (S <= 8 && rows >= 64) {
-      const unsigned wgs = a.g.d == 64 ? (unsigned)((rows + 15) / 16) : (unsigned)((rows + 7) / 8);
-      if (a.g.d == 64) merge_flat_rows_kernel<64><<<dim3(wgs), 256, 0, st>>>(a, (unsigned)rows);
-      else merge_flat_rows_kernel<128><<<dim3(wgs), 256, 0, st>>>(a, (unsigned)rows);
-      return hipGetLastError();
+      const int64_t wgs = a.g.d == 64 ? (rows + 15) / 16 : (rows + 7) / 8;
+      return launch_in_pieces(wgs, 256, [&](unsigned first, unsigned n_wgs) {
+        if (a.g.d == 64) merge_flat_rows_kernel<64><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
+        else merge_flat_rows_kernel<128><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
+      });
     }
     // Few rows: pieces of d, so that the row's splits are in flight at once over more
     // workgroups and wavefronts; many rows fill the GPU as they are.  Measured, us, for
@@ -446,17 +447,14 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
   }
   // splits the largest part is made of
   const int per_part = p.spb > p.st ? p.spb : p.st;
-  if (per_part <= 8 && rows >= 64) {
-    // many rows, few splits each: a row per 32 lanes
-    const unsigned wgs = (unsigned)((rows + 7) / 8);
-    if (a.g.d == 64) merge_rows_kernel<64, 4><<<dim3(wgs), 256, 0, st>>>(a, rows);
-    else merge_rows_kernel<128, 4><<<dim3(wgs), 256, 0, st>>>(a, rows);
-  } else if (a.g.d == 64) {
-    merge_kernel<64, 8, 4><<<dim3((unsigned)rows), 256, 0, st>>>(a);
-  } else {
-    merge_kernel<128, 8, 4><<<dim3((unsigned)rows), 256, 0, st>>>(a);
-  }
-  return hipGetLastError();
+  const bool many = per_part <= 8 && rows >= 64;      // many rows, few splits each: a row per 32 lanes
+  return launch_in_pieces(many ? (rows + 7) / 8 : rows, 256, [&](unsigned first, unsigned n_wgs) {
+    const dim3 grid(n_wgs);
+    if (many && a.g.d == 64) merge_rows_kernel<64, 4><<<grid, 256, 0, st>>>(a, rows, first);
+    else if (many) merge_rows_kernel<128, 4><<<grid, 256, 0, st>>>(a, rows, first);
+    else if (a.g.d == 64) merge_kernel<64, 8, 4><<<grid, 256, 0, st>>>(a, first);
+    else merge_kernel<128, 8, 4><<<grid, 256, 0, st>>>(a, first);
+  });
 }
 
 }  // namespace star

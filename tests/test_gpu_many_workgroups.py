@@ -80,3 +80,18 @@ def test_rope():
         sa.rope(sa.StarShape.make("bf16", 1, H, H, 128, n, n, 0, n), x, y, 500000.0, pos0=s)
         torch.cuda.synchronize()
         assert torch.equal(X[:, s:s + n], y), s
+
+
+def test_merge_of_single_pairs():
+    """2^27 and some rows of one pair each, 32 lanes to a row: the output is the pair's own."""
+    H, q, d = 129, 1 << 20, 128
+    A = torch.empty((1, 1, H, q, d), device="cuda")
+    for h in range(H):
+        A[0, 0, h].normal_()
+    LSE = torch.zeros((1, 1, H, q), device="cuda")
+    O = torch.zeros((1, q, H, d), dtype=torch.bfloat16, device="cuda")
+    print("merge", flush=True)
+    sa.merge(sa.StarShape.make("bf16", 1, H, H, d, q, q, 0, q), A, LSE, O=O)
+    torch.cuda.synchronize()
+    for h in range(H):
+        assert torch.equal(O[0, :, h], A[0, 0, h].to(torch.bfloat16)), h
