@@ -283,7 +283,8 @@ int star_attn_phase2_static(const star_attn_shape* shape,
  *              key: its slab may hold anything and contributes nothing
  *   O          out  [B, q_len, Hq, d] in the storage dtype; may be NULL if A is given
  *   A, LSE     out  the merged pair in fp32, layouts as above (for merging in
- *              stages); each may be NULL
+ *              stages); each may be NULL.  They may be one of the gathered slabs: the
+ *              pair is then merged in place
  * Needs no workspace.  Pairs are folded in index order: deterministic.
  */
 int star_attn_phase2_partial(const star_attn_shape* shape,

@@ -449,6 +449,10 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
     // (rows x splits) against the kernel with the chain from split to split and a workgroup
     // per row: 8 x 384 10.8 -> 4.3, 32 x 128 5.7 -> 3.9, 32 x 96 6.0 -> 4.7, 672 x 29
     // 7.4 -> 4.0 (pieces of 32: 6.2-8.2), 8 x 32 (d = 64) 8.6 -> 3.3.
+    // A result merged into one of its own slabs: another piece's workgroup may not have read the
+    // row's log-sum-exps yet when the first piece stores the new one, so a row stays whole.
+    const bool in_place = a.LSE >= a.LSE_sub && a.LSE < a.LSE_sub + rows * S;
+    if (in_place) return a.g.d == 64 ? launch_flat<16, 256, 4>(a, st) : launch_flat<32, 256, 4>(a, st);
     if (rows < 256) return S > 128 ? launch_flat<8, 512, 2>(a, st) : launch_flat<16, 256, 4>(a, st);
     if (S > 64) return launch_flat<16, 512, 4>(a, st);
     return a.g.d == 64 ? launch_flat<16, 256, 4>(a, st) : launch_flat<32, 256, 4>(a, st);

@@ -74,3 +74,26 @@ def test_fp32_merge_of_few_pairs_is_as_exact_as_its_roundings(n_parts, d):
     # and then adds less than another.  A weight from a rounded product and a rounded reciprocal
     # would add 6 (eight pairs) to 11 % (two)
     assert rms <= 1.03 * model
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,q,n_parts,slab", [(1, 1, 2, 0), (8, 1, 9, 0), (4, 3, 64, 63), (2, 1, 130, 7), (8, 1, 500, 0),
+                                              (8, 40, 20, 1), (4, 64, 70, 0), (16, 8, 4, 2)])
+def test_merge_into_one_of_its_own_slabs(H, q, n_parts, slab, d):
+    """Merging in stages: the pair may replace one of the gathered ones (few rows of many pairs
+    are spread over workgroups, which all read the row's log-sum-exps)."""
+    gen = torch.Generator(device="cuda").manual_seed(n_parts)
+    A = torch.randn((n_parts, 1, H, q, d), generator=gen, device="cuda")
+    LSE = 3.0 * torch.randn((n_parts, 1, H, q), generator=gen, device="cuda") + 9.0
+    shape = sa.StarShape.make("fp32", 1, H, H, d, 64, 64, 64, 64 + q)
+    want_A, want_L = torch.empty_like(A[0]), torch.empty_like(LSE[0])
+    sa.merge(shape, A, LSE, A=want_A, LSE=want_L)
+    print(f"d={d} H={H} q={q} parts={n_parts} slab={slab}", flush=True)
+    for _ in range(5):
+        A2, L2 = A.clone(), LSE.clone()
+        sa.merge(shape, A2, L2, A=A2[slab], LSE=L2[slab])
+        torch.cuda.synchronize()
+        # a row may be cut in another way than out of place: other groups of splits, so each
+        # result within 2e-6 (4e-6 for values near 20) of the exact one
+        assert (A2[slab] - want_A).abs().max().item() <= 4e-6
+        assert (L2[slab] - want_L).abs().max().item() <= 8e-6
