@@ -358,7 +358,11 @@ typedef struct star_attn_plan_info {
   int32_t steps_per_batch; /* decode kernel: 32-key steps loaded per batch (1 or 2); else 0 */
   int32_t reserved;
   int64_t split_len;       /* keys per split */
-  int64_t workspace_bytes; /* bytes of workspace this very call uses */
+  int64_t workspace_bytes; /* bytes of workspace this very call uses; it may use more on a longer
+                              cache (star_attn_workspace_bytes covers every length).  A row-tiled
+                              or fp32 call without per-part outputs makes do with the splits its
+                              workspace holds, down to one, if that is less; any other call is
+                              refused with STAR_ATTN_ERR_WORKSPACE_TOO_SMALL */
 } star_attn_plan_info;
 
 int star_attn_phase2_plan(const star_attn_shape* shape, int64_t cache_len, int64_t q_len,

@@ -173,11 +173,14 @@ static double rows_cost(const Geom& g, int64_t q_len, int tile, int64_t splits, 
   const double pairs = 8.0 * splits * g.B * g.Hq * q_len * (g.d + 1);
   return ceil((double)splits * rows_wgs(g, q_len, tile) / ROW_WGS) * (keys + 600) + pairs / 80000;
 }
+// Splits whose per-split pairs fit `bytes` of workspace.
+static int64_t splits_that_fit(const Geom& g, int64_t q_len, int64_t bytes) {
+  return bytes / 256 * 256 / ((int64_t)g.B * g.Hq * q_len * (g.d + 1) * 4);
+}
 // Largest number of splits whose per-split pairs a call may keep: what
 // star_attn_phase2_static's scratch holds, and at least `aligned`.
 static int64_t rows_splits_cap(const Geom& g, int64_t q_len, int64_t aligned) {
-  const int64_t pair = (int64_t)g.B * g.Hq * q_len * (g.d + 1) * 4;
-  const int64_t fit = STAR_ATTN_STATIC_SCRATCH_BYTES / pair;
+  const int64_t fit = splits_that_fit(g, q_len, STAR_ATTN_STATIC_SCRATCH_BYTES);
   return fit > aligned ? fit : aligned;
 }
 // Equal runs of keys for a call without per-part outputs: with either tile, the number of
@@ -210,14 +213,18 @@ static RowsChoice rows_flat(const Geom& g, int64_t q_len, int64_t total, int64_t
 // are cut into equal splits, one per resident workgroup; with per-part outputs
 // the splits respect block boundaries.  Larger calls are compute-bound and use
 // as few splits as still fill the GPU; fp32 calls ditto, in equal runs of keys when
-// no per-part outputs are asked for.
+// no per-part outputs are asked for.  The number of equal runs depends on `total`: a
+// caller whose workspace was sized for a shorter cache gets as many as fit
+// `max_bytes` (at least one), so that a call it could make does not become one it cannot.
 static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bool want_parts,
-                      SplitPlan* p) {
+                      SplitPlan* p, int64_t max_bytes = INT64_MAX) {
   Geom g = make_geom(s);
   int64_t n = ceil_div(g.L, g.b);
   int64_t bmax = g.b < g.L ? g.b : g.L;
   int64_t tail_cap = g.cap - g.L;
   int64_t rows = (int64_t)g.G * q_len;
+  int64_t fit = splits_that_fit(g, q_len, max_bytes);
+  if (fit < 1) fit = 1;
   p->decode = (s->dtype == STAR_ATTN_BF16 && rows <= 16) ? 1 : 0;
   p->flat = 0;
   p->tile_rows = 0;
@@ -243,6 +250,7 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     int64_t splits = f32_splits_max(g, q_len, p->tile_rows);
     if (splits > ceil_div(total, F32_SPLIT_MIN)) splits = ceil_div(total, F32_SPLIT_MIN);
     if (total * g.d * 8 <= F32_DIRECT_BYTES) splits = 1;
+    if (splits > fit) splits = fit;
     p->flat = 1;
     p->split_len = round_up(ceil_div(total, splits), 32);
     p->spb = 0;
@@ -258,8 +266,9 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   } else {
     int64_t want, min_len;   // splits over all blocks that fill the GPU; keys worth a split
     if (s->dtype == STAR_ATTN_F32) {
+      // (the same splits for every length of the cache)
       p->tile_rows = f32_tile_rows(g, q_len, total);
-      want = f32_splits_max(g, q_len, p->tile_rows);
+      want = f32_splits_max(g, q_len, f32_tile_rows(g, q_len, g.cap));
       min_len = F32_SPLIT_MIN;
     } else {
       const int64_t wgs = (int64_t)g.B * g.Hkv * (g.G / flash_heads_per_workgroup(g.G)) *
@@ -282,8 +291,9 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     p->tile_rows = c128 < c256 ? 128 : 256;
     // equal runs of keys instead of splits of every part, if they take less time
     if (!want_parts) {
-      const RowsChoice f = rows_flat(g, q_len, total, rows_splits_cap(g, q_len, s_total));
-      if (f.cost < (c128 < c256 ? c128 : c256)) {
+      const int64_t cap = rows_splits_cap(g, q_len, s_total);
+      const RowsChoice f = rows_flat(g, q_len, total, cap < fit ? cap : fit);
+      if (s_total > fit || f.cost < (c128 < c256 ? c128 : c256)) {
         p->flat = 1;
         p->tile_rows = f.tile;
         p->split_len = f.len;
@@ -567,6 +577,9 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
     return STAR_ATTN_ERR_MISALIGNED;
   SplitPlan plan;
   if (!make_plan(shape, q_len, total, O_part != nullptr, &plan))
+    return STAR_ATTN_ERR_INVALID_SHAPE;
+  if (!static_scratch && workspace_bytes < plan_bytes(shape, plan, q_len) &&
+      !make_plan(shape, q_len, total, O_part != nullptr, &plan, (int64_t)workspace_bytes))
     return STAR_ATTN_ERR_INVALID_SHAPE;
   if (workspace_bytes < plan_bytes(shape, plan, q_len)) return STAR_ATTN_ERR_WORKSPACE_TOO_SMALL;
   Geom g = make_geom(shape);

@@ -178,6 +178,17 @@ def test_plan_query(lib):
     assert call(ctypes.byref(small), small.ctx_len, 1, 0, None) == ERR["NULL_POINTER"]
 
 
+def test_workspace_of_per_part_calls_does_not_depend_on_the_cache_length(lib):
+    """Calls with per-part outputs keep one pair per split of every part, whatever the cache holds."""
+    for dtype, d in (("fp32", 64), ("fp32", 128), ("bf16", 128)):
+        for heads, kv, q in ((8, 2, 33), (8, 2, 5), (3, 1, 70), (40, 2, 1)):
+            shape = good_shape(dtype=dtype, head_dim=d, n_q_heads=heads, n_kv_heads=kv, ctx_len=300, block=100,
+                               anchor=10, cache_capacity=20000)
+            need = {sa.phase2_plan(shape, n, q, want_parts=True).workspace_bytes
+                    for n in (300, 600, 1500, 4000, 9000, 20000 - q)}
+            assert len(need) == 1, (dtype, heads, q, need)
+
+
 def test_static_scratch_entry_point_arguments(lib):
     """star_attn_phase2_static validates like star_attn_phase2 and refuses a call
     whose per-split pairs do not fit its static scratch."""

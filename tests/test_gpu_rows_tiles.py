@@ -58,3 +58,37 @@ def test_workspace_covers_every_shorter_call():
                 for parts in (False, True):
                     for cached in (30000, 33333, 35000 - q):
                         assert sa.phase2_plan(shape, cached, q, parts).workspace_bytes <= have, (Hq, q, parts)
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,q,lengths", [
+    ("bf16", 32, 8, 128, 32, (1000, 8000, 20000)),     # 2.6 MB on 1000 keys, 16.9 MB on 8000
+    ("bf16", 20, 1, 128, 1, (64, 700, 20000)),         # G = 20
+    ("fp32", 8, 2, 128, 1, (200, 1500, 9000)),         # one split, then many
+    ("fp32", 8, 2, 64, 33, (300, 4000, 9000)),
+])
+def test_workspace_of_the_first_call_serves_a_growing_cache(dtype, Hq, Hkv, d, q, lengths):
+    """A program that sizes its workspace by the plan of its first call and lets the cache grow
+    is not refused later; its results are those of any workspace."""
+    cap = lengths[-1] + q
+    shape = sa.StarShape.make(dtype, 1, Hq, Hkv, d, lengths[0], lengths[0], 0, cap)
+    gen = torch.Generator(device="cuda").manual_seed(q)
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda").to(dt)
+    Kc, Vc = rnd(1, Hkv, cap, d), rnd(1, Hkv, cap, d)
+    Q, K, V = rnd(1, q, Hq, d), rnd(1, q, Hkv, d), rnd(1, q, Hkv, d)
+    need = [sa.phase2_plan(shape, n, q).workspace_bytes for n in lengths]
+    assert need[0] < need[-1], need
+    first, full = torch.empty(need[0], dtype=torch.uint8, device="cuda"), sa.alloc_workspace(shape, q)
+    guard = torch.full((need[0] + 4096,), 171, dtype=torch.uint8, device="cuda")
+    for n in lengths:
+        print(f"{dtype} {Hq}/{Hkv} q={q} cache={n}: {need[0]} bytes of {need}", flush=True)
+        got, want = torch.empty_like(Q), torch.empty_like(Q)
+        sa.phase2(shape, n, Q, K, V, Kc, Vc, got, guard[:need[0]])
+        sa.phase2(shape, n, Q, K, V, Kc, Vc, want, full)
+        torch.cuda.synchronize()
+        tol = 2 * ph.TOL[dtype]["o"]          # other splits: each within the bound of the exact result
+        assert (got.float() - want.float()).abs().max().item() <= tol
+        assert (guard[need[0]:] == 171).all()
+    with pytest.raises(sa.StarAttnError) as e:            # not even one split fits
+        sa.phase2(shape, lengths[0], Q, K, V, Kc, Vc, got, first[:Hq * q * 4])
+    assert e.value.code == -7
