@@ -182,10 +182,10 @@ def test_workspace_of_per_part_calls_does_not_depend_on_the_cache_length(lib):
     """Calls with per-part outputs keep one pair per split of every part, whatever the cache holds."""
     for dtype, d in (("fp32", 64), ("fp32", 128), ("bf16", 128)):
         for heads, kv, q in ((8, 2, 33), (8, 2, 5), (3, 1, 70), (40, 2, 1)):
-            shape = good_shape(dtype=dtype, head_dim=d, n_q_heads=heads, n_kv_heads=kv, ctx_len=300, block=100,
+            shape = good_shape(dtype=dtype, head_dim=d, n_q_heads=heads, n_kv_heads=kv, ctx_len=3000, block=1500,
                                anchor=10, cache_capacity=20000)
             need = {sa.phase2_plan(shape, n, q, want_parts=True).workspace_bytes
-                    for n in (300, 600, 1500, 4000, 9000, 20000 - q)}
+                    for n in (3000, 3300, 4000, 9000, 20000 - q)}
             assert len(need) == 1, (dtype, heads, q, need)
 
 
