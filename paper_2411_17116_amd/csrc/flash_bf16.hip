@@ -1015,12 +1015,13 @@ __global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, i
   attend<W, NW / W>(w, seq, row_lim, wave_lo, c, lds0, lds_wg, W == NW ? tiles : (tiles + 1) / 2);
 
   // Algorithm 2, append: the split that holds a new token files its K and V rows, its row
-  // tiles in turn (the chain of round trips of one of them would outlast the rest of a call
-  // of few keys: 454 tokens on 5740, 6 / 3 heads, 43.8 us)
-  if (fused_append) {
+  // tiles in turn, up to 64 of them (the chain of round trips of one would outlast the rest
+  // of a call of few keys: 454 tokens on 5740, 6 / 3 heads, 43.8 us)
+  const int filers = row_tiles < 64 ? row_tiles : 64;
+  if (fused_append && tt < filers) {
     const int n_units = (seq.loc_hi - seq.loc_lo) * 16;
     const size_t dst = ((size_t)beta * g.Hkv + kvh) * (size_t)g.cap + seq.loc_lo;
-    for (int u = tt * NT + tid; u < n_units; u += row_tiles * NT) {
+    for (int u = tt * NT + tid; u < n_units; u += filers * NT) {
       const size_t from = (size_t)(seq.loc_lo - cache_len + (u >> 4)) * new_stride + (u & 15) * 16;
       const i32x4 k = *(const i32x4*)(Kn + from), v = *(const i32x4*)(Vn + from);
       *(i32x4*)((char*)a.Kc + dst * ROWB + (size_t)u * 16) = k;

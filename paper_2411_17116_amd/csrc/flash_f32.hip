@@ -300,11 +300,12 @@ __device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<NB, KW>& x, Store 
   }
 }
 
-// Copy `n` rows of d floats (K and V) into cache rows: 16 bytes per thread and step.
+// Copy `n` rows of d floats (K and V) into cache rows: 16 bytes per thread and step, the
+// calling thread being `thread` of `n_threads`.
 template <int D>
 __device__ __forceinline__ void file_rows(const float* K, const float* V, int64_t stride, float* Kc, float* Vc,
-                                          int n, int n_threads) {
-  for (int i = threadIdx.x; i < n * (D / 4); i += n_threads) {
+                                          int n, int thread, int n_threads) {
+  for (int i = thread; i < n * (D / 4); i += n_threads) {
     const int row = i / (D / 4), c = 4 * (i % (D / 4));
     const f32x4 k = *(const f32x4*)(K + row * stride + c), v = *(const f32x4*)(V + row * stride + c);
     *(f32x4*)(Kc + (int64_t)row * D + c) = k;
@@ -393,7 +394,8 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, in
   if (from_input) {
     const int t0 = tok0 + (head0 + g.G - 1) / g.G, t1 = tok0 + (head0 + live_rows + g.G - 1) / g.G;
     file_rows<D>(Kb + (int64_t)t0 * stride, Vb + (int64_t)t0 * stride, stride,
-                 (float*)a.Kc + cache0 + (int64_t)t0 * D, (float*)a.Vc + cache0 + (int64_t)t0 * D, t1 - t0, 64 * KW);
+                 (float*)a.Kc + cache0 + (int64_t)t0 * D, (float*)a.Vc + cache0 + (int64_t)t0 * D, t1 - t0, threadIdx.x,
+                 64 * KW);
   }
 }
 
@@ -469,11 +471,14 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
         else if (a.LSE) a.LSE[((int64_t)beta * g.Hq + head) * a.q_len + j] = lse;
       });
 
-  // Algorithm 2, append: the split that holds a new token files its row
-  if (fused_append && tile == 0 && seq.l_hi > seq.l_lo) {
+  // Algorithm 2, append: the split that holds a new token files its row, its row tiles
+  // in turn (as in phase2_rows_bf16_kernel)
+  const int filers = row_tiles < 64 ? row_tiles : 64;
+  if (fused_append && tile < filers && seq.l_hi > seq.l_lo) {
     const int64_t stride = (int64_t)g.Hkv * D, src = (int64_t)(seq.l_lo - cache_len) * stride;
     file_rows<D>(Kl + src, Vl + src, stride, (float*)a.Kc + cache0 + (int64_t)seq.l_lo * D,
-                 (float*)a.Vc + cache0 + (int64_t)seq.l_lo * D, seq.l_hi - seq.l_lo, 64 * KW);
+                 (float*)a.Vc + cache0 + (int64_t)seq.l_lo * D, seq.l_hi - seq.l_lo,
+                 tile * 64 * KW + threadIdx.x, filers * 64 * KW);
   }
 }
 
