@@ -520,8 +520,14 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
 // (2048 32-row tiles) 705 / 740 / 819, L = 4099 (1025) 151 / 156 / 193, L = 1024 (256)
 // 26.3 / 23.7 / 29.2; d = 64: L = 8192 369 / 375 / 395, L = 2048 (512) 39.0 / 37.3 / 39.4;
 // 1 head, d = 64, L = 1024 (32) 16.0 / 10.0 / 9.9.
+// Blocks of at most two units of keys have nothing to share: one wavefront per tile.  Against
+// the set-up above (and one thread per row), us, 8 / 8 heads: d = 64, 100000 tokens: b = 1, a = 0
+// 4790 -> 975 (3336), b = 4, a = 0 1245 -> 274 (1000), b = 4, a = 4 1379 -> 368 (1495); 50000 tokens,
+// d = 128: b = a = 16 474 -> 251 (2262); three units and more: 146 -> 144 (b = 32, a = 0), 165 -> 169 (64).
 hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   const Geom& g = a.g;
+  if ((g.a + UNIT - 1) / UNIT + ((g.b < g.L ? g.b : g.L) + UNIT - 1) / UNIT <= 2)
+    return g.d == 64 ? launch_phase1<64, 1, 1>(a, st) : launch_phase1<128, 1, 1>(a, st);
   const int64_t rows = g.L * g.G * g.Hkv * g.B;
   if (rows >= 1024 * 32)
     return g.d == 64 ? launch_phase1<64, 2, 4>(a, st) : launch_phase1<128, 2, 4>(a, st);
@@ -530,7 +536,13 @@ hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   return g.d == 64 ? launch_phase1<64, 1, 8>(a, st) : launch_phase1<128, 1, 8>(a, st);
 }
 
+// Per-part outputs over short blocks make splits of at most four units: one wavefront per
+// 32-row tile.  Against four (and one thread per row), us: 114 tokens on 54 keys in blocks of
+// 2, three sequences of 120 / 6 heads 418 -> 277 (373), 395 on 600 in blocks of 40, 7 heads
+// 58.8 -> 52.1 (91.6); splits of 128 keys and more lose by it (1000 on 1000 53.8 -> 59.3).
 hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st) {
+  if (a.plan.tile_rows == 32 && !a.plan.flat && a.plan.split_len <= 4 * UNIT)
+    return a.g.d == 64 ? launch_phase2<64, 2, 1>(a, st) : launch_phase2<128, 2, 1>(a, st);
   if (a.plan.tile_rows == 32) return a.g.d == 64 ? launch_phase2<64, 2, 4>(a, st) : launch_phase2<128, 2, 4>(a, st);
   return a.g.d == 64 ? launch_phase2<64, 1, 8>(a, st) : launch_phase2<128, 1, 8>(a, st);
 }

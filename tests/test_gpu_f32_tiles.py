@@ -21,6 +21,11 @@ pytestmark = pytest.mark.gpu
     (1, 2, 2, 128, 239, 100, 16, 17, 2),    # query call: 256 KiB of K and V, one workgroup per row tile
     (1, 2, 2, 128, 240, 100, 16, 17, 2),    # beyond that: splits and a merge
     (1, 4, 2, 64, 2500, 700, 1, 33, 2),     # 16-row and 32-row tiles, several splits
+    (2, 3, 1, 128, 333, 7, 0, 5, 1),        # one unit per block: a wavefront per tile
+    (1, 4, 2, 64, 500, 16, 16, 3, 1),       # two units
+    (1, 5, 5, 64, 300, 17, 0, 3, 1),        # the second of one key
+    (1, 8, 2, 64, 280, 20, 5, 300, 1),      # per-part splits of up to four units: a wavefront per 32-row tile
+    (1, 6, 3, 128, 250, 60, 60, 260, 1),
 ])
 def test_fp32_tile_edges(B, Hq, Hkv, d, L, b, a, lq, nd):
     cfg = workloads.StarConfig("f32tiles", "fp32", B, Hq, Hkv, d, L, b, a, lq, nd, seed=L + Hq, n_planted=2)

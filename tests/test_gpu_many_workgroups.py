@@ -37,8 +37,8 @@ def _prefill_of_one_token_blocks(dtype, d, L, H):
 
 
 def test_fp32_prefill():
-    # 8 x 2098000 row tiles of four wavefronts: 2^32 work-items and 6784 workgroups more
-    _prefill_of_one_token_blocks(torch.float32, 64, 2098000, 8)
+    # 8 x 8389608 row tiles of one wavefront: 2^32 work-items and 8000 workgroups more
+    _prefill_of_one_token_blocks(torch.float32, 64, 8389608, 8)
 
 
 def test_fp32_decode_step():
