@@ -745,16 +745,28 @@ __device__ __forceinline__ int next_item(unsigned int* tickets, int home, unsign
 //   W = 4, H = 1: four wavefronts, two workgroups per CU, so that one's loads and stores
 //   hide behind the other's key loop.  W = 4, H = 2: where there are no more items than
 //   CUs, the halves of an eight-wavefront workgroup share an item's keys instead.
-// Order: kv head fastest, then batch, head sub-group; then, in groups of `group` blocks
-// with the same anchor, tile within block (heavy first) and block; the first block last,
-// if it is the only one without an anchor.  `resident` workgroups start at once; if the
-// rest is no more than that many, it comes lightest first (`turn` of them), so that a CU
-// that starts with a heavy item gets a light one beside it.
+// Order: in groups of `group` blocks with the same anchor, kv head fastest, then block (batch
+// fastest), head sub-group and tile within block (heavy first); the first blocks last,
+// if they are the only ones without an anchor.  A group is one block of every batch, which
+// evens out best, unless the 64 workgroups of an XCD then read from 32 blocks or more and
+// hardly share keys: one block, if there are four rounds of them or more (sixteen prompts of
+// 2588 tokens, 32 / 32 heads: 1708 us in groups, 1075 block by block, 1371 from the queues;
+// eight prompts of 6625, 3 / 3 heads, blocks of 1656: 24 blocks at once, 132 and 145; 2.7 rounds
+// of 40 blocks at once: 58 and 74).
+//   `resident` workgroups start at once; if the rest is no more than that many, it comes
+// lightest first (`turn` of them), so that a CU that starts with a heavy item gets a light one
+// beside it.
+//   Workgroup v runs on XCD v mod 8.  Where a group's tiles are no multiple of 8 workgroups, the same
+// XCDs would get the heavy tiles of every block: 200 blocks of eight tiles, one head, 242 us
+// against 208 from the queues, which even out.  Either larger groups deal whole blocks to the
+// XCDs (193), or, with too few of them for that, each run of eight items starts `step` XCDs
+// further on (202).
 struct PlainGrid {
   int tpb, n_hs;       // tiles per block, head sub-groups
-  int n_same, group;   // blocks of the same weight, and how many of them are taken together
+  int n_same, group;   // blocks of the same weight per batch, and how many of them are taken together
   int first;           // the first of them (0 or 1)
   int resident, turn;  // see above; turn = 0: as they come
+  int step, whole;     // see above; step = 0: as they come; items in whole runs of eight
 };
 struct Item {
   int kvh, beta, hs, t, i;
@@ -762,18 +774,19 @@ struct Item {
 __device__ __forceinline__ Item plain_item(const Geom& g, const PlainGrid& p, int id) {
   Item x;
   if (p.turn > 0 && id >= p.resident) id = p.resident + p.turn - 1 - (id - p.resident);
+  if (p.step > 0 && id < p.whole) id = (id & ~7) | ((id + (id >> 3) * p.step) & 7);
   x.kvh = id % g.Hkv; id /= g.Hkv;
-  x.beta = id % g.B; id /= g.B;
-  x.hs = id % p.n_hs; id /= p.n_hs;
-  if (id < p.n_same * p.tpb) {
-    const int lo = id / (p.group * p.tpb) * p.group, in = p.n_same - lo < p.group ? p.n_same - lo : p.group;
-    id -= lo * p.tpb;
-    x.t = p.tpb - 1 - id / in;
-    x.i = p.first + lo + id % in;
-  } else {
-    x.t = p.tpb - 1 - (id - p.n_same * p.tpb);
-    x.i = 0;
-  }
+  const int n_same = p.n_same * g.B, per = p.n_hs * p.tpb;      // (block, batch), batch fastest; items of one
+  const bool alike = id < n_same * per;
+  if (!alike) id -= n_same * per;
+  const int n = alike ? n_same : g.B, lo = id / (p.group * per) * p.group, in = n - lo < p.group ? n - lo : p.group;
+  id -= lo * per;
+  const int block = lo + id % in;
+  id /= in;
+  x.hs = id % p.n_hs;
+  x.t = p.tpb - 1 - id / p.n_hs;
+  x.beta = block % g.B;
+  x.i = alike ? p.first + block / g.B : 0;
   return x;
 }
 template <int W, int H>
@@ -1116,14 +1129,24 @@ static bool plain_phase1(const Phase1Args& a, hipStream_t st, hipError_t* e) {
   p.n_same = (int)n - p.first;
   const int64_t longest = (g.a + TKEYS - 1) / TKEYS + (bmax + TKEYS - 1) / TKEYS;
   if (wgs <= a.n_cu && longest > 8) {
-    p.group = 1; p.resident = 0; p.turn = 0;
+    p.group = 1; p.resident = 0; p.turn = 0; p.step = 0; p.whole = 0;      // all start at once, one per CU
     *e = launch_phase1_plain<2>(a, hpw, p, wgs, st);
     return true;
   }
   // all resident at once, two per CU: what matters is which two, as long as the keys of all
   // blocks fit the L2 caches beside each other
   const bool pairs = wgs > a.n_cu && wgs <= 2 * a.n_cu && g.L * 2 * ROWB <= (2 << 20);
-  p.group = pairs ? p.n_same : 1;
+  const int64_t blocks = (int64_t)p.n_same * g.B;
+  const int64_t heads = g.Hkv % 8 == 0 ? g.Hkv / 8 : g.Hkv / (g.Hkv & -g.Hkv);      // an XCD's, at once
+  p.group = pairs ? (int)blocks : heads * g.B < 32 || wgs <= 8 * a.n_cu ? g.B : 1;
+  p.step = 0;
+  p.whole = (int)(wgs & ~(int64_t)7);
+  const int64_t alike = (int64_t)g.Hkv * p.n_hs * p.group, odd = alike % 8 & -(alike % 8);      // XCDs a tile goes to
+  if (!pairs && odd != 0) {
+    const int64_t more = a.n_cu / (alike * p.tpb) / (8 / odd) * (8 / odd);
+    if (more > 0) p.group = (int)(more * p.group < blocks ? more * p.group : blocks);
+    else p.step = (int)odd;
+  }
   p.resident = a.n_cu;
   p.turn = pairs ? (int)(wgs - a.n_cu) : 0;
   *e = launch_phase1_plain<1>(a, hpw, p, wgs, st);

@@ -24,6 +24,10 @@ pytestmark = pytest.mark.gpu
     (1, 64, 8, 1100, 275, 100, 1.5),       # several rounds, block by block
     (1, 8, 2, 1500, 500, 200, 6.0),        # scores far above the reference: the exact loop, halves
     (1, 32, 8, 1000, 250, 250, 6.0),       # and without them
+    (1, 3, 3, 14000, 500, 200, 1.5),       # heads no multiple of 8: groups of sixteen blocks, a ragged one
+    (1, 3, 3, 14000, 3500, 700, 1.5),      # blocks too long for that: runs of eight items turned on
+    (2, 6, 2, 9001, 1500, 0, 1.5),         # the same over two batches, no anchors: one section
+    (8, 5, 5, 7001, 3500, 100, 1.5),       # forty blocks at once in every XCD: block by block
 ])
 def test_plain_grids(B, Hq, Hkv, L, b, a, gamma):
     cfg = workloads.StarConfig("plain", "bf16", B, Hq, Hkv, 128, L, b, a, 1, 0, seed=L + Hq, n_planted=8 if L > 64 else 0,
