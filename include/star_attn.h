@@ -356,7 +356,7 @@ typedef struct star_attn_plan_info {
   int32_t n_splits;        /* splits per (batch, KV head) */
   int32_t non_temporal;    /* 1: the decode kernel reads the cache with non-temporal loads */
   int32_t steps_per_batch; /* decode kernel: 32-key steps loaded per batch (1 or 2); else 0 */
-  int32_t reserved;
+  int32_t tile_rows;       /* row-tiled kernels: rows (token x head) per workgroup; else 0 */
   int64_t split_len;       /* keys per split */
   int64_t workspace_bytes; /* bytes of workspace this very call uses; it may use more on a longer
                               cache (star_attn_workspace_bytes covers every length).  A row-tiled
@@ -367,6 +367,19 @@ typedef struct star_attn_plan_info {
 
 int star_attn_phase2_plan(const star_attn_shape* shape, int64_t cache_len, int64_t q_len,
                           int want_parts, star_attn_plan_info* out);
+
+/* The same for a star_attn_phase1 / _anchor / _rope call: which set-up takes it. */
+typedef struct star_attn_phase1_plan_info {
+  int32_t queued;          /* 1: row tiles drawn from the work queues (long bf16 prefills); 0: a
+                              workgroup per row tile */
+  int32_t tile_rows;       /* rows (token x head) per tile */
+  int32_t wavefronts;      /* wavefronts that work on a tile */
+  int32_t group;           /* workgroup per tile, bf16: blocks whose tiles are taken together */
+  int64_t n_tiles;         /* row tiles of the call */
+} star_attn_phase1_plan_info;
+
+int star_attn_phase1_plan(const star_attn_shape* shape, int anchor_mode,
+                          star_attn_phase1_plan_info* out);
 
 /* Static, NUL-terminated description of a status code (host memory, never freed). */
 const char* star_attn_status_string(int status);

@@ -53,8 +53,16 @@ class PlanInfo(ctypes.Structure):
     _fields_ = [
         ("decode", ctypes.c_int32), ("flat", ctypes.c_int32), ("n_splits", ctypes.c_int32),
         ("non_temporal", ctypes.c_int32), ("steps_per_batch", ctypes.c_int32),
-        ("reserved", ctypes.c_int32), ("split_len", ctypes.c_int64),
+        ("tile_rows", ctypes.c_int32), ("split_len", ctypes.c_int64),
         ("workspace_bytes", ctypes.c_int64),
+    ]
+
+
+class Phase1PlanInfo(ctypes.Structure):
+    """Mirror of `star_attn_phase1_plan_info`."""
+    _fields_ = [
+        ("queued", ctypes.c_int32), ("tile_rows", ctypes.c_int32), ("wavefronts", ctypes.c_int32),
+        ("group", ctypes.c_int32), ("n_tiles", ctypes.c_int64),
     ]
 
 
@@ -103,6 +111,8 @@ def load_library():
     lib.star_attn_status_string.argtypes = [ctypes.c_int]
     lib.star_attn_phase2_plan.restype = ctypes.c_int
     lib.star_attn_phase2_plan.argtypes = [P, i64, i64, ctypes.c_int, ctypes.POINTER(PlanInfo)]
+    lib.star_attn_phase1_plan.restype = ctypes.c_int
+    lib.star_attn_phase1_plan.argtypes = [P, ctypes.c_int, ctypes.POINTER(Phase1PlanInfo)]
     lib.star_attn_kernel_path.restype = ctypes.c_char_p
     lib.star_attn_kernel_path.argtypes = [P]
     _LIB = lib
@@ -123,6 +133,13 @@ def phase2_plan(shape: StarShape, cache_len: int, q_len: int, want_parts: bool =
     info = PlanInfo()
     _check(load_library().star_attn_phase2_plan(ctypes.byref(shape), int(cache_len), int(q_len),
                                                 int(bool(want_parts)), ctypes.byref(info)))
+    return info
+
+
+def phase1_plan(shape: StarShape, anchor_mode: int = ANCHOR_FIRST) -> Phase1PlanInfo:
+    """star_attn_phase1_plan: which set-up a phase-1 call would take."""
+    info = Phase1PlanInfo()
+    _check(load_library().star_attn_phase1_plan(ctypes.byref(shape), int(anchor_mode), ctypes.byref(info)))
     return info
 
 

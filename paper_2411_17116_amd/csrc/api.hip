@@ -456,6 +456,12 @@ size_t star_attn_phase1_workspace_bytes(const star_attn_shape* shape, int anchor
 
 }  // extern "C"
 
+static bool known_mode(int anchor_mode) {
+  return anchor_mode == STAR_ATTN_ANCHOR_FIRST || anchor_mode == STAR_ATTN_ANCHOR_PREVIOUS ||
+         anchor_mode == STAR_ATTN_ANCHOR_EXTERNAL || anchor_mode == STAR_ATTN_ANCHOR_PER_BLOCK ||
+         anchor_mode == STAR_ATTN_ANCHOR_ALL_BLOCKS;
+}
+
 // Phase 1 behind every public variant.  With `rope`, Q is rotated in place and K
 // on its way into the cache.
 static int phase1_impl(const star_attn_shape* shape, int anchor_mode, const Rope* rope, void* Q,
@@ -465,10 +471,7 @@ static int phase1_impl(const star_attn_shape* shape, int anchor_mode, const Rope
   int rc = validate_shape(shape);
   if (rc != STAR_ATTN_OK) return rc;
   if (rope && (rc = validate_rope(shape, rope->theta, rope->pos0)) != STAR_ATTN_OK) return rc;
-  if (anchor_mode != STAR_ATTN_ANCHOR_FIRST && anchor_mode != STAR_ATTN_ANCHOR_PREVIOUS &&
-      anchor_mode != STAR_ATTN_ANCHOR_EXTERNAL && anchor_mode != STAR_ATTN_ANCHOR_PER_BLOCK &&
-      anchor_mode != STAR_ATTN_ANCHOR_ALL_BLOCKS)
-    return STAR_ATTN_ERR_INVALID_MODE;
+  if (!known_mode(anchor_mode)) return STAR_ATTN_ERR_INVALID_MODE;
   if (!Q || !K || !V || !O_ctx || !K_cache || !V_cache) return STAR_ATTN_ERR_NULL_POINTER;
   if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O_ctx) ||
       misaligned(K_cache) || misaligned(V_cache) || ((uintptr_t)LSE_ctx & 3u))
@@ -774,9 +777,24 @@ int star_attn_phase2_plan(const star_attn_shape* shape, int64_t cache_len, int64
   out->n_splits = plan.s_total;
   out->non_temporal = plan.decode && !resident ? 1 : 0;
   out->steps_per_batch = plan.decode ? (resident ? 1 : 2) : 0;
-  out->reserved = 0;
+  out->tile_rows = plan.tile_rows;
   out->split_len = plan.split_len;
   out->workspace_bytes = (int64_t)plan_bytes(shape, plan, q_len);
+  return STAR_ATTN_OK;
+}
+
+int star_attn_phase1_plan(const star_attn_shape* shape, int anchor_mode, star_attn_phase1_plan_info* out) {
+  int rc = validate_shape(shape);
+  if (rc != STAR_ATTN_OK) return rc;
+  if (!known_mode(anchor_mode)) return STAR_ATTN_ERR_INVALID_MODE;
+  if (!out) return STAR_ATTN_ERR_NULL_POINTER;
+  const Geom g = make_geom(shape);
+  const Phase1Plan p = shape->dtype == STAR_ATTN_F32 ? phase1_plan_f32(g) : phase1_plan_bf16(g, anchor_mode, device_cu_count());
+  out->queued = p.queued;
+  out->tile_rows = p.rows;
+  out->wavefronts = p.waves;
+  out->group = p.group;
+  out->n_tiles = p.tiles;
   return STAR_ATTN_OK;
 }
 

@@ -1100,8 +1100,8 @@ static hipError_t launch_phase1_plain(const Phase1Args& a, int hpw, const PlainG
   });
 }
 
-// Launches a prefill of up to 600 key tiles (256 rows x 64 keys) per CU, about a
-// millisecond, as a plain grid of 128-row items; false: leave it to the queues.  Beyond
+// A prefill of up to 600 key tiles (256 rows x 64 keys) per CU, about a millisecond, is a
+// plain grid of 128-row items (true, and the grid); false: leave it to the queues.  Beyond
 // that the queues' 256-row items win: half the L2 -> LDS traffic, and no XCD waits for
 // another.  Measured, us, queues / plain (32 / 8 heads, b = a = L / 4, tiles per CU in
 // brackets): L = 300 (0.2) 25.3 / 11.7, 1000 (3) 33.4 / 17.5, 2000 (10) 49.3 / 29.7, 4000
@@ -1111,60 +1111,76 @@ static hipError_t launch_phase1_plain(const Phase1Args& a, int hpw, const PlainG
 // No more items than CUs, and longer than eight key tiles: the halves of a workgroup share
 // an item (8 / 2 heads, L = 4000: 36 us against 44, L = 2000: 22.5 and 24.5; L = 300, five
 // tiles: 11.8 and 11.0).
-static bool plain_phase1(const Phase1Args& a, hipStream_t st, hipError_t* e) {
-  const Geom& g = a.g;
-  const bool all = g.a == 0 || a.anchor_mode == ANCHOR_ALL_BLOCKS;       // every block alike
+// (`halves`: 2 if so; `wgs`: the number of workgroups.)
+static bool plain_phase1(const Geom& g, int anchor_mode, int n_cu, PlainGrid* grid, int* halves, int64_t* wgs_out) {
+  const bool all = g.a == 0 || anchor_mode == ANCHOR_ALL_BLOCKS;       // every block alike
   const int64_t bmax = g.b < g.L ? g.b : g.L, n = (g.L + g.b - 1) / g.b;
   // key tiles of 256 rows x 64 keys, in rounds of 256 workgroups
   const double work = (double)g.Hq * g.B * ((double)g.L * bmax / 2 + (double)(all ? g.L : g.L - bmax) * g.a) / (16384.0 * 256);
   if (work > 600) return false;
-  int hpw = flash_heads_per_workgroup(g.G);      // at most 8, the row blocks of four wavefronts
+  const int hpw = flash_heads_per_workgroup(g.G);      // at most 8, the row blocks of four wavefronts
   const int tm = 16 * (4 * RB / hpw);
-  PlainGrid p;
+  PlainGrid& p = *grid;
   p.tpb = (int)((bmax + tm - 1) / tm);
   p.n_hs = g.G / hpw;
   const int64_t wgs = (int64_t)g.Hkv * g.B * p.n_hs * p.tpb * n;
   if (wgs > 0x7fffffff) return false;
+  *wgs_out = wgs;
   p.first = all || n == 1 ? 0 : 1;
   p.n_same = (int)n - p.first;
   const int64_t longest = (g.a + TKEYS - 1) / TKEYS + (bmax + TKEYS - 1) / TKEYS;
-  if (wgs <= a.n_cu && longest > 8) {
+  if (wgs <= n_cu && longest > 8) {
     p.group = 1; p.resident = 0; p.turn = 0; p.step = 0; p.whole = 0;      // all start at once, one per CU
-    *e = launch_phase1_plain<2>(a, hpw, p, wgs, st);
+    *halves = 2;
     return true;
   }
   // all resident at once, two per CU: what matters is which two, as long as the keys of all
   // blocks fit the L2 caches beside each other
-  const bool pairs = wgs > a.n_cu && wgs <= 2 * a.n_cu && g.L * 2 * ROWB <= (2 << 20);
+  const bool pairs = wgs > n_cu && wgs <= 2 * n_cu && g.L * 2 * ROWB <= (2 << 20);
   const int64_t blocks = (int64_t)p.n_same * g.B;
   const int64_t heads = g.Hkv % 8 == 0 ? g.Hkv / 8 : g.Hkv / (g.Hkv & -g.Hkv);      // an XCD's, at once
-  p.group = pairs ? (int)blocks : heads * g.B < 32 || wgs <= 8 * a.n_cu ? g.B : 1;
+  p.group = pairs ? (int)blocks : heads * g.B < 32 || wgs <= 8 * n_cu ? g.B : 1;
   p.step = 0;
   p.whole = (int)(wgs & ~(int64_t)7);
   const int64_t alike = (int64_t)g.Hkv * p.n_hs * p.group, odd = alike % 8 & -(alike % 8);      // XCDs a tile goes to
   if (!pairs && odd != 0) {
-    const int64_t more = a.n_cu / (alike * p.tpb) / (8 / odd) * (8 / odd);
+    const int64_t more = n_cu / (alike * p.tpb) / (8 / odd) * (8 / odd);
     if (more > 0) p.group = (int)(more * p.group < blocks ? more * p.group : blocks);
     else p.step = (int)odd;
   }
-  p.resident = a.n_cu;
-  p.turn = pairs ? (int)(wgs - a.n_cu) : 0;
-  *e = launch_phase1_plain<1>(a, hpw, p, wgs, st);
+  p.resident = n_cu;
+  p.turn = pairs ? (int)(wgs - n_cu) : 0;
+  *halves = 1;
   return true;
+}
+
+// Row tiles of the queues.
+static int64_t queue_tiles(const Geom& g, int* tpb) {
+  const int tm = flash_tokens_per_workgroup(g.G);
+  const int64_t n = (g.L + g.b - 1) / g.b, bmax = g.b < g.L ? g.b : g.L;
+  *tpb = (int)((bmax + tm - 1) / tm);
+  return (int64_t)g.Hkv * g.B * (g.G / flash_heads_per_workgroup(g.G)) * *tpb * n;
+}
+
+Phase1Plan phase1_plan_bf16(const Geom& g, int anchor_mode, int n_cu) {
+  PlainGrid grid;
+  int halves, tpb;
+  int64_t wgs;
+  if (plain_phase1(g, anchor_mode, n_cu, &grid, &halves, &wgs)) return Phase1Plan{0, 16 * RB * 4, 4 * halves, grid.group, wgs};
+  return Phase1Plan{1, 16 * WG_BLOCKS, NW, 0, queue_tiles(g, &tpb)};
 }
 
 hipError_t launch_phase1_bf16(const Phase1Args& a, hipStream_t st) {
   const Geom& g = a.g;
   if (a.n_cu <= 0 || !a.tickets) return hipErrorInvalidValue;
   hipError_t e;
-  if (plain_phase1(a, st, &e)) return e;
-  int hpw = flash_heads_per_workgroup(g.G);
-  int tm = flash_tokens_per_workgroup(g.G);
-  int n_hs = g.G / hpw;
-  int64_t n = (g.L + g.b - 1) / g.b;
-  int64_t bmax = g.b < g.L ? g.b : g.L;
-  int tpb = (int)((bmax + tm - 1) / tm);
-  int64_t wgs = (int64_t)g.Hkv * g.B * n_hs * tpb * n;
+  const int hpw = flash_heads_per_workgroup(g.G), n_hs = g.G / hpw;
+  PlainGrid grid;
+  int halves, tpb;
+  int64_t wgs;
+  if (plain_phase1(g, a.anchor_mode, a.n_cu, &grid, &halves, &wgs))
+    return halves == 2 ? launch_phase1_plain<2>(a, hpw, grid, wgs, st) : launch_phase1_plain<1>(a, hpw, grid, wgs, st);
+  wgs = queue_tiles(g, &tpb);
   if (wgs > 0x7fffffff) return hipErrorInvalidValue;
   e = allow_tile_ring(ATTR_PHASE1, (const void*)phase1_bf16_kernel);
   if (e != hipSuccess) return e;

@@ -524,16 +524,22 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
 // the set-up above (and one thread per row), us, 8 / 8 heads: d = 64, 100000 tokens: b = 1, a = 0
 // 4790 -> 975 (3336), b = 4, a = 0 1245 -> 274 (1000), b = 4, a = 4 1379 -> 368 (1495); 50000 tokens,
 // d = 128: b = a = 16 474 -> 251 (2262); three units and more: 146 -> 144 (b = 32, a = 0), 165 -> 169 (64).
+Phase1Plan phase1_plan_f32(const Geom& g) {
+  const int64_t bmax = g.b < g.L ? g.b : g.L, n = (g.L + g.b - 1) / g.b, rows = g.L * g.G * g.Hkv * g.B;
+  Phase1Plan p = {0, 16, 8, 0, 0};
+  if ((g.a + UNIT - 1) / UNIT + (bmax + UNIT - 1) / UNIT <= 2) p.waves = 1;
+  else if (rows >= 1024 * 32) { p.rows = 32; p.waves = 4; }
+  else if (rows >= 256 * 16) p.waves = 4;
+  p.tiles = n * ((bmax * g.G + p.rows - 1) / p.rows) * g.B * g.Hkv;
+  return p;
+}
+
 hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
-  const Geom& g = a.g;
-  if ((g.a + UNIT - 1) / UNIT + ((g.b < g.L ? g.b : g.L) + UNIT - 1) / UNIT <= 2)
-    return g.d == 64 ? launch_phase1<64, 1, 1>(a, st) : launch_phase1<128, 1, 1>(a, st);
-  const int64_t rows = g.L * g.G * g.Hkv * g.B;
-  if (rows >= 1024 * 32)
-    return g.d == 64 ? launch_phase1<64, 2, 4>(a, st) : launch_phase1<128, 2, 4>(a, st);
-  if (rows >= 256 * 16)
-    return g.d == 64 ? launch_phase1<64, 1, 4>(a, st) : launch_phase1<128, 1, 4>(a, st);
-  return g.d == 64 ? launch_phase1<64, 1, 8>(a, st) : launch_phase1<128, 1, 8>(a, st);
+  const Phase1Plan p = phase1_plan_f32(a.g);
+  if (p.waves == 1) return a.g.d == 64 ? launch_phase1<64, 1, 1>(a, st) : launch_phase1<128, 1, 1>(a, st);
+  if (p.rows == 32) return a.g.d == 64 ? launch_phase1<64, 2, 4>(a, st) : launch_phase1<128, 2, 4>(a, st);
+  if (p.waves == 4) return a.g.d == 64 ? launch_phase1<64, 1, 4>(a, st) : launch_phase1<128, 1, 4>(a, st);
+  return a.g.d == 64 ? launch_phase1<64, 1, 8>(a, st) : launch_phase1<128, 1, 8>(a, st);
 }
 
 // Per-part outputs over short blocks make splits of at most four units: one wavefront per

@@ -182,6 +182,15 @@ inline hipError_t launch_in_pieces(int64_t workgroups, int threads, Launch launc
   return hipSuccess;
 }
 
+// What a phase-1 call launches: row tiles of `rows` rows shared by `waves` wavefronts, one
+// workgroup each, or (queued) drawn from the work queues.
+struct Phase1Plan {
+  int32_t queued, rows, waves, group;
+  int64_t tiles;
+};
+Phase1Plan phase1_plan_bf16(const Geom& g, int anchor_mode, int n_cu);
+Phase1Plan phase1_plan_f32(const Geom& g);
+
 // Host-side launchers (each returns the hipError_t of its launch).
 // X [B, n_tokens, H, d] rotated into Y (same layout; Y may be X), token t at pos0 + t; with
 // K and V (null: neither) [B, n_tokens, Hkv, d], rotated K and V as it is into cache rows

@@ -178,6 +178,43 @@ def test_plan_query(lib):
     assert call(ctypes.byref(small), small.ctx_len, 1, 0, None) == ERR["NULL_POINTER"]
 
 
+def test_phase1_plan_query(lib):
+    """star_attn_phase1_plan answers on the host: long bf16 prefills draw 256-row tiles from the
+    queues, short ones are a plain grid of 128-row tiles, in groups of blocks."""
+    def plan(mode=sa.ANCHOR_FIRST, **kw):
+        p = sa.phase1_plan(good_shape(**{"cache_capacity": kw.get("ctx_len", 1024), **kw}), mode)
+        return p.queued, p.tile_rows, p.wavefronts, p.group, p.n_tiles
+    llama = dict(n_q_heads=32, n_kv_heads=8)
+    assert plan(**llama, ctx_len=131072, block=16384, anchor=16384) == (1, 256, 8, 0, 8 * 8 * 256)
+    assert plan(**llama, ctx_len=8191, block=2048, anchor=2048) == (0, 128, 4, 1, 8 * 4 * 64)
+    assert plan(n_q_heads=8, n_kv_heads=2, ctx_len=4000, block=1000, anchor=1000)[:3] == (0, 128, 8)     # halves share
+    one = dict(n_q_heads=1, n_kv_heads=1)
+    assert plan(**one, ctx_len=200000, block=1000, anchor=1000) == (0, 128, 4, 32, 200 * 8)      # whole blocks per XCD
+    many = dict(n_q_heads=32, n_kv_heads=32, batch=16, block=2588, ctx_len=2588)
+    assert plan(**many, anchor=0)[:4] == (0, 128, 4, 1)                                          # block by block
+    f32 = dict(dtype="fp32", head_dim=64, n_q_heads=8, n_kv_heads=8)
+    assert plan(**f32, ctx_len=1000, block=16, anchor=0) == (0, 16, 1, 0, 8 * 63)
+    assert plan(**f32, ctx_len=8192, block=2048, anchor=0)[:3] == (0, 32, 4)
+    # no grid that a plan stands for is beyond what a launch can number
+    assert plan(n_q_heads=8, n_kv_heads=8, ctx_len=1 << 21, block=1, anchor=0)[4] == 1 << 24
+    info = binding.Phase1PlanInfo()
+    shape = good_shape()
+    assert lib.star_attn_phase1_plan(ctypes.byref(shape), 9, ctypes.byref(info)) == ERR["INVALID_MODE"]
+    assert lib.star_attn_phase1_plan(ctypes.byref(shape), 0, None) == ERR["NULL_POINTER"]
+    assert lib.star_attn_phase1_plan(None, 0, ctypes.byref(info)) == ERR["NULL_POINTER"]
+
+
+def test_row_tile_of_per_part_calls(lib):
+    """Splits that hold fewer keys than a full one, and none, are not counted as full: 256 tokens on
+    131072 in blocks of 16384 are one round of 256-row tiles and the tail beside it."""
+    c3 = good_shape(n_q_heads=32, n_kv_heads=8, ctx_len=131072, block=16384, anchor=16384, cache_capacity=131072 + 384)
+    assert sa.phase2_plan(c3, 131072, 256, want_parts=True).tile_rows == 256
+    g20 = good_shape(n_q_heads=60, n_kv_heads=3, batch=2, ctx_len=116742, block=29185, anchor=0, cache_capacity=117000)
+    assert sa.phase2_plan(g20, 116742, 47, want_parts=True).tile_rows == 256
+    few = good_shape(n_q_heads=4, n_kv_heads=1, ctx_len=94, block=47, anchor=0, cache_capacity=300)
+    assert sa.phase2_plan(few, 94, 91, want_parts=True).tile_rows == 128
+
+
 def test_workspace_of_per_part_calls_does_not_depend_on_the_cache_length(lib):
     """Calls with per-part outputs keep one pair per split of every part, whatever the cache holds."""
     for dtype, d in (("fp32", 64), ("fp32", 128), ("bf16", 128)):

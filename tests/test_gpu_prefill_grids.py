@@ -2,7 +2,8 @@
 keys the halves of a workgroup share (odd and even numbers of key tiles, a half without
 any), tiles taken block by block and interleaved with the light half turned round, head
 groups that exceed a workgroup, ragged last blocks, every kind of anchor, the exact
-fallback of the softmax; and the queues that longer prefills take."""
+fallback of the softmax; and the queues that longer prefills take, at ragged sizes, odd head
+groups and several head sub-groups.  star_attn_phase1_plan says which of them a call takes."""
 import pytest
 import torch
 
@@ -33,7 +34,24 @@ def test_plain_grids(B, Hq, Hkv, L, b, a, gamma):
     cfg = workloads.StarConfig("plain", "bf16", B, Hq, Hkv, 128, L, b, a, 1, 0, seed=L + Hq, n_planted=8 if L > 64 else 0,
                                gamma=gamma)
     print(f"[{cfg}]", flush=True)
+    plan = sa.phase1_plan(ph.shape_of(cfg))
+    assert plan.queued == 0 and plan.tile_rows == 128
+    assert plan.wavefronts == (8 if plan.n_tiles <= 256 and -(-a // 64) + -(-min(b, L) // 64) > 8 else 4)
     rep = ph.run_parity(cfg, all_rows=B * Hq * L <= 12000, n_random=2048)
+    assert rep.ok, rep.detail
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,b,a,gamma", [
+    (2, 12, 4, 15001, 7001, 7001, 1.5),    # G = 3, two sequences, a ragged last block and last tile
+    (1, 48, 3, 12007, 6007, 6007, 1.5),    # G = 16: two head sub-groups, heads no multiple of 8
+    (1, 40, 8, 12007, 6007, 6007, 6.0),    # G = 5; scores far above the reference: the exact loop
+    (1, 32, 8, 19999, 19999, 0, 1.5),      # one block
+])
+def test_work_queues(B, Hq, Hkv, L, b, a, gamma):
+    cfg = workloads.StarConfig("queues", "bf16", B, Hq, Hkv, 128, L, b, a, 1, 0, seed=L + Hq, n_planted=8, gamma=gamma)
+    print(f"[{cfg}]", flush=True)
+    assert sa.phase1_plan(ph.shape_of(cfg)).queued == 1
+    rep = ph.run_parity(cfg, n_random=512)
     assert rep.ok, rep.detail
 
 

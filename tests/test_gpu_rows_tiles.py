@@ -13,23 +13,29 @@ from tests import parity_harness as ph
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,L,b,a,lq,gamma", [
-    (1, 1, 1, 40, 64, 64, 17, 1.5),        # one ragged tile: the second half has none
-    (1, 1, 1, 64, 64, 64, 65, 1.5),        # cached and new rows in tiles of their own
-    (2, 3, 1, 700, 300, 100, 21, 1.5),     # G = 3: 63 rows, tokens straddle row blocks
-    (1, 5, 1, 1000, 256, 0, 51, 1.5),      # 255 rows: one 256-row tile
-    (1, 4, 2, 1300, 400, 64, 32, 1.5),     # 128 rows: one tile shared by the halves
-    (1, 4, 2, 1300, 400, 64, 33, 1.5),     # 132 rows: one 256-row tile
-    (1, 8, 2, 1300, 1300, 64, 65, 1.5),    # 260 rows: three 128-row tiles
-    (1, 8, 2, 900, 100, 100, 97, 1.5),     # 388 rows: two 256-row tiles
-    (1, 40, 2, 600, 200, 7, 3, 1.5),       # G = 20
-    (1, 8, 2, 6000, 1500, 64, 21, 6.0),    # scores far above the reference: the exact loop
-    (1, 4, 2, 3000, 800, 64, 60, 6.0),     # the same on a 256-row tile
+# tiles: rows of the tile with per-part outputs and without; a split of no more than 64 keys (every
+# tail here up to 64 tokens long) leaves the second half of a 128-row tile without any
+@pytest.mark.parametrize("B,Hq,Hkv,L,b,a,lq,gamma,tiles", [
+    (1, 1, 1, 40, 64, 64, 17, 1.5, (256, 256)),        # one ragged tile, 57 keys in all
+    (1, 1, 1, 64, 64, 64, 65, 1.5, (256, 256)),        # cached and new rows in key tiles of their own
+    (2, 3, 1, 700, 300, 100, 21, 1.5, (128, 128)),     # G = 3: 63 rows, tokens straddle row blocks
+    (1, 5, 1, 1000, 256, 0, 51, 1.5, (128, 128)),      # 255 rows: a whole tile and a ragged one
+    (1, 4, 2, 1300, 400, 64, 32, 1.5, (128, 128)),     # 64 rows: half a tile
+    (1, 4, 2, 1300, 400, 64, 33, 1.5, (128, 128)),     # 66 rows: into the next row block
+    (1, 8, 2, 1300, 1300, 64, 65, 1.5, (128, 128)),    # 260 rows: three tiles
+    (1, 8, 2, 900, 100, 100, 97, 1.5, (128, 128)),     # 388 rows: four tiles
+    (1, 40, 2, 600, 200, 7, 3, 1.5, (128, 128)),       # G = 20
+    (1, 8, 2, 6000, 1500, 64, 21, 6.0, (128, 128)),    # scores far above the reference: the exact loop
+    (1, 4, 2, 3000, 800, 64, 60, 6.0, (128, 128)),     # the same, another number of tiles per half
+    (2, 32, 8, 2000, 1000, 100, 150, 1.5, (256, 128)),     # 600 rows: three tiles, the last ragged
+    (1, 32, 8, 9000, 9000, 64, 300, 6.0, (256, 256)),      # 1200 rows: five tiles, the exact loop
+    (1, 32, 8, 12000, 12000, 0, 400, 1.5, (128, 256)),     # seven tiles of 256 rows
 ])
-def test_row_tile_edges(B, Hq, Hkv, L, b, a, lq, gamma):
+def test_row_tile_edges(B, Hq, Hkv, L, b, a, lq, gamma, tiles):
     cfg = workloads.StarConfig("rows", "bf16", B, Hq, Hkv, 128, L, b, a, lq, 1, seed=L + lq, n_planted=8,
                                gamma=gamma)
     print(f"[{cfg}]", flush=True)
+    assert tuple(sa.phase2_plan(ph.shape_of(cfg), L, lq, parts).tile_rows for parts in (True, False)) == tiles
     rep = ph.run_parity(cfg, all_rows=L < 1500)      # the query call with per-part outputs
     assert rep.ok, rep.detail
     # the same call as a serving program makes it, without per-part outputs
@@ -38,7 +44,7 @@ def test_row_tile_edges(B, Hq, Hkv, L, b, a, lq, gamma):
     run.phase1()
     O, _, _ = run.phase2(inp.Qq, inp.Kq, inp.Vq, want_parts=False)
     torch.cuda.synchronize()
-    heads = list(range(Hq)) if Hq <= 8 else [0, 19, 20, Hq - 1]
+    heads = list(range(Hq)) if Hq <= 8 else [0, 1, Hq // 2 - 1, Hq // 2, Hq - 1]
     res = ph.check_phase2(run, inp.Qq, ([inp.Kq], [inp.Vq]), L, O, None, None, heads, tag="flat")
     assert res["flat_O"] <= ph.TOL["bf16"]["o"], res
     for g in range(Hkv):
