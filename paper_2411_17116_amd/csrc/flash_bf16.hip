@@ -1032,13 +1032,12 @@ __global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, i
   // of a call of few keys: 454 tokens on 5740, 6 / 3 heads, 43.8 us)
   const int filers = row_tiles < 64 ? row_tiles : 64;
   if (fused_append && tt < filers) {
-    const int n_units = (seq.loc_hi - seq.loc_lo) * 16;
-    const size_t dst = ((size_t)beta * g.Hkv + kvh) * (size_t)g.cap + seq.loc_lo;
-    for (int u = tt * NT + tid; u < n_units; u += filers * NT) {
-      const size_t from = (size_t)(seq.loc_lo - cache_len + (u >> 4)) * new_stride + (u & 15) * 16;
+    for (int row = seq.loc_lo + tt * (NT / 16) + (tid >> 4); row < seq.loc_hi; row += filers * (NT / 16)) {
+      const size_t from = (size_t)(row - cache_len) * new_stride + (tid & 15) * 16;
+      const size_t to = (((size_t)beta * g.Hkv + kvh) * (size_t)g.cap + row) * ROWB + (tid & 15) * 16;
       const i32x4 k = *(const i32x4*)(Kn + from), v = *(const i32x4*)(Vn + from);
-      *(i32x4*)((char*)a.Kc + dst * ROWB + (size_t)u * 16) = k;
-      *(i32x4*)((char*)a.Vc + dst * ROWB + (size_t)u * 16) = v;
+      *(i32x4*)((char*)a.Kc + to) = k;
+      *(i32x4*)((char*)a.Vc + to) = v;
     }
   }
 
