@@ -87,5 +87,8 @@ def test_plain_grids_give_what_each_row_gives_alone(mode, Hq, Hkv, L, b, a):
                          V[:, s:e].contiguous(), o1, k1, v1, K_anchor=ka.contiguous(), V_anchor=va.contiguous())
         torch.cuda.synchronize()
         # both within 2e-2 of the exact result (two roundings of P and one of O each)
-        assert (o1.float() - O[:, s:e].float()).abs().max().item() <= 2e-2, i
+        diff, ref = o1.float() - O[:, s:e].float(), o1.float()
+        assert diff.abs().max().item() <= 2e-2, i
+        # relative: four roundings to 8 bits of mantissa, rms 2^-9 / sqrt(3) each, is 2.3e-3
+        assert diff.norm().item() <= 6e-3 * ref.norm().item(), i
         assert torch.equal(k1, Kc[:, :, s:e]) and torch.equal(v1, Vc[:, :, s:e])
