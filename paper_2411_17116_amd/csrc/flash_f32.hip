@@ -489,12 +489,14 @@ hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   const int64_t tpb = (bmax * g.G + 16 * NB - 1) / (16 * NB), wgs = n * tpb * g.B * g.Hkv;
   // (a block of 2^31 rows would be 550 GB of queries)
   if (wgs > 0x7fffffff || bmax * g.G > 0x7fffffff - 64) return hipErrorInvalidValue;
-  // All blocks in one group while a few rounds of workgroups are all there is and the keys in
-  // use at a time fit the 4 MiB L2 cache of an XCD (K and V of a KV head up to 6 MiB), else
-  // block by block.  8 / 2 heads, us in one group / block by block: d = 128: blocks of 2048 of
-  // 8192 tokens 816 / 705, of 1024 of 4099 (1025 workgroups) 151 / 155, of 256 of 1024 24 / 27;
-  // d = 64: of 2048 of 8192 (2048 workgroups) 434 / 369, of 1024 of 4099 86 / 90.
-  const int64_t group = wgs <= 1536 && g.L * g.d * 8 <= ((int64_t)6 << 20) ? n : 1;
+  // All blocks in one group where the tiles start at once (two workgroups per CU and more), so that
+  // heavy and light ones share CUs, else block by block: with several rounds of them a group of
+  // few blocks leaves the XCDs that get the light blocks idle.  us, in one group / block by
+  // block, 8 / 2 heads, blocks of L / 4, b = a: d = 128: L = 1024 (512 tiles) 24.2 / 26.5, 2048 (1024) 79 / 70,
+  // 4099 (1032) 256 / 209, 8192 (2048) 813 / 705; d = 64: 4099 135 / 118, 6000 (1504) 246 / 216.
+  // Over 350 drawn shapes, time lost against the better of the two: to 512 tiles 0.9 % and 1.1 %, from
+  // 513 to 1536 4.4 % and 3.4 %, beyond 3.8 % and 3.4 %.
+  const int64_t group = wgs <= 512 ? n : 1;
   return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
     phase1_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, (int)group, (int)tpb, (int)first);
   });
