@@ -23,7 +23,8 @@
  *     when the call that last used it has finished on the device, and a call
  *     that finds all 64 in flight -- or whose stream is being captured into a
  *     graph, where a set would be shared by every replay -- returns
- *     STAR_ATTN_ERR_BUSY without enqueueing anything.
+ *     STAR_ATTN_ERR_BUSY without enqueueing anything.  (A short prefill takes a set
+ *     like any other, though its kernel draws nothing from it.)
  *   - Calls are asynchronous: work is enqueued on `hip_stream` (a hipStream_t
  *     passed as void*, NULL = the default stream) and the function returns
  *     without synchronising.  Calls on one stream run in order.
@@ -385,8 +386,10 @@ int star_attn_phase1_plan(const star_attn_shape* shape, int anchor_mode,
 const char* star_attn_status_string(int status);
 
 /*
- * Name of the kernel path a shape would use ("f32-valu", "bf16-mfma"), for
- * logs and benchmarks; NULL for an unsupported shape.  Host memory, static.
+ * Name of the kernel path a shape would use, for logs and benchmarks; NULL for an
+ * unsupported shape.  "bf16-mfma", or "f32-valu": a label kept from the first fp32
+ * kernels, since callers may compare it -- the path runs on the fp32 matrix
+ * instructions.  Host memory, static.
  */
 const char* star_attn_kernel_path(const star_attn_shape* shape);
 

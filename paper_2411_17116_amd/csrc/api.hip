@@ -154,7 +154,9 @@ static int f32_tile_rows(const Geom& g, int64_t q_len, int64_t total) {
 // 13.9 at 530 (one row, d = 64), splits and their merge 11.7 us at either.
 constexpr int64_t F32_DIRECT_BYTES = 256 << 10;
 
-// ---- bf16 row-tiled kernel: one workgroup per CU is resident (256 of them).
+// ---- bf16 row-tiled kernel: one workgroup per CU is resident, 256 on the whole chip.  (The costs
+// below and the fp32 split counts are for the whole chip; on a partition of it calls are cut
+// finer than they need be, with the same results.)
 constexpr int64_t ROW_WGS = 256;
 
 // Workgroups of one split with tiles of `tile` rows.
@@ -298,7 +300,9 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     split_len = 256;
     while (split_len < want && split_len < 4096) split_len *= 2;
   } else {
-    int64_t want, min_len;   // splits over all blocks that fill the GPU; keys worth a split
+    // splits over all blocks that fill the GPU; keys worth a split.  (bf16: counted with tiles
+    // whose heads are not packed, fewer splits than packed rows would need for odd groups.)
+    int64_t want, min_len;
     if (s->dtype == STAR_ATTN_F32) {
       // (the same splits for every length of the cache)
       p->tile_rows = f32_tile_rows(g, q_len, total);
