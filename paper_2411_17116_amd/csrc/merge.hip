@@ -299,12 +299,17 @@ struct Fold {
 __device__ __forceinline__ Fold empty_fold() { return Fold{-INFINITY, 0.f, f32x4{0.f, 0.f, 0.f, 0.f}}; }
 __device__ __forceinline__ float finite(float m) { return m == -INFINITY ? 0.f : m; }
 
-// N splits at once: `ls` their log-sum-exps (-inf: empty, `v` unset).
 template <int N>
-__device__ __forceinline__ void fold_splits(Fold& f, const float (&ls)[N], const f32x4 (&v)[N]) {
-  float m = f.m;
+__device__ __forceinline__ float largest(const float (&ls)[N]) {
+  float m = ls[0];
 #pragma unroll
-  for (int u = 0; u < N; ++u) m = fmaxf(m, ls[u]);
+  for (int u = 1; u < N; ++u) m = fmaxf(m, ls[u]);
+  return m;
+}
+// N splits at once: `ls` their log-sum-exps (-inf: empty, `v` unset), none above `m`.
+template <int N>
+__device__ __forceinline__ void fold_splits(Fold& f, const float (&ls)[N], const f32x4 (&v)[N], float m) {
+  m = fmaxf(m, f.m);
   const float mm = finite(m), old = weight(f.m - mm);
   f.w *= old;
   f.acc *= old;
@@ -349,32 +354,31 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
   const int h = blockIdx.y, beta = blockIdx.z, S = a.plan.s_total;
   const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;
 
+  // the weights of a step are taken against the maximum of its splits over the whole wavefront:
+  // the groups' sums then meet without another weight
   Fold f = empty_fold();
-  for (int s0 = grp; s0 < S; s0 += INFL * GROUPS) {
+  for (int s0 = 0; s0 < S; s0 += INFL * GROUPS) {
     float ls[INFL];
     f32x4 v[INFL];
 #pragma unroll
     for (int u = 0; u < INFL; ++u) {
-      const int s = s0 + u * GROUPS;
-      const int64_t r = base + (int64_t)(s < S ? s : s0) * a.split_stride;
+      const int s = s0 + grp + u * GROUPS;
+      const int64_t r = base + (int64_t)(s < S ? s : S - 1) * a.split_stride;
       ls[u] = a.LSE_sub[r];
       v[u] = *(const f32x4*)(a.O_sub + r * g.d + d0);
       if (s >= S) ls[u] = -INFINITY;
     }
-    fold_splits<INFL>(f, ls, v);
+    float m = largest<INFL>(ls);
+#pragma unroll
+    for (int x = LPS; x < 64; x <<= 1) m = fmaxf(m, __shfl_xor(m, x));
+    fold_splits<INFL>(f, ls, v, m);
   }
   // the groups of a wavefront, then the wavefronts
 #pragma unroll
   for (int x = LPS; x < 64; x <<= 1) {
-    Fold o;
-    o.m = __shfl_xor(f.m, x);
-    o.w = __shfl_xor(f.w, x);
+    f.w += __shfl_xor(f.w, x);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o.acc[e] = __shfl_xor(f.acc[e], x);
-    const float m = fmaxf(f.m, o.m), mm = finite(m), sf = weight(f.m - mm), so = weight(o.m - mm);
-    f.w = f.w * sf + o.w * so;
-    f.acc = f.acc * sf + o.acc * so;
-    f.m = m;
+    for (int e = 0; e < 4; ++e) f.acc[e] += __shfl_xor(f.acc[e], x);
   }
   if ((tid & 63) < LPS) {
     if (li == 0) { red_m[tid >> 6] = f.m; red_w[tid >> 6] = f.w; }
@@ -396,10 +400,10 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
 }
 
 // Many rows of a few splits each (query encoding, pairs of other hosts): d / 4 lanes own a
-// row, up to eight splits in flight, nothing crosses lanes.
-template <int D>
+// row, INFL splits in flight, nothing crosses lanes.
+template <int D, int INFL>
 __global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, unsigned n_rows, unsigned first_wg) {
-  constexpr int LPR = D / 4, INFL = 8;
+  constexpr int LPR = D / 4;
   const Geom& g = a.g;
   const unsigned row = (first_wg + blockIdx.x) * (256 / LPR) + threadIdx.x / LPR;      // (beta, h, j), j fastest
   if (row >= n_rows) return;
@@ -417,7 +421,7 @@ __global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, unsig
       v[u] = *(const f32x4*)(a.O_sub + r * D + d0);
       if (s0 + u >= S) ls[u] = -INFINITY;
     }
-    fold_splits<INFL>(f, ls, v);
+    fold_splits<INFL>(f, ls, v, largest<INFL>(ls));
   }
   store_merged(a, (int)beta, (int)h, j, d0, f);
 }
@@ -440,8 +444,11 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
     if (S <= 8 && rows >= 64) {
       const int64_t wgs = a.g.d == 64 ? (rows + 15) / 16 : (rows + 7) / 8;
       return launch_in_pieces(wgs, 256, [&](unsigned first, unsigned n_wgs) {
-        if (a.g.d == 64) merge_flat_rows_kernel<64><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
-        else merge_flat_rows_kernel<128><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
+        // (a split past the last costs as much as one)
+        if (a.g.d == 64 && S <= 4) merge_flat_rows_kernel<64, 4><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
+        else if (a.g.d == 64) merge_flat_rows_kernel<64, 8><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
+        else if (S <= 4) merge_flat_rows_kernel<128, 4><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
+        else merge_flat_rows_kernel<128, 8><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
       });
     }
     // Few rows: pieces of d, so that the row's splits are in flight at once over more
