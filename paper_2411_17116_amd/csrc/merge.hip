@@ -282,7 +282,8 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(MergeArgs a, int64_t n_
 // and a division in store_merged() hold an fp32 merge to the error its roundings leave: rms
 // against 64 bits for 2 / 4 / 8 pairs 4.2 / 4.8 / 5.3e-8; with exp2 of a rounded product and a
 // rounded reciprocal it was 4.6 / 5.2 / 5.6e-8.  expf() is as exact and costs more where many
-// rows have 9 to 64 splits (20480 rows of 16: 26 us with the short forms, 33 like this, 37).
+// rows have 9 to 64 splits (20480 rows of 16, d = 64: 26 us with the short forms, 33 like this, 37
+// with expf(); 29 since the groups of a wavefront meet without a weight).
 __device__ __forceinline__ float weight(float x) {
   constexpr float HI = 1.4426950408889634f, LO = 1.925963e-8f;     // log2(e)
   x = x < -200.f ? -200.f : x;
