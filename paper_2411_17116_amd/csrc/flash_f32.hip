@@ -22,6 +22,8 @@
 //   * K of the next unit is requested once the scores of this one are done, V once
 //     its products are done: each load has half a unit of MFMAs (2048 cycles at
 //     NB = 2, d = 128) to arrive.
+//   * Softmax runs against a reference per row and wavefront that moves only when a score leaves its
+//     headroom, so that a unit has no maximum search over lanes and no rescaling of O.
 //   * The KW partial results (O, m, l) of a row meet in LDS once, at the end.
 // Phase 1 reads K and V where the caller left them and files its own tokens' rows in
 // the caches; phase 2 reads the new tokens from the call's Kq / Vq and appends them.
@@ -41,6 +43,13 @@ typedef const __attribute__((address_space(1))) char* GlobalBytes;
 typedef const __attribute__((address_space(1))) f32x4* GlobalVec;
 
 constexpr int UNIT = 16;   // keys per step of a wavefront
+// How far (log2 units) a score may rise above its row's reference before the reference moves.
+// O / l does not depend on the reference, and 2^8 times the largest numerator is as far from overflow
+// as it was, so nothing is lost; scores of N(0, 1) inputs stay within it of the first unit's, and a
+// unit then costs no exchange between lanes and no rescaling of O.  Against moving it to every new maximum, us
+// (8 / 2 heads): d = 128: L = 4099 (b = 1024, a = 512) 152 -> 142, 8192 (b = a = 2048) 706 -> 663, L = 3001 53.7 ->
+// 52.2; d = 64: 8192 375 -> 352, 4099 117.5 -> 107.7; 1 head, 1024 10.2 -> 9.8.
+constexpr float HEADROOM = 8.f;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -78,8 +87,9 @@ template <int D, int NB>
 struct RowState {
   f32x4 q[NB][D / 16];        // q[.][t][e] = Q[row][16 t + 4 j4 + e] * scale * log2(e)
   f32x4 o[NB][D / 64][4];     // o[.][h][e][w] = O[row][64 h + 16 j4 + 4 w + e]
-  float m[NB], l[NB];         // running maximum (log2 units; uniform over a row's four lanes) and
-                              // this lane's share of the sum of 2^(s - m)
+  float m[NB], top[NB];       // reference (log2 units; uniform over a row's four lanes; 0 until a key is
+                              // visible) and the score beyond which it moves (-inf until then)
+  float l[NB];                // this lane's share of the sum of 2^(s - m)
 };
 
 template <int D>
@@ -172,24 +182,33 @@ __device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, cons
       for (int v = 0; v < 4; ++v) s[b][v] = v < n ? s[b][v] : -INFINITY;
     }
   }
+  float t[NB];
+  bool beyond = false;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    float t = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
-    t = xor32_max(fmaxf(t, xor16(t)));
-    if (__builtin_amdgcn_ballot_w64(t > w.m[b]) != 0) {      // some row's maximum moved
-      const float m_new = fmaxf(w.m[b], t);
-      const float mm = m_new == -INFINITY ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(w.m[b] - mm);   // 0 while nothing was visible
-      w.m[b] = m_new;
+    t[b] = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
+    beyond |= t[b] > w.top[b];
+  }
+  if (__builtin_amdgcn_ballot_w64(beyond) != 0) {      // some row's reference moves
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const float row = xor32_max(fmaxf(t[b], xor16(t[b])));
+      const float m_old = w.top[b] == -INFINITY ? -INFINITY : w.m[b], m_new = fmaxf(m_old, row);
+      const float m = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m_old - m);   // 0 while nothing was visible
+      w.m[b] = m;
+      w.top[b] = m_new + HEADROOM;
       w.l[b] *= alpha;
 #pragma unroll
       for (int h = 0; h < D / 64; ++h)
 #pragma unroll
         for (int e = 0; e < 4; ++e) w.o[b][h][e] *= alpha;
     }
-    const float mm = w.m[b] == -INFINITY ? 0.f : w.m[b];
+  }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) s[b][v] = __builtin_amdgcn_exp2f(s[b][v] - mm);
+  for (int b = 0; b < NB; ++b) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s[b][v] = __builtin_amdgcn_exp2f(s[b][v] - w.m[b]);
     w.l[b] += (s[b][0] + s[b][1]) + (s[b][2] + s[b][3]);
   }
 #pragma unroll
@@ -214,7 +233,8 @@ __device__ __forceinline__ void load_row(RowState<D, NB>& w, int b, const float*
   for (int h = 0; h < D / 64; ++h)
 #pragma unroll
     for (int e = 0; e < 4; ++e) w.o[b][h][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-  w.m[b] = -INFINITY;
+  w.m[b] = 0.f;
+  w.top[b] = -INFINITY;
   w.l[b] = 0.f;
 }
 template <int D, int NB>
@@ -265,7 +285,7 @@ __device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<NB, KW>& x, Store 
   for (int b = 0; b < NB; ++b) {
     float l = w.l[b] + xor16(w.l[b]);
     l = xor32_sum(l);
-    if (j4 == 0) { x.m[wave][16 * b + col] = w.m[b]; x.l[wave][16 * b + col] = l; }
+    if (j4 == 0) { x.m[wave][16 * b + col] = w.top[b] == -INFINITY ? -INFINITY : w.m[b]; x.l[wave][16 * b + col] = l; }
   }
   __syncthreads();
   for (int i = tid; i < KW * ROWS; i += 64 * KW) {
