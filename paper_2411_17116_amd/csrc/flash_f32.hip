@@ -28,9 +28,9 @@
 // Phase 1 reads K and V where the caller left them and files its own tokens' rows in
 // the caches; phase 2 reads the new tokens from the call's Kq / Vq and appends them.
 // Measured, whole calls, against a kernel of one thread per row: 8 / 2 heads, d = 128,
-// L = 4099, b = 1024, a = 512: 3390 -> 151 us (100 TFLOP/s; 119 at 8192 tokens in blocks of
+// L = 4099, b = 1024, a = 512: 3390 -> 131 us (115 TFLOP/s; 129 at 8192 tokens in blocks of
 // 2048, where a library fp32 matrix product reaches 152); 1 head, d = 64, L = 1024,
-// b = a = 256: 274 -> 9.9 us.
+// b = a = 256: 274 -> 9.2 us.
 #include "star_internal.h"
 
 namespace star {
@@ -265,6 +265,13 @@ __device__ __forceinline__ void attend(RowState<D, NB>& w, const KeySeq& seq, in
   attend_unit<D, NB, false>(w, r, cur, cur, row_lim, wave_lim, lane);
 }
 
+// log(l 2^m) for l > 0: the exponent of l joins m without a rounding lost, so that l may be a large sum
+// (the reference m can lie HEADROOM below the row's maximum) or a small one.
+__device__ __forceinline__ float log_sum(float m, float l) {
+  const float e = (float)__builtin_amdgcn_frexp_expf(l), t = m + e, back = t - m, lost = (m - (t - back)) + (e - back);
+  return fmaf(t, LN2, (log2f(__builtin_amdgcn_frexp_mantf(l)) + lost) * LN2);
+}
+
 // LDS in which the KW wavefronts' results of a tile meet, 64 columns of d at a time.
 // The pitch of 68 floats spreads the 16 rows of a 16-byte write over all banks.
 template <int NB, int KW>
@@ -298,7 +305,7 @@ __device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<NB, KW>& x, Store 
 #pragma unroll
     for (int n = 0; n < KW; ++n) l += x.l[n][row] * __builtin_amdgcn_exp2f(x.m[n][row] - mm);
     x.scale[k][row] = l > 0.f ? __builtin_amdgcn_exp2f(x.m[k][row] - mm) * (1.f / l) : 0.f;
-    if (k == 0) store_lse(row, l > 0.f ? (m + log2f(l)) * LN2 : -INFINITY);
+    if (k == 0) store_lse(row, l > 0.f ? log_sum(m, l) : -INFINITY);
   }
 #pragma unroll
   for (int h = 0; h < D / 64; ++h) {
@@ -334,31 +341,70 @@ __device__ __forceinline__ void file_rows(const float* K, const float* V, int64_
 }
 
 // ------------------------------------------------------------------ phase 1
-// Workgroups are numbered (kv head fastest, batch, block in group -- block 0, which has no anchor,
-// last --, tile in block -- late, i.e. heavy, first --, group of blocks).  Inside a group
-// the tiles come in descending weight, so that those that share a CU, or come last,
-// even out.
+// Workgroups are numbered (kv head fastest, batch, tile), tiles in descending weight over all blocks.
+// A workgroup goes to the XCD of its number mod 8 and there to the four shader engines
+// strictly in turn, so numbers 32 apart share eight CUs, and none starts before those in front
+// of it have: tiles of one weight next to each other keep all engines in step, whereas
+// heavy tiles behind light ones, or numbers without a tile (a short last block's), leave engines idle.
+// Against block by block, heavy tiles of each first, us (8 / 2 heads): d = 128: L = 4099 (b = 1024, a = 512) 142.4 ->
+// 133.4, L = 3001 (b = 375, a = 93) 52.2 -> 46.5, 8192 (b = a = 2048) 662 -> 668; d = 64: 4099 (b = a = 1024) 107.5 ->
+// 97.2; two sequences of 6000, 4 / 2 heads 125.5 -> 118.0; 300 workgroups and fewer the same.  Divisions by
+// multiplication (struct Div) in place of the compiler's chains: another 1-2 us, 0.9 of 10 us at 1024 tokens of one head.
+// Class c holds the tiles that walk c + 1 tiles' worth of keys: tile c - anchor_tiles of the
+// blocks behind an anchor, tile c of a block without one (the first, unless there are no anchors or it
+// has one too).  Runs of classes with the same number of tiles:
+struct TileOrder {
+  int first[4];        // first tile of the run
+  int top[4];          // its highest class
+  Div per[4];          // tiles per class
+  int full[4];         // of which full-length blocks behind an anchor
+  int last[4];         // 1: and the short last block
+  int anchor_tiles, plain, n_blocks;      // plain: first block behind an anchor
+  int turn_from, turn;                    // workgroups from the one on: turn - number
+  Div Hkv, B, G;
+};
+struct Tile {
+  int kvh, beta, i, t;                    // t: tile within block i
+};
+__device__ __forceinline__ Tile tile_at(const TileOrder& p, int wg) {
+  uint32_t id = wg >= p.turn_from ? p.turn - wg : wg, q = quotient(id, p.Hkv);
+  const int kvh = id - q * p.Hkv.d;
+  id = q;
+  q = quotient(id, p.B);
+  const int beta = id - q * p.B.d;
+  id = q;
+  int first = p.first[0], top = p.top[0], full = p.full[0], last = p.last[0];
+  Div per = p.per[0];
+#pragma unroll
+  for (int k = 1; k < 4; ++k) {
+    // values of their own: chosen between as array elements, they would be put into scratch memory
+    int f = p.first[k], c = p.top[k], n = p.full[k], l = p.last[k];
+    Div x = p.per[k];
+    asm("" : "+s"(f), "+s"(c), "+s"(n), "+s"(l), "+s"(x.d), "+s"(x.m), "+s"(x.s));
+    if ((int)id >= f) { first = f; top = c; per = x; full = n; last = l; }
+  }
+  id -= first;
+  q = quotient(id, per);
+  const int c = top - (int)q, e = id - q * per.d;
+  const bool anchored = e < full + last;
+  const int i = e < full ? p.plain + e : anchored ? p.n_blocks - 1 : 0, t = anchored ? c - p.anchor_tiles : c;
+  return {__builtin_amdgcn_readfirstlane(kvh), __builtin_amdgcn_readfirstlane(beta), __builtin_amdgcn_readfirstlane(i),
+          __builtin_amdgcn_readfirstlane(t)};
+}
 template <int D, int NB, int KW>
-__global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, int group, int tiles_per_block,
-                                                                int first_wg) {
+__global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, TileOrder order, int first_wg) {
   __shared__ Meet<NB, KW> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
-  int id = first_wg + (int)blockIdx.x;
-  const int kvh = id % g.Hkv; id /= g.Hkv;
-  const int beta = id % g.B; id /= g.B;
-  const int n = (int)((g.L + g.b - 1) / g.b), first = id / (group * tiles_per_block) * group;
-  id -= first * tiles_per_block;
-  const int in_group = n - first < group ? n - first : group;
-  const int i = first + id % in_group + 1 == n ? 0 : first + id % in_group + 1;
-  const int t = tiles_per_block - 1 - id / in_group;
+  const Tile tile = tile_at(order, first_wg + (int)blockIdx.x);
+  const int kvh = tile.kvh, beta = tile.beta, i = tile.i, t = tile.t;
   const int s = (int)(i * g.b);
   const int e = (int)(s + g.b < g.L ? s + g.b : g.L);
   const int r0 = t * ROWS, n_rows = (e - s) * g.G;    // rows of this block
-  if (r0 >= n_rows) return;                           // tile beyond a short block
   const int live_rows = n_rows - r0 < ROWS ? n_rows - r0 : ROWS;
-  const int tok0 = s + r0 / g.G, head0 = r0 % g.G;    // the tile's first row; row rr is rr rows on
+  const int row0_tok = (int)quotient(r0, order.G);
+  const int tok0 = s + row0_tok, head0 = r0 - row0_tok * g.G;      // the tile's first row; row rr is rr rows on
 
   // K / V rows from the token-major inputs when they are handed over as they are
   // (then this kernel also files them in the caches), else from the filled caches
@@ -374,7 +420,8 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, in
   for (int b = 0; b < NB; ++b) {
     const int rr = 16 * b + col;
     const unsigned r = head0 + (rr < live_rows ? rr : 0);     // rows past the block repeat the first
-    const int tok = tok0 + (int)(r / (unsigned)g.G), head = kvh * g.G + (int)(r % (unsigned)g.G);
+    const unsigned j = quotient(r, order.G);
+    const int tok = tok0 + (int)j, head = kvh * g.G + (int)(r - j * g.G);
     row_lim[b] = tok + 1;
     load_row<D, NB>(w, b, (const float*)a.Q + (((int64_t)beta * g.L + tok) * g.Hq + head) * D, j4);
   }
@@ -385,34 +432,34 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, in
   const bool ext = anchor_range(g, a.anchor_mode, i, &a_lo, &a_hi);
   seq.a_lo = (int)a_lo; seq.a_hi = (int)a_hi;
   // separately given anchors: token-major, n_anchor * a rows per batch
-  const int64_t anchor_rows = (int64_t)(a.anchor_mode == ANCHOR_PER_BLOCK ? n : 1) * g.a;
+  const int64_t anchor_rows = (int64_t)(a.anchor_mode == ANCHOR_PER_BLOCK ? order.n_blocks : 1) * g.a;
   const int64_t anchor0 = ((int64_t)beta * anchor_rows * g.Hkv + kvh) * D;
   seq.Ka = (GlobalBytes)(ext ? (const float*)a.Ka + anchor0 : Kb);
   seq.Va = (GlobalBytes)(ext ? (const float*)a.Va + anchor0 : Vb);
   seq.a_stride = (unsigned)(ext ? (int64_t)g.Hkv * D : stride) * 4;
   seq.Kl = (GlobalBytes)Kb; seq.Vl = (GlobalBytes)Vb; seq.l_stride = (unsigned)stride * 4; seq.l_off = 0;
   seq.l_lo = s;
-  seq.l_hi = tok0 + (head0 + live_rows - 1) / g.G + 1;
+  seq.l_hi = tok0 + (int)quotient(head0 + live_rows - 1, order.G) + 1;
   seq.count();
   attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, g.scale * LOG2E, lane);
 
   meet<D, NB, KW>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
-        const unsigned r = head0 + row;
-        const int tok = tok0 + (int)(r / (unsigned)g.G), head = kvh * g.G + (int)(r % (unsigned)g.G);
+        const unsigned r = head0 + row, j = quotient(r, order.G);
+        const int tok = tok0 + (int)j, head = kvh * g.G + (int)(r - j * g.G);
         *(f32x4*)((float*)a.O + (((int64_t)beta * g.L + tok) * g.Hq + head) * D + c) = v;
       },
       [&](int row, float lse) {
         if (row >= live_rows || !a.LSE) return;
-        const unsigned r = head0 + row;
-        const int tok = tok0 + (int)(r / (unsigned)g.G), head = kvh * g.G + (int)(r % (unsigned)g.G);
+        const unsigned r = head0 + row, j = quotient(r, order.G);
+        const int tok = tok0 + (int)j, head = kvh * g.G + (int)(r - j * g.G);
         a.LSE[((int64_t)beta * g.Hq + head) * g.L + tok] = lse;
       });
 
   // Algorithm 1, "keep the block's K/V": a token is filed by the tile that holds its first row
   if (from_input) {
-    const int t0 = tok0 + (head0 + g.G - 1) / g.G, t1 = tok0 + (head0 + live_rows + g.G - 1) / g.G;
+    const int t0 = tok0 + (head0 > 0 ? 1 : 0), t1 = tok0 + (int)quotient(head0 + live_rows + g.G - 1, order.G);
     file_rows<D>(Kb + (int64_t)t0 * stride, Vb + (int64_t)t0 * stride, stride,
                  (float*)a.Kc + cache0 + (int64_t)t0 * D, (float*)a.Vc + cache0 + (int64_t)t0 * D, t1 - t0, threadIdx.x,
                  64 * KW);
@@ -421,17 +468,18 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, in
 
 // ------------------------------------------------------------------ phase 2
 // Workgroups are numbered (kv head fastest, row tile, split, batch).
+struct RowGrid {
+  Div Hkv, tiles, splits, G;
+};
 template <int D, int NB, int KW>
-__global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, int row_tiles, int first_wg) {
+__global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, RowGrid grid, int first_wg) {
   __shared__ Meet<NB, KW> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
-  int id = first_wg + (int)blockIdx.x;
-  const int kvh = id % g.Hkv; id /= g.Hkv;
-  const int tile = id % row_tiles; id /= row_tiles;
-  const int sp = id % a.plan.s_total;
-  const int beta = id / a.plan.s_total;
+  const uint32_t id = first_wg + blockIdx.x, of_head = quotient(id, grid.Hkv), of_tile = quotient(of_head, grid.tiles);
+  const int kvh = id - of_head * grid.Hkv.d, tile = of_head - of_tile * grid.tiles.d, beta = quotient(of_tile, grid.splits);
+  const int sp = of_tile - beta * grid.splits.d, row_tiles = grid.tiles.d;
   const int r0 = tile * ROWS, n_rows = g.G * a.q_len;  // row = token * G + head in group
   const int live_rows = n_rows - r0 < ROWS ? n_rows - r0 : ROWS;
 
@@ -444,11 +492,11 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const int rr = 16 * b + col, r = r0 + (rr < live_rows ? rr : 0);   // rows past the last repeat the first
-    const int j = r / g.G, head = kvh * g.G + r % g.G;
+    const int j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
     row_lim[b] = (int)visible_limit(a, j);
     load_row<D, NB>(w, b, (const float*)a.Qq + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D, j4);
   }
-  const int wave_lim = (int)visible_limit(a, r0 / g.G);
+  const int wave_lim = (int)visible_limit(a, quotient(r0, grid.G));
 
   // rows below cache_len are cached and visible to every token; the rest are the
   // call's own tokens, read where the caller left them (or from the caches, if a
@@ -478,7 +526,7 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
   meet<D, NB, KW>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
-        const int r = r0 + row, j = r / g.G, head = kvh * g.G + r % g.G;
+        const int r = r0 + row, j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
         float* dst = a.O ? (float*)a.O + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D
                    : a.A ? a.A + (((int64_t)beta * g.Hq + head) * a.q_len + j) * D
                          : a.O_sub + ((((int64_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j) * D;
@@ -486,7 +534,7 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
       },
       [&](int row, float lse) {
         if (row >= live_rows) return;
-        const int r = r0 + row, j = r / g.G, head = kvh * g.G + r % g.G;
+        const int r = r0 + row, j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
         if (!direct) a.LSE_sub[(((int64_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j] = lse;
         else if (a.LSE) a.LSE[((int64_t)beta * g.Hq + head) * a.q_len + j] = lse;
       });
@@ -502,23 +550,50 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, in
   }
 }
 
-template <int D, int NB, int KW>
-hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
+// The order of a call's tiles of `rows` rows; returns their number (of one KV head and batch), or -1 if
+// there are too many.
+int64_t tile_order(const Phase1Args& a, int rows, TileOrder* o) {
   const Geom& g = a.g;
   const int64_t n = (g.L + g.b - 1) / g.b, bmax = g.b < g.L ? g.b : g.L;
-  const int64_t tpb = (bmax * g.G + 16 * NB - 1) / (16 * NB), wgs = n * tpb * g.B * g.Hkv;
-  // (a block of 2^31 rows would be 550 GB of queries)
-  if (wgs > 0x7fffffff || bmax * g.G > 0x7fffffff - 64) return hipErrorInvalidValue;
-  // All blocks in one group where the tiles start at once (two workgroups per CU and more), so that
-  // heavy and light ones share CUs, else block by block: with several rounds of them a group of
-  // few blocks leaves the XCDs that get the light blocks idle.  us, in one group / block by
-  // block, 8 / 2 heads, blocks of L / 4, b = a: d = 128: L = 1024 (512 tiles) 24.2 / 26.5, 2048 (1024) 79 / 70,
-  // 4099 (1032) 256 / 209, 8192 (2048) 813 / 705; d = 64: 4099 135 / 118, 6000 (1504) 246 / 216.
-  // Over 350 drawn shapes, time lost against the better of the two: to 512 tiles 0.9 % and 1.1 %, from
-  // 513 to 1536 4.4 % and 3.4 %, beyond 3.8 % and 3.4 %.
-  const int64_t group = wgs <= 512 ? n : 1;
+  if (bmax * g.G > 0x7fffffff - 64) return -1;
+  const bool alike = g.a == 0 || a.anchor_mode == ANCHOR_ALL_BLOCKS || n == 1;      // no first block by itself
+  const int64_t per_block = (bmax * g.G + rows - 1) / rows, rest = g.L - (n - 1) * g.b;
+  const int64_t of_last = n > 1 && rest < g.b ? (rest * g.G + rows - 1) / rows : 0;
+  const int64_t most = 1 << 28, wide = (g.a * g.G + rows / 2) / rows, anchor = alike ? 0 : wide < most ? wide : most;
+  const int64_t n_full = n - (alike ? 0 : 1) - (of_last > 0 ? 1 : 0);
+  o->plain = alike ? 0 : 1; o->n_blocks = (int)n; o->anchor_tiles = (int)anchor;
+  // between two of these classes the same blocks have a tile in each
+  int64_t bound[5] = {anchor + per_block, anchor + of_last, alike ? 0 : per_block, anchor, 0}, tiles = 0;
+  for (int i = 1; i < 5; ++i)
+    for (int k = i; k > 0 && bound[k] > bound[k - 1]; --k) { const int64_t x = bound[k]; bound[k] = bound[k - 1]; bound[k - 1] = x; }
+  for (int k = 0; k < 4; ++k) {
+    const int64_t hi = bound[k], lo = bound[k + 1];
+    o->full[k] = (int)(lo >= anchor ? n_full : 0);
+    o->last[k] = lo >= anchor && hi <= anchor + of_last ? 1 : 0;
+    const int64_t per = o->full[k] + o->last[k] + (!alike && hi <= per_block ? 1 : 0);
+    o->per[k] = make_div((uint32_t)(per > 0 ? per : 1));
+    o->top[k] = (int)(hi - 1);
+    o->first[k] = per > 0 && hi > lo ? (int)tiles : 0x7fffffff;      // (a run of none is passed over)
+    tiles += per * (hi - lo);
+    if (tiles * g.B * g.Hkv > 0x7fffffff) return -1;
+  }
+  o->Hkv = make_div(g.Hkv); o->B = make_div(g.B); o->G = make_div(g.G);
+  return tiles;
+}
+
+template <int D, int NB, int KW>
+hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
+  TileOrder o;
+  const int64_t tiles = tile_order(a, 16 * NB, &o);
+  if (tiles < 0) return hipErrorInvalidValue;
+  const int64_t wgs = tiles * a.g.B * a.g.Hkv;
+  // Where all tiles start at once, two to a CU at most, the lighter half comes in reverse, so that a CU
+  // holds a heavy one and a light one: 8 / 2 heads, d = 128, L = 1024 (512 tiles) 23.6 -> 21.9 us.
+  const int64_t cus = 256;
+  o.turn_from = 0x7fffffff; o.turn = 0;
+  if (wgs > cus && wgs <= 2 * cus) { o.turn_from = (int)cus; o.turn = (int)(cus + wgs - 1); }
   return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-    phase1_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, (int)group, (int)tpb, (int)first);
+    phase1_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, o, (int)first);
   });
 }
 
@@ -528,8 +603,9 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
   const int64_t tiles = ((int64_t)g.G * a.q_len + 16 * NB - 1) / (16 * NB);
   const int64_t wgs = tiles * g.B * g.Hkv * a.plan.s_total;
   if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff - 64) return hipErrorInvalidValue;
+  const RowGrid grid = {make_div(g.Hkv), make_div((uint32_t)tiles), make_div(a.plan.s_total), make_div(g.G)};
   return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-    phase2_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, (int)tiles, (int)first);
+    phase2_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, grid, (int)first);
   });
 }
 

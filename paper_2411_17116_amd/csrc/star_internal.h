@@ -182,6 +182,20 @@ inline hipError_t launch_in_pieces(int64_t workgroups, int threads, Launch launc
   return hipSuccess;
 }
 
+// Division by a number that is the same for a whole launch, for numerators below 2^31: the kernels
+// that a short call waits for would otherwise spend a chain of twenty instructions on each.
+// (n / d = (mulhi(n, m) + n) >> s with s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1.)
+struct Div {
+  uint32_t d, m, s;
+};
+inline Div make_div(uint32_t d) {
+  Div x = {d, 0, 0};
+  while (x.s < 31 && ((uint32_t)1 << x.s) < d) ++x.s;
+  x.m = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << x.s) - d)) / d + 1);
+  return x;
+}
+__device__ inline uint32_t quotient(uint32_t n, const Div& x) { return (__umulhi(n, x.m) + n) >> x.s; }
+
 // What a phase-1 call launches: row tiles of `rows` rows shared by `waves` wavefronts, one
 // workgroup each, or (queued) drawn from the work queues.
 struct Phase1Plan {

@@ -67,6 +67,26 @@ def test_fp32_many_rows(B, Hq, Hkv, d, L, b, a):
     assert torch.equal(one.Kc, two.Kc) and torch.equal(one.Vc, two.Vc)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,b,a", [
+    (1, 2, 2, 64, 130, 64, 64),             # the last block of two keys
+    (2, 6, 3, 64, 351, 100, 30),            # its tiles end below, the first block's above those behind an anchor
+    (1, 4, 1, 128, 260, 90, 1),             # an anchor of less than half a tile: one class with the first block
+    (1, 4, 2, 64, 390, 128, 64),            # two blocks of each kind in a class
+    (1, 8, 2, 64, 1200, 400, 0),            # no anchor: all blocks alike
+    (3, 2, 1, 64, 700, 690, 690),           # one full block, and the last short
+    (1, 8, 2, 64, 1060, 265, 265),          # 16-row tiles, 268 of them: the lighter ones in reverse
+    (1, 8, 2, 64, 2050, 512, 512),          # 16-row tiles, 514: beyond two per CU
+    (1, 4, 4, 64, 2000, 2000, 2000),        # one block: 500 in reverse
+])
+def test_fp32_tile_order(B, Hq, Hkv, d, L, b, a):
+    """Every tile of every block once, whatever order a call's blocks give them (every row is
+    compared, and every cache row)."""
+    cfg = workloads.StarConfig("f32order", "fp32", B, Hq, Hkv, d, L, b, a, 2, 1, seed=L, n_planted=2)
+    print(f"[{cfg}]", flush=True)
+    rep = ph.run_parity(cfg, all_rows=True)
+    assert rep.ok, rep.detail
+
+
 def test_fp32_workspace_covers_every_shorter_call():
     """Whatever a query call of at most max_q tokens plans must fit what
     star_attn_workspace_bytes asked for (tiles hold 32 / G tokens: not a whole number)."""
