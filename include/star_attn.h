@@ -356,7 +356,8 @@ typedef struct star_attn_plan_info {
   int32_t flat;            /* 1: splits ignore part boundaries (only without per-part outputs) */
   int32_t n_splits;        /* splits per (batch, KV head) */
   int32_t non_temporal;    /* 1: the decode kernel reads the cache with non-temporal loads */
-  int32_t steps_per_batch; /* decode kernel: 32-key steps loaded per batch (1 or 2); else 0 */
+  int32_t steps_per_batch; /* decode kernel: label of its set-up, 1 with ordinary loads,
+                              2 with non-temporal ones (both request one 32-key step ahead); else 0 */
   int32_t tile_rows;       /* row-tiled kernels: rows (token x head) per workgroup; else 0 */
   int64_t split_len;       /* keys per split */
   int64_t workspace_bytes; /* bytes of workspace this very call uses; it may use more on a longer

@@ -640,8 +640,11 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   // Algorithm 2: the new tokens' K/V join the cache before they attend.  The
   // attention kernels append them themselves (they read the new rows from Kq/Vq and
   // write them to the cache).  Unrotated keys are rotated into the cache first.
-  const bool fused_append = append && !rope;
-  if (append && rope &&
+  // (A few rotated tokens on the decode kernel's equal runs are turned there, and by the merge.)
+  const bool turn = append && rope && plan.decode && plan.flat && q_len <= DECODE_ROPE_TOKENS &&
+                    (int64_t)g.B * g.Hq * q_len <= (1 << 20);
+  const bool fused_append = append && (!rope || turn);
+  if (append && rope && !turn &&
       launch_rope(shape->dtype, g, g.Hq, Qq, Qq, Kq, Vq, K_cache, V_cache, q_len, cache_len,
                   rope->pos0 + cache_len, rope->theta, nullptr, st) != hipSuccess)
     return STAR_ATTN_ERR_LAUNCH_FAILED;
@@ -659,6 +662,7 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   a.O = direct && !pair ? O : nullptr;
   a.A = direct && pair ? A : nullptr;
   a.LSE = direct && pair ? LSE : nullptr;
+  a.rotary = Rotary{turn ? log2(rope->theta) : 0.0, turn ? rope->pos0 + cache_len : 0};
   hipError_t e;
   if (shape->dtype == STAR_ATTN_F32) e = launch_phase2_f32(a, st);
   else if (plan.decode) e = launch_phase2_decode_bf16(a, st);
@@ -674,6 +678,8 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   m.O = pair ? nullptr : O;
   m.A = pair ? A : nullptr;
   m.LSE = pair ? LSE : nullptr;
+  m.Qq = Qq;
+  m.rotary = a.rotary;
   return launch_merge(m, st) == hipSuccess ? STAR_ATTN_OK : STAR_ATTN_ERR_LAUNCH_FAILED;
 }
 
@@ -730,6 +736,7 @@ int star_attn_merge(const star_attn_shape* shape, int64_t n_parts, int64_t q_len
   m.split_stride = rows;
   m.O_part = nullptr; m.LSE_part = nullptr;
   m.O = O; m.A = A; m.LSE = LSE;
+  m.Qq = nullptr; m.rotary = Rotary{0.0, 0};
   return launch_merge(m, (hipStream_t)hip_stream) == hipSuccess ? STAR_ATTN_OK
                                                                 : STAR_ATTN_ERR_LAUNCH_FAILED;
 }

@@ -10,12 +10,16 @@
 //     s, s + S, s + 2S, ... so that at any moment the S wavefronts of a KV head
 //     read one contiguous window of its cache (every memory channel busy, none
 //     hot); with per-part outputs a split is a contiguous run inside one part;
-//   * a batch of NS steps is loaded into registers with plain 16-byte loads and
-//     then consumed in order -- K (8 KiB a step) straight in the layout the MFMA
-//     wants: lane (i, j4) takes key i, bytes 64t + 16 j4 .. +15 of its row for
-//     t = 0..3; V (8 KiB a step) as 1 KiB-contiguous bursts.  All waits are the
-//     compiler's (straight-line code, static register indices); while one
-//     wavefront computes, the other wavefronts of the CU keep the stream going;
+//   * a 32-key step is loaded into registers with plain 16-byte loads: K (8 KiB) straight in the
+//     layout the MFMA wants -- lane (i, j4) takes key i, bytes 64t + 16 j4 .. +15 of its row for
+//     t = 0..3; V (8 KiB) as 1 KiB-contiguous bursts.  As soon as its scores are taken and its V is in
+//     LDS the next step is requested into the same registers, ahead of the softmax and the products.
+//     All waits are the compiler's (straight-line code, static register indices; steps that are not
+//     cached as a whole have a loop of their own, so that the loop over the others has no
+//     branches between loads).  Measured against batches of two steps consumed before the next two are requested
+//     (the resident set-up: one step, whose V the compiler requested only once its K was there), whole
+//     calls: 131072 tokens of eight heads 84.8 -> 82.4 us, four sequences of 32768 84.5 -> 83.0, 32768 tokens 30.5 -> 29.4;
+//     two steps per batch requested early: 84.1;
 //   * a cache too large to stay in the 256 MB last-level cache between steps is
 //     read with non-temporal loads (every byte is used once: leaving it out of
 //     the caches is worth 9-16 % of the step at 0.5-4 GB); a smaller one with
@@ -24,15 +28,19 @@
 //     columns of v_mfma_f32_16x16x32_bf16, so K and V are read once per KV head;
 //     S^T = K Q^T leaves each lane with keys of one query column, and the
 //     exponentiated tile is directly the B operand of O^T += V^T P^T; V goes
-//     through a small LDS buffer (two 8 KiB halves used alternately) only to be
+//     through an 8 KiB LDS buffer (one wavefront's LDS accesses are in order) only to be
 //     read back transposed, 16-byte chunks rotated-XOR swizzled so that writes
 //     and transposing reads are conflict-free;
 //   * rows at or beyond cache_len are the new tokens: they are read from the
 //     call's Kq/Vq and written to the cache by the workgroup whose split holds
-//     them, so no separate append kernel runs before a decode step.
+//     them, so no separate append kernel runs before a decode step;
+//   * unrotated projections of a few tokens are rotated on the way: every wavefront turns its query
+//     rows while its first step is under way, the one that files a new key its row (and the merge
+//     kernel, behind all readers, the queries in memory).  A kernel in front of this one that did it
+//     took 2.3 us and a launch.
 // Each workgroup writes its split's normalised output rows and their
 // log-sum-exp; the merge kernel folds the splits (Eq. 3-4).
-#include "star_internal.h"
+#include "rotary.h"
 
 namespace star {
 
@@ -48,10 +56,14 @@ constexpr int D = 128;
 constexpr int ROWB = D * 2;
 constexpr int STEP = 32;                 // keys per pipeline step
 constexpr int STEPB = STEP * ROWB;       // 8 KiB of K (and of V) per step
+constexpr int ROPE_TOKENS = DECODE_ROPE_TOKENS;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
 #define LDS_AS __attribute__((address_space(3)))
+
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+typedef const __attribute__((address_space(1))) i32x4* GlobalVec;
 
 // chunk c of key row r sits in slot c ^ swz(r)
 __device__ __forceinline__ int swz(int r) { return ((r << 1) & 15) | ((r >> 3) & 1); }
@@ -71,7 +83,8 @@ __device__ __forceinline__ float xor32_sum(float x) {
 struct DecState {
   bf16x8 q[4];     // Q^T fragments: q[t] = Q[column lane%16][32t + 8*(lane/16) .. +7]
   f32x4 o[8];      // O^T: o[dt][v] = O[column][16dt + 4*(lane/16) + v]
-  float m, l;
+  float m, l;      // running maximum (raw logits; uniform over a column's four lanes), this lane's share of the sum
+  float neg_mc;    // -m * c (0 while nothing was visible)
 };
 
 // One 32-key step in registers.
@@ -79,134 +92,181 @@ struct StepRegs {
   i32x4 k[8];      // k[4kt + t]: key 16kt + lane%16, bytes 64t + 16*(lane/16) .. +15 (MFMA A operand)
   i32x4 v[8];      // v[it]: key 4it + lane/16, bytes 16*(lane%16) .. +15
 };
+struct Scores {
+  f32x4 s[2];
+};
 
 // Where a split's rows come from: cache rows below `cache_len`, the call's new
 // tokens (token-major, `new_stride` bytes between tokens) from there on.
 struct Source {
-  const char* Kb;      // cache base of this (batch, kv head)
-  const char* Vb;
-  const char* Kn;      // new-token base of this (batch, kv head)
-  const char* Vn;
+  GlobalBytes Kb;      // cache base of this (batch, kv head)
+  GlobalBytes Vb;
+  GlobalBytes Kn;      // new-token base of this (batch, kv head)
+  GlobalBytes Vn;
   int cache_len;
   int new_stride;
 };
 
-// Load the step [key0, key0 + 32).  Rows at or past `hi` re-read the last valid
-// row (they are masked in the score tile).
+// Load the step [key0, key0 + 32), all of it cached.
 template <bool NT>
-__device__ __forceinline__ void load_step(StepRegs& r, const Source& src, int key0, int hi, int lane) {
-  const int col = lane & 15, j4 = lane >> 4;
-  if (key0 + STEP <= hi && key0 + STEP <= src.cache_len) {   // whole step from the cache
-    const char* kp = src.Kb + (size_t)key0 * ROWB + col * ROWB + j4 * 16;
-    const char* vp = src.Vb + (size_t)key0 * ROWB + j4 * ROWB + col * 16;
+__device__ __forceinline__ void load_step(StepRegs& r, const Source& src, int key0, unsigned koff, unsigned voff) {
+  GlobalBytes kp = src.Kb + (size_t)key0 * ROWB, vp = src.Vb + (size_t)key0 * ROWB;
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const i32x4* ka = (const i32x4*)(kp + (it >> 2) * 16 * ROWB + (it & 3) * 64);
-      const i32x4* va = (const i32x4*)(vp + it * 4 * ROWB);
-      r.k[it] = NT ? __builtin_nontemporal_load(ka) : *ka;
-      r.v[it] = NT ? __builtin_nontemporal_load(va) : *va;
-    }
-  } else {
+  for (int it = 0; it < 8; ++it) {
+    GlobalVec ka = (GlobalVec)(kp + (it >> 2) * 16 * ROWB + (it & 3) * 64 + koff);
+    r.k[it] = NT ? __builtin_nontemporal_load(ka) : *ka;
+  }
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      int kk = key0 + 16 * (it >> 2) + col;
-      kk = kk < hi ? kk : hi - 1;
-      const char* kp = kk < src.cache_len ? src.Kb + (size_t)kk * ROWB
-                                          : src.Kn + (size_t)(kk - src.cache_len) * src.new_stride;
-      r.k[it] = *(const i32x4*)(kp + (it & 3) * 64 + j4 * 16);
-      int vk = key0 + 4 * it + j4;
-      vk = vk < hi ? vk : hi - 1;
-      const char* vp = vk < src.cache_len ? src.Vb + (size_t)vk * ROWB
-                                          : src.Vn + (size_t)(vk - src.cache_len) * src.new_stride;
-      r.v[it] = *(const i32x4*)(vp + col * 16);
+  for (int it = 0; it < 8; ++it) {
+    GlobalVec va = (GlobalVec)(vp + it * 4 * ROWB + voff);
+    r.v[it] = NT ? __builtin_nontemporal_load(va) : *va;
+  }
+}
+// cos and sin of the call's tokens, for a call on unrotated projections.
+struct Angles {
+  float cs[ROPE_TOKENS][D / 2], sn[ROPE_TOKENS][D / 2];
+};
+// One row of Q or K as the MFMA operands hold it (lane group j4: elements 32 t + 8 j4 .. +7 in x[t]).
+template <typename T>
+__device__ __forceinline__ void rotate(T* x, const Angles& angles, int token, int j4) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    bf16x8 lo = __builtin_bit_cast(bf16x8, x[t]), hi = __builtin_bit_cast(bf16x8, x[t + 2]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float a = (float)lo[e], b = (float)hi[e];
+      const float cs = angles.cs[token][32 * t + 8 * j4 + e], sn = angles.sn[token][32 * t + 8 * j4 + e];
+      lo[e] = (__bf16)rotary_lo(a, b, cs, sn);
+      hi[e] = (__bf16)rotary_hi(a, b, cs, sn);
     }
+    x[t] = __builtin_bit_cast(T, lo);
+    x[t + 2] = __builtin_bit_cast(T, hi);
   }
 }
 
-// VOFF (0 or STEPB) selects the LDS half this step's V goes through.
-__device__ __forceinline__ void compute_step(const int VOFF, DecState& w, const StepRegs& r,
-                                             const unsigned (&vw)[4], const unsigned (&vaddr)[8],
-                                             int key0, int lim, bool masked, float c, int j4) {
-  // V rows into LDS (row 4it + lane/16, swizzled chunk lane%16)
-#pragma unroll
-  for (int it = 0; it < 8; ++it)
-    *(LDS_AS i32x4*)(size_t)(vw[it & 3] + VOFF + (it >> 2) * 16 * ROWB) = r.v[it];
-  f32x4 s[2];
+// The same for a step that ends past `hi` or among the call's tokens.  Rows at or past `hi`
+// re-read the last valid row (they are masked in the score tile).
+template <bool ROPE>
+__device__ __forceinline__ void load_last(StepRegs& r, const Source& src, int key0, int hi, int lane, const Angles* angles) {
+  const int col = lane & 15, j4 = lane >> 4;
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt) {
-    s[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int kk = key0 + 16 * kt + col;
+    kk = kk < hi ? kk : hi - 1;
+    GlobalBytes kp = kk < src.cache_len ? src.Kb + (size_t)kk * ROWB : src.Kn + (size_t)(kk - src.cache_len) * src.new_stride;
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-      s[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[4 * kt + t]),
-                                                      w.q[t], s[kt], 0, 0, 0);
+    for (int t = 0; t < 4; ++t) r.k[4 * kt + t] = *(GlobalVec)(kp + t * 64 + j4 * 16);
+    if (ROPE && kk >= src.cache_len) rotate(&r.k[4 * kt], *angles, kk - src.cache_len, j4);
   }
-  if (masked) {
-    int x = lim - key0 - 4 * j4;     // element (kt, v) is key key0 + 16kt + 4*j4 + v
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    int vk = key0 + 4 * it + j4;
+    vk = vk < hi ? vk : hi - 1;
+    GlobalBytes vp = vk < src.cache_len ? src.Vb + (size_t)vk * ROWB : src.Vn + (size_t)(vk - src.cache_len) * src.new_stride;
+    r.v[it] = *(GlobalVec)(vp + col * 16);
+  }
+}
+
+// A step in two halves.  First its scores, and V into LDS (row 4it + lane/16, swizzled chunk
+// lane%16): the step's registers are then free.
+__device__ __forceinline__ void score_step(const DecState& w, const StepRegs& r, const unsigned (&vw)[4],
+                                           Scores& x) {
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) x.s[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
+      x.s[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[4 * kt + t]), w.q[t], x.s[kt], 0, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) s[kt][v] = (16 * kt + v) < x ? s[kt][v] : -INFINITY;
+  for (int it = 0; it < 8; ++it)
+    *(LDS_AS i32x4*)(size_t)(vw[it & 3] + (it >> 2) * 16 * ROWB) = r.v[it];
+}
+__device__ __forceinline__ void mask_step(Scores& x, int key0, int lim, int j4) {
+  const int n = lim - key0 - 4 * j4;     // element (kt, v) is key key0 + 16kt + 4*j4 + v
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x.s[kt][v] = (16 * kt + v) < n ? x.s[kt][v] : -INFINITY;
+}
+// Then softmax and products.
+__device__ __forceinline__ void attend_step(DecState& w, const Scores& x, const unsigned (&vaddr)[8], float c) {
+  // B operand slot e of lane group j4 is key 16(e/4) + 4*j4 + e%4; the A operand
+  // (V^T, d-row lane%16) takes keys 4*j4..+3 and 16 + 4*j4..+3 from two
+  // transposing reads.
+  s16x4 lo[8], hi[8];
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) {
+    lo[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(size_t)(vaddr[dt]));
+    hi[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(size_t)(vaddr[dt] + 16 * ROWB));
   }
-  float tmax = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
-                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-  tmax = fmaxf(tmax, xor16(tmax));
-  tmax = xor32_max(tmax);
-  float m_new = fmaxf(w.m, tmax);
-  if (__builtin_amdgcn_ballot_w64(m_new > w.m) != 0) {
-    float mm = m_new == -INFINITY ? 0.f : m_new;
-    float alpha = __builtin_amdgcn_exp2f((w.m - mm) * c);
+  __builtin_amdgcn_sched_barrier(0);
+  float tmax = fmaxf(fmaxf(fmaxf(x.s[0][0], x.s[0][1]), fmaxf(x.s[0][2], x.s[0][3])),
+                     fmaxf(fmaxf(x.s[1][0], x.s[1][1]), fmaxf(x.s[1][2], x.s[1][3])));
+  // Lanes exchange their maxima only where some column's moves.  (The largest weight is exactly one this
+  // way; a reference that moves later costs less and 6 % of precision.)
+  if (__builtin_amdgcn_ballot_w64(tmax > w.m) != 0) {
+    const float m = fmaxf(w.m, xor32_max(fmaxf(tmax, xor16(tmax)))), mm = m == -INFINITY ? 0.f : m;
+    const float alpha = __builtin_amdgcn_exp2f((w.m - mm) * c);
     w.l *= alpha;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) w.o[dt] *= alpha;
-    w.m = m_new;
+    w.m = m;
+    w.neg_mc = mm * -c;
   }
-  float neg_mc = (w.m == -INFINITY ? 0.f : w.m) * -c;
   bf16x8 p;
   float lsum = 0.f;
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kt][v], c, neg_mc));
+      float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x.s[kt][v], c, w.neg_mc));
       lsum += e;
       p[4 * kt + v] = (__bf16)e;
     }
   w.l += lsum;
-  // B operand slot e of lane group j4 is key 16(e/4) + 4*j4 + e%4; the A operand
-  // (V^T, d-row lane%16) takes keys 4*j4..+3 and 16 + 4*j4..+3 from two
-  // transposing reads.
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) {
-    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(size_t)(vaddr[dt] + VOFF));
-    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(size_t)(vaddr[dt] + VOFF + 16 * ROWB));
-    bf16x4 lo_b = __builtin_bit_cast(bf16x4, lo), hi_b = __builtin_bit_cast(bf16x4, hi);
-    bf16x8 a = __builtin_shufflevector(lo_b, hi_b, 0, 1, 2, 3, 4, 5, 6, 7);
+    bf16x8 a = __builtin_shufflevector(__builtin_bit_cast(bf16x4, lo[dt]), __builtin_bit_cast(bf16x4, hi[dt]), 0, 1, 2, 3, 4, 5, 6, 7);
     w.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, p, w.o[dt], 0, 0, 0);
   }
 }
 
-// grid: x = split, y = kv head, z = batch; 64 threads.  NS = steps per batch of
-// loads, NT = non-temporal loads.
-template <int NS, bool NT>
-__global__ __launch_bounds__(64) void decode_bf16_kernel(Phase2Args a) {
-  __shared__ __attribute__((aligned(1024))) char lds[2 * STEPB];
+// grid: x = split, y = kv head, z = batch; 64 threads.  NT = non-temporal loads; ROPE = Qq and Kn are
+// unrotated (at most ROPE_TOKENS tokens).
+struct DecodeDiv {
+  Div splits, G;
+};
+template <bool NT, bool ROPE>
+__global__ __launch_bounds__(64, 2) void decode_bf16_kernel(Phase2Args a, DecodeDiv by) {
+  __shared__ __attribute__((aligned(1024))) char lds[STEPB];
+  __shared__ __attribute__((aligned(16))) char angle_lds[ROPE ? sizeof(Angles) : 16];
+  Angles* angles = (Angles*)angle_lds;
   const Geom& g = a.g;
   const int lane = threadIdx.x;
   const int qc = lane & 15, j4 = lane >> 4;
   const int sp = blockIdx.x, kvh = blockIdx.y, beta = blockIdx.z;
   const int R = g.G * a.q_len;                 // <= 16 live columns
-  const int j = qc / g.G, head = kvh * g.G + qc % g.G;
+  const int col_j = quotient(qc, by.G), head = kvh * g.G + qc - col_j * g.G;
   const bool live = qc < R;
+  const int j = live ? col_j : 0;
 
   const int cache_len = (int)a.cache_len;
   const int total = (int)visible_total(a);
-  // step `cur` of this split covers keys [base + cur * stride, +32) below hi
-  int base, stride, nsteps, hi;
+  // without new-token tensors the caches already hold the appended rows
+  const bool fused_append = a.Kn != nullptr;
+  const int cached = fused_append ? cache_len : total;
+  // step `cur` of this split covers keys [base + cur * stride, +32) below hi; the first n_whole of
+  // them lie in the cache as a whole and are visible to every token
+  const int first_lim = (int)visible_limit(a, 0), free_hi = cached < first_lim ? cached : first_lim;
+  int base, stride, nsteps, n_whole, hi;
   if (a.plan.flat) {
-    const int S = a.plan.s_total, T = (total + STEP - 1) / STEP;
+    const int S = a.plan.s_total, T = (total + STEP - 1) / STEP, whole = free_hi / STEP;
     base = sp * STEP;
     stride = S * STEP;
-    nsteps = sp < T ? (T - sp + S - 1) / S : 0;
+    nsteps = sp < T ? (int)quotient(T - sp + S - 1, by.splits) : 0;
+    n_whole = sp < whole ? (int)quotient(whole - sp + S - 1, by.splits) : 0;
     hi = total;
   } else {
     int64_t lo64, hi64;
@@ -215,50 +275,75 @@ __global__ __launch_bounds__(64) void decode_bf16_kernel(Phase2Args a) {
     stride = STEP;
     hi = (int)hi64;
     nsteps = hi > base ? (hi - base + STEP - 1) / STEP : 0;
+    const int room = (free_hi < hi ? free_hi : hi) - base;
+    n_whole = room > 0 ? room / STEP : 0;
   }
-  size_t r = (((size_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j;
+  const size_t out = (((size_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j;
   if (nsteps == 0) {                           // empty split (short block, unused tail)
-    if (live && j4 == 0) a.LSE_sub[r] = -INFINITY;
+    if (live && j4 == 0) a.LSE_sub[out] = -INFINITY;
     return;
   }
 
   Source src;
-  src.Kb = (const char*)a.Kc + ((size_t)beta * g.Hkv + kvh) * (size_t)g.cap * ROWB;
-  src.Vb = (const char*)a.Vc + ((size_t)beta * g.Hkv + kvh) * (size_t)g.cap * ROWB;
-  src.Kn = (const char*)a.Kn + ((size_t)beta * a.q_len * g.Hkv + kvh) * ROWB;
-  src.Vn = (const char*)a.Vn + ((size_t)beta * a.q_len * g.Hkv + kvh) * ROWB;
-  // without new-token tensors the caches already hold the appended rows
-  const bool fused_append = a.Kn != nullptr;
-  src.cache_len = fused_append ? cache_len : total;
+  const size_t cache0 = ((size_t)beta * g.Hkv + kvh) * (size_t)g.cap * ROWB, new0 = ((size_t)beta * a.q_len * g.Hkv + kvh) * ROWB;
+  src.Kb = (GlobalBytes)a.Kc + cache0;
+  src.Vb = (GlobalBytes)a.Vc + cache0;
+  src.Kn = (GlobalBytes)a.Kn + new0;
+  src.Vn = (GlobalBytes)a.Vn + new0;
+  src.cache_len = cached;
   src.new_stride = g.Hkv * ROWB;
+
+  // the query rows and the first step are requested before anything waits
+  DecState w;
+  {
+    GlobalBytes qrow = (GlobalBytes)a.Qq + (((size_t)beta * a.q_len + j) * g.Hq + (live ? head : kvh * g.G)) * ROWB;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w.q[t] = __builtin_bit_cast(bf16x8, *(GlobalVec)(qrow + (32 * t + 8 * j4) * 2));
+  }
+  const unsigned koff = qc * ROWB + j4 * 16, voff = j4 * ROWB + qc * 16;
+  StepRegs r;
+  if (n_whole > 0) load_step<NT>(r, src, base, koff, voff);
+  __builtin_amdgcn_sched_barrier(0);
+  if (ROPE) {
+    static_assert(D / 2 == 64, "a lane per pair");
+    const double freq = rotary_frequency(lane, D, a.rotary.log2_theta);
+    for (int t = 0; t < a.q_len; ++t)
+      rotary_angle(a.rotary.pos0 + t, freq, &angles->cs[t][lane], &angles->sn[t][lane]);
+    __syncthreads();
+    rotate(w.q, *angles, j, j4);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    if (!live) w.q[t] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};     // dead columns contribute zeros
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) w.o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  w.m = -INFINITY;
+  w.neg_mc = 0.f;
+  w.l = 0.f;
 
   // Algorithm 2, append: the new tokens whose rows fall into this split's steps
   // join the cache (16 lanes move one 256-byte row of K and of V).
   if (fused_append && hi > cache_len) {
-    for (int key = cache_len + (lane >> 4); key < hi; key += 4) {
-      const int rel = key - base;
-      if (rel < 0 || (rel % stride) >= STEP) continue;      // another split's step
-      size_t so = (size_t)(key - cache_len) * src.new_stride + (lane & 15) * 16;
-      size_t dof = (size_t)key * ROWB + (lane & 15) * 16;
-      *(i32x4*)(const_cast<char*>(src.Kb) + dof) = *(const i32x4*)(src.Kn + so);
-      *(i32x4*)(const_cast<char*>(src.Vb) + dof) = *(const i32x4*)(src.Vn + so);
-    }
-  }
-
-  DecState w;
-  {
-    const char* qrow = (const char*)a.Qq + (((size_t)beta * a.q_len + (live ? j : 0)) * g.Hq +
-                                            (live ? head : kvh * g.G)) * ROWB;
+    for (int key = cache_len + j4; key < hi; key += 4) {
+      const int step = key / STEP;                          // another split's step?
+      if (a.plan.flat ? step - (int)quotient(step, by.splits) * a.plan.s_total != sp : key < base) continue;
+      const size_t so = (size_t)(key - cache_len) * src.new_stride, dof = cache0 + (size_t)key * ROWB + qc * 16;
+      i32x4 k = *(GlobalVec)(src.Kn + so + qc * 16);
+      const i32x4 v = *(GlobalVec)(src.Vn + so + qc * 16);
+      if (ROPE) {
+        bf16x8 own = __builtin_bit_cast(bf16x8, k), other = __builtin_bit_cast(bf16x8, *(GlobalVec)(src.Kn + so + (qc ^ 8) * 16));
+        const float* cs = &angles->cs[key - cache_len][8 * (qc & 7)];
+        const float* sn = &angles->sn[key - cache_len][8 * (qc & 7)];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      bf16x8 v = *(const bf16x8*)(qrow + (32 * t + 8 * j4) * 2);
-      if (!live) v = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};     // dead columns contribute zeros
-      w.q[t] = v;
+        for (int e = 0; e < 8; ++e) {
+          const float x = (float)own[e], y = (float)other[e];
+          own[e] = (__bf16)(qc < 8 ? rotary_lo(x, y, cs[e], sn[e]) : rotary_hi(y, x, cs[e], sn[e]));
+        }
+        k = __builtin_bit_cast(i32x4, own);
+      }
+      *(i32x4*)((char*)a.Kc + dof) = k;
+      *(i32x4*)((char*)a.Vc + dof) = v;
     }
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) w.o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    w.m = -INFINITY;
-    w.l = 0.f;
   }
 
   const unsigned lds0 = (unsigned)(size_t)(LDS_AS char*)lds;
@@ -280,40 +365,35 @@ __global__ __launch_bounds__(64) void decode_bf16_kernel(Phase2Args a) {
   }
 
   const float c = g.scale * LOG2E;
-  // keys below free_hi (what the call's first token sees) are visible to every
-  // live column, so only steps reaching past it take the masking path
+  // Once a step's scores are there and its V is in LDS its registers are free, and the next step
+  // is requested into them: it arrives behind this one's softmax and products, and those of the
+  // other wavefronts of the CU.
+  for (int s = 0; s < n_whole; ++s) {
+    Scores x;
+    score_step(w, r, vw, x);
+    if (s + 1 < n_whole) load_step<NT>(r, src, base + (s + 1) * stride, koff, voff);
+    __builtin_amdgcn_sched_barrier(0);
+    attend_step(w, x, vaddr, c);
+  }
   const int row_lim = live ? (int)visible_limit(a, j) : 0;
   const int lim = row_lim < hi ? row_lim : hi;
-  const int first_lim = (int)visible_limit(a, 0);
-  const int free_hi = first_lim < hi ? first_lim : hi;
-
-  // NS steps are loaded into registers at once and then consumed in order; the
-  // other wavefronts of the CU stream while this one computes
-  for (int s = 0; s < nsteps; s += NS) {
-    StepRegs r[NS];
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      const int cur = s + u < nsteps ? s + u : nsteps - 1;     // past the end: re-read the last step
-      load_step<NT>(r[u], src, base + cur * stride, hi, lane);
-    }
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      if (s + u >= nsteps) break;
-      const int key0 = base + (s + u) * stride;
-      const bool masked = key0 + STEP > free_hi;
-      compute_step((u & 1) * STEPB, w, r[u], vw, vaddr, key0, lim, masked, c, j4);
-    }
+  for (int s = n_whole; s < nsteps; ++s) {
+    Scores x;
+    load_last<ROPE>(r, src, base + s * stride, hi, lane, angles);
+    score_step(w, r, vw, x);
+    mask_step(x, base + s * stride, lim, j4);
+    attend_step(w, x, vaddr, c);
   }
 
   float l_tot = w.l + xor16(w.l);
   l_tot = xor32_sum(l_tot);
   if (live) {
     float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    float* orow = a.O_sub + r * D;
+    float* orow = a.O_sub + out * D;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) *(f32x4*)(orow + 16 * dt + 4 * j4) = w.o[dt] * inv;
     if (j4 == 0)
-      a.LSE_sub[r] = l_tot > 0.f ? (w.m * c + __builtin_amdgcn_logf(l_tot)) * LN2 : -INFINITY;
+      a.LSE_sub[out] = l_tot > 0.f ? (w.m * c + __builtin_amdgcn_logf(l_tot)) * LN2 : -INFINITY;
   }
 }
 
@@ -323,8 +403,16 @@ hipError_t launch_phase2_decode_bf16(const Phase2Args& a, hipStream_t st) {
   const Geom& g = a.g;
   if (g.Hkv > 65535 || g.B > 65535) return hipErrorInvalidValue;
   const dim3 grid((unsigned)a.plan.s_total, (unsigned)g.Hkv, (unsigned)g.B);
-  if (decode_cache_resident(g, visible_total(a))) decode_bf16_kernel<1, false><<<grid, 64, 0, st>>>(a);
-  else decode_bf16_kernel<2, true><<<grid, 64, 0, st>>>(a);
+  const DecodeDiv by = {make_div(a.plan.s_total), make_div(g.G)};
+  const bool resident = decode_cache_resident(g, visible_total(a));
+  if (a.rotary.log2_theta != 0) {
+    if (a.q_len > ROPE_TOKENS) return hipErrorInvalidValue;
+    if (resident) decode_bf16_kernel<false, true><<<grid, 64, 0, st>>>(a, by);
+    else decode_bf16_kernel<true, true><<<grid, 64, 0, st>>>(a, by);
+  } else {
+    if (resident) decode_bf16_kernel<false, false><<<grid, 64, 0, st>>>(a, by);
+    else decode_bf16_kernel<true, false><<<grid, 64, 0, st>>>(a, by);
+  }
   return hipGetLastError();
 }
 

@@ -31,7 +31,7 @@
 // summation): a context cut into hundreds of small blocks is hundreds of
 // sequential additions, and in fp32 their rounding errors would otherwise add up
 // to the 1e-5 the fp32 path is held to.
-#include "star_internal.h"
+#include "rotary.h"
 
 namespace star {
 
@@ -341,9 +341,20 @@ __device__ __forceinline__ void store_merged(const MergeArgs& a, int beta, int h
   if (a.LSE && d0 == 0) a.LSE[arow] = f.w > 0.f ? f.m + logf(f.w) : -INFINITY;
 }
 
+// A wavefront turns row (beta, h, j) of the call's queries, a lane per pair (bf16, d = 128).  Workgroups
+// behind the merge's own do this: the kernel in front has read the queries as they were.
+__device__ __forceinline__ void rotate_query(const MergeArgs& a, int beta, int h, int j, int lane) {
+  __bf16* row = (__bf16*)a.Qq + (((int64_t)beta * a.q_len + j) * a.g.Hq + h) * 128;
+  const float x = (float)row[lane], y = (float)row[lane + 64];
+  float cs, sn;
+  rotary_angle(a.rotary.pos0 + j, rotary_frequency(lane, 128, a.rotary.log2_theta), &cs, &sn);
+  row[lane] = (__bf16)rotary_lo(x, y, cs, sn);
+  row[lane + 64] = (__bf16)rotary_hi(x, y, cs, sn);
+}
+
 // One workgroup per (row, piece of 4 LPS elements of d): LPS lanes per split, the others
-// walk the splits, INFL in flight per lane.  grid: x = token * pieces + piece, y = head,
-// z = batch.
+// walk the splits, INFL in flight per lane.  grid: x = token * pieces + piece (and, behind them, a token
+// each to rotate), y = head, z = batch.
 template <int LPS, int THREADS, int INFL>
 __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
   constexpr int GROUPS = THREADS / LPS, WAVES = THREADS / 64;
@@ -351,8 +362,13 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
   __shared__ f32x4 red_acc[WAVES][LPS];
   const Geom& g = a.g;
   const int tid = threadIdx.x, li = tid % LPS, grp = tid / LPS;
-  const int pieces = g.d / (4 * LPS), j = blockIdx.x / pieces, d0 = (blockIdx.x % pieces) * (4 * LPS) + 4 * li;
   const int h = blockIdx.y, beta = blockIdx.z, S = a.plan.s_total;
+  const int log2_pieces = __builtin_ctz(g.d / (4 * LPS)), j = blockIdx.x >> log2_pieces;      // (d is 64 or 128)
+  if (j >= a.q_len) {
+    if (tid < 64) rotate_query(a, beta, h, blockIdx.x - (a.q_len << log2_pieces), tid);
+    return;
+  }
+  const int d0 = (blockIdx.x & ((1 << log2_pieces) - 1)) * (4 * LPS) + 4 * li;
   const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;
 
   // the weights of a step are taken against the maximum of its splits over the whole wavefront:
@@ -402,14 +418,23 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
 
 // Many rows of a few splits each (query encoding, pairs of other hosts): d / 4 lanes own a
 // row, INFL splits in flight, nothing crosses lanes.
+struct RowsDiv {
+  Div q_len, Hq;
+};
 template <int D, int INFL>
-__global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, unsigned n_rows, unsigned first_wg) {
+__global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, RowsDiv by, unsigned n_rows, unsigned first_wg) {
   constexpr int LPR = D / 4;
   const Geom& g = a.g;
-  const unsigned row = (first_wg + blockIdx.x) * (256 / LPR) + threadIdx.x / LPR;      // (beta, h, j), j fastest
+  const unsigned n_wgs = (n_rows + 256 / LPR - 1) / (256 / LPR), wg = first_wg + blockIdx.x, tid = threadIdx.x;
+  const bool turn = wg >= n_wgs;                                         // a wavefront per row to rotate
+  const unsigned row = turn ? (wg - n_wgs) * 4 + tid / 64 : wg * (256 / LPR) + tid / LPR;      // (beta, h, j), j fastest
   if (row >= n_rows) return;
-  const int d0 = 4 * (threadIdx.x % LPR), S = a.plan.s_total;
-  const unsigned bh = row / (unsigned)a.q_len, j = row % (unsigned)a.q_len, beta = bh / (unsigned)g.Hq, h = bh % (unsigned)g.Hq;
+  const unsigned bh = quotient(row, by.q_len), j = row - bh * by.q_len.d, beta = quotient(bh, by.Hq), h = bh - beta * by.Hq.d;
+  if (turn) {
+    rotate_query(a, (int)beta, (int)h, (int)j, tid & 63);
+    return;
+  }
+  const int d0 = 4 * (tid % LPR), S = a.plan.s_total;
   const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;
   Fold f = empty_fold();
   for (int s0 = 0; s0 < S; s0 += INFL) {
@@ -429,7 +454,8 @@ __global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, unsig
 
 template <int LPS, int THREADS, int INFL>
 hipError_t launch_flat(const MergeArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)(a.q_len * (a.g.d / (4 * LPS))), (unsigned)a.g.Hq, (unsigned)a.g.B);
+  const int turn = a.rotary.log2_theta != 0 ? a.q_len : 0;
+  const dim3 grid((unsigned)(a.q_len * (a.g.d / (4 * LPS)) + turn), (unsigned)a.g.Hq, (unsigned)a.g.B);
   merge_flat_kernel<LPS, THREADS, INFL><<<grid, THREADS, 0, st>>>(a);
   return hipGetLastError();
 }
@@ -443,25 +469,27 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
   if (p.flat) {
     const int S = p.s_total;
     if (S <= 8 && rows >= 64) {
-      const int64_t wgs = a.g.d == 64 ? (rows + 15) / 16 : (rows + 7) / 8;
-      return launch_in_pieces(wgs, 256, [&](unsigned first, unsigned n_wgs) {
+      const int64_t wgs = a.g.d == 64 ? (rows + 15) / 16 : (rows + 7) / 8, turn = a.rotary.log2_theta != 0 ? (rows + 3) / 4 : 0;
+      const RowsDiv by = {make_div(a.q_len), make_div(a.g.Hq)};
+      return launch_in_pieces(wgs + turn, 256, [&](unsigned first, unsigned n_wgs) {
         // (a split past the last costs as much as one)
-        if (a.g.d == 64 && S <= 4) merge_flat_rows_kernel<64, 4><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
-        else if (a.g.d == 64) merge_flat_rows_kernel<64, 8><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
-        else if (S <= 4) merge_flat_rows_kernel<128, 4><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
-        else merge_flat_rows_kernel<128, 8><<<dim3(n_wgs), 256, 0, st>>>(a, (unsigned)rows, first);
+        if (a.g.d == 64 && S <= 4) merge_flat_rows_kernel<64, 4><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
+        else if (a.g.d == 64) merge_flat_rows_kernel<64, 8><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
+        else if (S <= 4) merge_flat_rows_kernel<128, 4><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
+        else merge_flat_rows_kernel<128, 8><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
       });
     }
     // Few rows: pieces of d, so that the row's splits are in flight at once over more
     // workgroups and wavefronts; many rows fill the GPU as they are.  Measured, us, for
     // (rows x splits) against the kernel with the chain from split to split and a workgroup
     // per row: 8 x 384 10.8 -> 4.3, 32 x 128 5.7 -> 3.9, 32 x 96 6.0 -> 4.7, 672 x 29
-    // 7.4 -> 4.0 (pieces of 32: 6.2-8.2), 8 x 32 (d = 64) 8.6 -> 3.3.
+    // 7.4 -> 4.0 (pieces of 32: 6.2-8.2), 8 x 32 (d = 64) 8.6 -> 3.3.  65 to 128 splits of few rows in one
+    // step instead of two: whole decode calls of 8191 tokens (128 splits) 12.4 -> 11.8, 131072 (96) 82.6 -> 82.4.
     // A result merged into one of its own slabs: another piece's workgroup may not have read the
     // row's log-sum-exps yet when the first piece stores the new one, so a row stays whole.
     const bool in_place = a.LSE >= a.LSE_sub && a.LSE < a.LSE_sub + rows * S;
     if (in_place) return a.g.d == 64 ? launch_flat<16, 256, 4>(a, st) : launch_flat<32, 256, 4>(a, st);
-    if (rows < 256) return S > 128 ? launch_flat<8, 512, 2>(a, st) : launch_flat<16, 256, 4>(a, st);
+    if (rows < 256) return S > 64 ? launch_flat<8, 512, 2>(a, st) : launch_flat<16, 256, 4>(a, st);
     if (S > 64) return launch_flat<16, 512, 4>(a, st);
     return a.g.d == 64 ? launch_flat<16, 256, 4>(a, st) : launch_flat<32, 256, 4>(a, st);
   }

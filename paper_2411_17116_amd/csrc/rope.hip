@@ -21,7 +21,7 @@
 //     trips (nothing may be loaded ahead of a store that could alias it).
 // Measured: a decode token of the 32 / 8-head shape (48 rows) 2.6 us, where two kernels
 // that walked the heads in turn and a copy took 15 + 6 + 2.8 (and two more launch gaps).
-#include "star_internal.h"
+#include "rotary.h"
 
 namespace star {
 
@@ -65,20 +65,6 @@ struct RopeArgs {
   unsigned int* clear;    // eight counters to zero for the launch behind this one, or null
 };
 
-// theta^(-2i/d), and cos and sin of pos times that
-__device__ __forceinline__ double frequency(int i, int d, double log2_theta) {
-  return exp2(-2.0 * (double)i / (double)d * log2_theta);
-}
-__device__ __forceinline__ void angle(int64_t pos, double inv_freq, float* cs, float* sn) {
-  const double TWO_PI = 6.283185307179586476925, INV_TWO_PI = 0.1591549430918953357689;
-  double ang = (double)pos * inv_freq;
-  double r = fma(-rint(ang * INV_TWO_PI), TWO_PI, ang);     // |r| <= pi
-  double s, c;
-  sincos(r, &s, &c);
-  *cs = (float)c;
-  *sn = (float)s;
-}
-
 template <typename T, int half, int TT>
 __global__ __launch_bounds__(THREADS) void rope_kernel(RopeArgs a) {
   constexpr int N = Chunk<T>::N;
@@ -90,12 +76,12 @@ __global__ __launch_bounds__(THREADS) void rope_kernel(RopeArgs a) {
   {
     static_assert(THREADS % half == 0, "a thread's angles share their frequency");
     const int i = tid % half;
-    const double inv_freq = frequency(i, 2 * half, a.log2_theta);
+    const double inv_freq = rotary_frequency(i, 2 * half, a.log2_theta);
 #pragma unroll
     for (int k0 = 0; k0 < TT; k0 += THREADS / half) {
       const int k = k0 + tid / half;
       if (k < TT)                                  // tokens past the last: angles nobody reads
-        angle(a.pos0 + (tok0 + k) % a.n_tokens, inv_freq, &cs_all[k][i], &sn_all[k][i]);
+        rotary_angle(a.pos0 + (tok0 + k) % a.n_tokens, inv_freq, &cs_all[k][i], &sn_all[k][i]);
     }
   }
   __syncthreads();
@@ -140,8 +126,8 @@ __global__ __launch_bounds__(THREADS) void rope_kernel(RopeArgs a) {
 #pragma unroll
         for (int e = 0; e < N; ++e) {
           const float x = (float)lo[u][e], y = (float)hi[u][e];
-          ylo[e] = x * cs[e] - y * sn[e];
-          yhi[e] = y * cs[e] + x * sn[e];
+          ylo[e] = rotary_lo(x, y, cs[e], sn[e]);
+          yhi[e] = rotary_hi(x, y, cs[e], sn[e]);
         }
         lo[u] = Chunk<T>::pack(ylo);
         hi[u] = Chunk<T>::pack(yhi);

@@ -8,6 +8,20 @@
 
 namespace star {
 
+// Division by a number that is the same for a whole launch, for numerators below 2^31: the kernels
+// that a short call waits for would otherwise spend a chain of twenty instructions on each.
+// (n / d = (mulhi(n, m) + n) >> s with s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1.)
+struct Div {
+  uint32_t d, m, s;
+};
+inline Div make_div(uint32_t d) {
+  Div x = {d, 0, 0};
+  while (x.s < 31 && ((uint32_t)1 << x.s) < d) ++x.s;
+  x.m = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << x.s) - d)) / d + 1);
+  return x;
+}
+__device__ inline uint32_t quotient(uint32_t n, const Div& x) { return (__umulhi(n, x.m) + n) >> x.s; }
+
 // ---------------------------------------------------------------------------
 // Phase-2 split plan: every part of the cache (one per context block, plus the
 // tail) is cut into `splits of split_len keys`; a split never straddles a part
@@ -78,6 +92,12 @@ __host__ __device__ inline bool anchor_range(const Geom& g, int mode, int64_t i,
   return mode == ANCHOR_EXTERNAL || mode == ANCHOR_ALL_BLOCKS;
 }
 
+// Rotary embedding a kernel applies on the way; log2_theta == 0: none.
+struct Rotary {
+  double log2_theta;
+  int64_t pos0;         // position of the call's first new token
+};
+
 struct Phase2Args {
   Geom g;
   SplitPlan plan;
@@ -95,6 +115,7 @@ struct Phase2Args {
   void* O;              // fp32 kernel, flat plan of one split: the call's own results (MergeArgs'
   float* A;             // O, A, LSE) instead of O_sub / LSE_sub; else all null
   float* LSE;
+  Rotary rotary;        // decode kernel: Qq and Kn as given are unrotated (log2_theta != 0), token j at pos0 + j
 };
 
 // Cache rows a phase-2 call may see in all, and new token j's exclusive bound.
@@ -122,16 +143,24 @@ struct MergeArgs {
   void* O;              // [B, q_len, Hq, d] in the storage dtype, or null
   float* A;             // the same result in fp32, [B, Hq, q_len, d] (Eq. 1 of everything
   float* LSE;           // merged), and its log-sum-exp [B, Hq, q_len]; each may be null
+  void* Qq;             // with rotary.log2_theta != 0: the call's queries [B, q_len, Hq, 128] in bf16, to be
+  Rotary rotary;        // rotated in place (flat plans; the kernels in front have read them as they were)
 };
 
 // The streaming decode kernel runs in two set-ups.  K and V of a call that fit
 // the 256 MB last-level cache with room to spare are found there by the next
-// decode step: ordinary loads, one step per batch, four single-wavefront
-// workgroups per CU.  Larger ones are used once per step and gone before the
-// next: non-temporal loads, two steps per batch (256 registers), three per CU.
+// decode step: ordinary loads, four single-wavefront workgroups per CU.  Larger ones are
+// used once per step and gone before the next: non-temporal loads, three per CU.
+// (131072 tokens of eight heads: 82.6 us with three, 83.2 with four, 85.6 with six, 83.0 with two; 32768 of them, resident:
+// 29.4 with four, 30.0 with six, 29.5 with eight.)
 __host__ __device__ inline bool decode_cache_resident(const Geom& g, int64_t total_keys) {
   return 2 * (int64_t)g.B * g.Hkv * total_keys * g.d * 2 <= ((int64_t)192 << 20);
 }
+// Tokens of a call on unrotated projections up to which the decode kernel and the merge rotate them,
+// instead of a kernel in front: every wavefront evaluates their angles.  us, front / here: 1 token on 8191 (32 / 8
+// heads) 14.4 / 12.4, 4 tokens 15.9 / 13.8, 5 on 3000 (12 / 4) 12.3 / 10.1, 8 on 8191 (16 / 16) 18.6 / 18.7, 16 tokens
+// 19.9 / 22.2.
+constexpr int DECODE_ROPE_TOKENS = 8;
 inline int decode_workgroups_per_cu(bool resident) { return resident ? 4 : 3; }
 
 // Key range [lo, hi) of split s of a plan other than the decode kernel's flat one (hi
@@ -181,20 +210,6 @@ inline hipError_t launch_in_pieces(int64_t workgroups, int threads, Launch launc
   }
   return hipSuccess;
 }
-
-// Division by a number that is the same for a whole launch, for numerators below 2^31: the kernels
-// that a short call waits for would otherwise spend a chain of twenty instructions on each.
-// (n / d = (mulhi(n, m) + n) >> s with s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1.)
-struct Div {
-  uint32_t d, m, s;
-};
-inline Div make_div(uint32_t d) {
-  Div x = {d, 0, 0};
-  while (x.s < 31 && ((uint32_t)1 << x.s) < d) ++x.s;
-  x.m = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << x.s) - d)) / d + 1);
-  return x;
-}
-__device__ inline uint32_t quotient(uint32_t n, const Div& x) { return (__umulhi(n, x.m) + n) >> x.s; }
 
 // What a phase-1 call launches: row tiles of `rows` rows shared by `waves` wavefronts, one
 // workgroup each, or (queued) drawn from the work queues.

@@ -224,3 +224,38 @@ def test_rotation_workgroup_shapes(dtype, d, B, T, H):
     sa.rope(shape, X, X, 500000.0, pos0=77)
     torch.cuda.synchronize()
     assert _storage_close(X, want, dtype)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,q", [
+    (1, 32, 8, 1000, 1),
+    (1, 16, 16, 5, 1),          # one split of one step
+    (1, 16, 16, 31, 1),         # the new token ends a 32-key step
+    (1, 16, 16, 32, 1),         # and begins one
+    (2, 16, 16, 61, 8),         # eight tokens in two steps, of two splits
+    (1, 12, 4, 3000, 5),        # 15 of 16 rows
+    (1, 16, 1, 700, 1),
+    (5, 64, 32, 500, 2),        # few splits of many rows: merged by rows
+    (3, 32, 16, 90000, 1),      # beyond the last-level cache
+    (1, 16, 16, 600, 9),        # more tokens than the decode kernel turns
+])
+def test_decode_on_unrotated_projections_is_decode_on_rotated_ones(B, Hq, Hkv, L, q):
+    """A decode call that turns its tokens on the way gives the bits of star_attn_rope followed by
+    star_attn_phase2: outputs, queries in place and appended rows."""
+    gen = torch.Generator(device="cuda").manual_seed(L + q)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)
+    shape = sa.StarShape.make("bf16", B, Hq, Hkv, 128, L, max(1, L // 4), 0, L + q)
+    assert sa.phase2_plan(shape, L, q).decode == 1
+    Kc, Vc = new(B, Hkv, L + q, 128), new(B, Hkv, L + q, 128)
+    Q, K, V = new(B, q, Hq, 128), new(B, q, Hkv, 128), new(B, q, Hkv, 128)
+    ws = sa.alloc_workspace(shape, q)
+    pos0, theta = 54321, 500000.0
+    Qr, Kr, Kc2, Vc2, O, O2 = Q.clone(), torch.empty_like(K), Kc.clone(), Vc.clone(), torch.empty_like(Q), torch.empty_like(Q)
+    sa.rope(shape, Qr, Qr, theta, pos0=pos0 + L)
+    sa.rope(shape, K, Kr, theta, pos0=pos0 + L)
+    sa.phase2(shape, L, Qr, Kr, V, Kc2, Vc2, O2, ws)
+    print(f"[{B} {Hq}/{Hkv} L={L} q={q}]", flush=True)
+    sa.phase2_rope(shape, theta, L, Q, K, V, Kc, Vc, O, ws, pos0=pos0)
+    torch.cuda.synchronize()
+    assert torch.equal(O, O2)
+    assert torch.equal(Q, Qr)
+    assert torch.equal(Kc, Kc2) and torch.equal(Vc, Vc2)
