@@ -767,6 +767,10 @@ struct PlainGrid {
   int first;           // the first of them (0 or 1)
   int resident, turn;  // see above; turn = 0: as they come
   int step, whole;     // see above; step = 0: as they come; items in whole runs of eight
+  int n_blocks;        // of the context
+  Div Hkv, B, hs;
+  Div in_group, in_last;        // blocks of a group, of the last one
+  Div per_group;       // items of a whole group
 };
 struct Item {
   int kvh, beta, hs, t, i;
@@ -775,18 +779,32 @@ __device__ __forceinline__ Item plain_item(const Geom& g, const PlainGrid& p, in
   Item x;
   if (p.turn > 0 && id >= p.resident) id = p.resident + p.turn - 1 - (id - p.resident);
   if (p.step > 0 && id < p.whole) id = (id & ~7) | ((id + (id >> 3) * p.step) & 7);
-  x.kvh = id % g.Hkv; id /= g.Hkv;
+  int q = quotient(id, p.Hkv);
+  x.kvh = id - q * g.Hkv; id = q;
   const int n_same = p.n_same * g.B, per = p.n_hs * p.tpb;      // (block, batch), batch fastest; items of one
-  const bool alike = id < n_same * per;
-  if (!alike) id -= n_same * per;
-  const int n = alike ? n_same : g.B, lo = id / (p.group * per) * p.group, in = n - lo < p.group ? n - lo : p.group;
-  id -= lo * per;
-  const int block = lo + id % in;
-  id /= in;
-  x.hs = id % p.n_hs;
-  x.t = p.tpb - 1 - id / p.n_hs;
-  x.beta = block % g.B;
-  x.i = alike ? p.first + block / g.B : 0;
+  int block;
+  if (id < n_same * per) {
+    const int lo = (int)quotient(id, p.per_group) * p.group;
+    id -= lo * per;
+    // (the two divisors as values of their own: chosen between in memory, they would go through scratch)
+    Div whole = p.in_group, last = p.in_last;
+    asm("" : "+s"(whole.d), "+s"(whole.m), "+s"(whole.s), "+s"(last.d), "+s"(last.m), "+s"(last.s));
+    const Div in = n_same - lo < p.group ? last : whole;
+    q = quotient(id, in);
+    block = lo + id - q * (int)in.d;
+    const int b = quotient(block, p.B);
+    x.beta = block - b * g.B;
+    x.i = p.first + b;
+  } else {                                                      // the first block of every batch
+    id -= n_same * per;
+    q = quotient(id, p.B);
+    x.beta = id - q * g.B;
+    x.i = 0;
+  }
+  id = q;
+  q = quotient(id, p.hs);
+  x.hs = id - q * p.n_hs;
+  x.t = p.tpb - 1 - q;
   return x;
 }
 template <int W, int H>
@@ -812,7 +830,7 @@ __device__ __forceinline__ void phase1_item(const Phase1Args& a, int hpw, int tp
   } else {
     const Item x = plain_item(g, *plain, id);
     kvh = x.kvh; beta = x.beta; hs = x.hs; t = x.t; i = x.i;
-    n = (int)((g.L + g.b - 1) / g.b);
+    n = plain->n_blocks;
   }
 
   int s = (int)(i * g.b);
@@ -961,18 +979,19 @@ __global__ __launch_bounds__(64 * W * H, W * H == 4 ? 2 : 1) void phase1_bf16_pl
 // tiles with three in flight was 2.5 % slower for 256 rows: latency is not what bounds it.
 // Workgroups are numbered (kv head fastest, row tile, split, batch): with Hkv a multiple of 8 an
 // XCD's L2 serves one KV head, and the row tiles of a split read its keys there.
+struct RowGrid {
+  Div Hkv, tiles, splits, G;
+};
 template <int W>
-__global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, int row_tiles, int first_wg) {
+__global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, RowGrid grid, int first_wg) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const Geom& g = a.g;
   const int tid = threadIdx.x, wave = (tid >> 6) % W, half = __builtin_amdgcn_readfirstlane((tid >> 6) / W);
   const int lane = tid & 63, col = lane & 15, j4 = lane >> 4;
 
-  int id = first_wg + (int)blockIdx.x;
-  const int kvh = id % g.Hkv; id /= g.Hkv;
-  const int tt = id % row_tiles; id /= row_tiles;
-  const int sp = id % a.plan.s_total;
-  const int beta = id / a.plan.s_total;
+  const uint32_t id = first_wg + blockIdx.x, of_head = quotient(id, grid.Hkv), of_tile = quotient(of_head, grid.tiles);
+  const int kvh = id - of_head * grid.Hkv.d, tt = of_head - of_tile * grid.tiles.d, beta = quotient(of_tile, grid.splits);
+  const int sp = of_tile - beta * grid.splits.d, row_tiles = grid.tiles.d;
 
   const int total = (int)visible_total(a), cache_len = (int)a.cache_len;
   int64_t lo64, hi64;
@@ -991,8 +1010,8 @@ __global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, i
     const unsigned rr = r0 + 16 * (wave * RB + rb) + col;
     active[rb] = rr < n_rows;
     const unsigned r = active[rb] ? rr : n_rows - 1;     // rows past the last repeat it
-    jrow[rb] = (int)(r / (unsigned)g.G);
-    head[rb] = kvh * g.G + (int)(r % (unsigned)g.G);
+    jrow[rb] = (int)quotient(r, grid.G);
+    head[rb] = kvh * g.G + (int)(r - jrow[rb] * g.G);
     load_q(w, rb, (const char*)a.Qq + (((size_t)beta * a.q_len + jrow[rb]) * g.Hq + head[rb]) * ROWB, j4);
     row_lim[rb] = (int)visible_limit(a, jrow[rb]);
     wave_lo = row_lim[rb] < wave_lo ? row_lim[rb] : wave_lo;
@@ -1099,6 +1118,13 @@ static hipError_t launch_phase1_plain(const Phase1Args& a, int hpw, const PlainG
   });
 }
 
+static void group_divisors(const Geom& g, PlainGrid* p) {
+  const int blocks = p->n_same * g.B, rest = blocks % p->group;
+  p->in_group = make_div(p->group);
+  p->in_last = make_div(rest > 0 ? rest : p->group);
+  p->per_group = make_div((uint32_t)(p->group * p->n_hs * p->tpb));      // (no more items than workgroups)
+}
+
 // A prefill of up to 600 key tiles (256 rows x 64 keys) per CU, about a millisecond, is a
 // plain grid of 128-row items (true, and the grid); false: leave it to the queues.  Beyond
 // that the queues' 256-row items win: half the L2 -> LDS traffic, and no XCD waits for
@@ -1125,11 +1151,14 @@ static bool plain_phase1(const Geom& g, int anchor_mode, int n_cu, PlainGrid* gr
   const int64_t wgs = (int64_t)g.Hkv * g.B * p.n_hs * p.tpb * n;
   if (wgs > 0x7fffffff) return false;
   *wgs_out = wgs;
+  p.n_blocks = (int)n;
+  p.Hkv = make_div(g.Hkv); p.B = make_div(g.B); p.hs = make_div(p.n_hs);
   p.first = all || n == 1 ? 0 : 1;
   p.n_same = (int)n - p.first;
   const int64_t longest = (g.a + TKEYS - 1) / TKEYS + (bmax + TKEYS - 1) / TKEYS;
   if (wgs <= n_cu && longest > 8) {
     p.group = 1; p.resident = 0; p.turn = 0; p.step = 0; p.whole = 0;      // all start at once, one per CU
+    group_divisors(g, &p);
     *halves = 2;
     return true;
   }
@@ -1149,6 +1178,7 @@ static bool plain_phase1(const Geom& g, int anchor_mode, int n_cu, PlainGrid* gr
   }
   p.resident = n_cu;
   p.turn = pairs ? (int)(wgs - n_cu) : 0;
+  group_divisors(g, &p);
   *halves = 1;
   return true;
 }
@@ -1203,8 +1233,9 @@ static hipError_t launch_phase2_rows(const Phase2Args& a, int which, hipStream_t
   if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff) return hipErrorInvalidValue;
   hipError_t e = allow_tile_ring(which, (const void*)phase2_rows_bf16_kernel<W>);
   if (e != hipSuccess) return e;
+  const RowGrid grid = {make_div(g.Hkv), make_div((uint32_t)row_tiles), make_div(a.plan.s_total), make_div(g.G)};
   return launch_in_pieces(wgs, NT, [&](unsigned first, unsigned n_wgs) {
-    phase2_rows_bf16_kernel<W><<<dim3(n_wgs), NT, (NW / W) * 4 * TILEB, st>>>(a, (int)row_tiles, (int)first);
+    phase2_rows_bf16_kernel<W><<<dim3(n_wgs), NT, (NW / W) * 4 * TILEB, st>>>(a, grid, (int)first);
   });
 }
 
