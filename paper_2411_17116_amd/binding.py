@@ -1,7 +1,10 @@
-"""ctypes binding of libstarattn.so (see include/star_attn.h for the contract)."""
+"""Binding of libstarattn.so (see include/star_attn.h for the contract): queries through ctypes, the
+calls that enqueue work through the extension module built from csrc/marshal.cpp."""
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional
 
@@ -17,6 +20,7 @@ ANCHOR_ALL_BLOCKS = 4
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_MARSHAL = None       # the extension module, bound to _LIB's entry points
 
 
 class StarAttnError(RuntimeError):
@@ -73,7 +77,7 @@ def lib_path() -> str:
 def load_library():
     """Load the built library; raises if it has not been built (no fallback)."""
     global _LIB
-    if _LIB is not None:
+    if _LIB is not None and _MARSHAL is not None:
         return _LIB
     path = lib_path()
     if not os.path.exists(path):
@@ -115,8 +119,35 @@ def load_library():
     lib.star_attn_phase1_plan.argtypes = [P, ctypes.c_int, ctypes.POINTER(Phase1PlanInfo)]
     lib.star_attn_kernel_path.restype = ctypes.c_char_p
     lib.star_attn_kernel_path.argtypes = [P]
+    _bind(lib)
     _LIB = lib
     return lib
+
+
+def _bind(lib) -> None:
+    """Load the extension module and hand it the library's entry points."""
+    global _MARSHAL
+    path = os.path.join(_HERE, "_marshal.so")
+    if not os.path.exists(path):
+        raise FileNotFoundError(
+            f"{path} not found: build it with `python -m paper_2411_17116_amd.build`")
+    if _MARSHAL is None:
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
+        loader.exec_module(module)
+    else:
+        module = _MARSHAL
+    names = ("phase1", "phase1_anchor", "phase1_rope", "phase2", "phase2_rope", "phase2_static",
+             "phase2_partial", "merge", "rope")
+    module.bind(StarShape, tuple(ctypes.cast(getattr(lib, "star_attn_" + n), ctypes.c_void_p).value
+                                 for n in names))
+    _MARSHAL = module
+
+
+def _calls():
+    if _MARSHAL is None:
+        load_library()
+    return _MARSHAL
 
 
 def status_string(code: int) -> str:
@@ -147,19 +178,8 @@ def workspace_bytes(shape: StarShape, max_q_len: int) -> int:
     return int(load_library().star_attn_workspace_bytes(ctypes.byref(shape), int(max_q_len)))
 
 
-# A decode step on a short cache takes about as long on the GPU as its call takes on the
-# host, so marshalling is kept to what the call needs: addresses go through ctypes as plain
-# integers, and the current stream's handle comes from torch's own raw look-up (0.3 us;
-# a torch.cuda.Stream object made for its handle 3 us).  Measured: 11.5 -> 8.6 us per
-# phase2() call, of which two kernel launches are 6.9.
-def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
-    if t is None:
-        return None
-    if not t.is_contiguous():
-        raise ValueError("star_attn tensors must be contiguous")
-    return t.data_ptr()
-
-
+# The current stream's handle comes from torch's own raw look-up (0.3 us; a torch.cuda.Stream object made
+# for its handle 3 us).
 _RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
@@ -193,11 +213,7 @@ def alloc_workspace(shape: StarShape, max_q_len: int, device="cuda") -> torch.Te
 def phase1(shape: StarShape, Q, K, V, O_ctx, K_cache, V_cache, LSE_ctx=None,
            workspace=None, stream=None) -> None:
     """star_attn_phase1: context encoding; fills O_ctx, the caches and LSE_ctx."""
-    ws_n = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = load_library().star_attn_phase1(
-        ctypes.byref(shape), _ptr(Q), _ptr(K), _ptr(V), _ptr(O_ctx), _ptr(LSE_ctx),
-        _ptr(K_cache), _ptr(V_cache), _ptr(workspace), ws_n, _stream(stream))
-    _check(rc)
+    _check(_calls().phase1(shape, Q, K, V, O_ctx, LSE_ctx, K_cache, V_cache, workspace, _stream(stream)))
 
 
 def phase1_workspace_bytes(shape: StarShape, anchor_mode: int) -> int:
@@ -207,55 +223,35 @@ def phase1_workspace_bytes(shape: StarShape, anchor_mode: int) -> int:
 def phase1_anchor(shape: StarShape, anchor_mode: int, Q, K, V, O_ctx, K_cache, V_cache,
                   K_anchor=None, V_anchor=None, LSE_ctx=None, workspace=None, stream=None) -> None:
     """star_attn_phase1_anchor: phase 1 under an anchor variant of the ablation study."""
-    ws_n = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = load_library().star_attn_phase1_anchor(
-        ctypes.byref(shape), int(anchor_mode), _ptr(Q), _ptr(K), _ptr(V), _ptr(K_anchor),
-        _ptr(V_anchor), _ptr(O_ctx), _ptr(LSE_ctx), _ptr(K_cache), _ptr(V_cache),
-        _ptr(workspace), ws_n, _stream(stream))
-    _check(rc)
+    _check(_calls().phase1_anchor(shape, int(anchor_mode), Q, K, V, K_anchor, V_anchor, O_ctx, LSE_ctx,
+                                  K_cache, V_cache, workspace, _stream(stream)))
 
 
 def phase1_rope(shape: StarShape, rope_theta: float, Q, K, V, O_ctx, K_cache, V_cache, pos0=0,
                 LSE_ctx=None, workspace=None, stream=None) -> None:
     """star_attn_phase1_rope: phase 1 on unrotated Q (rotated in place) and K."""
-    ws_n = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = load_library().star_attn_phase1_rope(
-        ctypes.byref(shape), float(rope_theta), int(pos0), _ptr(Q), _ptr(K), _ptr(V), _ptr(O_ctx),
-        _ptr(LSE_ctx), _ptr(K_cache), _ptr(V_cache), _ptr(workspace), ws_n, _stream(stream))
-    _check(rc)
+    _check(_calls().phase1_rope(shape, float(rope_theta), int(pos0), Q, K, V, O_ctx, LSE_ctx, K_cache, V_cache,
+                                workspace, _stream(stream)))
 
 
 def phase2_rope(shape: StarShape, rope_theta: float, cache_len: int, Qq, Kq, Vq, K_cache, V_cache,
                 O, workspace, pos0=0, O_part=None, LSE_part=None, stream=None) -> None:
     """star_attn_phase2_rope: phase 2 on unrotated Qq (rotated in place) and Kq."""
-    q_len = Qq.shape[1]
-    ws_n = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = load_library().star_attn_phase2_rope(
-        ctypes.byref(shape), float(rope_theta), int(pos0), int(cache_len), int(q_len), _ptr(Qq),
-        _ptr(Kq), _ptr(Vq), _ptr(K_cache), _ptr(V_cache), _ptr(O_part), _ptr(LSE_part), _ptr(O),
-        _ptr(workspace), ws_n, _stream(stream))
-    _check(rc)
+    _check(_calls().phase2_rope(shape, float(rope_theta), int(pos0), int(cache_len), Qq, Kq, Vq, K_cache, V_cache,
+                                O_part, LSE_part, O, workspace, _stream(stream)))
 
 
 def rope(shape: StarShape, X, Y, rope_theta: float, pos0=0, stream=None) -> None:
     """star_attn_rope: rotate X [B, T, H, d] into Y (may be X), token t at pos0 + t."""
-    rc = load_library().star_attn_rope(ctypes.byref(shape), int(X.shape[2]), int(X.shape[1]),
-                                       int(pos0), float(rope_theta), _ptr(X), _ptr(Y),
-                                       _stream(stream))
-    _check(rc)
+    _check(_calls().rope(shape, X, Y, float(rope_theta), int(pos0), _stream(stream)))
 
 
 def phase2(shape: StarShape, cache_len: int, Qq, Kq, Vq, K_cache, V_cache, O, workspace,
            O_part=None, LSE_part=None, stream=None) -> None:
     """star_attn_phase2: appends Kq/Vq at cache_len, then global attention of the
     q_len = Qq.shape[1] new tokens; fills O (and the per-part outputs if given)."""
-    q_len = Qq.shape[1]
-    ws_n = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = load_library().star_attn_phase2(
-        ctypes.byref(shape), int(cache_len), int(q_len), _ptr(Qq), _ptr(Kq), _ptr(Vq),
-        _ptr(K_cache), _ptr(V_cache), _ptr(O_part), _ptr(LSE_part), _ptr(O),
-        _ptr(workspace), ws_n, _stream(stream))
-    _check(rc)
+    _check(_calls().phase2(shape, int(cache_len), Qq, Kq, Vq, K_cache, V_cache, O_part, LSE_part, O, workspace,
+                           _stream(stream)))
 
 
 STATIC_SCRATCH_BYTES = 16 << 20
@@ -265,29 +261,17 @@ def phase2_static(shape: StarShape, cache_len: int, Qq, Kq, Vq, K_cache, V_cache
                   stream=None) -> None:
     """star_attn_phase2_static: star_attn_phase2 with the library's static scratch
     in place of a workspace (allocates nothing; calls must not overlap on a GPU)."""
-    q_len = Qq.shape[1]
-    rc = load_library().star_attn_phase2_static(
-        ctypes.byref(shape), int(cache_len), int(q_len), _ptr(Qq), _ptr(Kq), _ptr(Vq),
-        _ptr(K_cache), _ptr(V_cache), _ptr(O), _stream(stream))
-    _check(rc)
+    _check(_calls().phase2_static(shape, int(cache_len), Qq, Kq, Vq, K_cache, V_cache, O, _stream(stream)))
 
 
 def phase2_partial(shape: StarShape, cache_len: int, Qq, K_cache, V_cache, A, LSE, workspace,
                    Kq=None, Vq=None, stream=None) -> None:
     """star_attn_phase2_partial: one host's pair (A, LSE) for the q_len = Qq.shape[1]
     new tokens; with Kq/Vq the query host's share (append, then attend causally)."""
-    q_len = Qq.shape[1]
-    ws_n = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = load_library().star_attn_phase2_partial(
-        ctypes.byref(shape), int(cache_len), int(q_len), _ptr(Qq), _ptr(Kq), _ptr(Vq),
-        _ptr(K_cache), _ptr(V_cache), _ptr(A), _ptr(LSE), _ptr(workspace), ws_n, _stream(stream))
-    _check(rc)
+    _check(_calls().phase2_partial(shape, int(cache_len), Qq, Kq, Vq, K_cache, V_cache, A, LSE, workspace,
+                                   _stream(stream)))
 
 
 def merge(shape: StarShape, A_parts, LSE_parts, O=None, A=None, LSE=None, stream=None) -> None:
     """star_attn_merge: Eq. 3-4 over the n_parts = A_parts.shape[0] gathered pairs."""
-    n_parts, q_len = A_parts.shape[0], A_parts.shape[3]
-    rc = load_library().star_attn_merge(
-        ctypes.byref(shape), int(n_parts), int(q_len), _ptr(A_parts), _ptr(LSE_parts), _ptr(O),
-        _ptr(A), _ptr(LSE), _stream(stream))
-    _check(rc)
+    _check(_calls().merge(shape, A_parts, LSE_parts, O, A, LSE, _stream(stream)))

@@ -1,5 +1,6 @@
 """Builds libstarattn.so (the C-ABI HIP library) and libstarcalib.so (the
-benchmark's calibration kernels) in-tree with hipcc for gfx950.
+benchmark's calibration kernels) in-tree with hipcc for gfx950, and _marshal.so (the
+binding's calls, host code against torch's headers) with g++.
 
 Usage:  python -m paper_2411_17116_amd.build
 The library is written next to this file so that it travels with the source
@@ -23,6 +24,22 @@ CALIB_SOURCES = ["calib.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
+
+MARSHAL_LIB = os.path.join(HERE, "_marshal.so")
+MARSHAL_SOURCE = "marshal.cpp"
+
+
+def marshal_command() -> list:
+    import sysconfig
+
+    import torch
+    base = os.path.dirname(torch.__file__)
+    lib = os.path.join(base, "lib")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", os.path.join(base, "include"), "-I" + sysconfig.get_paths()["include"],
+            os.path.join(CSRC, MARSHAL_SOURCE), "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+            "-Wl,-rpath," + lib, "-o", MARSHAL_LIB]
 
 
 def hipcc() -> str:
@@ -52,6 +69,10 @@ def build(verbose: bool = True, jobs: int = 6) -> str:
                 if p.poll() is None:
                     p.wait()
                     break
+    cmd = marshal_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs.append((MARSHAL_SOURCE, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -63,7 +84,7 @@ def build(verbose: bool = True, jobs: int = 6) -> str:
         elif verbose and out.strip():
             print(out)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("a compiler failed")
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     if verbose:
         print(" ".join(cmd), flush=True)
