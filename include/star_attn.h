@@ -352,7 +352,8 @@ int star_attn_rope(const star_attn_shape* shape, int32_t n_heads, int64_t n_toke
  * `out` is HOST memory.  Returns a status code; nothing is enqueued.
  */
 typedef struct star_attn_plan_info {
-  int32_t decode;          /* 1: streaming split-KV kernel (G * q_len <= 16, bf16); 0: row-tiled kernel */
+  int32_t decode;          /* 1: streaming split-KV kernel (bf16, G * q_len <= 16; without per-part outputs up to
+                              32, or 64 where K + V exceed 192 MiB); 0: row-tiled kernel */
   int32_t flat;            /* 1: splits ignore part boundaries (only without per-part outputs) */
   int32_t n_splits;        /* splits per (batch, KV head) */
   int32_t non_temporal;    /* 1: the decode kernel reads the cache with non-temporal loads */

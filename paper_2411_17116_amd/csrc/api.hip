@@ -123,12 +123,32 @@ static Geom make_geom(const star_attn_shape* s) {
 static int64_t ceil_div(int64_t x, int64_t y) { return (x + y - 1) / y; }
 static int64_t round_up(int64_t x, int64_t y) { return ceil_div(x, y) * y; }
 
-// Workgroups of the decode kernel that are resident at once on the current
-// device (256 CUs on an MI355X): one split each under a flat plan.
+// Wavefronts of the decode kernel that are resident at once on the current
+// device (256 CUs on an MI355X): one split each under a flat plan of up to 16 rows.
 static int64_t decode_slots(const Geom& g, int64_t total) {
-  return device_cu_count() * (int64_t)decode_workgroups_per_cu(decode_cache_resident(g, total));
+  return device_cu_count() * (int64_t)decode_wavefronts_per_cu(decode_cache_resident(g, total));
 }
 static int64_t decode_slots_max() { return device_cu_count() * (int64_t)4; }
+
+// Rows per KV head up to which a call without per-part outputs streams the cache through the decode kernel.
+// More than 16 (a block of columns each 16) leave one wavefront too many pairs, so four share a split (two
+// where the cache is at most 64 steps long, and none takes more than one or two) and meet in LDS; against
+// the row-tiled kernel's 128-row tiles, us (32 / 8 heads): 20 rows on 600 keys 13.0 -> 8.9, 32 on 2000 13.0 -> 9.9, on
+// 16384 20.0 -> 18.0, on 131072 101.6 -> 85.3.  33 to 64 rows take all registers of a SIMD for one wavefront,
+// which pays where the cache comes from HBM: 48 rows on 131072 103.7 -> 89.2, 64 104.4 -> 91.4, 48 on 50000
+// 47.8 -> 43.5; 48 on 32768 (resident) 37.5 against 36.3, on 16384 21.0 against 22.8, 64 21.6 and 26.4.
+// A single key tile has nothing to stream.
+static int stream_rows_max(const Geom& g, int64_t total) {
+  return total <= 64 ? 16 : decode_cache_resident(g, total) ? 32 : 64;
+}
+constexpr int64_t STREAM_WGS = 256;        // workgroups of four wavefronts: one per CU
+// Most splits of 17 rows and more that any call on caches of up to `keys` keys is cut into.
+static int64_t stream_splits(const Geom& g, int64_t keys, int waves) {
+  const int64_t pairs = (int64_t)g.B * g.Hkv, steps = ceil_div(keys, 32), slots = STREAM_WGS * (waves == 2 ? 2 : 1) / pairs;
+  const int64_t most = ceil_div(steps, waves);
+  return slots < 1 ? 1 : slots < most ? slots : most;
+}
+constexpr int64_t STREAM_PAIRED_KEYS = 64 * 32;
 
 // ---- fp32 kernel: tiles of 16 rows shared by eight wavefronts (one workgroup per CU), or
 // of 32 rows shared by four (two per CU).
@@ -261,12 +281,24 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   int64_t rows = (int64_t)g.G * q_len;
   int64_t fit = splits_that_fit(g, q_len, max_bytes);
   if (fit < 1) fit = 1;
-  p->decode = (s->dtype == STAR_ATTN_BF16 && rows <= 16) ? 1 : 0;
+  p->decode = (s->dtype == STAR_ATTN_BF16 && rows <= (want_parts ? 16 : stream_rows_max(g, total))) ? 1 : 0;
   p->flat = 0;
   p->tile_rows = 0;
+  p->waves = 1;
   p->n_blocks = (int32_t)n;
   if (n > (1 << 24)) return false;
   int64_t split_len;
+  if (p->decode && rows > 16) {
+    p->waves = rows <= 32 && total <= STREAM_PAIRED_KEYS ? 2 : 4;
+    int64_t splits = stream_splits(g, total, p->waves);
+    if (splits > fit) splits = fit;
+    p->flat = 1;
+    p->split_len = round_up(ceil_div(total, splits), 32);
+    p->spb = 0;
+    p->st = 0;
+    p->s_total = (int32_t)splits;
+    return true;
+  }
   if (p->decode && !want_parts) {
     int64_t pairs = (int64_t)g.B * g.Hkv;
     int64_t slots = decode_slots(g, total);
@@ -279,6 +311,20 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     p->spb = 0;
     p->st = 0;
     p->s_total = (int32_t)ceil_div(total, split_len);
+    // More than 64 splits of a resident cache: four wavefronts share one, and a quarter or half of them is left
+    // to merge.  Two such workgroups per CU, one where there are fewer than eight KV heads and four times the
+    // splits per head.  us: 8191 tokens of eight heads 11.6 -> 11.0, 32768 29.4 -> 27.9; 30000 of two 12.4 -> 11.1, 131072
+    // 29.6 -> 27.2; up to 64 splits the meeting costs more than the merge saves (2000 of eight 7.5 and 7.9,
+    // 16000 of sixteen 26.7 and 27.2), and caches read from HBM gain nothing (131072 of eight 82.3 and 82.2, four
+    // sequences of 32768 83.1 and 83.8).
+    if (p->s_total > 64 && decode_cache_resident(g, total)) {
+      const int64_t wgs = device_cu_count() * (int64_t)(pairs < 8 ? 1 : 2), most = ceil_div(ceil_div(total, 32), 4);
+      int64_t splits = wgs / pairs < most ? wgs / pairs : most;
+      if (splits < 1) splits = 1;
+      p->waves = 4;
+      p->split_len = round_up(ceil_div(total, splits), 32);
+      p->s_total = (int32_t)splits;
+    }
     return true;
   }
   if (s->dtype == STAR_ATTN_F32 && !want_parts) {
@@ -423,6 +469,11 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
         need(most < worth ? most : worth, q);
       }
     } else if (ok) {
+      if ((int64_t)g.G * q <= 64) {
+        const int64_t keys = g.cap < STREAM_PAIRED_KEYS ? g.cap : STREAM_PAIRED_KEYS;
+        need(stream_splits(g, keys, 2), q);
+        need(stream_splits(g, g.cap, 4), q);
+      }
       int64_t most = 4 * ROW_WGS / rows_wgs(g, q, 256), worth = ceil_div(g.cap, 256);
       if (most > worth) most = worth;
       if (most < 1) most = 1;
@@ -641,7 +692,7 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   // attention kernels append them themselves (they read the new rows from Kq/Vq and
   // write them to the cache).  Unrotated keys are rotated into the cache first.
   // (A few rotated tokens on the decode kernel's equal runs are turned there, and by the merge.)
-  const bool turn = append && rope && plan.decode && plan.flat && q_len <= DECODE_ROPE_TOKENS &&
+  const bool turn = append && rope && plan.decode && plan.flat && g.G * q_len <= 16 && q_len <= DECODE_ROPE_TOKENS &&
                     (int64_t)g.B * g.Hq * q_len <= (1 << 20);
   const bool fused_append = append && (!rope || turn);
   if (append && rope && !turn &&
@@ -728,7 +779,7 @@ int star_attn_merge(const star_attn_shape* shape, int64_t n_parts, int64_t q_len
   if (rows > (int64_t)0x7fffffff || rows * n_parts > ((int64_t)1 << 40)) return STAR_ATTN_ERR_INVALID_SHAPE;
   MergeArgs m;
   m.g = g;
-  m.plan = SplitPlan{0, 0, 0, 0, (int32_t)n_parts, 0, 1, 0};    // one part made of n_parts splits
+  m.plan = SplitPlan{0, 0, 0, 0, (int32_t)n_parts, 0, 1, 0, 0};    // one part made of n_parts splits
   m.q_len = (int32_t)q_len;
   m.out_bf16 = shape->dtype == STAR_ATTN_BF16;
   m.O_sub = A_parts; m.LSE_sub = LSE_parts;

@@ -1,15 +1,17 @@
 // bf16 split-KV partial attention for decode-sized phase-2 calls (head_dim 128,
-// G * q_len <= 16 rows per KV head): Eq. 1-2 evaluated per split of the cache,
-// with Algorithm 2's "append, then attend" fused in.
+// G * q_len <= 16 rows per KV head, up to 32 or 64 without per-part outputs): Eq. 1-2
+// evaluated per split of the cache, with Algorithm 2's "append, then attend" fused in.
 //
 // A decode step reads every cached K and V byte exactly once and does 4-8 flops
 // per byte, so the kernel is built as an HBM stream:
-//   * one wavefront per workgroup, one split (a set of keys of one KV head) per
-//     workgroup, no barriers; without per-part outputs there is one split per
-//     resident workgroup slot and split s is the comb of 32-key steps
-//     s, s + S, s + 2S, ... so that at any moment the S wavefronts of a KV head
+//   * a wavefront walks its keys with no barriers; without per-part outputs the
+//     N wavefronts of a KV head that are resident at once take the comb of 32-key steps
+//     w, w + N, w + 2N, ... so that at any moment they
 //     read one contiguous window of its cache (every memory channel busy, none
 //     hot); with per-part outputs a split is a contiguous run inside one part;
+//   * a split is one wavefront's keys and a workgroup one wavefront, or (SplitPlan::waves) four or two
+//     wavefronts share one and meet in LDS behind the key loop, where the pairs of more splits would cost
+//     more to store and merge (stream_rows_max() and make_plan() in api.hip, with both sides measured);
 //   * a 32-key step is loaded into registers with plain 16-byte loads: K (8 KiB) straight in the
 //     layout the MFMA wants -- lane (i, j4) takes key i, bytes 64t + 16 j4 .. +15 of its row for
 //     t = 0..3; V (8 KiB) as 1 KiB-contiguous bursts.  As soon as its scores are taken and its V is in
@@ -25,7 +27,9 @@
 //     the caches is worth 9-16 % of the step at 0.5-4 GB); a smaller one with
 //     ordinary loads, so that the next step finds it there;
 //   * all G query heads of the KV group (and up to 16/G new tokens) form the 16
-//     columns of v_mfma_f32_16x16x32_bf16, so K and V are read once per KV head;
+//     columns of v_mfma_f32_16x16x32_bf16, so K and V are read once per KV head; more rows are up to four
+//     such column blocks (RB), every K and V^T fragment feeding all of them: 32 rows leave room for two wavefronts
+//     on a SIMD (252 registers; three blocks would spill 70), 48 and 64 for one;
 //     S^T = K Q^T leaves each lane with keys of one query column, and the
 //     exponentiated tile is directly the B operand of O^T += V^T P^T; V goes
 //     through an 8 KiB LDS buffer (one wavefront's LDS accesses are in order) only to be
@@ -80,11 +84,13 @@ __device__ __forceinline__ float xor32_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// RB blocks of 16 rows: the lane's columns.
+template <int RB>
 struct DecState {
-  bf16x8 q[4];     // Q^T fragments: q[t] = Q[column lane%16][32t + 8*(lane/16) .. +7]
-  f32x4 o[8];      // O^T: o[dt][v] = O[column][16dt + 4*(lane/16) + v]
-  float m, l;      // running maximum (raw logits; uniform over a column's four lanes), this lane's share of the sum
-  float neg_mc;    // -m * c (0 while nothing was visible)
+  bf16x8 q[RB][4];     // Q^T fragments: q[.][t] = Q[column lane%16][32t + 8*(lane/16) .. +7]
+  f32x4 o[RB][8];      // O^T: o[.][dt][v] = O[column][16dt + 4*(lane/16) + v]
+  float m[RB], l[RB];  // running maximum (raw logits; uniform over a column's four lanes), this lane's share of the sum
+  float neg_mc[RB];    // -m * c (0 while nothing was visible)
 };
 
 // One 32-key step in registers.
@@ -92,8 +98,9 @@ struct StepRegs {
   i32x4 k[8];      // k[4kt + t]: key 16kt + lane%16, bytes 64t + 16*(lane/16) .. +15 (MFMA A operand)
   i32x4 v[8];      // v[it]: key 4it + lane/16, bytes 16*(lane%16) .. +15
 };
+template <int RB>
 struct Scores {
-  f32x4 s[2];
+  f32x4 s[RB][2];
 };
 
 // Where a split's rows come from: cache rows below `cache_len`, the call's new
@@ -169,29 +176,37 @@ __device__ __forceinline__ void load_last(StepRegs& r, const Source& src, int ke
 
 // A step in two halves.  First its scores, and V into LDS (row 4it + lane/16, swizzled chunk
 // lane%16): the step's registers are then free.
-__device__ __forceinline__ void score_step(const DecState& w, const StepRegs& r, const unsigned (&vw)[4],
-                                           Scores& x) {
-#pragma unroll
-  for (int kt = 0; kt < 2; ++kt) x.s[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+template <int RB>
+__device__ __forceinline__ void score_step(const DecState<RB>& w, const StepRegs& r, const unsigned (&vw)[4],
+                                           Scores<RB>& x) {
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
-      x.s[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[4 * kt + t]), w.q[t], x.s[kt], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        const f32x4 acc = t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : x.s[b][kt];
+        x.s[b][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.k[4 * kt + t]), w.q[b][t], acc, 0, 0, 0);
+      }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int it = 0; it < 8; ++it)
     *(LDS_AS i32x4*)(size_t)(vw[it & 3] + (it >> 2) * 16 * ROWB) = r.v[it];
 }
-__device__ __forceinline__ void mask_step(Scores& x, int key0, int lim, int j4) {
-  const int n = lim - key0 - 4 * j4;     // element (kt, v) is key key0 + 16kt + 4*j4 + v
+template <int RB>
+__device__ __forceinline__ void mask_step(Scores<RB>& x, int key0, const int (&lim)[RB], int j4) {
 #pragma unroll
-  for (int kt = 0; kt < 2; ++kt)
+  for (int b = 0; b < RB; ++b) {
+    const int n = lim[b] - key0 - 4 * j4;     // element (kt, v) is key key0 + 16kt + 4*j4 + v
 #pragma unroll
-    for (int v = 0; v < 4; ++v) x.s[kt][v] = (16 * kt + v) < n ? x.s[kt][v] : -INFINITY;
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x.s[b][kt][v] = (16 * kt + v) < n ? x.s[b][kt][v] : -INFINITY;
+  }
 }
 // Then softmax and products.
-__device__ __forceinline__ void attend_step(DecState& w, const Scores& x, const unsigned (&vaddr)[8], float c) {
+template <int RB>
+__device__ __forceinline__ void attend_step(DecState<RB>& w, const Scores<RB>& x, const unsigned (&vaddr)[8], float c) {
   // B operand slot e of lane group j4 is key 16(e/4) + 4*j4 + e%4; the A operand
   // (V^T, d-row lane%16) takes keys 4*j4..+3 and 16 + 4*j4..+3 from two
   // transposing reads.
@@ -202,71 +217,137 @@ __device__ __forceinline__ void attend_step(DecState& w, const Scores& x, const 
     hi[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(size_t)(vaddr[dt] + 16 * ROWB));
   }
   __builtin_amdgcn_sched_barrier(0);
-  float tmax = fmaxf(fmaxf(fmaxf(x.s[0][0], x.s[0][1]), fmaxf(x.s[0][2], x.s[0][3])),
-                     fmaxf(fmaxf(x.s[1][0], x.s[1][1]), fmaxf(x.s[1][2], x.s[1][3])));
-  // Lanes exchange their maxima only where some column's moves.  (The largest weight is exactly one this
-  // way; a reference that moves later costs less and 6 % of precision.)
-  if (__builtin_amdgcn_ballot_w64(tmax > w.m) != 0) {
-    const float m = fmaxf(w.m, xor32_max(fmaxf(tmax, xor16(tmax)))), mm = m == -INFINITY ? 0.f : m;
-    const float alpha = __builtin_amdgcn_exp2f((w.m - mm) * c);
-    w.l *= alpha;
+  bf16x8 p[RB];
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) w.o[dt] *= alpha;
-    w.m = m;
-    w.neg_mc = mm * -c;
-  }
-  bf16x8 p;
-  float lsum = 0.f;
+  for (int b = 0; b < RB; ++b) {
+    const f32x4(&s)[2] = x.s[b];
+    const float tmax = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                             fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    // Lanes exchange their maxima only where some column's moves.  (The largest weight is exactly one this
+    // way; a reference that moves later costs less and 6 % of precision.)
+    if (__builtin_amdgcn_ballot_w64(tmax > w.m[b]) != 0) {
+      const float m = fmaxf(w.m[b], xor32_max(fmaxf(tmax, xor16(tmax)))), mm = m == -INFINITY ? 0.f : m;
+      const float alpha = __builtin_amdgcn_exp2f((w.m[b] - mm) * c);
+      w.l[b] *= alpha;
 #pragma unroll
-  for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x.s[kt][v], c, w.neg_mc));
-      lsum += e;
-      p[4 * kt + v] = (__bf16)e;
+      for (int dt = 0; dt < 8; ++dt) w.o[b][dt] *= alpha;
+      w.m[b] = m;
+      w.neg_mc[b] = mm * -c;
     }
-  w.l += lsum;
+    float lsum = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kt][v], c, w.neg_mc[b]));
+        lsum += e;
+        p[b][4 * kt + v] = (__bf16)e;
+      }
+    w.l[b] += lsum;
+  }
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) {
     bf16x8 a = __builtin_shufflevector(__builtin_bit_cast(bf16x4, lo[dt]), __builtin_bit_cast(bf16x4, hi[dt]), 0, 1, 2, 3, 4, 5, 6, 7);
-    w.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, p, w.o[dt], 0, 0, 0);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) w.o[b][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, p[b], w.o[b][dt], 0, 0, 0);
   }
 }
 
-// grid: x = split, y = kv head, z = batch; 64 threads.  NT = non-temporal loads; ROPE = Qq and Kn are
-// unrotated (at most ROPE_TOKENS tokens).
-struct DecodeDiv {
-  Div splits, G;
+// LDS of a workgroup of KW wavefronts: a step's V of each; behind the key loop, a half of d at a time,
+// their results (row 16 b + lane % 16, 16-byte chunk of the half XORed with the row's low four bits).
+template <int RB, int KW>
+struct Meeting {
+  union {
+    char v[KW][STEPB];
+    float o[KW][16 * RB][D / (RB > 2 ? 4 : 2)];
+  };
+  float m[KW][16 * RB], l[KW][16 * RB], scale[KW][16 * RB];
 };
-template <bool NT, bool ROPE>
-__global__ __launch_bounds__(64, 2) void decode_bf16_kernel(Phase2Args a, DecodeDiv by) {
-  __shared__ __attribute__((aligned(1024))) char lds[STEPB];
-  __shared__ __attribute__((aligned(16))) char angle_lds[ROPE ? sizeof(Angles) : 16];
-  Angles* angles = (Angles*)angle_lds;
+// KW wavefronts have walked different keys of the same rows: their sum goes to O_sub / LSE_sub, `to(row)`
+// being a row's number there.  The order is fixed.
+template <int RB, int KW, typename To>
+__device__ __forceinline__ void meet(const Phase2Args& a, Meeting<RB, KW>& x, const DecState<RB>& w, int n_rows, float c, To to) {
+  constexpr int ROWS = 16 * RB;
+  constexpr int PIECES = RB > 2 ? 4 : 2, CHUNKS = 32 / PIECES;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, j4 = lane >> 4;
+#pragma unroll
+  for (int b = 0; b < RB; ++b) {
+    const float l = xor32_sum(w.l[b] + xor16(w.l[b]));
+    if (j4 == 0) { x.m[wave][16 * b + col] = w.m[b]; x.l[wave][16 * b + col] = l; }
+  }
+  __syncthreads();
+  for (int i = tid; i < KW * ROWS; i += 64 * KW) {
+    const int k = i / ROWS, row = i % ROWS;
+    float m = -INFINITY;
+#pragma unroll
+    for (int n = 0; n < KW; ++n) m = fmaxf(m, x.m[n][row]);
+    const float mm = m == -INFINITY ? 0.f : m;
+    float l = 0.f;
+#pragma unroll
+    for (int n = 0; n < KW; ++n) l += x.l[n][row] * __builtin_amdgcn_exp2f((x.m[n][row] - mm) * c);
+    x.scale[k][row] = l > 0.f ? __builtin_amdgcn_exp2f((x.m[k][row] - mm) * c) * (1.f / l) : 0.f;
+    if (k == 0 && row < n_rows) a.LSE_sub[to(row)] = l > 0.f ? (m * c + __builtin_amdgcn_logf(l)) * LN2 : -INFINITY;
+  }
+#pragma unroll
+  for (int h = 0; h < PIECES; ++h) {
+    if (h > 0) __syncthreads();
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+      for (int dt = 0; dt < 8 / PIECES; ++dt)
+        *(f32x4*)&x.o[wave][16 * b + col][((4 * dt + j4) ^ (col & (CHUNKS - 1))) * 4] = w.o[b][8 / PIECES * h + dt];
+    __syncthreads();
+    for (int i = tid; i < ROWS * CHUNKS; i += 64 * KW) {
+      const int row = i / CHUNKS, chunk = i % CHUNKS;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < KW; ++k) acc += *(const f32x4*)&x.o[k][row][(chunk ^ (row & (CHUNKS - 1))) * 4] * x.scale[k][row];
+      if (row < n_rows) *(f32x4*)(a.O_sub + to(row) * D + D / PIECES * h + 4 * chunk) = acc;
+    }
+  }
+}
+
+// grid: x = split, y = kv head, z = batch; KW wavefronts, which take the split's steps in turn.  NT = non-temporal
+// loads; ROPE = Qq and Kn are unrotated (at most ROPE_TOKENS tokens).  KW > 1: flat plans only.
+struct DecodeDiv {
+  Div steps, G;        // steps between two of a wavefront's (flat plans): splits times KW
+};
+template <bool NT, bool ROPE, int RB, int KW>
+__global__ __launch_bounds__(64 * KW, RB > 2 ? 1 : 2) void decode_bf16_kernel(Phase2Args a, DecodeDiv by) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  Meeting<RB, KW>& meeting = *(Meeting<RB, KW>*)lds;
   const Geom& g = a.g;
-  const int lane = threadIdx.x;
+  const int wave = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = KW == 1 ? threadIdx.x : threadIdx.x & 63;
+  Angles* angles = (Angles*)(lds + sizeof(Meeting<RB, KW>)) + wave;      // each wavefront its own: no barrier
   const int qc = lane & 15, j4 = lane >> 4;
   const int sp = blockIdx.x, kvh = blockIdx.y, beta = blockIdx.z;
-  const int R = g.G * a.q_len;                 // <= 16 live columns
-  const int col_j = quotient(qc, by.G), head = kvh * g.G + qc - col_j * g.G;
-  const bool live = qc < R;
-  const int j = live ? col_j : 0;
+  const int R = g.G * a.q_len;                 // <= 16 RB live columns
+  int head[RB], j[RB];
+  bool live[RB];
+#pragma unroll
+  for (int b = 0; b < RB; ++b) {
+    const int row = 16 * b + qc, token = quotient(row, by.G);
+    live[b] = row < R;
+    head[b] = kvh * g.G + row - token * g.G;
+    j[b] = live[b] ? token : 0;
+  }
 
   const int cache_len = (int)a.cache_len;
   const int total = (int)visible_total(a);
   // without new-token tensors the caches already hold the appended rows
   const bool fused_append = a.Kn != nullptr;
   const int cached = fused_append ? cache_len : total;
-  // step `cur` of this split covers keys [base + cur * stride, +32) below hi; the first n_whole of
+  // step `cur` of this wavefront covers keys [base + cur * stride, +32) below hi; the first n_whole of
   // them lie in the cache as a whole and are visible to every token
   const int first_lim = (int)visible_limit(a, 0), free_hi = cached < first_lim ? cached : first_lim;
   int base, stride, nsteps, n_whole, hi;
-  if (a.plan.flat) {
-    const int S = a.plan.s_total, T = (total + STEP - 1) / STEP, whole = free_hi / STEP;
-    base = sp * STEP;
-    stride = S * STEP;
-    nsteps = sp < T ? (int)quotient(T - sp + S - 1, by.splits) : 0;
-    n_whole = sp < whole ? (int)quotient(whole - sp + S - 1, by.splits) : 0;
+  const int first_step = sp * KW + wave, all_steps = a.plan.s_total * KW;      // (flat)
+  if (KW > 1 || a.plan.flat) {
+    const int T = (total + STEP - 1) / STEP, whole = free_hi / STEP;
+    base = first_step * STEP;
+    stride = all_steps * STEP;
+    nsteps = first_step < T ? (int)quotient(T - first_step + all_steps - 1, by.steps) : 0;
+    n_whole = first_step < whole ? (int)quotient(whole - first_step + all_steps - 1, by.steps) : 0;
     hi = total;
   } else {
     int64_t lo64, hi64;
@@ -278,9 +359,11 @@ __global__ __launch_bounds__(64, 2) void decode_bf16_kernel(Phase2Args a, Decode
     const int room = (free_hi < hi ? free_hi : hi) - base;
     n_whole = room > 0 ? room / STEP : 0;
   }
-  const size_t out = (((size_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j;
-  if (nsteps == 0) {                           // empty split (short block, unused tail)
-    if (live && j4 == 0) a.LSE_sub[out] = -INFINITY;
+  const size_t out0 = ((size_t)beta * a.plan.s_total + sp) * g.Hq * a.q_len;
+  if (KW == 1 && nsteps == 0) {                // empty split (short block, unused tail)
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+      if (live[b] && j4 == 0) a.LSE_sub[out0 + (size_t)head[b] * a.q_len + j[b]] = -INFINITY;
     return;
   }
 
@@ -294,39 +377,45 @@ __global__ __launch_bounds__(64, 2) void decode_bf16_kernel(Phase2Args a, Decode
   src.new_stride = g.Hkv * ROWB;
 
   // the query rows and the first step are requested before anything waits
-  DecState w;
-  {
-    GlobalBytes qrow = (GlobalBytes)a.Qq + (((size_t)beta * a.q_len + j) * g.Hq + (live ? head : kvh * g.G)) * ROWB;
+  DecState<RB> w;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) w.q[t] = __builtin_bit_cast(bf16x8, *(GlobalVec)(qrow + (32 * t + 8 * j4) * 2));
+  for (int b = 0; b < RB; ++b) {
+    GlobalBytes qrow = (GlobalBytes)a.Qq + (((size_t)beta * a.q_len + j[b]) * g.Hq + (live[b] ? head[b] : kvh * g.G)) * ROWB;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w.q[b][t] = __builtin_bit_cast(bf16x8, *(GlobalVec)(qrow + (32 * t + 8 * j4) * 2));
   }
   const unsigned koff = qc * ROWB + j4 * 16, voff = j4 * ROWB + qc * 16;
   StepRegs r;
   if (n_whole > 0) load_step<NT>(r, src, base, koff, voff);
   __builtin_amdgcn_sched_barrier(0);
   if (ROPE) {
+    static_assert(!ROPE || RB == 1, "a row per column");
     static_assert(D / 2 == 64, "a lane per pair");
     const double freq = rotary_frequency(lane, D, a.rotary.log2_theta);
     for (int t = 0; t < a.q_len; ++t)
       rotary_angle(a.rotary.pos0 + t, freq, &angles->cs[t][lane], &angles->sn[t][lane]);
-    __syncthreads();
-    rotate(w.q, *angles, j, j4);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    rotate(w.q[0], *angles, j[0], j4);
   }
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
-    if (!live) w.q[t] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};     // dead columns contribute zeros
+  for (int b = 0; b < RB; ++b) {
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) w.o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  w.m = -INFINITY;
-  w.neg_mc = 0.f;
-  w.l = 0.f;
+    for (int t = 0; t < 4; ++t)
+      if (!live[b]) w.q[b][t] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};     // dead columns contribute zeros
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) w.o[b][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    w.m[b] = -INFINITY;
+    w.neg_mc[b] = 0.f;
+    w.l[b] = 0.f;
+  }
 
-  // Algorithm 2, append: the new tokens whose rows fall into this split's steps
+  // Algorithm 2, append: the new tokens whose rows fall into this wavefront's steps
   // join the cache (16 lanes move one 256-byte row of K and of V).
   if (fused_append && hi > cache_len) {
     for (int key = cache_len + j4; key < hi; key += 4) {
       const int step = key / STEP;                          // another split's step?
-      if (a.plan.flat ? step - (int)quotient(step, by.splits) * a.plan.s_total != sp : key < base) continue;
+      if (KW > 1 || a.plan.flat ? step - (int)quotient(step, by.steps) * all_steps != first_step : key < base) continue;
       const size_t so = (size_t)(key - cache_len) * src.new_stride, dof = cache0 + (size_t)key * ROWB + qc * 16;
       i32x4 k = *(GlobalVec)(src.Kn + so + qc * 16);
       const i32x4 v = *(GlobalVec)(src.Vn + so + qc * 16);
@@ -346,7 +435,7 @@ __global__ __launch_bounds__(64, 2) void decode_bf16_kernel(Phase2Args a, Decode
     }
   }
 
-  const unsigned lds0 = (unsigned)(size_t)(LDS_AS char*)lds;
+  const unsigned lds0 = (unsigned)(size_t)(LDS_AS char*)lds + wave * STEPB;
   // V rows into LDS: lane writes row 4it + lane/16, chunk lane%16 (swizzled)
   unsigned vw[4];
 #pragma unroll
@@ -369,51 +458,78 @@ __global__ __launch_bounds__(64, 2) void decode_bf16_kernel(Phase2Args a, Decode
   // is requested into them: it arrives behind this one's softmax and products, and those of the
   // other wavefronts of the CU.
   for (int s = 0; s < n_whole; ++s) {
-    Scores x;
+    Scores<RB> x;
     score_step(w, r, vw, x);
     if (s + 1 < n_whole) load_step<NT>(r, src, base + (s + 1) * stride, koff, voff);
     __builtin_amdgcn_sched_barrier(0);
     attend_step(w, x, vaddr, c);
   }
-  const int row_lim = live ? (int)visible_limit(a, j) : 0;
-  const int lim = row_lim < hi ? row_lim : hi;
+  int lim[RB];
+#pragma unroll
+  for (int b = 0; b < RB; ++b) {
+    const int row_lim = live[b] ? (int)visible_limit(a, j[b]) : 0;
+    lim[b] = row_lim < hi ? row_lim : hi;
+  }
   for (int s = n_whole; s < nsteps; ++s) {
-    Scores x;
+    Scores<RB> x;
     load_last<ROPE>(r, src, base + s * stride, hi, lane, angles);
     score_step(w, r, vw, x);
     mask_step(x, base + s * stride, lim, j4);
     attend_step(w, x, vaddr, c);
   }
 
-  float l_tot = w.l + xor16(w.l);
-  l_tot = xor32_sum(l_tot);
-  if (live) {
-    float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  if (KW > 1) {
+    meet<RB, KW>(a, meeting, w, R, c, [&](int row) {
+      const int token = quotient(row, by.G);
+      return out0 + (size_t)(kvh * g.G + row - token * g.G) * a.q_len + token;
+    });
+    return;
+  }
+#pragma unroll
+  for (int b = 0; b < RB; ++b) {
+    const float l_tot = xor32_sum(w.l[b] + xor16(w.l[b]));
+    if (!live[b]) continue;
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const size_t out = out0 + (size_t)head[b] * a.q_len + j[b];
     float* orow = a.O_sub + out * D;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) *(f32x4*)(orow + 16 * dt + 4 * j4) = w.o[dt] * inv;
+    for (int dt = 0; dt < 8; ++dt) *(f32x4*)(orow + 16 * dt + 4 * j4) = w.o[b][dt] * inv;
     if (j4 == 0)
-      a.LSE_sub[out] = l_tot > 0.f ? (w.m * c + __builtin_amdgcn_logf(l_tot)) * LN2 : -INFINITY;
+      a.LSE_sub[out] = l_tot > 0.f ? (w.m[b] * c + __builtin_amdgcn_logf(l_tot)) * LN2 : -INFINITY;
   }
+}
+
+template <bool NT, bool ROPE, int RB, int KW>
+hipError_t launch(const Phase2Args& a, hipStream_t st) {
+  const Geom& g = a.g;
+  const dim3 grid((unsigned)a.plan.s_total, (unsigned)g.Hkv, (unsigned)g.B);
+  const DecodeDiv by = {make_div((uint32_t)a.plan.s_total * KW), make_div(g.G)};
+  decode_bf16_kernel<NT, ROPE, RB, KW><<<grid, 64 * KW, sizeof(Meeting<RB, KW>) + (ROPE ? KW * sizeof(Angles) : 0), st>>>(a, by);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_phase2_decode_bf16(const Phase2Args& a, hipStream_t st) {
   const Geom& g = a.g;
-  if (g.Hkv > 65535 || g.B > 65535) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)a.plan.s_total, (unsigned)g.Hkv, (unsigned)g.B);
-  const DecodeDiv by = {make_div(a.plan.s_total), make_div(g.G)};
+  const int64_t rows = (int64_t)g.G * a.q_len;
+  const int waves = a.plan.waves;
+  if (g.Hkv > 65535 || g.B > 65535 || rows > 64 || (waves > 1 && !a.plan.flat)) return hipErrorInvalidValue;
   const bool resident = decode_cache_resident(g, visible_total(a));
   if (a.rotary.log2_theta != 0) {
-    if (a.q_len > ROPE_TOKENS) return hipErrorInvalidValue;
-    if (resident) decode_bf16_kernel<false, true><<<grid, 64, 0, st>>>(a, by);
-    else decode_bf16_kernel<true, true><<<grid, 64, 0, st>>>(a, by);
-  } else {
-    if (resident) decode_bf16_kernel<false, false><<<grid, 64, 0, st>>>(a, by);
-    else decode_bf16_kernel<true, false><<<grid, 64, 0, st>>>(a, by);
+    if (rows > 16 || a.q_len > ROPE_TOKENS) return hipErrorInvalidValue;
+    if (waves == 4) return launch<false, true, 1, 4>(a, st);
+    return resident ? launch<false, true, 1, 1>(a, st) : launch<true, true, 1, 1>(a, st);
   }
-  return hipGetLastError();
+  if (rows <= 16) {
+    if (waves == 4) return launch<false, false, 1, 4>(a, st);
+    return resident ? launch<false, false, 1, 1>(a, st) : launch<true, false, 1, 1>(a, st);
+  }
+  if (rows <= 32) {
+    if (waves == 2) return launch<false, false, 2, 2>(a, st);
+    return resident ? launch<false, false, 2, 4>(a, st) : launch<true, false, 2, 4>(a, st);
+  }
+  return rows <= 48 ? launch<true, false, 3, 4>(a, st) : launch<true, false, 4, 4>(a, st);
 }
 
 }  // namespace star

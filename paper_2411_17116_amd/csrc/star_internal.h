@@ -46,6 +46,8 @@ struct SplitPlan {
   int32_t decode;      // 1: streaming split-KV kernel, 0: row-tiled kernel
   int32_t flat;        // 1: splits ignore part boundaries
   int32_t tile_rows;   // row-tiled kernels: rows per workgroup (bf16 256 or 128, fp32 32 or 16)
+  int32_t waves;       // decode kernel: wavefronts that share a split (more than one: flat plans only), taking
+                       // its steps in turn: wavefront w of split s the steps s * waves + w, + S * waves, ...
 };
 
 // Geometry every kernel needs.  Strides are in elements.
@@ -161,7 +163,7 @@ __host__ __device__ inline bool decode_cache_resident(const Geom& g, int64_t tot
 // heads) 14.4 / 12.4, 4 tokens 15.9 / 13.8, 5 on 3000 (12 / 4) 12.3 / 10.1, 8 on 8191 (16 / 16) 18.6 / 18.7, 16 tokens
 // 19.9 / 22.2.
 constexpr int DECODE_ROPE_TOKENS = 8;
-inline int decode_workgroups_per_cu(bool resident) { return resident ? 4 : 3; }
+inline int decode_wavefronts_per_cu(bool resident) { return resident ? 4 : 3; }
 
 // Key range [lo, hi) of split s of a plan other than the decode kernel's flat one (hi
 // clipped to what exists for this call).
