@@ -722,7 +722,13 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   if (direct) return STAR_ATTN_OK;
 
   MergeArgs m;
-  m.g = g; m.plan = plan; m.q_len = (int32_t)q_len; m.out_bf16 = shape->dtype == STAR_ATTN_BF16;
+  m.g = g; m.plan = plan;
+  // Without per-part outputs the splits of all parts are merged at once, whatever they were cut along: part
+  // by part it is a chain of round trips.  us (8 / 2 heads): 21 tokens on 16384 keys in blocks of 2048 32.2 -> 15.9, 84 on
+  // 4096 in blocks of 1024 21.1 -> 15.9, 64 on 1024 in blocks of 256 18.4 -> 14.3; 23 on 2048 (32 / 8 heads) 19.1 -> 14.3.
+  // (The kernels of one part number a row's pieces in one launch.)
+  if (!O_part && (int64_t)g.B * g.Hq * q_len <= (1 << 22)) m.plan.flat = 1;
+  m.q_len = (int32_t)q_len; m.out_bf16 = shape->dtype == STAR_ATTN_BF16;
   m.O_sub = a.O_sub; m.LSE_sub = a.LSE_sub; m.O_part = O_part; m.LSE_part = LSE_part;
   m.batch_stride = (int64_t)plan.s_total * g.Hq * q_len;
   m.split_stride = (int64_t)g.Hq * q_len;

@@ -53,6 +53,32 @@ def test_row_tile_edges(B, Hq, Hkv, L, b, a, lq, gamma, tiles):
         assert not run.Kc[:, g, L + lq:].any()
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L,b,lq", [
+    (1, 8, 2, 1024, 256, 64),       # a split per block and one behind
+    (1, 8, 2, 750, 256, 47),        # the last block short
+    (1, 8, 2, 4096, 1024, 84),      # four splits per block
+    (2, 16, 16, 1024, 512, 40),
+    (1, 12, 4, 1024, 1024, 30),
+])
+def test_splits_along_blocks_without_per_part_outputs(B, Hq, Hkv, L, b, lq):
+    """Splits that follow the blocks are merged at once where no per-part outputs are asked for; the result is that
+    of the call which writes them."""
+    gen = torch.Generator(device="cuda").manual_seed(L + lq)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)
+    cap = L + lq
+    shape = sa.StarShape.make("bf16", B, Hq, Hkv, 128, L, b, 0, cap)
+    assert sa.phase2_plan(shape, L, lq).flat == 0
+    Kc, Vc, Q, K, V = rnd(B, Hkv, cap, 128), rnd(B, Hkv, cap, 128), rnd(B, lq, Hq, 128), rnd(B, lq, Hkv, 128), rnd(B, lq, Hkv, 128)
+    ws, got, want = sa.alloc_workspace(shape, lq), torch.empty_like(Q), torch.empty_like(Q)
+    parts = -(-L // b) + 1
+    O_part, LSE_part = torch.empty((B, parts, Hq, lq, 128), device="cuda"), torch.empty((B, parts, Hq, lq), device="cuda")
+    sa.phase2(shape, L, Q, K, V, Kc, Vc, got, ws)
+    sa.phase2(shape, L, Q, K, V, Kc, Vc, want, ws, O_part=O_part, LSE_part=LSE_part)
+    torch.cuda.synchronize()
+    # fp32 folds in another order before one rounding to bf16: no more than neighbouring values
+    torch.testing.assert_close(got.float(), want.float(), rtol=2.0 ** -7, atol=1e-4)
+
+
 def test_workspace_covers_every_shorter_call():
     """Whatever a call of at most max_q tokens on a cache of any length plans fits what
     star_attn_workspace_bytes asked for."""
