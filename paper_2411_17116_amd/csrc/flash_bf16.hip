@@ -903,20 +903,25 @@ __device__ __forceinline__ void phase1_item(const Phase1Args& a, int hpw, int tp
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     float l_tot = H == 1 ? quad_sum(w.l[rb]) : l_half[rb];
-    if (active[rb] && (H == 1 || half == 0)) {
-      float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-      char* orow = (char*)a.O + (((size_t)beta * g.L + tok[rb]) * g.Hq + head[rb]) * ROWB;
+    const bool mine = active[rb] && (H == 1 || half == 0);      // (the same for the four lanes of a row)
+    // A lane holds four elements of every 16; lane rows 2 j and 2 j + 1 exchange halves of two such pieces, so that a
+    // store is 16 bytes a lane and 64 a row.  Against 8 and 32, us: 64 / 8 heads, two sequences of 12289 (a = 1024) 2205 -> 2184,
+    // 65536 tokens (b = 4096, a = 512) 4935 -> 4854; 32 / 8 heads, L = 300 10.9 -> 10.6.
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    char* orow = (char*)a.O + (((size_t)beta * g.L + tok[rb]) * g.Hq + head[rb]) * ROWB;
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        bf16x4 v;
+    for (int dt = 0; dt < 8; dt += 2) {
+      bf16x4 v[2];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = (__bf16)(w.o[rb][dt][k] * inv);
-        *(bf16x4*)(orow + (16 * dt + 4 * j4) * 2) = v;
-      }
-      if (a.LSE && j4 == 0)
-        a.LSE[((size_t)beta * g.Hq + head[rb]) * g.L + tok[rb]] =
-            l_tot > 0.f ? (w.m[rb] * g.scale * LOG2E + __builtin_amdgcn_logf(l_tot)) * LN2 : -INFINITY;
+      for (int k = 0; k < 4; ++k) { v[0][k] = (__bf16)(w.o[rb][dt][k] * inv); v[1][k] = (__bf16)(w.o[rb][dt + 1][k] * inv); }
+      const uint2 x = __builtin_bit_cast(uint2, v[0]), y = __builtin_bit_cast(uint2, v[1]);
+      const auto lo = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+      if (mine) *(i32x4*)(orow + (16 * (dt + (j4 & 1)) + 4 * (j4 & 2)) * 2) = i32x4{(int)lo[0], (int)hi[0], (int)lo[1], (int)hi[1]};
     }
+    if (mine && a.LSE && j4 == 0)
+      a.LSE[((size_t)beta * g.Hq + head[rb]) * g.L + tok[rb]] =
+          l_tot > 0.f ? (w.m[rb] * g.scale * LOG2E + __builtin_amdgcn_logf(l_tot)) * LN2 : -INFINITY;
   }
 
   // Algorithm 1, "keep the block's K/V": the workgroup files the K and V rows of
