@@ -150,8 +150,8 @@ static int64_t stream_splits(const Geom& g, int64_t keys, int waves) {
 }
 constexpr int64_t STREAM_PAIRED_KEYS = 64 * 32;
 
-// ---- fp32 kernel: tiles of 16 rows shared by eight wavefronts (one workgroup per CU), or
-// of 32 rows shared by four (two per CU).
+// ---- fp32 kernel: tiles of 16 rows shared by eight wavefronts (one workgroup per CU) or, for short runs of
+// one tile per KV head, by four, or of 32 rows shared by four (two per CU).
 // Most splits: what the resident workgroups can take at once, and never more than
 // 4096 / (B Hq ceil(q / 64)), which bounds the per-split pairs a call keeps.
 static int64_t f32_splits_max(const Geom& g, int64_t q_len, int tile) {
@@ -160,6 +160,16 @@ static int64_t f32_splits_max(const Geom& g, int64_t q_len, int tile) {
   return fill < 1 ? 1 : fill < bound ? fill : bound;
 }
 constexpr int64_t F32_SPLIT_MIN = 128;     // keys: one or two 16-key units for each wavefront
+// Runs of 64 keys, one unit for each of four wavefronts, where a KV head's rows are one tile and all the runs start at
+// once: what counts is the chain of units a wavefront walks.  More than 128 runs cost more to merge than
+// they save.  us per call of one row against eight wavefronts and 128 keys: 1024 keys (1 head, d = 64) 8.7 -> 8.0, 4000 (8 / 2
+// heads, d = 128) 11.3 -> 9.1, 8000 (1 head, d = 128) 11.3 -> 9.7, 16000 (8 / 2, d = 64) 9.5 -> 8.9; with more runs than start
+// at once, two sequences of 9000 (8 / 2, d = 128) 12.1 as it was and 13.2 so.  0: not such a call.
+static int64_t f32_short_runs(const Geom& g, int64_t q_len, int64_t total) {
+  const int64_t worth = ceil_div(total, 64), runs = worth < 128 ? worth : 128;
+  return (int64_t)g.G * q_len <= 16 && (int64_t)g.B * g.Hkv * runs <= 256 &&
+                 runs <= ceil_div(4096, (int64_t)g.B * g.Hq * ceil_div(q_len, 64)) ? runs : 0;
+}
 // Rows per tile: 16 while those tiles with splits of that size leave CUs idle or fill them
 // about twice (a unit of 16 keys then takes half as long), 32 beyond.  Measured, us, against
 // 32-row tiles shared by eight wavefronts, one workgroup per CU (8 / 2 heads, d = 128):
@@ -329,10 +339,15 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   }
   if (s->dtype == STAR_ATTN_F32 && !want_parts) {
     p->tile_rows = f32_tile_rows(g, q_len, total);
-    int64_t splits = f32_splits_max(g, q_len, p->tile_rows);
-    if (splits > ceil_div(total, F32_SPLIT_MIN)) splits = ceil_div(total, F32_SPLIT_MIN);
+    int64_t splits = f32_short_runs(g, q_len, total);
+    p->waves = splits > 0 ? 4 : 8;
+    if (splits == 0) {
+      splits = f32_splits_max(g, q_len, p->tile_rows);
+      if (splits > ceil_div(total, F32_SPLIT_MIN)) splits = ceil_div(total, F32_SPLIT_MIN);
+    }
     if (total * g.d * 8 <= F32_DIRECT_BYTES) splits = 1;
     if (splits > fit) splits = fit;
+    if (splits == 1) p->waves = 8;
     p->flat = 1;
     p->split_len = round_up(ceil_div(total, splits), 32);
     p->spb = 0;
@@ -464,6 +479,10 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
       if (make_plan(shape, q, shape->cache_capacity, false, &f)) need(f.s_total > s0 ? f.s_total : s0, q);
     } else if (shape->dtype == STAR_ATTN_F32) {
       const int64_t worth = ceil_div(g.cap, F32_SPLIT_MIN);
+      if ((int64_t)g.G * q <= 16) {       // the most short runs of any length of the cache
+        const int64_t all = 256 / ((int64_t)g.B * g.Hkv), most = all < 128 ? all : 128, short_worth = ceil_div(g.cap, 64);
+        if (most > 0) need(most < short_worth ? most : short_worth, q);
+      }
       for (int tile = 16; tile <= 32; tile += 16) {
         const int64_t most = f32_splits_max(g, q, tile);
         need(most < worth ? most : worth, q);

@@ -648,6 +648,7 @@ hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st) {
   if (a.plan.tile_rows == 32 && !a.plan.flat && a.plan.split_len <= 4 * UNIT)
     return a.g.d == 64 ? launch_phase2<64, 2, 1>(a, st) : launch_phase2<128, 2, 1>(a, st);
   if (a.plan.tile_rows == 32) return a.g.d == 64 ? launch_phase2<64, 2, 4>(a, st) : launch_phase2<128, 2, 4>(a, st);
+  if (a.plan.waves == 4) return a.g.d == 64 ? launch_phase2<64, 1, 4>(a, st) : launch_phase2<128, 1, 4>(a, st);
   return a.g.d == 64 ? launch_phase2<64, 1, 8>(a, st) : launch_phase2<128, 1, 8>(a, st);
 }
 

@@ -48,6 +48,7 @@ struct SplitPlan {
   int32_t tile_rows;   // row-tiled kernels: rows per workgroup (bf16 256 or 128, fp32 32 or 16)
   int32_t waves;       // decode kernel: wavefronts that share a split (more than one: flat plans only), taking
                        // its steps in turn: wavefront w of split s the steps s * waves + w, + S * waves, ...
+                       // fp32 kernel: wavefronts that share a 16-row tile (4; anything else: 8)
 };
 
 // Geometry every kernel needs.  Strides are in elements.

@@ -1,0 +1,49 @@
+"""fp32 phase-2 calls whose rows are one 16-row tile per KV head, cut into equal runs of 64 keys and more: at the edges
+of the units, of the tile and of the rule, against plain fp64 attention."""
+import math
+
+import pytest
+import torch
+
+import paper_2411_17116_amd as sa
+from tests import parity_harness as ph
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,q,splits", [
+    (1, 1, 1, 64, 511, 1, 1),          # 256 KiB of K + V: one workgroup
+    (1, 1, 1, 64, 512, 1, 9),          # a run of one key at the end
+    (2, 6, 2, 64, 1000, 5, 16),        # 15 rows
+    (1, 16, 1, 128, 575, 1, 9),        # a whole tile; 64 keys to every run
+    (1, 17, 1, 128, 575, 1, 5),        # 17 rows: runs of 128 keys
+    (1, 2, 2, 128, 8150, 2, 128),      # 8152 keys: as many runs as are worth merging, all that start at once
+    (1, 3, 3, 128, 8150, 2, 64),       # more than that: runs of 128 keys
+])
+def test_short_runs(B, Hq, Hkv, d, L, q, splits):
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    cap, G = L + q + 30, Hq // Hkv
+    shape = sa.StarShape.make("fp32", B, Hq, Hkv, d, L, max(1, L // 4), 0, cap)
+    print(f"[{B} {Hq}/{Hkv} d={d} L={L} q={q}]", flush=True)
+    assert sa.phase2_plan(shape, L, q).n_splits == splits
+    Kc, Vc = new(B, Hkv, cap, d), new(B, Hkv, cap, d)
+    Q, K, V = new(B, q, Hq, d), new(B, q, Hkv, d), new(B, q, Hkv, d)
+    O, ws = torch.empty_like(Q), sa.alloc_workspace(shape, q)
+    A, lse = torch.empty((B, Hq, q, d), device="cuda"), torch.empty((B, Hq, q), device="cuda")
+    sa.phase2(shape, L, Q, K, V, Kc, Vc, O, ws)
+    sa.phase2_partial(shape, L + q, Q, Kc, Vc, A, lse, ws)      # a host's share: all L + q rows visible
+    torch.cuda.synchronize()
+    assert torch.equal(Kc[:, :, L:L + q], K.transpose(1, 2)) and torch.equal(Vc[:, :, L:L + q], V.transpose(1, 2))
+    tol = ph.TOL["fp32"]["o"]
+    for beta in range(B):
+        for g in range(Hkv):
+            hs = slice(g * G, (g + 1) * G)
+            k, v = Kc[beta, g, :L + q].double(), Vc[beta, g, :L + q].double()
+            s = Q[beta, :, hs].double().reshape(q * G, d) @ k.T / math.sqrt(d)
+            # (natural logarithms near log(L): a few ulp of 5e-7)
+            assert (lse[beta, hs].T.reshape(-1) - torch.logsumexp(s, 1)).abs().max().item() <= 1e-5
+            assert (A[beta, hs].double() - (torch.softmax(s, 1) @ v).view(q, G, d).transpose(0, 1)).abs().max().item() <= tol
+            bound = L + 1 + torch.arange(q, device="cuda").repeat_interleave(G)
+            s.masked_fill_(torch.arange(L + q, device="cuda")[None] >= bound[:, None], -math.inf)
+            assert (O[beta, :, hs].double() - (torch.softmax(s, 1) @ v).view(q, G, d)).abs().max().item() <= tol
