@@ -235,7 +235,7 @@ int star_attn_phase2(const star_attn_shape* shape,
  * address is looked up once per device, on the first call there).
  *
  *   - The scratch a call needs is star_attn_phase2_plan(...).workspace_bytes: at
- *     most 8.5 MB for any decode-sized call (G * q_len <= 16) on an MI355X, 0.2 to
+ *     most 8.5 MB for any decode-sized call (G * q_len <= 16) on an MI355X, 0.1 to
  *     tens of MB for query encoding.  A call that needs more than
  *     STAR_ATTN_STATIC_SCRATCH_BYTES is refused with
  *     STAR_ATTN_ERR_WORKSPACE_TOO_SMALL before anything is enqueued.

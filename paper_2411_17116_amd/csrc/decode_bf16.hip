@@ -253,8 +253,8 @@ __device__ __forceinline__ void attend_step(DecState<RB>& w, const Scores<RB>& x
   }
 }
 
-// LDS of a workgroup of KW wavefronts: a step's V of each; behind the key loop, a half of d at a time,
-// their results (row 16 b + lane % 16, 16-byte chunk of the half XORed with the row's low four bits).
+// LDS of a workgroup of KW wavefronts: a step's V of each; behind the key loop, a half of d at a time (a quarter where
+// that would pass 64 KiB), their results: row 16 b + lane % 16, 16-byte chunk of the piece XORed with the row's low bits.
 template <int RB, int KW>
 struct Meeting {
   union {
