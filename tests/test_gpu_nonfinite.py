@@ -16,9 +16,11 @@ def _tensors(dtype, seed, *sizes):
 
 
 # dtype, heads, KV heads, d, cached, new tokens: streaming decode, 128-row and 256-row tiles, fp32 in one
-# workgroup per tile, 16-row and 32-row tiles
+# workgroup per tile, 16-row and 32-row tiles; streamed calls of two wavefronts to a split, of four with one and two
+# blocks of rows, and of a cache beyond the last-level cache with four
 CALLS = [("bf16", 8, 2, 128, 1001, 1), ("bf16", 8, 2, 128, 1001, 33), ("bf16", 32, 8, 128, 9001, 300),
-         ("fp32", 4, 2, 64, 203, 3), ("fp32", 4, 2, 64, 3001, 3), ("fp32", 8, 2, 128, 5001, 100)]
+         ("fp32", 4, 2, 64, 203, 3), ("fp32", 4, 2, 64, 3001, 3), ("fp32", 8, 2, 128, 5001, 100),
+         ("bf16", 8, 2, 128, 1001, 5), ("bf16", 32, 8, 128, 8190, 1), ("bf16", 8, 2, 128, 4001, 7), ("bf16", 32, 8, 128, 50001, 15)]
 
 
 @pytest.mark.parametrize("parts", [False, True])
