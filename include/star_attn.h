@@ -315,9 +315,11 @@ int star_attn_merge(const star_attn_shape* shape, int64_t n_parts, int64_t q_len
  *
  * star_attn_phase1_rope / star_attn_phase2_rope are star_attn_phase1 /
  * star_attn_phase2 on unrotated Q and K:
- *   Q, Qq   in/out  rotated IN PLACE (on return they hold the rotated queries)
+ *   Q, Qq   in/out  rotated IN PLACE (on return they hold the rotated queries, or O
+ *                   where a phase-2 call's O is the same buffer)
  *   K, Kq   in      unrotated; they are rotated on their way into K_cache, so
- *                   the cache holds rotated keys (what later calls attend to)
+ *                   the cache holds rotated keys (what later calls attend to); Kq and Vq
+ *                   may be the cache rows that they are appended to
  *   rope_theta      base of the frequencies, > 1 (e.g. 10000, 500000)
  *   pos0            position of context token 0, >= 0
  * Every other argument, the outputs and the error codes are those of the plain

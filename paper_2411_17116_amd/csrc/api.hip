@@ -419,6 +419,9 @@ static size_t plan_bytes(const star_attn_shape* s, const SplitPlan& p, int64_t q
 }
 
 static bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
+static bool overlap(const void* x, size_t nx, const void* y, size_t ny) {
+  return (uintptr_t)x < (uintptr_t)y + ny && (uintptr_t)y < (uintptr_t)x + nx;
+}
 
 // Rotary embedding requested by the *_rope entry points (theta == 0: none).
 struct Rope {
@@ -710,9 +713,13 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   // Algorithm 2: the new tokens' K/V join the cache before they attend.  The
   // attention kernels append them themselves (they read the new rows from Kq/Vq and
   // write them to the cache).  Unrotated keys are rotated into the cache first.
-  // (A few rotated tokens on the decode kernel's equal runs are turned there, and by the merge.)
+  // (A few rotated tokens on the decode kernel's equal runs are turned there, and by the merge.  Not where O is
+  // stored over Qq, which one launch would both merge into and rotate, nor where Kq are rows of the cache, which
+  // would be read behind their rotation.)
+  const size_t q_bytes = (size_t)g.B * q_len * g.Hq * g.d * 2, k_bytes = (size_t)g.B * q_len * g.Hkv * g.d * 2;
   const bool turn = append && rope && plan.decode && plan.flat && g.G * q_len <= 16 && q_len <= DECODE_ROPE_TOKENS &&
-                    (int64_t)g.B * g.Hq * q_len <= (1 << 20);
+                    (int64_t)g.B * g.Hq * q_len <= (1 << 20) && !overlap(O, q_bytes, Qq, q_bytes) &&
+                    !overlap(Kq, k_bytes, K_cache, (size_t)g.B * g.Hkv * g.cap * g.d * 2);
   const bool fused_append = append && (!rope || turn);
   if (append && rope && !turn &&
       launch_rope(shape->dtype, g, g.Hq, Qq, Qq, Kq, Vq, K_cache, V_cache, q_len, cache_len,

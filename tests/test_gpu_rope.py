@@ -260,3 +260,36 @@ def test_decode_on_unrotated_projections_is_decode_on_rotated_ones(B, Hq, Hkv, L
     assert torch.equal(O, O2)
     assert torch.equal(Q, Qr)
     assert torch.equal(Kc, Kc2) and torch.equal(Vc, Vc2)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,q", [
+    (1, 16, 1, 700, 1),
+    (1, 2, 1, 61, 8),           # eight tokens in two 32-key steps
+    (1, 4, 1, 9000, 4),         # four wavefronts to a split
+    (5, 64, 32, 500, 2),        # merged by rows
+])
+def test_decode_on_unrotated_projections_in_shared_buffers(B, Hq, Hkv, L, q):
+    """O stored over Qq, and new keys and values that are their own cache rows already, give the bits of buffers
+    of their own."""
+    gen = torch.Generator(device="cuda").manual_seed(L + q)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)
+    shape = sa.StarShape.make("bf16", B, Hq, Hkv, 128, L, max(1, L // 4), 0, L + q)
+    assert sa.phase2_plan(shape, L, q).decode == 1
+    Kc, Vc = new(B, Hkv, L + q, 128), new(B, Hkv, L + q, 128)
+    Q, K, V = new(B, q, Hq, 128), new(B, q, Hkv, 128), new(B, q, Hkv, 128)
+    ws, theta = sa.alloc_workspace(shape, q), 500000.0
+    Q1, Kc1, Vc1, O = Q.clone(), Kc.clone(), Vc.clone(), torch.empty_like(Q)
+    sa.phase2_rope(shape, theta, L, Q1, K, V, Kc1, Vc1, O, ws)
+    print(f"[{B} {Hq}/{Hkv} L={L} q={q}]", flush=True)
+    Q2, Kc2, Vc2 = Q.clone(), Kc.clone(), Vc.clone()
+    sa.phase2_rope(shape, theta, L, Q2, K, V, Kc2, Vc2, Q2, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(Q2, O) and torch.equal(Kc2, Kc1) and torch.equal(Vc2, Vc1)
+    if B * Hkv > 1:                       # elsewhere a call's tokens do not lie as the cache's rows do
+        return
+    Q3, Kc3, Vc3 = Q.clone(), Kc.clone(), Vc.clone()
+    Kc3[0, 0, L:], Vc3[0, 0, L:] = K[0, :, 0], V[0, :, 0]
+    O3 = torch.empty_like(Q)
+    sa.phase2_rope(shape, theta, L, Q3, Kc3[0, 0, L:].view(1, q, 1, 128), Vc3[0, 0, L:].view(1, q, 1, 128), Kc3, Vc3, O3, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(O3, O) and torch.equal(Q3, Q1) and torch.equal(Kc3, Kc1) and torch.equal(Vc3, Vc1)
