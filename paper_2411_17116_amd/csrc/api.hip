@@ -750,10 +750,12 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   MergeArgs m;
   m.g = g; m.plan = plan;
   // Without per-part outputs the splits of all parts are merged at once, whatever they were cut along: part
-  // by part it is a chain of round trips.  us (8 / 2 heads): 21 tokens on 16384 keys in blocks of 2048 32.2 -> 15.9, 84 on
-  // 4096 in blocks of 1024 21.1 -> 15.9, 64 on 1024 in blocks of 256 18.4 -> 14.3; 23 on 2048 (32 / 8 heads) 19.1 -> 14.3.
-  // (The kernels of one part number a row's pieces in one launch.)
-  if (!O_part && (int64_t)g.B * g.Hq * q_len <= (1 << 22)) m.plan.flat = 1;
+  // by part it is a chain of round trips.  us (8 / 2 heads), part by part / at once: 21 tokens on 16384 keys in blocks of
+  // 2048 34.7 / 19.4, of 256 73.4 / 19.7, 84 on 4096 in blocks of 1024 23.7 / 18.6, 64 on 1024 in blocks of 256 18.5 / 14.8;
+  // 23 on 2048 (32 / 8 heads) 20.2 / 16.2.  The sums are held in 64 bits, as merge part by part compensates its own (in
+  // 32 bits: 18.3, 18.4, 18.1, 14.4, 15.7).  (The kernels of one part number a row's pieces in one launch.)
+  m.wide = 0;
+  if (!O_part && !plan.flat && (int64_t)g.B * g.Hq * q_len < (1 << 22)) { m.plan.flat = 1; m.wide = 1; }
   m.q_len = (int32_t)q_len; m.out_bf16 = shape->dtype == STAR_ATTN_BF16;
   m.O_sub = a.O_sub; m.LSE_sub = a.LSE_sub; m.O_part = O_part; m.LSE_part = LSE_part;
   m.batch_stride = (int64_t)plan.s_total * g.Hq * q_len;
@@ -819,7 +821,7 @@ int star_attn_merge(const star_attn_shape* shape, int64_t n_parts, int64_t q_len
   m.split_stride = rows;
   m.O_part = nullptr; m.LSE_part = nullptr;
   m.O = O; m.A = A; m.LSE = LSE;
-  m.Qq = nullptr; m.rotary = Rotary{0.0, 0};
+  m.Qq = nullptr; m.rotary = Rotary{0.0, 0}; m.wide = 0;
   return launch_merge(m, (hipStream_t)hip_stream) == hipSuccess ? STAR_ATTN_OK
                                                                 : STAR_ATTN_ERR_LAUNCH_FAILED;
 }

@@ -28,7 +28,7 @@
 // Traffic is s_total * (d + 1) floats per row -- negligible next to the cache.
 //
 // The fold over parts keeps a compensation term per accumulator (Kahan
-// summation): a context cut into hundreds of small blocks is hundreds of
+// summation; 64-bit sums where all splits are folded at once): a context cut into hundreds of small blocks is hundreds of
 // sequential additions, and in fp32 their rounding errors would otherwise add up
 // to the 1e-5 the fp32 path is held to.
 #include "rotary.h"
@@ -292,12 +292,20 @@ __device__ __forceinline__ float weight(float x) {
 }
 
 // What one lane gathers: the weighted sum of its four elements of the splits' outputs, the
-// sum of weights, both relative to exp(m).
+// sum of weights, both relative to exp(m).  Sum is double where the splits follow blocks (MergeArgs::wide),
+// of which there may be hundreds: float sums of 64 and 128 of them were off by up to 1.3 and 1.6e-7, these round twice.
+template <typename Sum>
 struct Fold {
-  float m, w;
-  f32x4 acc;
+  typedef __attribute__((ext_vector_type(4))) Sum Sum4;
+  float m;
+  Sum w;
+  Sum4 acc;
 };
-__device__ __forceinline__ Fold empty_fold() { return Fold{-INFINITY, 0.f, f32x4{0.f, 0.f, 0.f, 0.f}}; }
+template <typename Sum>
+__device__ __forceinline__ Fold<Sum> empty_fold() {
+  typedef typename Fold<Sum>::Sum4 Sum4;
+  return Fold<Sum>{-INFINITY, Sum(0), Sum4{Sum(0), Sum(0), Sum(0), Sum(0)}};
+}
 __device__ __forceinline__ float finite(float m) { return m == -INFINITY ? 0.f : m; }
 
 template <int N>
@@ -308,24 +316,26 @@ __device__ __forceinline__ float largest(const float (&ls)[N]) {
   return m;
 }
 // N splits at once: `ls` their log-sum-exps (-inf: empty, `v` unset), none above `m`.
-template <int N>
-__device__ __forceinline__ void fold_splits(Fold& f, const float (&ls)[N], const f32x4 (&v)[N], float m) {
+template <typename Sum, int N>
+__device__ __forceinline__ void fold_splits(Fold<Sum>& f, const float (&ls)[N], const f32x4 (&v)[N], float m) {
   m = fmaxf(m, f.m);
-  const float mm = finite(m), old = weight(f.m - mm);
+  const float mm = finite(m);
+  const Sum old = weight(f.m - mm);
   f.w *= old;
   f.acc *= old;
 #pragma unroll
   for (int u = 0; u < N; ++u) {
-    const float w = weight(ls[u] - mm);
+    const Sum w = weight(ls[u] - mm);
     f.w += w;
     const f32x4 x = ls[u] == -INFINITY ? f32x4{0.f, 0.f, 0.f, 0.f} : v[u];
-    f.acc += x * w;                          // (one rounding: the product must not pass a select)
+    f.acc += __builtin_convertvector(x, typename Fold<Sum>::Sum4) * w;      // (one rounding: the product must not pass a select)
   }
   f.m = m;
 }
-__device__ __forceinline__ void store_merged(const MergeArgs& a, int beta, int h, int64_t j, int d0, const Fold& f) {
+template <typename Sum>
+__device__ __forceinline__ void store_merged(const MergeArgs& a, int beta, int h, int64_t j, int d0, const Fold<Sum>& f) {
   const Geom& g = a.g;
-  const f32x4 out = f.w > 0.f ? f.acc / f.w : f32x4{0.f, 0.f, 0.f, 0.f};
+  const f32x4 out = f.w > 0 ? __builtin_convertvector(f.acc / f.w, f32x4) : f32x4{0.f, 0.f, 0.f, 0.f};
   const int64_t orow = ((int64_t)beta * a.q_len + j) * g.Hq + h, arow = ((int64_t)beta * g.Hq + h) * a.q_len + j;
   if (a.A) *(f32x4*)(a.A + arow * g.d + d0) = out;
   if (a.O) {
@@ -338,7 +348,7 @@ __device__ __forceinline__ void store_merged(const MergeArgs& a, int beta, int h
       *(f32x4*)((float*)a.O + orow * g.d + d0) = out;
     }
   }
-  if (a.LSE && d0 == 0) a.LSE[arow] = f.w > 0.f ? f.m + logf(f.w) : -INFINITY;
+  if (a.LSE && d0 == 0) a.LSE[arow] = f.w > 0 ? f.m + logf((float)f.w) : -INFINITY;
 }
 
 // A wavefront turns row (beta, h, j) of the call's queries, a lane per pair (bf16, d = 128).  Workgroups
@@ -355,11 +365,12 @@ __device__ __forceinline__ void rotate_query(const MergeArgs& a, int beta, int h
 // One workgroup per (row, piece of 4 LPS elements of d): LPS lanes per split, the others
 // walk the splits, INFL in flight per lane.  grid: x = token * pieces + piece (and, behind them, a token
 // each to rotate), y = head, z = batch.
-template <int LPS, int THREADS, int INFL>
+template <int LPS, int THREADS, int INFL, typename Sum>
 __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
   constexpr int GROUPS = THREADS / LPS, WAVES = THREADS / 64;
-  __shared__ float red_m[WAVES], red_w[WAVES];
-  __shared__ f32x4 red_acc[WAVES][LPS];
+  __shared__ float red_m[WAVES];
+  __shared__ Sum red_w[WAVES];
+  __shared__ typename Fold<Sum>::Sum4 red_acc[WAVES][LPS];
   const Geom& g = a.g;
   const int tid = threadIdx.x, li = tid % LPS, grp = tid / LPS;
   const int h = blockIdx.y, beta = blockIdx.z, S = a.plan.s_total;
@@ -373,7 +384,7 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
 
   // the weights of a step are taken against the maximum of its splits over the whole wavefront:
   // the groups' sums then meet without another weight
-  Fold f = empty_fold();
+  Fold<Sum> f = empty_fold<Sum>();
   for (int s0 = 0; s0 < S; s0 += INFL * GROUPS) {
     float ls[INFL];
     f32x4 v[INFL];
@@ -388,7 +399,7 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
     float m = largest<INFL>(ls);
 #pragma unroll
     for (int x = LPS; x < 64; x <<= 1) m = fmaxf(m, __shfl_xor(m, x));
-    fold_splits<INFL>(f, ls, v, m);
+    fold_splits<Sum, INFL>(f, ls, v, m);
   }
   // the groups of a wavefront, then the wavefronts
 #pragma unroll
@@ -403,13 +414,13 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
   }
   __syncthreads();
   if (tid >= LPS) return;
-  f = empty_fold();
+  f = empty_fold<Sum>();
 #pragma unroll
   for (int k = 0; k < WAVES; ++k) f.m = fmaxf(f.m, red_m[k]);
   const float mm = finite(f.m);
 #pragma unroll
   for (int k = 0; k < WAVES; ++k) {
-    const float w = weight(red_m[k] - mm);
+    const Sum w = weight(red_m[k] - mm);
     f.w += red_w[k] * w;
     f.acc += red_acc[k][li] * w;
   }
@@ -421,7 +432,7 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
 struct RowsDiv {
   Div q_len, Hq;
 };
-template <int D, int INFL>
+template <int D, int INFL, typename Sum>
 __global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, RowsDiv by, unsigned n_rows, unsigned first_wg) {
   constexpr int LPR = D / 4;
   const Geom& g = a.g;
@@ -436,7 +447,7 @@ __global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, RowsD
   }
   const int d0 = 4 * (tid % LPR), S = a.plan.s_total;
   const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;
-  Fold f = empty_fold();
+  Fold<Sum> f = empty_fold<Sum>();
   for (int s0 = 0; s0 < S; s0 += INFL) {
     float ls[INFL];
     f32x4 v[INFL];
@@ -447,17 +458,46 @@ __global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, RowsD
       v[u] = *(const f32x4*)(a.O_sub + r * D + d0);
       if (s0 + u >= S) ls[u] = -INFINITY;
     }
-    fold_splits<INFL>(f, ls, v, largest<INFL>(ls));
+    fold_splits<Sum, INFL>(f, ls, v, largest<INFL>(ls));
   }
   store_merged(a, (int)beta, (int)h, j, d0, f);
 }
 
-template <int LPS, int THREADS, int INFL>
+template <int LPS, int THREADS, int INFL, typename Sum>
 hipError_t launch_flat(const MergeArgs& a, hipStream_t st) {
   const int turn = a.rotary.log2_theta != 0 ? a.q_len : 0;
   const dim3 grid((unsigned)(a.q_len * (a.g.d / (4 * LPS)) + turn), (unsigned)a.g.Hq, (unsigned)a.g.B);
-  merge_flat_kernel<LPS, THREADS, INFL><<<grid, THREADS, 0, st>>>(a);
+  merge_flat_kernel<LPS, THREADS, INFL, Sum><<<grid, THREADS, 0, st>>>(a);
   return hipGetLastError();
+}
+
+template <typename Sum>
+hipError_t merge_one_part(const MergeArgs& a, int64_t rows, hipStream_t st) {
+  const int S = a.plan.s_total;
+  if (S <= 8 && rows >= 64) {
+    const int64_t wgs = a.g.d == 64 ? (rows + 15) / 16 : (rows + 7) / 8, turn = a.rotary.log2_theta != 0 ? (rows + 3) / 4 : 0;
+    const RowsDiv by = {make_div(a.q_len), make_div(a.g.Hq)};
+    return launch_in_pieces(wgs + turn, 256, [&](unsigned first, unsigned n_wgs) {
+      // (a split past the last costs as much as one)
+      if (a.g.d == 64 && S <= 4) merge_flat_rows_kernel<64, 4, Sum><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
+      else if (a.g.d == 64) merge_flat_rows_kernel<64, 8, Sum><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
+      else if (S <= 4) merge_flat_rows_kernel<128, 4, Sum><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
+      else merge_flat_rows_kernel<128, 8, Sum><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
+    });
+  }
+  // Few rows: pieces of d, so that the row's splits are in flight at once over more
+  // workgroups and wavefronts; many rows fill the GPU as they are.  Measured, us, for
+  // (rows x splits) against the kernel with the chain from split to split and a workgroup
+  // per row: 8 x 384 10.8 -> 4.3, 32 x 128 5.7 -> 3.9, 32 x 96 6.0 -> 4.7, 672 x 29
+  // 7.4 -> 4.0 (pieces of 32: 6.2-8.2), 8 x 32 (d = 64) 8.6 -> 3.3.  65 to 128 splits of few rows in one
+  // step instead of two: whole decode calls of 8191 tokens (128 splits) 12.4 -> 11.8, 131072 (96) 82.6 -> 82.4.
+  // A result merged into one of its own slabs: another piece's workgroup may not have read the
+  // row's log-sum-exps yet when the first piece stores the new one, so a row stays whole.
+  const bool in_place = a.LSE >= a.LSE_sub && a.LSE < a.LSE_sub + rows * S;
+  if (in_place) return a.g.d == 64 ? launch_flat<16, 256, 4, Sum>(a, st) : launch_flat<32, 256, 4, Sum>(a, st);
+  if (rows < 256) return S > 64 ? launch_flat<8, 512, 2, Sum>(a, st) : launch_flat<16, 256, 4, Sum>(a, st);
+  if (S > 64) return launch_flat<16, 512, 4, Sum>(a, st);
+  return a.g.d == 64 ? launch_flat<16, 256, 4, Sum>(a, st) : launch_flat<32, 256, 4, Sum>(a, st);
 }
 
 }  // namespace
@@ -466,33 +506,7 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
   const int64_t rows = (int64_t)a.g.B * a.g.Hq * a.q_len;
   if (rows > 0x7fffffff) return hipErrorInvalidValue;
   const SplitPlan& p = a.plan;
-  if (p.flat) {
-    const int S = p.s_total;
-    if (S <= 8 && rows >= 64) {
-      const int64_t wgs = a.g.d == 64 ? (rows + 15) / 16 : (rows + 7) / 8, turn = a.rotary.log2_theta != 0 ? (rows + 3) / 4 : 0;
-      const RowsDiv by = {make_div(a.q_len), make_div(a.g.Hq)};
-      return launch_in_pieces(wgs + turn, 256, [&](unsigned first, unsigned n_wgs) {
-        // (a split past the last costs as much as one)
-        if (a.g.d == 64 && S <= 4) merge_flat_rows_kernel<64, 4><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
-        else if (a.g.d == 64) merge_flat_rows_kernel<64, 8><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
-        else if (S <= 4) merge_flat_rows_kernel<128, 4><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
-        else merge_flat_rows_kernel<128, 8><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
-      });
-    }
-    // Few rows: pieces of d, so that the row's splits are in flight at once over more
-    // workgroups and wavefronts; many rows fill the GPU as they are.  Measured, us, for
-    // (rows x splits) against the kernel with the chain from split to split and a workgroup
-    // per row: 8 x 384 10.8 -> 4.3, 32 x 128 5.7 -> 3.9, 32 x 96 6.0 -> 4.7, 672 x 29
-    // 7.4 -> 4.0 (pieces of 32: 6.2-8.2), 8 x 32 (d = 64) 8.6 -> 3.3.  65 to 128 splits of few rows in one
-    // step instead of two: whole decode calls of 8191 tokens (128 splits) 12.4 -> 11.8, 131072 (96) 82.6 -> 82.4.
-    // A result merged into one of its own slabs: another piece's workgroup may not have read the
-    // row's log-sum-exps yet when the first piece stores the new one, so a row stays whole.
-    const bool in_place = a.LSE >= a.LSE_sub && a.LSE < a.LSE_sub + rows * S;
-    if (in_place) return a.g.d == 64 ? launch_flat<16, 256, 4>(a, st) : launch_flat<32, 256, 4>(a, st);
-    if (rows < 256) return S > 64 ? launch_flat<8, 512, 2>(a, st) : launch_flat<16, 256, 4>(a, st);
-    if (S > 64) return launch_flat<16, 512, 4>(a, st);
-    return a.g.d == 64 ? launch_flat<16, 256, 4>(a, st) : launch_flat<32, 256, 4>(a, st);
-  }
+  if (p.flat) return a.wide ? merge_one_part<double>(a, rows, st) : merge_one_part<float>(a, rows, st);
   // splits the largest part is made of
   const int per_part = p.spb > p.st ? p.spb : p.st;
   const bool many = per_part <= 8 && rows >= 64;      // many rows, few splits each: a row per 32 lanes

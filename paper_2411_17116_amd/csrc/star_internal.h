@@ -148,6 +148,7 @@ struct MergeArgs {
   float* LSE;           // merged), and its log-sum-exp [B, Hq, q_len]; each may be null
   void* Qq;             // with rotary.log2_theta != 0: the call's queries [B, q_len, Hq, 128] in bf16, to be
   Rotary rotary;        // rotated in place (flat plans; the kernels in front have read them as they were)
+  int32_t wide;         // 1: the sums of a flat plan in 64 bits
 };
 
 // The streaming decode kernel runs in two set-ups.  K and V of a call that fit

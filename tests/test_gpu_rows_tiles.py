@@ -3,6 +3,8 @@ heads (groups that do and do not divide a tile), tiles of 128 rows whose workgro
 share the keys (odd and even numbers of key tiles, a half without any) and tiles of 256,
 splits of equal runs and of parts, new tokens read from the call's tensors and appended by
 the kernel, and the exact fallback of the softmax in both halves."""
+import math
+
 import pytest
 import torch
 
@@ -124,3 +126,29 @@ def test_workspace_of_the_first_call_serves_a_growing_cache(dtype, Hq, Hkv, d, q
     with pytest.raises(sa.StarAttnError) as e:            # not even one split fits
         sa.phase2(shape, lengths[0], Q, K, V, Kc, Vc, got, first[:Hq * q * 4])
     assert e.value.code == -7
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,lq", [(8, 2, 16384, 21), (2, 1, 32768, 40), (4, 1, 16384, 80)])
+def test_sums_over_many_parts_lose_nothing(Hq, Hkv, L, lq):
+    """A host's pair whose splits follow the blocks: every split's output is a whole number of 24 bits and its weight
+    one, so that only the merge rounds.  Sums held to more than 32 bits leave two roundings, of the sum and of
+    the quotient: 2^-23.  Plain fp32 sums of 64 and 128 splits miss that."""
+    b, d, cap, n = 256, 128, L + lq, L // 256
+    shape = sa.StarShape.make("bf16", 1, Hq, Hkv, d, L, b, 0, cap)
+    plan = sa.phase2_plan(shape, L, lq)
+    assert plan.flat == 0 and plan.split_len == b
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    whole = torch.randint(1 << 23, 1 << 24, (Hkv, n, d), generator=gen, device="cuda")
+    Kc, Vc = (torch.zeros((1, Hkv, cap, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    rows = Vc[0, :, :L].view(Hkv, n, b, d)                     # three bytes of it, at keys of their own; the rest are zero
+    for key, shift in ((0, 16), (64, 8), (128, 0)):
+        rows[:, :, key] = (((whole >> shift) & 255) << shift).bfloat16()
+    Q = torch.zeros((1, lq, Hq, d), dtype=torch.bfloat16, device="cuda")
+    K = torch.zeros((1, lq, Hkv, d), dtype=torch.bfloat16, device="cuda")
+    Q[..., 0], K[..., 0] = 1.0, -30000.0                       # equal logits in the context; the new tokens weigh nothing
+    A, lse = torch.empty((1, Hq, lq, d), device="cuda"), torch.empty((1, Hq, lq), device="cuda")
+    sa.phase2_partial(shape, L, Q, Kc, Vc, A, lse, sa.alloc_workspace(shape, lq), Kq=K, Vq=torch.zeros_like(K))
+    torch.cuda.synchronize()
+    want = (whole.double().sum(dim=1) / (n * b)).repeat_interleave(Hq // Hkv, dim=0)[:, None]
+    assert ((A[0].double() - want) / want).abs().max().item() <= 2.0 ** -23
+    assert (lse.double() - math.log(L)).abs().max().item() <= 2.0 ** -20       # ulp near 10
