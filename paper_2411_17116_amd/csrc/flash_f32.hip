@@ -44,12 +44,14 @@ typedef const __attribute__((address_space(1))) f32x4* GlobalVec;
 
 constexpr int UNIT = 16;   // keys per step of a wavefront
 // How far (log2 units) a score may rise above its row's reference before the reference moves.
-// O / l does not depend on the reference, and 2^8 times the largest numerator is as far from overflow
-// as it was, so nothing is lost; scores of N(0, 1) inputs stay within it of the first unit's, and a
+// O / l does not depend on the reference.  Scores of N(0, 1) inputs stay within it of the first unit's, and a
 // unit then costs no exchange between lanes and no rescaling of O.  Against moving it to every new maximum, us
-// (8 / 2 heads): d = 128: L = 4099 (b = 1024, a = 512) 152 -> 142, 8192 (b = a = 2048) 706 -> 663, L = 3001 53.7 ->
-// 52.2; d = 64: 8192 375 -> 352, 4099 117.5 -> 107.7; 1 head, 1024 10.2 -> 9.8.
-constexpr float HEADROOM = 8.f;
+// (8 / 2 heads): d = 128: L = 4099 (b = 1024, a = 512) 140.3 -> 134.1, 8192 (b = a = 2048) 704 -> 673; d = 64: 4099
+// (b = a = 1024) 103.1 -> 99.8; 1 head, 1024 10.2 -> 9.9.
+// The weights in O are held 2^-HEADROOM as large, so that none is above one and sums of V overflow no earlier than
+// with the maximum itself as reference (products with V below 1e-35 go denormal 8 bits earlier).  Without that
+// sums of |V| beyond 1e36 could overflow, and the three prefills took 134.3, 671 and 97.7 us.
+constexpr float HEADROOM = 8.f, HELD = 1.f / 256;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -86,7 +88,7 @@ struct KeySeq {
 template <int D, int NB>
 struct RowState {
   f32x4 q[NB][D / 16];        // q[.][t][e] = Q[row][16 t + 4 j4 + e] * scale * log2(e)
-  f32x4 o[NB][D / 64][4];     // o[.][h][e][w] = O[row][64 h + 16 j4 + 4 w + e]
+  f32x4 o[NB][D / 64][4];     // o[.][h][e][w] = HELD O[row][64 h + 16 j4 + 4 w + e]
   float m[NB], top[NB];       // reference (log2 units; uniform over a row's four lanes; 0 until a key is
                               // visible) and the score beyond which it moves (-inf until then)
   float l[NB];                // this lane's share of the sum of 2^(s - m)
@@ -210,6 +212,8 @@ __device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, cons
 #pragma unroll
     for (int v = 0; v < 4; ++v) s[b][v] = __builtin_amdgcn_exp2f(s[b][v] - w.m[b]);
     w.l[b] += (s[b][0] + s[b][1]) + (s[b][2] + s[b][3]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s[b][v] *= HELD;
   }
 #pragma unroll
   for (int v = 0; v < 4; ++v)
@@ -304,7 +308,7 @@ __device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<NB, KW>& x, Store 
     float l = 0.f;
 #pragma unroll
     for (int n = 0; n < KW; ++n) l += x.l[n][row] * __builtin_amdgcn_exp2f(x.m[n][row] - mm);
-    x.scale[k][row] = l > 0.f ? __builtin_amdgcn_exp2f(x.m[k][row] - mm) * (1.f / l) : 0.f;
+    x.scale[k][row] = l > 0.f ? __builtin_amdgcn_exp2f(x.m[k][row] - mm) * (1.f / l) * (1.f / HELD) : 0.f;
     if (k == 0) store_lse(row, l > 0.f ? log_sum(m, l) : -INFINITY);
   }
 #pragma unroll

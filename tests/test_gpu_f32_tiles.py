@@ -3,6 +3,8 @@ heads of a KV group (groups that do and do not divide a tile), 16-key units deal
 the wavefronts of a workgroup (fewer units than wavefronts, ragged last units), calls
 of one workgroup per row tile that write their results themselves and calls whose
 splits are merged, with and without per-part outputs."""
+import math
+
 import pytest
 import torch
 
@@ -98,3 +100,37 @@ def test_fp32_workspace_covers_every_shorter_call():
                 for parts in (False, True):
                     for cached in (3000, 3400 - q):
                         assert sa.phase2_plan(shape, cached, q, parts).workspace_bytes <= have, (Hq, q, parts)
+
+
+@pytest.mark.parametrize("d,G", [(64, 1), (128, 4)])
+@pytest.mark.parametrize("run", [16, 64, 128])           # keys of a step: one unit of one, of four and of eight wavefronts
+@pytest.mark.parametrize("step", [7.9, 8.1])             # log2 units: within the softmax's headroom, and beyond it
+def test_scores_that_climb_over_large_values(step, run, d, G):
+    """Rows whose scores rise in steps, over values whose weighted sums are within fp32 as long as no weight is above
+    one (128 keys of up to 1e36 at the top step) and beyond it with weights of 2^7.9."""
+    L, q, big = 512, 20, 1e36
+    shape = sa.StarShape.make("fp32", 1, G, 1, d, L, L, 0, L + q, softmax_scale=1.0)
+    gen = torch.Generator(device="cuda").manual_seed(run)
+    V = big * (0.5 + 0.5 * torch.rand((1, L + q, 1, d), generator=gen, device="cuda"))
+    K = torch.zeros_like(V)
+    K[0, :, 0, 0] = torch.arange(L + q, device="cuda") // run * (step * math.log(2.0))
+    Q = torch.zeros((1, L + q, G, d), device="cuda")
+    Q[..., 0] = 1.0
+    O, lse = torch.empty((1, L, G, d), device="cuda"), torch.empty((1, G, L), device="cuda")
+    Kc, Vc = sa.alloc_cache(shape)
+    sa.phase1(shape, Q[:, :L].contiguous(), K[:, :L].contiguous(), V[:, :L].contiguous(), O, Kc, Vc, LSE_ctx=lse)
+    s = K[0, :, 0, 0].double().repeat(L + q, 1).masked_fill(torch.ones((L + q, L + q), device="cuda").triu(1).bool(), -math.inf)
+    want, want_lse = torch.softmax(s, 1) @ (V[0, :, 0].double() / big), torch.logsumexp(s, 1)
+    tol = ph.TOL["fp32"]["o"]
+    torch.cuda.synchronize()
+    for h in range(G):
+        assert (O[0, :, h].double() / big - want[:L]).abs().max().item() <= tol
+        assert ((lse[0, h].double() - want_lse[:L]).abs() <= 2.0 ** -22 * want_lse[:L].abs() + 1e-6).all()
+    cached = L
+    for n in (1, q - 1):                                 # one token, then several
+        Oq, ws = torch.empty((1, n, G, d), device="cuda"), sa.alloc_workspace(shape, n)
+        part = slice(cached, cached + n)
+        sa.phase2(shape, cached, Q[:, part].contiguous(), K[:, part].contiguous(), V[:, part].contiguous(), Kc, Vc, Oq, ws)
+        torch.cuda.synchronize()
+        assert (Oq[0].double() / big - want[part][:, None]).abs().max().item() <= tol
+        cached += n
