@@ -162,12 +162,14 @@ static int64_t f32_splits_max(const Geom& g, int64_t q_len, int tile) {
 constexpr int64_t F32_SPLIT_MIN = 128;     // keys: one or two 16-key units for each wavefront
 // Runs of 64 keys, one unit for each of four wavefronts, where a KV head's rows are one tile and all the runs start at
 // once: what counts is the chain of units a wavefront walks.  More than 128 runs cost more to merge than
-// they save.  us per call of one row against eight wavefronts and 128 keys: 1024 keys (1 head, d = 64) 8.5 -> 7.5, 4000 (8 / 2
-// heads, d = 128) 11.4 -> 9.0, 8000 (1 head, d = 128) 11.2 -> 9.6, 16000 (8 / 2, d = 64) 9.3 -> 9.1; with more runs than start
-// at once it loses: two sequences of 9000 (8 / 2, d = 128), five tokens and one, 34.7 as it was and 35.9 so.  0: not such a call.
+// they save, so beyond 8192 keys the runs grow.  us per call of one row, eight wavefronts and 128 keys / this: 1000 keys (2
+// heads, d = 64) 8.6 / 7.7, 4000 (8 / 2 heads, d = 128) 11.8 / 9.8, 16000 14.2 / 13.3, 65000 31.1 / 30.6.  One KV head leaves half
+// the CUs idle with them, which pays up to five units for each wavefront: d = 64, 32000 11.8 / 11.4, 40000 12.2 / 12.1,
+// 50000 13.0 / 13.4, 131000 17.9 / 19.4, 262000 30.3 / 37.2.  With more runs than start at once they
+// lose: two sequences of 9000 (8 / 2, d = 128), five tokens and one, 34.7 / 35.9.  0: not such a call.
 static int64_t f32_short_runs(const Geom& g, int64_t q_len, int64_t total) {
-  const int64_t worth = ceil_div(total, 64), runs = worth < 128 ? worth : 128;
-  return (int64_t)g.G * q_len <= 16 && (int64_t)g.B * g.Hkv * runs <= 256 &&
+  const int64_t worth = ceil_div(total, 64), runs = worth < 128 ? worth : 128, wgs = (int64_t)g.B * g.Hkv * runs;
+  return (int64_t)g.G * q_len <= 16 && wgs <= 256 && (wgs > 128 || total <= 128 * 5 * 64) &&
                  runs <= ceil_div(4096, (int64_t)g.B * g.Hq * ceil_div(q_len, 64)) ? runs : 0;
 }
 // Rows per tile: 16 while those tiles with splits of that size leave CUs idle or fill them

@@ -215,6 +215,14 @@ def test_row_tile_of_per_part_calls(lib):
     assert sa.phase2_plan(few, 94, 91, want_parts=True).tile_rows == 128
 
 
+def test_fp32_runs_of_one_kv_head_use_the_whole_chip_on_long_caches(lib):
+    for total, splits in ((512, 1), (513, 9), (8192, 128), (40960, 128), (40961, 214), (131072, 256), (1 << 20, 256)):
+        s = sa.StarShape.make("fp32", 1, 1, 1, 64, total - 1, total, 0, total)
+        info = sa.phase2_plan(s, total - 1, 1)
+        assert info.n_splits == splits, total
+        assert info.workspace_bytes <= sa.workspace_bytes(s, 1)
+
+
 def test_workspace_of_per_part_calls_does_not_depend_on_the_cache_length(lib):
     """Calls with per-part outputs keep one pair per split of every part, whatever the cache holds."""
     for dtype, d in (("fp32", 64), ("fp32", 128), ("bf16", 128)):

@@ -19,6 +19,9 @@ pytestmark = pytest.mark.gpu
     (1, 17, 1, 128, 575, 1, 5),        # 17 rows: runs of 128 keys
     (1, 2, 2, 128, 8150, 2, 128),      # 8152 keys: as many runs as are worth merging, all that start at once
     (1, 3, 3, 128, 8150, 2, 64),       # more than that: runs of 128 keys
+    (1, 4, 1, 64, 40959, 1, 128),      # one KV head: five units for each of four wavefronts
+    (1, 4, 1, 64, 40960, 1, 214),      # beyond that eight wavefronts on all CUs
+    (1, 2, 2, 64, 50000, 1, 121),      # two: as many runs as start at once at any length
 ])
 def test_short_runs(B, Hq, Hkv, d, L, q, splits):
     gen = torch.Generator(device="cuda").manual_seed(L)
