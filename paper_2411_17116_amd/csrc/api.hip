@@ -325,17 +325,23 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     p->s_total = (int32_t)ceil_div(total, split_len);
     // More than 64 splits of a resident cache: four wavefronts share one, and a quarter or half of them is left
     // to merge.  Two such workgroups per CU, one where there are fewer than eight KV heads and four times the
-    // splits per head.  us: 8191 tokens of eight heads 11.6 -> 11.0, 32768 29.4 -> 27.9; 30000 of two 12.4 -> 11.1, 131072
-    // 29.6 -> 27.2; up to 64 splits the meeting costs more than the merge saves (2000 of eight 7.5 and 7.9,
-    // 16000 of sixteen 26.7 and 27.2), and caches read from HBM gain nothing (131072 of eight 82.3 and 82.2, four
-    // sequences of 32768 83.1 and 83.8).
+    // splits per head.  us, one wavefront / four: 8191 tokens of eight heads 11.1 / 10.4, 13900 15.3 / 15.1; 27800 of two 12.0 /
+    // 10.3, 131000 26.6 / 25.1; up to 64 splits the meeting costs more than the merge saves (2000 of eight 7.5 / 7.9,
+    // 16000 of sixteen 26.7 / 27.2), and caches read from HBM gain nothing (131072 of eight 82.3 / 82.2, four
+    // sequences of 32768 83.1 / 83.8).  Eight heads and more have two wavefronts on a SIMD: where a sixth and more of
+    // the last round's have no step (a quarter with more than eight rows, whose pairs weigh more), the others' take longer
+    // than one wavefront with more steps: 8400 tokens of eight 10.9 / 12.6, 10600 13.2 / 14.2, 16800 17.0 / 18.2, 25400 21.5 / 22.4;
+    // twelve rows 12.8 / 13.4, 14.8 / 15.0, 18.3 / 19.0, 22.7 / 22.7, but 12283 16.2 / 15.2 (four rows 14.4 / 14.6).
     if (p->s_total > 64 && decode_cache_resident(g, total)) {
-      const int64_t wgs = device_cu_count() * (int64_t)(pairs < 8 ? 1 : 2), most = ceil_div(ceil_div(total, 32), 4);
+      const int64_t wgs = device_cu_count() * (int64_t)(pairs < 8 ? 1 : 2), steps = ceil_div(total, 32), most = ceil_div(steps, 4);
       int64_t splits = wgs / pairs < most ? wgs / pairs : most;
       if (splits < 1) splits = 1;
-      p->waves = 4;
-      p->split_len = round_up(ceil_div(total, splits), 32);
-      p->s_total = (int32_t)splits;
+      const int64_t room = ceil_div(steps, 4 * splits) * 4 * splits;      // steps of as many rounds
+      if (pairs < 8 || 12 * steps >= (rows > 8 ? 9 : 10) * room) {
+        p->waves = 4;
+        p->split_len = round_up(ceil_div(total, splits), 32);
+        p->s_total = (int32_t)splits;
+      }
     }
     return true;
   }

@@ -223,6 +223,18 @@ def test_fp32_runs_of_one_kv_head_use_the_whole_chip_on_long_caches(lib):
         assert info.workspace_bytes <= sa.workspace_bytes(s, 1)
 
 
+def test_wavefronts_share_a_decode_split_where_their_last_round_is_nearly_full(lib):
+    """Splits of 512 / 8 workgroups of four wavefronts are 256 steps of 32 keys; short of 5 / 6 of a last round, or of 3 / 4
+    with more than eight rows, the call keeps one wavefront to a split."""
+    for q, lengths in ((1, ((8192, 64), (8193, 86), (10240, 107), (13632, 107), (13633, 64), (16384, 64), (16416, 103), (24576, 64))),
+                       (3, ((8192, 64), (8193, 86), (12256, 128), (12257, 64), (16416, 103)))):
+        for total, splits in lengths:
+            s = sa.StarShape.make("bf16", 1, 32, 8, 128, total - q, total, 0, total)
+            info = sa.phase2_plan(s, total - q, q)
+            assert info.n_splits == splits, (q, total, info.n_splits)
+            assert info.workspace_bytes <= sa.workspace_bytes(s, q)
+
+
 def test_workspace_of_per_part_calls_does_not_depend_on_the_cache_length(lib):
     """Calls with per-part outputs keep one pair per split of every part, whatever the cache holds."""
     for dtype, d in (("fp32", 64), ("fp32", 128), ("bf16", 128)):

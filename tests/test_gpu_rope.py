@@ -237,7 +237,8 @@ def test_rotation_workgroup_shapes(dtype, d, B, T, H):
     (5, 64, 32, 500, 2),        # few splits of many rows: merged by rows
     (3, 32, 16, 90000, 1),      # beyond the last-level cache
     (1, 16, 16, 600, 9),        # more tokens than the decode kernel turns
-    (1, 32, 8, 8190, 4),        # four wavefronts to a split, the tokens in steps of two
+    (1, 32, 8, 8158, 4),        # four wavefronts to a split, the tokens in steps of two
+    (1, 32, 8, 8190, 4),        # one again
 ])
 def test_decode_on_unrotated_projections_is_decode_on_rotated_ones(B, Hq, Hkv, L, q):
     """A decode call that turns its tokens on the way gives the bits of star_attn_rope followed by

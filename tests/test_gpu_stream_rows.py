@@ -23,7 +23,8 @@ pytestmark = pytest.mark.gpu
     (1, 12, 4, 5000, 9, 1, 40),        # 27 rows, tokens straddle the row blocks
     (33, 64, 8, 300, 3, 1, 1),         # a split per KV head
     (1, 32, 8, 4096, 4, 1, 33),        # 16 rows: 65 splits become 33 of four wavefronts
-    (1, 32, 8, 8190, 4, 1, 64),        # new tokens in the last step and one of their own
+    (1, 32, 8, 8158, 4, 1, 64),        # new tokens in the last step and one of their own
+    (1, 32, 8, 8190, 4, 1, 86),        # a step more than the wavefronts of 64 splits: one to a split again
     (1, 4, 1, 9000, 1, 1, 71),         # few KV heads
     (1, 32, 1, 400000, 1, 1, 256),     # beyond the last-level cache: 32 rows
     (1, 33, 1, 400000, 1, 1, 256),     # 33, 48, 49 and 64 rows
