@@ -130,25 +130,41 @@ static int64_t decode_slots(const Geom& g, int64_t total) {
 }
 static int64_t decode_slots_max() { return device_cu_count() * (int64_t)4; }
 
-// Rows per KV head up to which a call without per-part outputs streams the cache through the decode kernel.
-// More than 16 (a block of columns each 16) leave one wavefront too many pairs, so four share a split (two
-// where the cache is at most 64 steps long, and none takes more than one or two) and meet in LDS; against
-// the row-tiled kernel's 128-row tiles, us (32 / 8 heads): 20 rows on 600 keys 13.0 -> 8.9, 32 on 2000 13.0 -> 9.9, on
-// 16384 20.0 -> 18.0, on 131072 101.6 -> 85.3.  33 to 64 rows take all registers of a SIMD for one wavefront,
-// which pays where the cache comes from HBM: 48 rows on 131072 103.7 -> 89.2, 64 104.4 -> 91.4, 48 on 50000
-// 47.8 -> 43.5; 48 on 32768 (resident) 37.5 against 36.3, on 16384 21.0 against 22.8, 64 21.6 and 26.4.
+// Calls of 17 to 64 rows per KV head without per-part outputs that stream the cache through the decode kernel.
+// More than 16 rows (a block of columns each 16) leave one wavefront too many pairs, so four share a split (two
+// where a short cache gives none of them more than one step) and meet in LDS, one workgroup per CU. us, row-tiled
+// (128 rows) / streamed, 32 / 8 heads: 20 rows on 600 keys 11.7 / 9.6, 32 on 2000 15.0 / 11.5, on 20000 24.7 / 20.8, on 131072
+// 100.5 / 88.0; four sequences (32 KV heads) 20 on 1000 15.6 / 12.2, 32 on 2000 18.2 / 14.6; eight 17.9 / 14.9, 22.4 / 18.6.
+// (With up to two workgroups per CU and a step to every wavefront it was slower than row-tiled at 300 to 800 keys of 32 to 96
+// KV heads: 32 rows on 800 keys of 48 15.1 / 18.5.)
+//   * 33 to 64 rows take all registers of a SIMD for one wavefront, which pays where a long cache comes from HBM: 48 on
+//     131072 102.5 / 90.6, 64 104.2 / 90.8, 48 on 60000 55.9 / 50.2; resident 36.3 / 37.5 on 32768, 22.8 / 21.0 on 16384, 64 rows
+//     26.4 / 21.6; 64 on 9000 of 44 KV heads 48.9 / 51.5, of 64 67.2 / 69.0.
+//   * Where KV heads leave CUs idle, the row-tiled kernel is cut into as many splits as fill them: streaming has to keep four
+//     fifths of the CUs busy once there is more than a launch's time to lose. 20000 keys: 132 KV heads (52 %) 264 / 331,
+//     264 (52 % of two rounds) 558 / 651, 128 (all) 261 / 233; 60000: 96 (75 %) 521 / 548; 3000: 132 54.8 / 59.3; 2000 47.6 / 40.3.
 // A single key tile has nothing to stream.
-static int stream_rows_max(const Geom& g, int64_t total) {
-  return total <= 64 ? 16 : decode_cache_resident(g, total) ? 32 : 64;
+constexpr int64_t STREAM_WGS = 256;                  // one per CU
+constexpr int64_t STREAM_PAIRED_KEYS = 64 * 32;      // most for two wavefronts to a split
+constexpr int64_t STREAM_WIDE_KEYS = 16384;          // fewest for 33 rows and more
+constexpr int64_t STREAM_ANY_KEYS = 2560;            // most that stream however few CUs they keep busy
+static int64_t stream_slots(const Geom& g) {
+  const int64_t slots = STREAM_WGS / ((int64_t)g.B * g.Hkv);
+  return slots > 1 ? slots : 1;
 }
-constexpr int64_t STREAM_WGS = 256;        // workgroups of four wavefronts: one per CU
-// Most splits of 17 rows and more that any call on caches of up to `keys` keys is cut into.
-static int64_t stream_splits(const Geom& g, int64_t keys, int waves) {
-  const int64_t pairs = (int64_t)g.B * g.Hkv, steps = ceil_div(keys, 32), slots = STREAM_WGS * (waves == 2 ? 2 : 1) / pairs;
-  const int64_t most = ceil_div(steps, waves);
-  return slots < 1 ? 1 : slots < most ? slots : most;
+// Whether a call streams; if so, into how many splits and how many wavefronts share one.
+static bool streams(const Geom& g, int64_t rows, int64_t total, int* waves, int64_t* splits) {
+  if (total <= 64 || rows > 64) return false;
+  if (rows > 32 && (decode_cache_resident(g, total) || total < STREAM_WIDE_KEYS)) return false;
+  const int64_t pairs = (int64_t)g.B * g.Hkv, slots = stream_slots(g), steps = ceil_div(total, 32);
+  *waves = steps <= 2 * slots && total <= STREAM_PAIRED_KEYS ? 2 : 4;
+  const int64_t worth = ceil_div(steps, *waves);
+  *splits = slots < worth ? slots : worth;
+  if (total <= STREAM_PAIRED_KEYS)         // no more than the longest chain of steps asks for: fewer pairs to merge
+    *splits = ceil_div(steps, ceil_div(steps, *splits * *waves) * *waves);
+  const int64_t wgs = pairs * slots;
+  return total <= STREAM_ANY_KEYS || slots >= worth || 5 * wgs >= 4 * STREAM_WGS * ceil_div(wgs, STREAM_WGS);
 }
-constexpr int64_t STREAM_PAIRED_KEYS = 64 * 32;
 
 // ---- fp32 kernel: tiles of 16 rows shared by eight wavefronts (one workgroup per CU) or, for short runs of
 // one tile per KV head, by four, or of 32 rows shared by four (two per CU).
@@ -293,7 +309,9 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   int64_t rows = (int64_t)g.G * q_len;
   int64_t fit = splits_that_fit(g, q_len, max_bytes);
   if (fit < 1) fit = 1;
-  p->decode = (s->dtype == STAR_ATTN_BF16 && rows <= (want_parts ? 16 : stream_rows_max(g, total))) ? 1 : 0;
+  int waves = 1;
+  int64_t splits = 0;
+  p->decode = s->dtype == STAR_ATTN_BF16 && (rows <= 16 || (!want_parts && streams(g, rows, total, &waves, &splits))) ? 1 : 0;
   p->flat = 0;
   p->tile_rows = 0;
   p->waves = 1;
@@ -301,8 +319,7 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
   if (n > (1 << 24)) return false;
   int64_t split_len;
   if (p->decode && rows > 16) {
-    p->waves = rows <= 32 && total <= STREAM_PAIRED_KEYS ? 2 : 4;
-    int64_t splits = stream_splits(g, total, p->waves);
+    p->waves = waves;
     if (splits > fit) splits = fit;
     p->flat = 1;
     p->split_len = round_up(ceil_div(total, splits), 32);
@@ -500,9 +517,8 @@ size_t star_attn_workspace_bytes(const star_attn_shape* shape, int64_t max_q_len
       }
     } else if (ok) {
       if ((int64_t)g.G * q <= 64) {
-        const int64_t keys = g.cap < STREAM_PAIRED_KEYS ? g.cap : STREAM_PAIRED_KEYS;
-        need(stream_splits(g, keys, 2), q);
-        need(stream_splits(g, g.cap, 4), q);
+        const int64_t worth = ceil_div(ceil_div(g.cap, 32), 2), slots = stream_slots(g);
+        need(slots < worth ? slots : worth, q);
       }
       int64_t most = 4 * ROW_WGS / rows_wgs(g, q, 256), worth = ceil_div(g.cap, 256);
       if (most > worth) most = worth;

@@ -11,7 +11,7 @@
 //     hot); with per-part outputs a split is a contiguous run inside one part;
 //   * a split is one wavefront's keys and a workgroup one wavefront, or (SplitPlan::waves) four or two
 //     wavefronts share one and meet in LDS behind the key loop, where the pairs of more splits would cost
-//     more to store and merge (stream_rows_max() and make_plan() in api.hip, with both sides measured);
+//     more to store and merge (streams() and make_plan() in api.hip, with both sides measured);
 //   * a 32-key step is loaded into registers with plain 16-byte loads: K (8 KiB) straight in the
 //     layout the MFMA wants -- lane (i, j4) takes key i, bytes 64t + 16 j4 .. +15 of its row for
 //     t = 0..3; V (8 KiB) as 1 KiB-contiguous bursts.  As soon as its scores are taken and its V is in

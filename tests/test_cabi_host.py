@@ -235,6 +235,20 @@ def test_wavefronts_share_a_decode_split_where_their_last_round_is_nearly_full(l
             assert info.workspace_bytes <= sa.workspace_bytes(s, q)
 
 
+def test_calls_of_17_to_64_rows_stream_where_they_keep_the_chip_busy(lib):
+    """(batch, query heads, KV heads, keys, tokens) -> streaming, splits; and what streams fits the workspace asked for."""
+    for B, Hq, Hkv, total, q, decode, splits in (
+            (1, 32, 8, 131072, 5, 1, 32), (1, 32, 8, 131072, 12, 1, 32), (1, 32, 8, 16384, 12, 0, None), (4, 32, 8, 9000, 16, 0, None),
+            (3, 32, 8, 20000, 5, 1, 10), (12, 32, 8, 60000, 5, 0, None), (16, 32, 8, 20000, 5, 1, 2), (33, 48, 4, 40000, 4, 0, None),
+            (33, 8, 4, 20000, 12, 0, None), (33, 8, 4, 2560, 12, 1, 1), (33, 8, 4, 2561, 12, 0, None), (66, 8, 4, 20000, 12, 0, None),
+            (6, 32, 8, 800, 8, 1, 4), (8, 32, 8, 600, 8, 1, 3), (2, 16, 16, 800, 32, 1, 7), (64, 8, 4, 5000, 12, 1, 1)):
+        s = sa.StarShape.make("bf16", B, Hq, Hkv, 128, total - q, total, 0, total)
+        info = sa.phase2_plan(s, total - q, q)
+        assert info.decode == decode and (splits is None or info.n_splits == splits), (B, Hkv, total, q, info.decode, info.n_splits)
+        assert info.workspace_bytes <= sa.workspace_bytes(s, q)
+        assert info.non_temporal == (decode and 2 * B * Hkv * total * 256 > 192 << 20)
+
+
 def test_workspace_of_per_part_calls_does_not_depend_on_the_cache_length(lib):
     """Calls with per-part outputs keep one pair per split of every part, whatever the cache holds."""
     for dtype, d in (("fp32", 64), ("fp32", 128), ("bf16", 128)):

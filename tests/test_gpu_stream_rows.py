@@ -22,6 +22,10 @@ pytestmark = pytest.mark.gpu
     (1, 32, 1, 2048, 1, 1, 17),        # and the first with four, the last split with one step
     (1, 12, 4, 5000, 9, 1, 40),        # 27 rows, tokens straddle the row blocks
     (33, 64, 8, 300, 3, 1, 1),         # a split per KV head
+    (6, 32, 8, 796, 8, 1, 4),          # 48 KV heads: as few splits as two steps for each of four wavefronts ask for
+    (4, 32, 8, 2000, 5, 1, 8),         # 32
+    (32, 32, 8, 2000, 5, 1, 1),        # 256, beyond the last-level cache: four wavefronts and non-temporal loads
+    (33, 8, 4, 2600, 9, 0, None),      # 132 keep half the CUs busy: row-tiled beyond 2560 keys
     (1, 32, 8, 4096, 4, 1, 33),        # 16 rows: 65 splits become 33 of four wavefronts
     (1, 32, 8, 8158, 4, 1, 64),        # new tokens in the last step and one of their own
     (1, 32, 8, 8190, 4, 1, 86),        # a step more than the wavefronts of 64 splits: one to a split again
