@@ -627,12 +627,13 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
 // 4790 -> 975 (3336), b = 4, a = 0 1245 -> 274 (1000), b = 4, a = 4 1379 -> 368 (1495); 50000 tokens,
 // d = 128: b = a = 16 474 -> 251 (2262); three units and more: 146 -> 144 (b = 32, a = 0), 165 -> 169 (64).
 Phase1Plan phase1_plan_f32(const Geom& g) {
-  const int64_t bmax = g.b < g.L ? g.b : g.L, n = (g.L + g.b - 1) / g.b, rows = g.L * g.G * g.Hkv * g.B;
+  const int64_t bmax = g.b < g.L ? g.b : g.L, rows = g.L * g.G * g.Hkv * g.B;
   Phase1Plan p = {0, 16, 8, 0, 0};
   if ((g.a + UNIT - 1) / UNIT + (bmax + UNIT - 1) / UNIT <= 2) p.waves = 1;
   else if (rows >= 1024 * 32) { p.rows = 32; p.waves = 4; }
   else if (rows >= 256 * 16) p.waves = 4;
-  p.tiles = n * ((bmax * g.G + p.rows - 1) / p.rows) * g.B * g.Hkv;
+  const int64_t full = g.L / g.b, rest = g.L - full * g.b;      // (the short last block has fewer)
+  p.tiles = (full * ((g.b * g.G + p.rows - 1) / p.rows) + (rest * g.G + p.rows - 1) / p.rows) * g.B * g.Hkv;
   return p;
 }
 

@@ -195,6 +195,8 @@ def test_phase1_plan_query(lib):
     f32 = dict(dtype="fp32", head_dim=64, n_q_heads=8, n_kv_heads=8)
     assert plan(**f32, ctx_len=1000, block=16, anchor=0) == (0, 16, 1, 0, 8 * 63)
     assert plan(**f32, ctx_len=8192, block=2048, anchor=0)[:3] == (0, 32, 4)
+    assert plan(**f32, ctx_len=1060, block=500, anchor=0) == (0, 16, 4, 0, 8 * (32 + 32 + 4))    # a short last block
+    assert plan(**f32, ctx_len=30, block=500, anchor=0) == (0, 16, 1, 0, 8 * 2)
     # no grid that a plan stands for is beyond what a launch can number
     assert plan(n_q_heads=8, n_kv_heads=8, ctx_len=1 << 21, block=1, anchor=0)[4] == 1 << 24
     info = binding.Phase1PlanInfo()
