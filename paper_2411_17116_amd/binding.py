@@ -1,11 +1,13 @@
 """Binding of libstarattn.so (see include/star_attn.h for the contract): queries through ctypes, the
-calls that enqueue work through the extension module built from csrc/marshal.cpp."""
+calls that enqueue work through the extension module built from csrc/marshal.cpp, or through ctypes too, at some
+4 us of host time more, where it has not been built or does not load with this torch."""
 from __future__ import annotations
 
 import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -20,7 +22,7 @@ ANCHOR_ALL_BLOCKS = 4
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
-_MARSHAL = None       # the extension module, bound to _LIB's entry points
+_MARSHAL = None       # the calls that enqueue work: the extension module, bound to _LIB's entry points, or _CtypesCalls
 
 
 class StarAttnError(RuntimeError):
@@ -77,7 +79,7 @@ def lib_path() -> str:
 def load_library():
     """Load the built library; raises if it has not been built (no fallback)."""
     global _LIB
-    if _LIB is not None and _MARSHAL is not None:
+    if _LIB is not None:
         return _LIB
     path = lib_path()
     if not os.path.exists(path):
@@ -119,7 +121,6 @@ def load_library():
     lib.star_attn_phase1_plan.argtypes = [P, ctypes.c_int, ctypes.POINTER(Phase1PlanInfo)]
     lib.star_attn_kernel_path.restype = ctypes.c_char_p
     lib.star_attn_kernel_path.argtypes = [P]
-    _bind(lib)
     _LIB = lib
     return lib
 
@@ -131,7 +132,7 @@ def _bind(lib) -> None:
     if not os.path.exists(path):
         raise FileNotFoundError(
             f"{path} not found: build it with `python -m paper_2411_17116_amd.build`")
-    if _MARSHAL is None:
+    if not hasattr(_MARSHAL, "bind"):
         loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
         module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
         loader.exec_module(module)
@@ -144,9 +145,56 @@ def _bind(lib) -> None:
     _MARSHAL = module
 
 
+class _CtypesCalls:
+    """The extension module's calls by ctypes alone: same arguments, same refusals."""
+    # what follows the shape and precedes the stream: t a tensor's address, w and its bytes, q behind its shape[1],
+    # m behind its shape[0] and shape[3]; i and d numbers
+    _KINDS = {"phase1": "tttttttw", "phase1_anchor": "itttttttttw", "phase1_rope": "ditttttttw", "phase2": "iqtttttttw",
+              "phase2_rope": "diiqtttttttw", "phase2_static": "iqttttt", "phase2_partial": "iqttttttw", "merge": "mtttt"}
+
+    def __init__(self, lib):
+        self._rope = lib.star_attn_rope
+        for name, kinds in self._KINDS.items():
+            setattr(self, name, self._entry(getattr(lib, "star_attn_" + name), kinds))
+
+    @staticmethod
+    def _address(t):
+        if t is None:
+            return None
+        if not t.is_contiguous():
+            raise ValueError("star_attn tensors must be contiguous")
+        return t.data_ptr()
+
+    def _entry(self, fn, kinds):
+        def call(shape, *args):
+            *values, stream = args
+            if len(values) != len(kinds):
+                raise TypeError("wrong number of arguments")
+            out = [ctypes.byref(shape)]
+            for kind, x in zip(kinds, values):
+                if kind == "q":
+                    out.append(x.shape[1])
+                elif kind == "m":
+                    out += [x.shape[0], x.shape[3]]
+                out.append(x if kind in "id" else self._address(x))
+                if kind == "w":
+                    out.append(0 if x is None else x.numel() * x.element_size())
+            return fn(*out, stream)
+        return call
+
+    def rope(self, shape, X, Y, theta, pos0, stream):
+        return self._rope(ctypes.byref(shape), X.shape[2], X.shape[1], pos0, theta, self._address(X), self._address(Y), stream)
+
+
 def _calls():
+    global _MARSHAL
     if _MARSHAL is None:
-        load_library()
+        lib = load_library()
+        try:
+            _bind(lib)
+        except (ImportError, OSError) as e:
+            warnings.warn(f"star_attn calls go through ctypes, some 4 us of host time more each: {e}")
+            _MARSHAL = _CtypesCalls(lib)
     return _MARSHAL
 
 

@@ -69,17 +69,22 @@ def build(verbose: bool = True, jobs: int = 6) -> str:
                 if p.poll() is None:
                     p.wait()
                     break
+    if os.path.exists(MARSHAL_LIB):      # (the binding does without it, but not with an old one)
+        os.remove(MARSHAL_LIB)
     cmd = marshal_command()
     if verbose:
         print(" ".join(cmd), flush=True)
-    procs.append((MARSHAL_SOURCE, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    try:
+        procs.append((MARSHAL_SOURCE, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    except OSError as e:
+        print(f"[build] {MARSHAL_SOURCE} FAILED\n{e}", file=sys.stderr)
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
         out = "\n".join(ln for ln in out.splitlines()
                         if "packed-fp32-ops" not in ln)   # host pass does not know the feature
         if p.returncode != 0:
-            failed = True
+            failed |= src != MARSHAL_SOURCE
             print(f"[build] {src} FAILED\n{out}", file=sys.stderr)
         elif verbose and out.strip():
             print(out)

@@ -1,5 +1,5 @@
-"""The calls of the binding (csrc/marshal.cpp) on the CPU: every argument of every entry point arrives at
-its place, and what was refused in Python is refused."""
+"""The calls of the binding (csrc/marshal.cpp, and by ctypes alone) on the CPU: every argument of every entry point
+arrives at its place, and what was refused in Python is refused."""
 import ctypes
 
 import pytest
@@ -15,8 +15,8 @@ class Stream:
     cuda_stream = 0x7700
 
 
-@pytest.fixture()
-def seen(monkeypatch):
+@pytest.fixture(params=["extension", "ctypes"])
+def seen(request, monkeypatch):
     """Entry points that note what they are called with and answer `status`."""
     lib = sa.load_library()
     log = {"status": 0}
@@ -37,6 +37,10 @@ def seen(monkeypatch):
         fn = ctypes.CFUNCTYPE(ctypes.c_int, *kinds)(call)
         keep.append(fn)
         setattr(fake, "star_attn_" + name, fn)
+    if request.param == "ctypes":
+        monkeypatch.setattr(binding, "_MARSHAL", binding._CtypesCalls(fake))
+        yield log
+        return
     binding._bind(fake)
     yield log
     binding._bind(lib)
@@ -102,3 +106,21 @@ def test_what_is_refused_and_what_is_asked_through_python(seen):
     assert seen["rope"][-3:-1] == (t.data_ptr(), t.data_ptr()) and seen["rope"][1:3] == (4, 3)
     sa.phase2(SHAPE, 4400, sub, t, t, t, t, t, sub, stream=st)
     assert seen["phase2"][2] == 3 and seen["phase2"][-2] == 2 * t.numel()
+
+
+def test_without_the_extension(monkeypatch):
+    """A library without its extension module, or with one that this torch does not load, answers queries and takes
+    calls; with it, calls go through it."""
+    assert type(binding._calls()).__name__ == "module"
+
+    def refuse(lib):
+        raise ImportError("undefined symbol")
+
+    monkeypatch.setattr(binding, "_MARSHAL", None)
+    monkeypatch.setattr(binding, "_LIB", None)
+    monkeypatch.setattr(binding, "_bind", refuse)
+    assert sa.workspace_bytes(SHAPE, 1) > 0 and sa.phase2_plan(SHAPE, 4400, 1).decode == 1
+    t = _t(1, 1, 2, 128)
+    with pytest.warns(UserWarning, match="ctypes"), pytest.raises(sa.StarAttnError) as e:
+        sa.phase2(SHAPE, 4400, t, None, None, t, t, t, t, stream=Stream())       # refused by the library itself
+    assert e.value.code == -2
