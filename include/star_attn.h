@@ -355,7 +355,8 @@ int star_attn_rope(const star_attn_shape* shape, int32_t n_heads, int64_t n_toke
  */
 typedef struct star_attn_plan_info {
   int32_t decode;          /* 1: streaming split-KV kernel (bf16, G * q_len <= 16; without per-part outputs up to
-                              32, or 64 where K + V exceed 192 MiB); 0: row-tiled kernel */
+                              32 on more than 64 keys, or 64 on 16384 and more whose K + V exceed 192 MiB, where
+                              batch times KV heads then keep the chip busy); 0: row-tiled kernel */
   int32_t flat;            /* 1: splits ignore part boundaries (only without per-part outputs) */
   int32_t n_splits;        /* splits per (batch, KV head) */
   int32_t non_temporal;    /* 1: the decode kernel reads the cache with non-temporal loads */
@@ -364,10 +365,10 @@ typedef struct star_attn_plan_info {
   int32_t tile_rows;       /* row-tiled kernels: rows (token x head) per workgroup; else 0 */
   int64_t split_len;       /* keys per split */
   int64_t workspace_bytes; /* bytes of workspace this very call uses; it may use more on a longer
-                              cache (star_attn_workspace_bytes covers every length).  A row-tiled
-                              or fp32 call without per-part outputs makes do with the splits its
-                              workspace holds, down to one, if that is less; any other call is
-                              refused with STAR_ATTN_ERR_WORKSPACE_TOO_SMALL */
+                              cache (star_attn_workspace_bytes covers every length).  A call
+                              without per-part outputs that is fp32 or has G * q_len > 16 makes do
+                              with the splits its workspace holds, down to one, if that is less; any
+                              other call is refused with STAR_ATTN_ERR_WORKSPACE_TOO_SMALL */
 } star_attn_plan_info;
 
 int star_attn_phase2_plan(const star_attn_shape* shape, int64_t cache_len, int64_t q_len,

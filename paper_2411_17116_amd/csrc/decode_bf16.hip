@@ -516,6 +516,9 @@ hipError_t launch_phase2_decode_bf16(const Phase2Args& a, hipStream_t st) {
   const int waves = a.plan.waves;
   if (g.Hkv > 65535 || g.B > 65535 || rows > 64 || (waves > 1 && !a.plan.flat)) return hipErrorInvalidValue;
   const bool resident = decode_cache_resident(g, visible_total(a));
+  // what make_plan() gives, and nothing else: set-ups that share their splits are not told apart by their results
+  if (rows <= 16 ? waves != 1 && (waves != 4 || !resident) : rows <= 32 ? waves != 4 && (waves != 2 || !resident) : waves != 4 || resident)
+    return hipErrorInvalidValue;
   if (a.rotary.log2_theta != 0) {
     if (rows > 16 || a.q_len > ROPE_TOKENS) return hipErrorInvalidValue;
     if (waves == 4) return launch<false, true, 1, 4>(a, st);

@@ -153,7 +153,7 @@ def test_workspace_query_covers_every_call_size(lib):
 def test_plan_query(lib):
     """star_attn_phase2_plan answers on the host: decode-sized calls stream the
     cache, flat only without per-part outputs; caches beyond 192 MiB of K + V are
-    read with non-temporal loads, two steps per batch."""
+    read with non-temporal loads (which steps_per_batch labels 2)."""
     small = good_shape()
     p = sa.phase2_plan(small, small.ctx_len, 1)
     assert (p.decode, p.flat, p.non_temporal, p.steps_per_batch) == (1, 1, 0, 1)
