@@ -28,7 +28,7 @@
 // Phase 1 reads K and V where the caller left them and files its own tokens' rows in
 // the caches; phase 2 reads the new tokens from the call's Kq / Vq and appends them.
 // Measured, whole calls, against a kernel of one thread per row: 8 / 2 heads, d = 128,
-// L = 4099, b = 1024, a = 512: 3390 -> 131 us (115 TFLOP/s; 129 at 8192 tokens in blocks of
+// L = 4099, b = 1024, a = 512: 3390 -> 134 us (113 TFLOP/s; 129 at 8192 tokens in blocks of
 // 2048, where a library fp32 matrix product reaches 152); 1 head, d = 64, L = 1024,
 // b = a = 256: 274 -> 9.2 us.
 #include "star_internal.h"

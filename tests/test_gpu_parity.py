@@ -82,7 +82,7 @@ def test_bf16_extreme_scores_take_the_exact_softmax_path():
 def test_config2_bf16_sampled():
     rep = ph.run_parity(workloads.CONFIGS["C2"], verbose=True)
     _report(rep)
-    # K + V = 134 MB stay in the last-level cache: flat plan, ordinary loads, one step per batch
+    # K + V = 134 MB stay in the last-level cache: flat plan, ordinary loads (label 1)
     assert set(rep.flat_plans.values()) == {(1, 1, 0, 1)}, rep.flat_plans
     assert "decode_flat_O" in rep.checks
 
@@ -90,7 +90,7 @@ def test_config2_bf16_sampled():
 def _assert_streaming_decode_was_checked(rep):
     """The decode steps compared as `decode_flat_O` ran the set-up a serving loop
     (and the benchmark) runs at this size: the flat comb plan on the non-temporal
-    kernel that loads two steps per batch."""
+    kernel (label 2)."""
     assert rep.flat_plans and set(rep.flat_plans.values()) == {(1, 1, 1, 2)}, rep.flat_plans
     assert rep.checks["decode_flat_O"] <= 2e-2
 
