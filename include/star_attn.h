@@ -238,7 +238,10 @@ int star_attn_phase2(const star_attn_shape* shape,
  *     most 8.5 MB for any decode-sized call (G * q_len <= 16) on an MI355X, 0.1 to
  *     tens of MB for query encoding.  A call that needs more than
  *     STAR_ATTN_STATIC_SCRATCH_BYTES is refused with
- *     STAR_ATTN_ERR_WORKSPACE_TOO_SMALL before anything is enqueued.
+ *     STAR_ATTN_ERR_WORKSPACE_TOO_SMALL before anything is enqueued, but for bf16
+ *     calls of 17 to 32 rows (G * q_len; 64 where K + V exceed 192 MiB) on more than
+ *     64 keys: they make do with the splits it holds, as star_attn_phase2 does with a
+ *     workspace of that size.
  *   - Every call on a GPU shares that GPU's one array: calls on one stream run in
  *     order and are safe; calls that overlap on one GPU (two streams, two
  *     threads, two graphs replayed at once) race on it and give wrong results.

@@ -152,10 +152,13 @@ static int64_t stream_slots(const Geom& g) {
   const int64_t slots = STREAM_WGS / ((int64_t)g.B * g.Hkv);
   return slots > 1 ? slots : 1;
 }
+// A bf16 call of few rows, too many for one block of columns.
+static bool few_rows(const Geom& g, int64_t rows, int64_t total) {
+  return total > 64 && rows > 16 && rows <= (decode_cache_resident(g, total) ? 32 : 64);
+}
 // Whether a call streams; if so, into how many splits and how many wavefronts share one.
 static bool streams(const Geom& g, int64_t rows, int64_t total, int* waves, int64_t* splits) {
-  if (total <= 64 || rows > 64) return false;
-  if (rows > 32 && (decode_cache_resident(g, total) || total < STREAM_WIDE_KEYS)) return false;
+  if (!few_rows(g, rows, total) || (rows > 32 && total < STREAM_WIDE_KEYS)) return false;
   const int64_t pairs = (int64_t)g.B * g.Hkv, slots = stream_slots(g), steps = ceil_div(total, 32);
   *waves = steps <= 2 * slots && total <= STREAM_PAIRED_KEYS ? 2 : 4;
   const int64_t worth = ceil_div(steps, *waves);
@@ -718,11 +721,14 @@ static int phase2_impl(const star_attn_shape* shape, const Rope* rope, int64_t c
   SplitPlan plan;
   if (!make_plan(shape, q_len, total, O_part != nullptr, &plan))
     return STAR_ATTN_ERR_INVALID_SHAPE;
-  if (!static_scratch && workspace_bytes < plan_bytes(shape, plan, q_len) &&
+  // (A call of few rows makes do with the static scratch too: whether it streams, in few splits, or is row-tiled, in
+  // more, is a matter of the CUs that it keeps busy.)
+  Geom g = make_geom(shape);
+  const bool makes_do = !static_scratch || (shape->dtype == STAR_ATTN_BF16 && few_rows(g, (int64_t)g.G * q_len, total));
+  if (makes_do && workspace_bytes < plan_bytes(shape, plan, q_len) &&
       !make_plan(shape, q_len, total, O_part != nullptr, &plan, (int64_t)workspace_bytes))
     return STAR_ATTN_ERR_INVALID_SHAPE;
   if (workspace_bytes < plan_bytes(shape, plan, q_len)) return STAR_ATTN_ERR_WORKSPACE_TOO_SMALL;
-  Geom g = make_geom(shape);
   if ((int64_t)g.B * plan.s_total * ((q_len + 31) / 32) * g.Hq > (int64_t)0x7fffffff)
     return STAR_ATTN_ERR_INVALID_SHAPE;
   if (static_scratch) {

@@ -81,6 +81,29 @@ def test_static_scratch_entry_fp32_and_its_size_limit():
     assert rc == -7                                    # STAR_ATTN_ERR_WORKSPACE_TOO_SMALL
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L,q", [
+    (11, 56, 28, 2638, 32),     # 308 (batch, KV head) pairs: two splits of 10 MB each would fill the CUs best
+    (24, 8, 8, 17000, 44),      # 33 rows and more, K + V of 1.7 GB
+])
+def test_static_scratch_entry_makes_do_with_calls_of_few_rows(B, Hq, Hkv, L, q):
+    """Calls of few rows that keep the chip busier row-tiled than streamed, in more splits than the scratch holds, are taken
+    all the same: with the bits of star_attn_phase2 in a workspace of that size."""
+    shape = sa.StarShape.make("bf16", B, Hq, Hkv, 128, L, max(256, L // 4), 0, L + q)
+    plan = sa.phase2_plan(shape, L, q)
+    assert plan.decode == 0 and plan.workspace_bytes > sa.STATIC_SCRATCH_BYTES
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)
+    Q, K, V, Kc, Vc = new(B, q, Hq, 128), new(B, q, Hkv, 128), new(B, q, Hkv, 128), new(B, Hkv, L + q, 128), new(B, Hkv, L + q, 128)
+    O, O_st, O_all = (torch.empty_like(Q) for _ in range(3))
+    print(f"[{B} {Hq}/{Hkv} L={L} q={q}]", flush=True)
+    sa.phase2_static(shape, L, Q, K, V, Kc, Vc, O_st)
+    sa.phase2(shape, L, Q, K, V, Kc, Vc, O, torch.empty(sa.STATIC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda"))
+    sa.phase2(shape, L, Q, K, V, Kc, Vc, O_all, sa.alloc_workspace(shape, q))
+    torch.cuda.synchronize()
+    assert torch.equal(O_st, O)
+    assert (O_st.float() - O_all.float()).abs().max().item() <= 2 * ph.TOL["bf16"]["o"]      # each within it of the exact one
+
+
 def test_static_scratch_entry_under_graph_capture():
     """The callers the entry point is for: a decode loop captured into a HIP graph
     with no workspace to bring.  Every replay (with eager work in between) gives
