@@ -1,9 +1,9 @@
-// fp32 path (head_dim 64 or 128): row-tiled attention on the fp32 matrix
-// instructions, fp32 storage, products, sums and softmax throughout, so the result
-// stays within 1e-5 of an fp64 evaluation at the sizes this path is meant for.
+// fp32 path (head_dim 64 or 128): row-tiled attention, fp32 storage, sums and softmax throughout and products good to 24 bits, so
+// the result stays within 1e-5 of an fp64 evaluation at the sizes this path is meant for.  Tiles of 16 rows take their products on the
+// fp32 matrix instructions, tiles of 32 rows in parts on the bf16 ones ("split products" below), but on short key ranges.
 //
 // What bounds it: the fp32 MFMA rate (157 TFLOP/s, 32 cycles for the 2048 flops of
-// v_mfma_f32_16x16x4_f32) for long key ranges, latency for short ones.  Both are
+// v_mfma_f32_16x16x4_f32) for long key ranges of 16-row tiles, latency for short ones.  Both are
 // served by the same split:
 //   * A workgroup owns a tile of 16 NB query rows of one KV group, and its KW
 //     wavefronts share the tile's KEYS: wavefront w takes the 16-key units
@@ -27,10 +27,9 @@
 //   * The KW partial results (O, m, l) of a row meet in LDS once, at the end.
 // Phase 1 reads K and V where the caller left them and files its own tokens' rows in
 // the caches; phase 2 reads the new tokens from the call's Kq / Vq and appends them.
-// Measured, whole calls, against a kernel of one thread per row: 8 / 2 heads, d = 128,
-// L = 4099, b = 1024, a = 512: 3390 -> 134 us (113 TFLOP/s; 129 at 8192 tokens in blocks of
-// 2048, where a library fp32 matrix product reaches 152); 1 head, d = 64, L = 1024,
-// b = a = 256: 274 -> 9.2 us.
+// Measured, whole calls, against a kernel of one thread per row and fp32 products throughout: 8 / 2 heads, d = 128,
+// L = 4099, b = 1024, a = 512: 3390 -> 134 -> 102.5 us (147 TFLOP/s; 174 at 8192 tokens in blocks of 2048, 129 with fp32 products;
+// a library fp32 matrix product reaches 152); 1 head, d = 64, L = 1024, b = a = 256: 274 -> 9.2 us.
 #include "star_internal.h"
 
 namespace star {
@@ -78,10 +77,11 @@ struct KeySeq {
   GlobalBytes Ka, Va, Kl, Vl;
   unsigned a_stride, l_stride;
   int a_lo, a_hi, l_lo, l_hi, l_off;
-  int n_a, n_units;
+  int n_a, n_units;            // in units of KEYS keys
+  template <int KEYS>
   __device__ __forceinline__ void count() {
-    n_a = (a_hi - a_lo + UNIT - 1) / UNIT;
-    n_units = n_a + (l_hi - l_lo + UNIT - 1) / UNIT;
+    n_a = (a_hi - a_lo + KEYS - 1) / KEYS;
+    n_units = n_a + (l_hi - l_lo + KEYS - 1) / KEYS;
   }
 };
 
@@ -110,6 +110,7 @@ struct UnitAt {
   int key0;
   bool local;
 };
+template <int KEYS>
 __device__ __forceinline__ UnitAt unit_at(const KeySeq& seq, int u) {
   // the four bases as scalars of their own: chosen between as struct members, the
   // compiler would keep the struct in scratch memory and index it
@@ -117,7 +118,7 @@ __device__ __forceinline__ UnitAt unit_at(const KeySeq& seq, int u) {
   asm("" : "+s"(Ka), "+s"(Va), "+s"(Kl), "+s"(Vl));
   UnitAt x;
   x.local = u >= seq.n_a;
-  x.key0 = x.local ? seq.l_lo + (u - seq.n_a) * UNIT : seq.a_lo + u * UNIT;
+  x.key0 = x.local ? seq.l_lo + (u - seq.n_a) * KEYS : seq.a_lo + u * KEYS;
   x.n_rows = (x.local ? seq.l_hi : seq.a_hi) - x.key0;
   x.stride = x.local ? seq.l_stride : seq.a_stride;
   const size_t off = (size_t)(x.local ? x.key0 - seq.l_off : x.key0) * x.stride;
@@ -144,6 +145,29 @@ __device__ __forceinline__ void load_v(Unit<D>& r, const UnitAt& x, int lane) {
     const unsigned off = (unsigned)i * x.stride + 16 * (lane & 15);
 #pragma unroll
     for (int h = 0; h < D / 64; ++h) r.v[v][h] = *(GlobalVec)(x.V + off + 256 * h);
+  }
+}
+
+// Moves the references that a score of the unit leaves; t: the lane's largest.
+template <int D, int NB>
+__device__ __forceinline__ void move_references(RowState<D, NB>& w, const float (&t)[NB]) {
+  bool beyond = false;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) beyond |= t[b] > w.top[b];
+  if (__builtin_amdgcn_ballot_w64(beyond) == 0) return;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const float row = xor32_max(fmaxf(t[b], xor16(t[b])));
+    const float m_old = w.top[b] == -INFINITY ? -INFINITY : w.m[b], m_new = fmaxf(m_old, row);
+    const float m = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m_old - m);   // 0 while nothing was visible
+    w.m[b] = m;
+    w.top[b] = m_new + HEADROOM;
+    w.l[b] *= alpha;
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w.o[b][h][e] *= alpha;
   }
 }
 
@@ -186,28 +210,9 @@ __device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, cons
     }
   }
   float t[NB];
-  bool beyond = false;
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    t[b] = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
-    beyond |= t[b] > w.top[b];
-  }
-  if (__builtin_amdgcn_ballot_w64(beyond) != 0) {      // some row's reference moves
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const float row = xor32_max(fmaxf(t[b], xor16(t[b])));
-      const float m_old = w.top[b] == -INFINITY ? -INFINITY : w.m[b], m_new = fmaxf(m_old, row);
-      const float m = m_new == -INFINITY ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m_old - m);   // 0 while nothing was visible
-      w.m[b] = m;
-      w.top[b] = m_new + HEADROOM;
-      w.l[b] *= alpha;
-#pragma unroll
-      for (int h = 0; h < D / 64; ++h)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w.o[b][h][e] *= alpha;
-    }
-  }
+  for (int b = 0; b < NB; ++b) t[b] = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
+  move_references<D, NB>(w, t);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
 #pragma unroll
@@ -258,16 +263,284 @@ __device__ __forceinline__ void attend(RowState<D, NB>& w, const KeySeq& seq, in
                                        const int (&row_lim)[NB], int wave_lim, float qk_scale, int lane) {
   if (first >= seq.n_units) return;
   Unit<D> r;
-  UnitAt cur = unit_at(seq, first);
+  UnitAt cur = unit_at<UNIT>(seq, first);
   load_k<D>(r, cur, lane);
   load_v<D>(r, cur, lane);
   scale_rows<D, NB>(w, qk_scale);
   for (int u = first + step; u < seq.n_units; u += step) {
-    const UnitAt nxt = unit_at(seq, u);
+    const UnitAt nxt = unit_at<UNIT>(seq, u);
     attend_unit<D, NB, true>(w, r, cur, nxt, row_lim, wave_lim, lane);
     cur = nxt;
   }
   attend_unit<D, NB, false>(w, r, cur, cur, row_lim, wave_lim, lane);
+}
+
+// ------------------------------------------------------------------ split products
+// 32-row tiles take both products on the bf16 matrix instructions, which do sixteen times the work: an fp32 number is three bf16
+// parts of 8 bits, x = h + m + l, and a product the sum of the six products of parts that reach its 24 bits (what is left out is
+// below 2^-24 of it), summed in fp32, 32 products at a time where an fp32 instruction adds four.  Error against 64 bits, rms over 16 seeds,
+// fp32 products / split: prefill, 8 / 2 heads, 4099 tokens: d = 128 2.75 / 1.92e-7 (log-sum-exp 1.79 / 1.64e-7), d = 64 2.79 / 2.08e-7
+// (1.81 / 1.80e-7); 100 tokens on 4000 keys 1.78 / 1.58e-7.
+// What bounds this loop is the sum of 192 MFMAs (3072 cycles) and 640 VALU instructions per 32 keys and 32 rows, two thirds of them
+// to split K and V (a dot product and an MFMA do not overlap; split with shifts and subtractions, which do, they are 960, and the
+// prefill above takes 114 us); with one row block to a wavefront (16-row tiles) that outweighs what the MFMAs save.  Tiles whose
+// wavefronts share the split of K and V through LDS, two barriers per 32 keys, took 116 to 126 us.
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+constexpr int SPLIT_UNIT = 32;
+
+struct Parts {                 // of eight elements
+  u32x4 h, m, l;
+};
+__device__ __forceinline__ uint32_t rounded(float x, float y) { return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)x, (__bf16)y}); }
+__device__ __forceinline__ float left(float x, uint32_t pair, uint32_t minus) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, minus), x, false);
+}
+// Elements 2 i and 2 i + 1: the rounded pair and, by a product with (-1, 0) or (0, -1), what it leaves of each (exact).
+__device__ __forceinline__ void split_pair(Parts& p, int i, float x, float y) {
+  // (in registers: as a literal the second would be taken for the inline constant -1.0, which is another pair)
+  uint32_t first = 0x0000bf80u, second = 0xbf800000u;
+  asm("" : "+s"(first), "+s"(second));
+  p.h[i] = rounded(x, y);
+  x = left(x, p.h[i], first); y = left(y, p.h[i], second);
+  p.m[i] = rounded(x, y);
+  x = left(x, p.m[i], first); y = left(y, p.m[i], second);
+  p.l[i] = rounded(x, y);
+}
+__device__ __forceinline__ f32x4 multiply(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The query rows' parts: step t of the scores takes Q[row][32 t + 4 j4 .. +3] and Q[row][32 t + 16 + 4 j4 .. +3].  At d = 128 the two
+// smaller ones are in LDS, for all wavefronts of the tile (they hold the same rows).
+template <int D>
+struct SharedRows {
+  u32x4 m[2][D / 32][64], l[2][D / 32][64];
+};
+template <int D>
+struct SplitRows {
+  static constexpr bool SHARED = D == 128;
+  u32x4 h[2][D / 32], m[2][SHARED ? 1 : D / 32], l[2][SHARED ? 1 : D / 32];
+};
+
+// Two 16-key pieces c of K, and V in pieces h of 64 columns.
+template <int D>
+struct SplitUnit {
+  f32x4 k[2][D / 16];
+  f32x4 v[D / 64][2][4];
+};
+template <int D>
+__device__ __forceinline__ void load_k(SplitUnit<D>& r, const UnitAt& x, int c, int lane) {
+  int i = 16 * c + (lane & 15);
+  if (x.n_rows < SPLIT_UNIT) i = i < x.n_rows ? i : x.n_rows - 1;
+  const unsigned off = (unsigned)i * x.stride + 16 * (lane >> 4);
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t) r.k[c][t] = *(GlobalVec)(x.K + off + 64 * t);
+}
+template <int D>
+__device__ __forceinline__ void load_v(SplitUnit<D>& r, const UnitAt& x, int h, int lane) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      int i = 16 * c + 4 * (lane >> 4) + v;
+      if (x.n_rows < SPLIT_UNIT) i = i < x.n_rows ? i : x.n_rows - 1;
+      r.v[h][c][v] = *(GlobalVec)(x.V + (unsigned)i * x.stride + 16 * (lane & 15) + 256 * h);
+    }
+}
+
+// One unit, as attend_unit().  At d = 128 there are registers for half of K and of V: V is requested where K has been used up,
+// and the next unit's K where V has; at d = 64 each a whole unit ahead.
+template <int D, bool MORE>
+__device__ __forceinline__ void attend_split_unit(RowState<D, 2>& w, const SplitRows<D>& q, const SharedRows<D>* shared, SplitUnit<D>& r,
+                                                  const UnitAt& cur, const UnitAt& nxt, const int (&row_lim)[2], int wave_lim, int lane) {
+  constexpr bool SHARED = SplitRows<D>::SHARED, LATE = D == 128;
+  const int j4 = lane >> 4;
+  f32x4 s[2][2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    // sums of their own for large and small products; d = 64 has registers for two of the large, which keeps the rounding of a
+    // large logit below the fp32 products'
+    constexpr int CH = D == 64 ? 2 : 1;
+    f32x4 sum[2][CH], small[2], least[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) sum[b][0] = sum[b][CH - 1] = small[b] = least[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < D / 32; ++t) {
+      Parts k;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) split_pair(k, e, r.k[c][2 * t + e / 2][2 * (e & 1)], r.k[c][2 * t + e / 2][2 * (e & 1) + 1]);
+      u32x4 qm[2], ql[2];
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        qm[b] = SHARED ? shared->m[b][t][lane] : q.m[b][SHARED ? 0 : t];
+        ql[b] = SHARED ? shared->l[b][t][lane] : q.l[b][SHARED ? 0 : t];
+      }
+#pragma unroll
+      for (int b = 0; b < 2; ++b) sum[b][t % CH] = multiply(k.h, q.h[b][t], sum[b][t % CH]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) small[b] = multiply(k.m, q.h[b][t], small[b]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) least[b] = multiply(k.l, q.h[b][t], least[b]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) small[b] = multiply(k.h, qm[b], small[b]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) least[b] = multiply(k.m, qm[b], least[b]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) least[b] = multiply(k.h, ql[b], least[b]);
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) s[b][c] = (CH == 1 ? sum[b][0] : sum[b][0] + sum[b][CH - 1]) + (small[b] + least[b]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (LATE) load_v<D>(r, cur, c, lane);
+    else if (MORE) load_k<D>(r, nxt, c, lane);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (cur.n_rows < SPLIT_UNIT || (cur.local && cur.key0 + SPLIT_UNIT > wave_lim)) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int room = row_lim[b] - cur.key0;
+      const int n = (cur.local && room < cur.n_rows ? room : cur.n_rows) - 4 * j4;
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s[b][c][v] = 16 * c + v < n ? s[b][c][v] : -INFINITY;
+    }
+  }
+  float top[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+    top[b] = fmaxf(fmaxf(fmaxf(s[b][0][0], s[b][0][1]), fmaxf(s[b][0][2], s[b][0][3])),
+                   fmaxf(fmaxf(s[b][1][0], s[b][1][1]), fmaxf(s[b][1][2], s[b][1][3])));
+  move_references<D, 2>(w, top);
+  Parts p[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s[b][c][v] = __builtin_amdgcn_exp2f(s[b][c][v] - w.m[b]);
+    w.l[b] += ((s[b][0][0] + s[b][0][1]) + (s[b][0][2] + s[b][0][3])) + ((s[b][1][0] + s[b][1][1]) + (s[b][1][2] + s[b][1][3]));
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      s[b][c] *= HELD;
+      split_pair(p[b], 2 * c, s[b][c][0], s[b][c][1]);
+      split_pair(p[b], 2 * c + 1, s[b][c][2], s[b][c][3]);
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < D / 64; ++h) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      Parts v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) split_pair(v, i, r.v[h][i / 2][2 * (i & 1)][e], r.v[h][i / 2][2 * (i & 1) + 1][e]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) w.o[b][h][e] = multiply(v.l, p[b].h, w.o[b][h][e]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) w.o[b][h][e] = multiply(v.m, p[b].m, w.o[b][h][e]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) w.o[b][h][e] = multiply(v.h, p[b].l, w.o[b][h][e]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) w.o[b][h][e] = multiply(v.m, p[b].h, w.o[b][h][e]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) w.o[b][h][e] = multiply(v.h, p[b].m, w.o[b][h][e]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) w.o[b][h][e] = multiply(v.h, p[b].h, w.o[b][h][e]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (MORE) {
+      if (LATE) load_k<D>(r, nxt, h, lane);
+      else load_v<D>(r, nxt, h, lane);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Whether the parts may have gone wrong: an infinite one (inputs from 3.39e38 on) shows as a result that is not finite --
+// infinities of both signs, or zero times infinity, in a sum -- and values whose last part is denormal (below 2^-110 or so) as
+// results below 2^-90.
+template <int D>
+__device__ __forceinline__ bool unsafe(const RowState<D, 2>& w) {
+  float zero = 0.f, least = INFINITY;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    zero = fmaf(w.l[b], 0.f, zero);
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          zero = fmaf(w.o[b][h][e][v], 0.f, zero);
+          const float size = fabsf(w.o[b][h][e][v]);
+          least = fminf(least, size > 0.f ? size : INFINITY);
+        }
+  }
+  return __builtin_amdgcn_ballot_w64(!(zero == 0.f) || least < 0x1p-90f) != 0;
+}
+
+// As attend() for wavefront `wave` of KW, all of which call it (`w` holds the rows); `again()` loads the rows once more.
+template <int D, int KW, typename Again>
+__device__ __forceinline__ void attend_split(RowState<D, 2>& w, SharedRows<D>* shared, KeySeq& seq, int wave, const int (&row_lim)[2],
+                                             int wave_lim, float qk_scale, int lane, Again again) {
+  constexpr bool SHARED = SplitRows<D>::SHARED, LATE = D == 128;
+  seq.count<SPLIT_UNIT>();
+  const bool any = wave < seq.n_units;
+  SplitUnit<D> r;
+  UnitAt cur;
+  if (any) {
+    cur = unit_at<SPLIT_UNIT>(seq, wave);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) load_k<D>(r, cur, c, lane);
+    if (!LATE)
+#pragma unroll
+      for (int h = 0; h < D / 64; ++h) load_v<D>(r, cur, h, lane);
+  }
+  scale_rows<D, 2>(w, qk_scale);
+  SplitRows<D> q;
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int t = 0; t < D / 32; ++t) {
+      Parts x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) split_pair(x, e, w.q[b][2 * t + e / 2][2 * (e & 1)], w.q[b][2 * t + e / 2][2 * (e & 1) + 1]);
+      q.h[b][t] = x.h;
+      if (!SHARED) {
+        q.m[b][SHARED ? 0 : t] = x.m;
+        q.l[b][SHARED ? 0 : t] = x.l;
+      } else if ((b * (D / 32) + t) % KW == wave) {
+        shared->m[b][t][lane] = x.m;
+        shared->l[b][t][lane] = x.l;
+      }
+    }
+  if (SHARED) __syncthreads();
+  if (!any) return;
+  for (int u = wave + KW; u < seq.n_units; u += KW) {
+    const UnitAt nxt = unit_at<SPLIT_UNIT>(seq, u);
+    attend_split_unit<D, true>(w, q, shared, r, cur, nxt, row_lim, wave_lim, lane);
+    cur = nxt;
+  }
+  attend_split_unit<D, false>(w, q, shared, r, cur, cur, row_lim, wave_lim, lane);
+  if (__builtin_expect(unsafe<D>(w), 0)) {      // the same keys in fp32 products, which take every value
+    again();
+    scale_rows<D, 2>(w, qk_scale);
+    for (int u = wave; u < seq.n_units; u += KW) {
+      cur = unit_at<SPLIT_UNIT>(seq, u);
+      for (int done = 0; done < SPLIT_UNIT && cur.n_rows > 0; done += UNIT) {
+        Unit<D> one;
+        load_k<D>(one, cur, lane);
+        load_v<D>(one, cur, lane);
+        attend_unit<D, 2, false>(w, one, cur, cur, row_lim, wave_lim, lane);
+        cur.K += (size_t)UNIT * cur.stride;
+        cur.V += (size_t)UNIT * cur.stride;
+        cur.key0 += UNIT;
+        cur.n_rows -= UNIT;
+      }
+    }
+  }
 }
 
 // log(l 2^m) for l > 0: the exponent of l joins m without a rounding lost, so that l may be a large sum
@@ -277,11 +550,17 @@ __device__ __forceinline__ float log_sum(float m, float l) {
   return fmaf(t, LN2, (log2f(__builtin_amdgcn_frexp_mantf(l)) + lost) * LN2);
 }
 
+template <bool A, typename X, typename Y> struct Either { typedef X type; };
+template <typename X, typename Y> struct Either<false, X, Y> { typedef Y type; };
 // LDS in which the KW wavefronts' results of a tile meet, 64 columns of d at a time.
 // The pitch of 68 floats spreads the 16 rows of a 16-byte write over all banks.
-template <int NB, int KW>
+template <int D, int NB, int KW, bool SPLIT>
 struct Meet {
-  float o[KW][16 * NB][68];
+  struct None {};
+  union {
+    typename Either<SPLIT && D == 128, SharedRows<D>, None>::type rows;      // split products: until the key loop ends
+    float o[KW][16 * NB][68];
+  };
   float m[KW][16 * NB], l[KW][16 * NB];
   float scale[KW][16 * NB];
 };
@@ -289,8 +568,8 @@ struct Meet {
 // Fold the wavefronts' partial results; `store(row, col, f32x4)` takes the normalised
 // output of tile row `row`, columns col .. col + 3, and `store_lse(row, lse)` its
 // natural-log denominator (-inf, output 0, for a row that saw no key).
-template <int D, int NB, int KW, typename Store, typename StoreLse>
-__device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<NB, KW>& x, Store store, StoreLse store_lse) {
+template <int D, int NB, int KW, bool SPLIT, typename Store, typename StoreLse>
+__device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<D, NB, KW, SPLIT>& x, Store store, StoreLse store_lse) {
   constexpr int ROWS = 16 * NB;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, j4 = lane >> 4;
 #pragma unroll
@@ -329,6 +608,18 @@ __device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<NB, KW>& x, Store 
       store(row, 64 * h + c, acc);
     }
     if (h + 1 < D / 64) __syncthreads();
+  }
+}
+
+// The key loop of wavefront `wave`.
+template <int D, int NB, int KW, bool SPLIT, typename Again>
+__device__ __forceinline__ void attend_rows(RowState<D, NB>& w, Meet<D, NB, KW, SPLIT>& x, KeySeq& seq, int wave, const int (&row_lim)[NB],
+                                            int wave_lim, float qk_scale, int lane, Again again) {
+  if constexpr (SPLIT) {
+    attend_split<D, KW>(w, (SharedRows<D>*)&x.rows, seq, wave, row_lim, wave_lim, qk_scale, lane, again);
+  } else {
+    seq.count<UNIT>();
+    attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, qk_scale, lane);
   }
 }
 
@@ -396,9 +687,9 @@ __device__ __forceinline__ Tile tile_at(const TileOrder& p, int wg) {
   return {__builtin_amdgcn_readfirstlane(kvh), __builtin_amdgcn_readfirstlane(beta), __builtin_amdgcn_readfirstlane(i),
           __builtin_amdgcn_readfirstlane(t)};
 }
-template <int D, int NB, int KW>
+template <int D, int NB, int KW, bool SPLIT>
 __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, TileOrder order, int first_wg) {
-  __shared__ Meet<NB, KW> x;
+  __shared__ Meet<D, NB, KW, SPLIT> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
@@ -421,15 +712,18 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
 
   RowState<D, NB> w;
   int row_lim[NB];
+  const auto load_rows = [&]() {
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int rr = 16 * b + col;
-    const unsigned r = head0 + (rr < live_rows ? rr : 0);     // rows past the block repeat the first
-    const unsigned j = quotient(r, order.G);
-    const int tok = tok0 + (int)j, head = kvh * g.G + (int)(r - j * g.G);
-    row_lim[b] = tok + 1;
-    load_row<D, NB>(w, b, (const float*)a.Q + (((int64_t)beta * g.L + tok) * g.Hq + head) * D, j4);
-  }
+    for (int b = 0; b < NB; ++b) {
+      const int rr = 16 * b + col;
+      const unsigned r = head0 + (rr < live_rows ? rr : 0);     // rows past the block repeat the first
+      const unsigned j = quotient(r, order.G);
+      const int tok = tok0 + (int)j, head = kvh * g.G + (int)(r - j * g.G);
+      row_lim[b] = tok + 1;
+      load_row<D, NB>(w, b, (const float*)a.Q + (((int64_t)beta * g.L + tok) * g.Hq + head) * D, j4);
+    }
+  };
+  load_rows();
   const int wave_lim = tok0 + 1;                      // the tile's first row sees least
 
   KeySeq seq;
@@ -445,10 +739,9 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
   seq.Kl = (GlobalBytes)Kb; seq.Vl = (GlobalBytes)Vb; seq.l_stride = (unsigned)stride * 4; seq.l_off = 0;
   seq.l_lo = s;
   seq.l_hi = tok0 + (int)quotient(head0 + live_rows - 1, order.G) + 1;
-  seq.count();
-  attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, g.scale * LOG2E, lane);
+  attend_rows<D, NB, KW, SPLIT>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
 
-  meet<D, NB, KW>(w, x,
+  meet<D, NB, KW, SPLIT>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
         const unsigned r = head0 + row, j = quotient(r, order.G);
@@ -476,9 +769,9 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
 struct RowGrid {
   Div Hkv, tiles, splits, G;
 };
-template <int D, int NB, int KW>
+template <int D, int NB, int KW, bool SPLIT>
 __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, RowGrid grid, int first_wg) {
-  __shared__ Meet<NB, KW> x;
+  __shared__ Meet<D, NB, KW, SPLIT> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
@@ -494,13 +787,16 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, Ro
 
   RowState<D, NB> w;
   int row_lim[NB];
+  const auto load_rows = [&]() {
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int rr = 16 * b + col, r = r0 + (rr < live_rows ? rr : 0);   // rows past the last repeat the first
-    const int j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
-    row_lim[b] = (int)visible_limit(a, j);
-    load_row<D, NB>(w, b, (const float*)a.Qq + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D, j4);
-  }
+    for (int b = 0; b < NB; ++b) {
+      const int rr = 16 * b + col, r = r0 + (rr < live_rows ? rr : 0);   // rows past the last repeat the first
+      const int j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
+      row_lim[b] = (int)visible_limit(a, j);
+      load_row<D, NB>(w, b, (const float*)a.Qq + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D, j4);
+    }
+  };
+  load_rows();
   const int wave_lim = (int)visible_limit(a, quotient(r0, grid.G));
 
   // rows below cache_len are cached and visible to every token; the rest are the
@@ -524,11 +820,10 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, Ro
   seq.Kl = (GlobalBytes)Kl; seq.Vl = (GlobalBytes)Vl;
   seq.l_stride = (unsigned)(fused_append ? g.Hkv * D : D) * 4;
   seq.l_off = fused_append ? cache_len : 0;
-  seq.count();
-  attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, g.scale * LOG2E, lane);
+  attend_rows<D, NB, KW, SPLIT>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
 
   const bool direct = a.O != nullptr || a.A != nullptr;      // one split: nothing to merge
-  meet<D, NB, KW>(w, x,
+  meet<D, NB, KW, SPLIT>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
         const int r = r0 + row, j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
@@ -586,7 +881,7 @@ int64_t tile_order(const Phase1Args& a, int rows, TileOrder* o) {
   return tiles;
 }
 
-template <int D, int NB, int KW>
+template <int D, int NB, int KW, bool SPLIT>
 hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   TileOrder o;
   const int64_t tiles = tile_order(a, 16 * NB, &o);
@@ -598,11 +893,11 @@ hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   o.turn_from = 0x7fffffff; o.turn = 0;
   if (wgs > cus && wgs <= 2 * cus) { o.turn_from = (int)cus; o.turn = (int)(cus + wgs - 1); }
   return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-    phase1_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, o, (int)first);
+    phase1_f32_kernel<D, NB, KW, SPLIT><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, o, (int)first);
   });
 }
 
-template <int D, int NB, int KW>
+template <int D, int NB, int KW, bool SPLIT>
 hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
   const Geom& g = a.g;
   const int64_t tiles = ((int64_t)g.G * a.q_len + 16 * NB - 1) / (16 * NB);
@@ -610,29 +905,36 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
   if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff - 64) return hipErrorInvalidValue;
   const RowGrid grid = {make_div(g.Hkv), make_div((uint32_t)tiles), make_div(a.plan.s_total), make_div(g.G)};
   return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-    phase2_f32_kernel<D, NB, KW><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, grid, (int)first);
+    phase2_f32_kernel<D, NB, KW, SPLIT><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, grid, (int)first);
   });
 }
 
 }  // namespace
 
-// 32-row tiles shared by four wavefronts (two workgroups per CU) once there are four such
-// tiles per CU; down to one 16-row tile per CU, 16-row tiles shared by four (three per CU);
-// fewer rows than that are bound by the latency of a tile: eight wavefronts share it.
-// Measured (32 x 4 / 16 x 4 / 16 x 8, us; 8 / 2 heads except the last): d = 128: L = 8192
-// (2048 32-row tiles) 705 / 740 / 819, L = 4099 (1025) 151 / 156 / 193, L = 1024 (256)
-// 26.3 / 23.7 / 29.2; d = 64: L = 8192 369 / 375 / 395, L = 2048 (512) 39.0 / 37.3 / 39.4;
-// 1 head, d = 64, L = 1024 (32) 16.0 / 10.0 / 9.9.
-// Blocks of at most two units of keys have nothing to share: one wavefront per tile.  Against
-// the set-up above (and one thread per row), us, 8 / 8 heads: d = 64, 100000 tokens: b = 1, a = 0
-// 4790 -> 975 (3336), b = 4, a = 0 1245 -> 274 (1000), b = 4, a = 4 1379 -> 368 (1495); 50000 tokens,
-// d = 128: b = a = 16 474 -> 251 (2262); three units and more: 146 -> 144 (b = 32, a = 0), 165 -> 169 (64).
+// Blocks of at most two units of keys have nothing to share: one wavefront per tile.  Against the set-ups below (and one thread
+// per row), us, 8 / 8 heads: d = 64, 100000 tokens: b = 1, a = 0 4790 -> 975 (3336), b = 4, a = 0 1245 -> 274 (1000), b = 4, a = 4
+// 1379 -> 368 (1495); 50000 tokens, d = 128: b = a = 16 474 -> 251 (2262); three units and more: 146 -> 144 (b = 32, a = 0), 165 -> 169
+// (64).
+// 32-row tiles shared by four wavefronts (two workgroups per CU) from more than one such tile per CU on; down to one 16-row tile
+// per CU, 16-row tiles shared by four (three per CU); fewer rows than that are bound by the latency of a tile: eight wavefronts
+// share it.  Measured, 16-row tiles / 32-row tiles in split products, us: d = 128: 8 / 2 heads, b = a = L / 4: L = 1060 (265 32-row tiles)
+// 25.5 / 25.4, 1150 29.2 / 26.5, 2048 62 / 44, 4000 191 / 134; one head, 8192 (256 tiles) 103 / 102, blocks as long as the
+// context 153 / 193, 9000 259 / 214.  At d = 64 a tile's start weighs more: 1060 14.1 / 16.4, 1350 (338) 19.6 / 20.1, 1500 (375) 21.5 /
+// 21.9, 2048 (512) 33.9 / 26.9, but one head, 9000 (282), b = a = 2250 79.4 / 68.2.  Eight wavefronts: one head, d = 64, L = 1024
+// (32) 10.0 (four) / 9.9, d = 64, 8 / 2 heads, 2048 37.3 / 39.4.
+// Split products against fp32 products in the same 32-row tiles, us: d = 128: 8 / 2 heads, 4099 (b = 1024, a = 512) 134 / 102.5, 8192 (b = a =
+// 2048) 668 / 496; d = 64: 98 / 78, 354 / 273; two sequences of 3000, b = a = 187 40.4 / 39.7.  Units of 32 keys for four wavefronts
+// leave some idle on short ranges, which shows at d = 64 (8 / 8 heads, 20000 tokens): b = 150, a = 75 102.8 / 111.2, b = 64, a = 32 75.6 /
+// 82.9 (d = 128: 226 / 203, 162 / 144).
+constexpr int SPLIT_KEYS_64 = 256;      // longest range that d = 64 takes in fp32 products in phase 1
 Phase1Plan phase1_plan_f32(const Geom& g) {
-  const int64_t bmax = g.b < g.L ? g.b : g.L, rows = g.L * g.G * g.Hkv * g.B;
-  Phase1Plan p = {0, 16, 8, 0, 0};
+  const int64_t bmax = g.b < g.L ? g.b : g.L, rows = g.L * g.G * g.Hkv * g.B, keys = g.a + bmax;
+  Phase1Plan p = {0, 16, 8, 0, 0, 0};
   if ((g.a + UNIT - 1) / UNIT + (bmax + UNIT - 1) / UNIT <= 2) p.waves = 1;
-  else if (rows >= 1024 * 32) { p.rows = 32; p.waves = 4; }
-  else if (rows >= 256 * 16) p.waves = 4;
+  else if (rows > 256 * 32 && (g.d == 128 || rows > 384 * 32 || keys > 1024)) {
+    p.rows = 32; p.waves = 4;
+    p.split = g.d == 128 || keys > SPLIT_KEYS_64;
+  } else if (rows >= 256 * 16) p.waves = 4;
   const int64_t full = g.L / g.b, rest = g.L - full * g.b;      // (the short last block has fewer)
   p.tiles = (full * ((g.b * g.G + p.rows - 1) / p.rows) + (rest * g.G + p.rows - 1) / p.rows) * g.B * g.Hkv;
   return p;
@@ -640,22 +942,27 @@ Phase1Plan phase1_plan_f32(const Geom& g) {
 
 hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   const Phase1Plan p = phase1_plan_f32(a.g);
-  if (p.waves == 1) return a.g.d == 64 ? launch_phase1<64, 1, 1>(a, st) : launch_phase1<128, 1, 1>(a, st);
-  if (p.rows == 32) return a.g.d == 64 ? launch_phase1<64, 2, 4>(a, st) : launch_phase1<128, 2, 4>(a, st);
-  if (p.waves == 4) return a.g.d == 64 ? launch_phase1<64, 1, 4>(a, st) : launch_phase1<128, 1, 4>(a, st);
-  return a.g.d == 64 ? launch_phase1<64, 1, 8>(a, st) : launch_phase1<128, 1, 8>(a, st);
+  if (p.waves == 1) return a.g.d == 64 ? launch_phase1<64, 1, 1, false>(a, st) : launch_phase1<128, 1, 1, false>(a, st);
+  if (p.rows == 32 && a.g.d == 128) return launch_phase1<128, 2, 4, true>(a, st);
+  if (p.rows == 32) return p.split ? launch_phase1<64, 2, 4, true>(a, st) : launch_phase1<64, 2, 4, false>(a, st);
+  if (p.waves == 4) return a.g.d == 64 ? launch_phase1<64, 1, 4, false>(a, st) : launch_phase1<128, 1, 4, false>(a, st);
+  return a.g.d == 64 ? launch_phase1<64, 1, 8, false>(a, st) : launch_phase1<128, 1, 8, false>(a, st);
 }
 
 // Per-part outputs over short blocks make splits of at most four units: one wavefront per
 // 32-row tile.  Against four (and one thread per row), us: 114 tokens on 54 keys in blocks of
 // 2, three sequences of 120 / 6 heads 418 -> 277 (373), 395 on 600 in blocks of 40, 7 heads
 // 58.8 -> 52.1 (91.6); splits of 128 keys and more lose by it (1000 on 1000 53.8 -> 59.3).
+// Split products (as in phase 1), fp32 / split, us: d = 128: 100 tokens on 16000 keys (8 / 2 heads) 69.6 / 54.0, on 4000 31.1 / 26.5, 20 on
+// 4000 15.0 / 14.8; d = 64: 100 on 16000 40.1 / 33.3 (runs of 864 keys), but 40 on 16000 20.7 / 21.3 (320), 20 on 16000 16.7 / 19.0 (192).
+constexpr int SPLIT_RUN_64 = 512;       // longest splits that d = 64 takes in fp32 products in phase 2
 hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st) {
   if (a.plan.tile_rows == 32 && !a.plan.flat && a.plan.split_len <= 4 * UNIT)
-    return a.g.d == 64 ? launch_phase2<64, 2, 1>(a, st) : launch_phase2<128, 2, 1>(a, st);
-  if (a.plan.tile_rows == 32) return a.g.d == 64 ? launch_phase2<64, 2, 4>(a, st) : launch_phase2<128, 2, 4>(a, st);
-  if (a.plan.waves == 4) return a.g.d == 64 ? launch_phase2<64, 1, 4>(a, st) : launch_phase2<128, 1, 4>(a, st);
-  return a.g.d == 64 ? launch_phase2<64, 1, 8>(a, st) : launch_phase2<128, 1, 8>(a, st);
+    return a.g.d == 64 ? launch_phase2<64, 2, 1, false>(a, st) : launch_phase2<128, 2, 1, false>(a, st);
+  if (a.plan.tile_rows == 32 && a.g.d == 128) return launch_phase2<128, 2, 4, true>(a, st);
+  if (a.plan.tile_rows == 32) return a.plan.split_len > SPLIT_RUN_64 ? launch_phase2<64, 2, 4, true>(a, st) : launch_phase2<64, 2, 4, false>(a, st);
+  if (a.plan.waves == 4) return a.g.d == 64 ? launch_phase2<64, 1, 4, false>(a, st) : launch_phase2<128, 1, 4, false>(a, st);
+  return a.g.d == 64 ? launch_phase2<64, 1, 8, false>(a, st) : launch_phase2<128, 1, 8, false>(a, st);
 }
 
 }  // namespace star

@@ -220,6 +220,7 @@ inline hipError_t launch_in_pieces(int64_t workgroups, int threads, Launch launc
 struct Phase1Plan {
   int32_t queued, rows, waves, group;
   int64_t tiles;
+  int32_t split;       // fp32: products of bf16 parts
 };
 Phase1Plan phase1_plan_bf16(const Geom& g, int anchor_mode, int n_cu);
 Phase1Plan phase1_plan_f32(const Geom& g);
