@@ -1200,8 +1200,8 @@ Phase1Plan phase1_plan_bf16(const Geom& g, int anchor_mode, int n_cu) {
   PlainGrid grid;
   int halves, tpb;
   int64_t wgs;
-  if (plain_phase1(g, anchor_mode, n_cu, &grid, &halves, &wgs)) return Phase1Plan{0, 16 * RB * 4, 4 * halves, grid.group, wgs, 0};
-  return Phase1Plan{1, 16 * WG_BLOCKS, NW, 0, queue_tiles(g, &tpb), 0};
+  if (plain_phase1(g, anchor_mode, n_cu, &grid, &halves, &wgs)) return Phase1Plan{0, 16 * RB * 4, 4 * halves, grid.group, wgs, 0, 1};
+  return Phase1Plan{1, 16 * WG_BLOCKS, NW, 0, queue_tiles(g, &tpb), 0, 1};
 }
 
 hipError_t launch_phase1_bf16(const Phase1Args& a, hipStream_t st) {

@@ -85,20 +85,29 @@ struct KeySeq {
   }
 };
 
+// The columns of d a workgroup computes: one of P pieces, H times 16 E of them (E adjacent ones a lane).
+template <int D, int P>
+struct Piece {
+  static constexpr int C = D / P, E = C < 64 ? C / 16 : 4, H = C / (16 * E);
+  typedef __attribute__((ext_vector_type(E))) float vec;
+  typedef const __attribute__((address_space(1))) vec* Vec;
+};
+
 // A wavefront's state.  Lane (col, j4) belongs to row col of each of NB 16-row blocks.
-template <int D, int NB>
+template <int D, int NB, int P = 1>
 struct RowState {
+  typedef Piece<D, P> Cols;
   f32x4 q[NB][D / 16];        // q[.][t][e] = Q[row][16 t + 4 j4 + e] * scale * log2(e)
-  f32x4 o[NB][D / 64][4];     // o[.][h][e][w] = HELD O[row][64 h + 16 j4 + 4 w + e]
+  f32x4 o[NB][Cols::H][Cols::E];      // o[.][h][e][w] = HELD O[row][E (16 h + 4 j4 + w) + e] of the piece
   float m[NB], top[NB];       // reference (log2 units; uniform over a row's four lanes; 0 until a key is
                               // visible) and the score beyond which it moves (-inf until then)
   float l[NB];                // this lane's share of the sum of 2^(s - m)
 };
 
-template <int D>
+template <int D, int P = 1>
 struct Unit {
   f32x4 k[D / 16];
-  f32x4 v[4][D / 64];
+  typename Piece<D, P>::vec v[4][Piece<D, P>::H];
 };
 
 // Unit u: its first row in K / V, how many rows of the range are left from there on,
@@ -128,29 +137,30 @@ __device__ __forceinline__ UnitAt unit_at(const KeySeq& seq, int u) {
 }
 
 // Rows past the range's end re-read its last row (their scores are masked).
-template <int D>
-__device__ __forceinline__ void load_k(Unit<D>& r, const UnitAt& x, int lane) {
+template <int D, int P>
+__device__ __forceinline__ void load_k(Unit<D, P>& r, const UnitAt& x, int lane) {
   int i = lane & 15;
   if (x.n_rows < UNIT) i = i < x.n_rows ? i : x.n_rows - 1;
   const unsigned off = (unsigned)i * x.stride + 16 * (lane >> 4);
 #pragma unroll
   for (int t = 0; t < D / 16; ++t) r.k[t] = *(GlobalVec)(x.K + off + 64 * t);
 }
-template <int D>
-__device__ __forceinline__ void load_v(Unit<D>& r, const UnitAt& x, int lane) {
+template <int D, int P>
+__device__ __forceinline__ void load_v(Unit<D, P>& r, const UnitAt& x, int lane) {
+  typedef Piece<D, P> Cols;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     int i = 4 * (lane >> 4) + v;
     if (x.n_rows < UNIT) i = i < x.n_rows ? i : x.n_rows - 1;
-    const unsigned off = (unsigned)i * x.stride + 16 * (lane & 15);
+    const unsigned off = (unsigned)i * x.stride + 4 * Cols::E * (lane & 15);
 #pragma unroll
-    for (int h = 0; h < D / 64; ++h) r.v[v][h] = *(GlobalVec)(x.V + off + 256 * h);
+    for (int h = 0; h < Cols::H; ++h) r.v[v][h] = *(typename Cols::Vec)(x.V + off + 64 * Cols::E * h);
   }
 }
 
 // Moves the references that a score of the unit leaves; t: the lane's largest.
-template <int D, int NB>
-__device__ __forceinline__ void move_references(RowState<D, NB>& w, const float (&t)[NB]) {
+template <int D, int NB, int P>
+__device__ __forceinline__ void move_references(RowState<D, NB, P>& w, const float (&t)[NB]) {
   bool beyond = false;
 #pragma unroll
   for (int b = 0; b < NB; ++b) beyond |= t[b] > w.top[b];
@@ -165,17 +175,17 @@ __device__ __forceinline__ void move_references(RowState<D, NB>& w, const float 
     w.top[b] = m_new + HEADROOM;
     w.l[b] *= alpha;
 #pragma unroll
-    for (int h = 0; h < D / 64; ++h)
+    for (int h = 0; h < Piece<D, P>::H; ++h)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w.o[b][h][e] *= alpha;
+      for (int e = 0; e < Piece<D, P>::E; ++e) w.o[b][h][e] *= alpha;
   }
 }
 
 // One unit: scores, softmax, products.  MORE: K and V of unit `nxt` are requested as soon
 // as this unit's are used up -- without a branch, so that the compiler's waits for V
 // need not include them.
-template <int D, int NB, bool MORE>
-__device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, const UnitAt& cur, const UnitAt& nxt,
+template <int D, int NB, bool MORE, int P>
+__device__ __forceinline__ void attend_unit(RowState<D, NB, P>& w, Unit<D, P>& r, const UnitAt& cur, const UnitAt& nxt,
                                             const int (&row_lim)[NB], int wave_lim, int lane) {
   const int j4 = lane >> 4;
   // four chains per score tile (element e of every 16-byte piece has its own; two where the
@@ -196,7 +206,7 @@ __device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, cons
 #pragma unroll
         for (int k = e; k < e + 2; ++k)
           part[b][k % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][k], w.q[b][t][k], part[b][k % CH], 0, 0, 0);
-  if (MORE) load_k<D>(r, nxt, lane);
+  if (MORE) load_k<D, P>(r, nxt, lane);
 #pragma unroll
   for (int b = 0; b < NB; ++b)
     s[b] = CH == 2 ? part[b][0] + part[b][1] : (part[b][0] + part[b][1]) + (part[b][CH - 2] + part[b][CH - 1]);
@@ -212,7 +222,7 @@ __device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, cons
   float t[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) t[b] = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
-  move_references<D, NB>(w, t);
+  move_references<D, NB, P>(w, t);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
 #pragma unroll
@@ -224,31 +234,31 @@ __device__ __forceinline__ void attend_unit(RowState<D, NB>& w, Unit<D>& r, cons
 #pragma unroll
   for (int v = 0; v < 4; ++v)
 #pragma unroll
-    for (int h = 0; h < D / 64; ++h)
+    for (int h = 0; h < Piece<D, P>::H; ++h)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < Piece<D, P>::E; ++e)
 #pragma unroll
         for (int b = 0; b < NB; ++b)
           w.o[b][h][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.v[v][h][e], s[b][v], w.o[b][h][e], 0, 0, 0);
-  if (MORE) load_v<D>(r, nxt, lane);
+  if (MORE) load_v<D, P>(r, nxt, lane);
 }
 
 // The lane's query row of row block b, as it is in memory (scale_rows() follows once the
 // first keys have been requested, so that both round trips overlap).
-template <int D, int NB>
-__device__ __forceinline__ void load_row(RowState<D, NB>& w, int b, const float* q, int j4) {
+template <int D, int NB, int P>
+__device__ __forceinline__ void load_row(RowState<D, NB, P>& w, int b, const float* q, int j4) {
 #pragma unroll
   for (int t = 0; t < D / 16; ++t) w.q[b][t] = *(const f32x4*)(q + 16 * t + 4 * j4);
 #pragma unroll
-  for (int h = 0; h < D / 64; ++h)
+  for (int h = 0; h < Piece<D, P>::H; ++h)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) w.o[b][h][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < Piece<D, P>::E; ++e) w.o[b][h][e] = f32x4{0.f, 0.f, 0.f, 0.f};
   w.m[b] = 0.f;
   w.top[b] = -INFINITY;
   w.l[b] = 0.f;
 }
-template <int D, int NB>
-__device__ __forceinline__ void scale_rows(RowState<D, NB>& w, float qk_scale) {
+template <int D, int NB, int P>
+__device__ __forceinline__ void scale_rows(RowState<D, NB, P>& w, float qk_scale) {
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -258,21 +268,21 @@ __device__ __forceinline__ void scale_rows(RowState<D, NB>& w, float qk_scale) {
 // Attend the wavefront's rows to units first, first + step, ... of the sequence.
 //   row_lim   this lane's exclusive bound on keys of the second range, per row block
 //   wave_lim  smallest bound of the wavefront's live rows
-template <int D, int NB>
-__device__ __forceinline__ void attend(RowState<D, NB>& w, const KeySeq& seq, int first, int step,
+template <int D, int NB, int P>
+__device__ __forceinline__ void attend(RowState<D, NB, P>& w, const KeySeq& seq, int first, int step,
                                        const int (&row_lim)[NB], int wave_lim, float qk_scale, int lane) {
   if (first >= seq.n_units) return;
-  Unit<D> r;
+  Unit<D, P> r;
   UnitAt cur = unit_at<UNIT>(seq, first);
-  load_k<D>(r, cur, lane);
-  load_v<D>(r, cur, lane);
-  scale_rows<D, NB>(w, qk_scale);
+  load_k<D, P>(r, cur, lane);
+  load_v<D, P>(r, cur, lane);
+  scale_rows<D, NB, P>(w, qk_scale);
   for (int u = first + step; u < seq.n_units; u += step) {
     const UnitAt nxt = unit_at<UNIT>(seq, u);
-    attend_unit<D, NB, true>(w, r, cur, nxt, row_lim, wave_lim, lane);
+    attend_unit<D, NB, true, P>(w, r, cur, nxt, row_lim, wave_lim, lane);
     cur = nxt;
   }
-  attend_unit<D, NB, false>(w, r, cur, cur, row_lim, wave_lim, lane);
+  attend_unit<D, NB, false, P>(w, r, cur, cur, row_lim, wave_lim, lane);
 }
 
 // ------------------------------------------------------------------ split products
@@ -413,7 +423,7 @@ __device__ __forceinline__ void attend_split_unit(RowState<D, 2>& w, const Split
   for (int b = 0; b < 2; ++b)
     top[b] = fmaxf(fmaxf(fmaxf(s[b][0][0], s[b][0][1]), fmaxf(s[b][0][2], s[b][0][3])),
                    fmaxf(fmaxf(s[b][1][0], s[b][1][1]), fmaxf(s[b][1][2], s[b][1][3])));
-  move_references<D, 2>(w, top);
+  move_references<D, 2, 1>(w, top);
   Parts p[2];
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
@@ -498,7 +508,7 @@ __device__ __forceinline__ void attend_split(RowState<D, 2>& w, SharedRows<D>* s
 #pragma unroll
       for (int h = 0; h < D / 64; ++h) load_v<D>(r, cur, h, lane);
   }
-  scale_rows<D, 2>(w, qk_scale);
+  scale_rows<D, 2, 1>(w, qk_scale);
   SplitRows<D> q;
 #pragma unroll
   for (int b = 0; b < 2; ++b)
@@ -526,14 +536,14 @@ __device__ __forceinline__ void attend_split(RowState<D, 2>& w, SharedRows<D>* s
   attend_split_unit<D, false>(w, q, shared, r, cur, cur, row_lim, wave_lim, lane);
   if (__builtin_expect(unsafe<D>(w), 0)) {      // the same keys in fp32 products, which take every value
     again();
-    scale_rows<D, 2>(w, qk_scale);
+    scale_rows<D, 2, 1>(w, qk_scale);
     for (int u = wave; u < seq.n_units; u += KW) {
       cur = unit_at<SPLIT_UNIT>(seq, u);
       for (int done = 0; done < SPLIT_UNIT && cur.n_rows > 0; done += UNIT) {
         Unit<D> one;
-        load_k<D>(one, cur, lane);
-        load_v<D>(one, cur, lane);
-        attend_unit<D, 2, false>(w, one, cur, cur, row_lim, wave_lim, lane);
+        load_k<D, 1>(one, cur, lane);
+        load_v<D, 1>(one, cur, lane);
+        attend_unit<D, 2, false, 1>(w, one, cur, cur, row_lim, wave_lim, lane);
         cur.K += (size_t)UNIT * cur.stride;
         cur.V += (size_t)UNIT * cur.stride;
         cur.key0 += UNIT;
@@ -568,9 +578,10 @@ struct Meet {
 // Fold the wavefronts' partial results; `store(row, col, f32x4)` takes the normalised
 // output of tile row `row`, columns col .. col + 3, and `store_lse(row, lse)` its
 // natural-log denominator (-inf, output 0, for a row that saw no key).
-template <int D, int NB, int KW, bool SPLIT, typename Store, typename StoreLse>
-__device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<D, NB, KW, SPLIT>& x, Store store, StoreLse store_lse) {
-  constexpr int ROWS = 16 * NB;
+template <int D, int NB, int KW, bool SPLIT, int P, typename Store, typename StoreLse>
+__device__ __forceinline__ void meet(RowState<D, NB, P>& w, Meet<D, NB, KW, SPLIT>& x, Store store, StoreLse store_lse) {
+  constexpr int ROWS = 16 * NB, E = Piece<D, P>::E, H = Piece<D, P>::H;
+  typedef typename Piece<D, P>::vec vec;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, j4 = lane >> 4;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
@@ -592,34 +603,37 @@ __device__ __forceinline__ void meet(RowState<D, NB>& w, Meet<D, NB, KW, SPLIT>&
     if (k == 0) store_lse(row, l > 0.f ? log_sum(m, l) : -INFINITY);
   }
 #pragma unroll
-  for (int h = 0; h < D / 64; ++h) {
+  for (int h = 0; h < H; ++h) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        *(f32x4*)&x.o[wave][16 * b + col][16 * j4 + 4 * c] =
-            f32x4{w.o[b][h][0][c], w.o[b][h][1][c], w.o[b][h][2][c], w.o[b][h][3][c]};
+      for (int c = 0; c < 4; ++c) {
+        vec v;
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = w.o[b][h][e][c];
+        *(vec*)&x.o[wave][16 * b + col][E * (4 * j4 + c)] = v;
+      }
     __syncthreads();
-    for (int i = tid; i < ROWS * 16; i += 64 * KW) {
-      const int row = i >> 4, c = 4 * (i & 15);
+    for (int i = tid; i < ROWS * 4 * E; i += 64 * KW) {
+      const int row = i / (4 * E), c = 4 * (i % (4 * E));
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int k = 0; k < KW; ++k) acc += *(const f32x4*)&x.o[k][row][c] * x.scale[k][row];
-      store(row, 64 * h + c, acc);
+      store(row, 16 * E * h + c, acc);
     }
-    if (h + 1 < D / 64) __syncthreads();
+    if (h + 1 < H) __syncthreads();
   }
 }
 
 // The key loop of wavefront `wave`.
-template <int D, int NB, int KW, bool SPLIT, typename Again>
-__device__ __forceinline__ void attend_rows(RowState<D, NB>& w, Meet<D, NB, KW, SPLIT>& x, KeySeq& seq, int wave, const int (&row_lim)[NB],
+template <int D, int NB, int KW, bool SPLIT, int P, typename Again>
+__device__ __forceinline__ void attend_rows(RowState<D, NB, P>& w, Meet<D, NB, KW, SPLIT>& x, KeySeq& seq, int wave, const int (&row_lim)[NB],
                                             int wave_lim, float qk_scale, int lane, Again again) {
   if constexpr (SPLIT) {
     attend_split<D, KW>(w, (SharedRows<D>*)&x.rows, seq, wave, row_lim, wave_lim, qk_scale, lane, again);
   } else {
     seq.count<UNIT>();
-    attend<D, NB>(w, seq, wave, KW, row_lim, wave_lim, qk_scale, lane);
+    attend<D, NB, P>(w, seq, wave, KW, row_lim, wave_lim, qk_scale, lane);
   }
 }
 
@@ -687,13 +701,14 @@ __device__ __forceinline__ Tile tile_at(const TileOrder& p, int wg) {
   return {__builtin_amdgcn_readfirstlane(kvh), __builtin_amdgcn_readfirstlane(beta), __builtin_amdgcn_readfirstlane(i),
           __builtin_amdgcn_readfirstlane(t)};
 }
-template <int D, int NB, int KW, bool SPLIT>
+template <int D, int NB, int KW, bool SPLIT, int P>
 __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, TileOrder order, int first_wg) {
   __shared__ Meet<D, NB, KW, SPLIT> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
-  const Tile tile = tile_at(order, first_wg + (int)blockIdx.x);
+  const int wg = first_wg + (int)blockIdx.x, piece = wg % P;
+  const Tile tile = tile_at(order, wg / P);
   const int kvh = tile.kvh, beta = tile.beta, i = tile.i, t = tile.t;
   const int s = (int)(i * g.b);
   const int e = (int)(s + g.b < g.L ? s + g.b : g.L);
@@ -710,7 +725,7 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
   const float* Kb = from_input ? (const float*)a.Kin + in0 : (const float*)a.Kc + cache0;
   const float* Vb = from_input ? (const float*)a.Vin + in0 : (const float*)a.Vc + cache0;
 
-  RowState<D, NB> w;
+  RowState<D, NB, P> w;
   int row_lim[NB];
   const auto load_rows = [&]() {
 #pragma unroll
@@ -720,7 +735,7 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
       const unsigned j = quotient(r, order.G);
       const int tok = tok0 + (int)j, head = kvh * g.G + (int)(r - j * g.G);
       row_lim[b] = tok + 1;
-      load_row<D, NB>(w, b, (const float*)a.Q + (((int64_t)beta * g.L + tok) * g.Hq + head) * D, j4);
+      load_row<D, NB, P>(w, b, (const float*)a.Q + (((int64_t)beta * g.L + tok) * g.Hq + head) * D, j4);
     }
   };
   load_rows();
@@ -734,22 +749,23 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
   const int64_t anchor_rows = (int64_t)(a.anchor_mode == ANCHOR_PER_BLOCK ? order.n_blocks : 1) * g.a;
   const int64_t anchor0 = ((int64_t)beta * anchor_rows * g.Hkv + kvh) * D;
   seq.Ka = (GlobalBytes)(ext ? (const float*)a.Ka + anchor0 : Kb);
-  seq.Va = (GlobalBytes)(ext ? (const float*)a.Va + anchor0 : Vb);
+  constexpr int C = Piece<D, P>::C;
+  seq.Va = (GlobalBytes)((ext ? (const float*)a.Va + anchor0 : Vb) + piece * C);
   seq.a_stride = (unsigned)(ext ? (int64_t)g.Hkv * D : stride) * 4;
-  seq.Kl = (GlobalBytes)Kb; seq.Vl = (GlobalBytes)Vb; seq.l_stride = (unsigned)stride * 4; seq.l_off = 0;
+  seq.Kl = (GlobalBytes)Kb; seq.Vl = (GlobalBytes)(Vb + piece * C); seq.l_stride = (unsigned)stride * 4; seq.l_off = 0;
   seq.l_lo = s;
   seq.l_hi = tok0 + (int)quotient(head0 + live_rows - 1, order.G) + 1;
-  attend_rows<D, NB, KW, SPLIT>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
+  attend_rows<D, NB, KW, SPLIT, P>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
 
-  meet<D, NB, KW, SPLIT>(w, x,
+  meet<D, NB, KW, SPLIT, P>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
         const unsigned r = head0 + row, j = quotient(r, order.G);
         const int tok = tok0 + (int)j, head = kvh * g.G + (int)(r - j * g.G);
-        *(f32x4*)((float*)a.O + (((int64_t)beta * g.L + tok) * g.Hq + head) * D + c) = v;
+        *(f32x4*)((float*)a.O + (((int64_t)beta * g.L + tok) * g.Hq + head) * D + piece * C + c) = v;
       },
       [&](int row, float lse) {
-        if (row >= live_rows || !a.LSE) return;
+        if (row >= live_rows || !a.LSE || piece != 0) return;
         const unsigned r = head0 + row, j = quotient(r, order.G);
         const int tok = tok0 + (int)j, head = kvh * g.G + (int)(r - j * g.G);
         a.LSE[((int64_t)beta * g.Hq + head) * g.L + tok] = lse;
@@ -759,8 +775,8 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
   if (from_input) {
     const int t0 = tok0 + (head0 > 0 ? 1 : 0), t1 = tok0 + (int)quotient(head0 + live_rows + g.G - 1, order.G);
     file_rows<D>(Kb + (int64_t)t0 * stride, Vb + (int64_t)t0 * stride, stride,
-                 (float*)a.Kc + cache0 + (int64_t)t0 * D, (float*)a.Vc + cache0 + (int64_t)t0 * D, t1 - t0, threadIdx.x,
-                 64 * KW);
+                 (float*)a.Kc + cache0 + (int64_t)t0 * D, (float*)a.Vc + cache0 + (int64_t)t0 * D, t1 - t0,
+                 piece * 64 * KW + threadIdx.x, P * 64 * KW);
   }
 }
 
@@ -769,13 +785,13 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
 struct RowGrid {
   Div Hkv, tiles, splits, G;
 };
-template <int D, int NB, int KW, bool SPLIT>
+template <int D, int NB, int KW, bool SPLIT, int P>
 __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, RowGrid grid, int first_wg) {
   __shared__ Meet<D, NB, KW, SPLIT> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
-  const uint32_t id = first_wg + blockIdx.x, of_head = quotient(id, grid.Hkv), of_tile = quotient(of_head, grid.tiles);
+  const uint32_t wg = first_wg + blockIdx.x, id = wg / P, of_head = quotient(id, grid.Hkv), of_tile = quotient(of_head, grid.tiles);
   const int kvh = id - of_head * grid.Hkv.d, tile = of_head - of_tile * grid.tiles.d, beta = quotient(of_tile, grid.splits);
   const int sp = of_tile - beta * grid.splits.d, row_tiles = grid.tiles.d;
   const int r0 = tile * ROWS, n_rows = g.G * a.q_len;  // row = token * G + head in group
@@ -785,7 +801,8 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, Ro
   int64_t lo, hi;
   split_range(a.plan, g.L, g.b, total, sp, &lo, &hi);
 
-  RowState<D, NB> w;
+  const int piece = wg % P, first_d = piece * Piece<D, P>::C;      // (P > 1: calls of one split)
+  RowState<D, NB, P> w;
   int row_lim[NB];
   const auto load_rows = [&]() {
 #pragma unroll
@@ -793,7 +810,7 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, Ro
       const int rr = 16 * b + col, r = r0 + (rr < live_rows ? rr : 0);   // rows past the last repeat the first
       const int j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
       row_lim[b] = (int)visible_limit(a, j);
-      load_row<D, NB>(w, b, (const float*)a.Qq + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D, j4);
+      load_row<D, NB, P>(w, b, (const float*)a.Qq + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D, j4);
     }
   };
   load_rows();
@@ -807,7 +824,7 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, Ro
   KeySeq seq;
   const float* Kb = (const float*)a.Kc + cache0;
   const float* Vb = (const float*)a.Vc + cache0;
-  seq.Ka = (GlobalBytes)Kb; seq.Va = (GlobalBytes)Vb; seq.a_stride = 4 * D;
+  seq.Ka = (GlobalBytes)Kb; seq.Va = (GlobalBytes)(Vb + first_d); seq.a_stride = 4 * D;
   seq.a_lo = (int)lo;
   seq.a_hi = (int)(hi < cache_len ? hi : cache_len);
   if (seq.a_hi < seq.a_lo) seq.a_hi = seq.a_lo;
@@ -817,23 +834,23 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, Ro
   const int64_t new0 = ((int64_t)beta * a.q_len * g.Hkv + kvh) * D;
   const float* Kl = fused_append ? (const float*)a.Kn + new0 : Kb;
   const float* Vl = fused_append ? (const float*)a.Vn + new0 : Vb;
-  seq.Kl = (GlobalBytes)Kl; seq.Vl = (GlobalBytes)Vl;
+  seq.Kl = (GlobalBytes)Kl; seq.Vl = (GlobalBytes)(Vl + first_d);
   seq.l_stride = (unsigned)(fused_append ? g.Hkv * D : D) * 4;
   seq.l_off = fused_append ? cache_len : 0;
-  attend_rows<D, NB, KW, SPLIT>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
+  attend_rows<D, NB, KW, SPLIT, P>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
 
   const bool direct = a.O != nullptr || a.A != nullptr;      // one split: nothing to merge
-  meet<D, NB, KW, SPLIT>(w, x,
+  meet<D, NB, KW, SPLIT, P>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
         const int r = r0 + row, j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
         float* dst = a.O ? (float*)a.O + (((int64_t)beta * a.q_len + j) * g.Hq + head) * D
                    : a.A ? a.A + (((int64_t)beta * g.Hq + head) * a.q_len + j) * D
                          : a.O_sub + ((((int64_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j) * D;
-        *(f32x4*)(dst + c) = v;
+        *(f32x4*)(dst + first_d + c) = v;
       },
       [&](int row, float lse) {
-        if (row >= live_rows) return;
+        if (row >= live_rows || piece != 0) return;
         const int r = r0 + row, j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
         if (!direct) a.LSE_sub[(((int64_t)beta * a.plan.s_total + sp) * g.Hq + head) * a.q_len + j] = lse;
         else if (a.LSE) a.LSE[((int64_t)beta * g.Hq + head) * a.q_len + j] = lse;
@@ -846,7 +863,7 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, Ro
     const int64_t stride = (int64_t)g.Hkv * D, src = (int64_t)(seq.l_lo - cache_len) * stride;
     file_rows<D>(Kl + src, Vl + src, stride, (float*)a.Kc + cache0 + (int64_t)seq.l_lo * D,
                  (float*)a.Vc + cache0 + (int64_t)seq.l_lo * D, seq.l_hi - seq.l_lo,
-                 tile * 64 * KW + threadIdx.x, filers * 64 * KW);
+                 (tile * P + piece) * 64 * KW + threadIdx.x, filers * P * 64 * KW);
   }
 }
 
@@ -881,7 +898,7 @@ int64_t tile_order(const Phase1Args& a, int rows, TileOrder* o) {
   return tiles;
 }
 
-template <int D, int NB, int KW, bool SPLIT>
+template <int D, int NB, int KW, bool SPLIT, int P = 1>
 hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   TileOrder o;
   const int64_t tiles = tile_order(a, 16 * NB, &o);
@@ -892,20 +909,20 @@ hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   const int64_t cus = 256;
   o.turn_from = 0x7fffffff; o.turn = 0;
   if (wgs > cus && wgs <= 2 * cus) { o.turn_from = (int)cus; o.turn = (int)(cus + wgs - 1); }
-  return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-    phase1_f32_kernel<D, NB, KW, SPLIT><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, o, (int)first);
+  return launch_in_pieces(wgs * P, 64 * KW, [&](unsigned first, unsigned n_wgs) {
+    phase1_f32_kernel<D, NB, KW, SPLIT, P><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, o, (int)first);
   });
 }
 
-template <int D, int NB, int KW, bool SPLIT>
+template <int D, int NB, int KW, bool SPLIT, int P = 1>
 hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
   const Geom& g = a.g;
   const int64_t tiles = ((int64_t)g.G * a.q_len + 16 * NB - 1) / (16 * NB);
   const int64_t wgs = tiles * g.B * g.Hkv * a.plan.s_total;
   if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff - 64) return hipErrorInvalidValue;
   const RowGrid grid = {make_div(g.Hkv), make_div((uint32_t)tiles), make_div(a.plan.s_total), make_div(g.G)};
-  return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-    phase2_f32_kernel<D, NB, KW, SPLIT><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, grid, (int)first);
+  return launch_in_pieces(wgs * P, 64 * KW, [&](unsigned first, unsigned n_wgs) {
+    phase2_f32_kernel<D, NB, KW, SPLIT, P><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, grid, (int)first);
   });
 }
 
@@ -917,7 +934,11 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
 // (64).
 // 32-row tiles shared by four wavefronts (two workgroups per CU) from more than one such tile per CU on; down to one 16-row tile
 // per CU, 16-row tiles shared by four (three per CU); fewer rows than that are bound by the latency of a tile: eight wavefronts
-// share it.  Measured, 16-row tiles / 32-row tiles in split products, us: d = 128: 8 / 2 heads, b = a = L / 4: L = 1060 (265 32-row tiles)
+// share it, and where a tile and CUs for it are left over, two or four workgroups compute a half or a quarter of its columns of d each:
+// every one takes all scores, but the products with V, the other half of a tile's MFMAs, are shared (one head, b = a = L / 4,
+// us, whole tiles / halves / quarters: d = 64: L = 500 (32 tiles) 6.9 / 6.5 / 6.3, 1024 (64) 9.25 / 8.45 / 8.0, 1500 (96) 11.6 / 10.6
+// / 14.1; d = 128: 500 11.8 / 9.7 / 9.1, 1000 16.3 / 13.5 / 13.4, 2000 (128) 25.2 / 22.0 / 33.8; sixteen wavefronts to a tile 11.3
+// where eight take 9.25).  Measured, 16-row tiles / 32-row tiles in split products, us: d = 128: 8 / 2 heads, b = a = L / 4: L = 1060 (265 32-row tiles)
 // 25.5 / 25.4, 1150 29.2 / 26.5, 2048 62 / 44, 4000 191 / 134; one head, 8192 (256 tiles) 103 / 102, blocks as long as the
 // context 153 / 193, 9000 259 / 214.  At d = 64 a tile's start weighs more: 1060 14.1 / 16.4, 1350 (338) 19.6 / 20.1, 1500 (375) 21.5 /
 // 21.9, 2048 (512) 33.9 / 26.9, but one head, 9000 (282), b = a = 2250 79.4 / 68.2.  Eight wavefronts: one head, d = 64, L = 1024
@@ -929,7 +950,7 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
 constexpr int SPLIT_KEYS_64 = 256;      // longest range that d = 64 takes in fp32 products in phase 1
 Phase1Plan phase1_plan_f32(const Geom& g) {
   const int64_t bmax = g.b < g.L ? g.b : g.L, rows = g.L * g.G * g.Hkv * g.B, keys = g.a + bmax;
-  Phase1Plan p = {0, 16, 8, 0, 0, 0};
+  Phase1Plan p = {0, 16, 8, 0, 0, 0, 1};
   if ((g.a + UNIT - 1) / UNIT + (bmax + UNIT - 1) / UNIT <= 2) p.waves = 1;
   else if (rows > 256 * 32 && (g.d == 128 || rows > 384 * 32 || keys > 1024)) {
     p.rows = 32; p.waves = 4;
@@ -937,6 +958,7 @@ Phase1Plan phase1_plan_f32(const Geom& g) {
   } else if (rows >= 256 * 16) p.waves = 4;
   const int64_t full = g.L / g.b, rest = g.L - full * g.b;      // (the short last block has fewer)
   p.tiles = (full * ((g.b * g.G + p.rows - 1) / p.rows) + (rest * g.G + p.rows - 1) / p.rows) * g.B * g.Hkv;
+  if (p.waves == 8) p.pieces = p.tiles <= 64 ? 4 : p.tiles <= 128 ? 2 : 1;
   return p;
 }
 
@@ -946,6 +968,8 @@ hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   if (p.rows == 32 && a.g.d == 128) return launch_phase1<128, 2, 4, true>(a, st);
   if (p.rows == 32) return p.split ? launch_phase1<64, 2, 4, true>(a, st) : launch_phase1<64, 2, 4, false>(a, st);
   if (p.waves == 4) return a.g.d == 64 ? launch_phase1<64, 1, 4, false>(a, st) : launch_phase1<128, 1, 4, false>(a, st);
+  if (p.pieces == 4) return a.g.d == 64 ? launch_phase1<64, 1, 8, false, 4>(a, st) : launch_phase1<128, 1, 8, false, 4>(a, st);
+  if (p.pieces == 2) return a.g.d == 64 ? launch_phase1<64, 1, 8, false, 2>(a, st) : launch_phase1<128, 1, 8, false, 2>(a, st);
   return a.g.d == 64 ? launch_phase1<64, 1, 8, false>(a, st) : launch_phase1<128, 1, 8, false>(a, st);
 }
 
@@ -962,6 +986,13 @@ hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st) {
   if (a.plan.tile_rows == 32 && a.g.d == 128) return launch_phase2<128, 2, 4, true>(a, st);
   if (a.plan.tile_rows == 32) return a.plan.split_len > SPLIT_RUN_64 ? launch_phase2<64, 2, 4, true>(a, st) : launch_phase2<64, 2, 4, false>(a, st);
   if (a.plan.waves == 4) return a.g.d == 64 ? launch_phase2<64, 1, 4, false>(a, st) : launch_phase2<128, 1, 4, false>(a, st);
+  // One split: few tiles share their columns of d, as in phase 1.  us, one token, one head: d = 64: 500 keys 8.7 -> 7.5, 250 6.3 -> 5.8;
+  // d = 128: 250 10.6 -> 8.1; two sequences of 20 tokens on 200 (8 / 2 heads) 11.8 -> 9.4.
+  if (a.O || a.A) {
+    const int64_t tiles = (int64_t)a.g.B * a.g.Hkv * (((int64_t)a.g.G * a.q_len + 15) / 16);
+    if (tiles <= 64) return a.g.d == 64 ? launch_phase2<64, 1, 8, false, 4>(a, st) : launch_phase2<128, 1, 8, false, 4>(a, st);
+    if (tiles <= 128) return a.g.d == 64 ? launch_phase2<64, 1, 8, false, 2>(a, st) : launch_phase2<128, 1, 8, false, 2>(a, st);
+  }
   return a.g.d == 64 ? launch_phase2<64, 1, 8, false>(a, st) : launch_phase2<128, 1, 8, false>(a, st);
 }
 

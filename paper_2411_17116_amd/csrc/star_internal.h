@@ -221,6 +221,7 @@ struct Phase1Plan {
   int32_t queued, rows, waves, group;
   int64_t tiles;
   int32_t split;       // fp32: products of bf16 parts
+  int32_t pieces;      // fp32: workgroups that share a tile's columns of d
 };
 Phase1Plan phase1_plan_bf16(const Geom& g, int anchor_mode, int n_cu);
 Phase1Plan phase1_plan_f32(const Geom& g);

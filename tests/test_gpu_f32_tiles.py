@@ -134,3 +134,28 @@ def test_scores_that_climb_over_large_values(step, run, d, G):
         torch.cuda.synchronize()
         assert (Oq[0].double() / big - want[part][:, None]).abs().max().item() <= tol
         cached += n
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,b,a,lq", [
+    (1, 1, 1, 64, 1024, 256, 256, 1),       # 64 tiles: quarters of d
+    (1, 3, 3, 128, 337, 100, 33, 70),       # 66 tiles (short last blocks): halves; 15 tiles of 407 keys
+    (2, 5, 1, 128, 200, 200, 0, 3),         # 126 tiles that end between tokens: halves; two tiles of 203 keys: quarters
+    (1, 2, 2, 64, 1025, 1025, 0, 40),       # 130 tiles: whole
+    (1, 33, 1, 128, 31, 31, 0, 33),         # 64 tiles; 69 of 64 keys: halves
+    (1, 16, 4, 64, 64, 64, 7, 64),          # 64 tiles, 64 tiles
+])
+def test_fp32_columns_shared_by_workgroups(B, Hq, Hkv, d, L, b, a, lq):
+    """Calls of few tiles, whose columns of d are computed by two or four workgroups."""
+    cfg = workloads.StarConfig("f32pieces", "fp32", B, Hq, Hkv, d, L, b, a, lq, 1, seed=L, n_planted=2)
+    print(f"[{cfg}]", flush=True)
+    rep = ph.run_parity(cfg, all_rows=True)
+    assert rep.ok, rep.detail
+    inp = workloads.make_inputs(cfg, "cuda")
+    parts, whole = ph.HipRun(cfg, inp, "cuda"), ph.HipRun(cfg, inp, "cuda")
+    parts.phase1()
+    whole.phase1()
+    want, _, _ = parts.phase2(inp.Qq, inp.Kq, inp.Vq, want_parts=True)
+    got, _, _ = whole.phase2(inp.Qq, inp.Kq, inp.Vq, want_parts=False)      # (one workgroup per tile and piece)
+    torch.cuda.synchronize()
+    assert (want - got).abs().max().item() <= 2 * ph.TOL["fp32"]["o"]
+    assert torch.equal(parts.Kc, whole.Kc) and torch.equal(parts.Vc, whole.Vc)
