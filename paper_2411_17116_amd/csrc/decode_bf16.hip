@@ -312,9 +312,36 @@ __device__ __forceinline__ void meet(const Phase2Args& a, Meeting<RB, KW>& x, co
 struct DecodeDiv {
   Div steps, G;        // steps between two of a wavefront's (flat plans): splits times KW
 };
-template <bool NT, bool ROPE, int RB, int KW>
-__global__ __launch_bounds__(64 * KW, RB > 2 ? 1 : 2) void decode_bf16_kernel(Phase2Args a, DecodeDiv by) {
+// What a launch is handed: packed under a flat plan (m[0] and m[3] the divisors'), else as it is.
+struct Call {
+  Phase2Args a;
+  DecodeDiv by;
+};
+struct FlatTurnedCall {
+  FlatCall call;
+  Rotary rotary;
+};
+template <int KW>
+__device__ __forceinline__ Call unpacked(const Call& c) { return c; }
+template <int KW>
+__device__ __forceinline__ Call unpacked(const FlatCall& c) {
+  Call x;
+  unpack(c, D, &x.a);
+  x.by = DecodeDiv{div_of(c.s_total * KW, c.m[0]), div_of(x.a.g.G, c.m[3])};
+  return x;
+}
+template <int KW>
+__device__ __forceinline__ Call unpacked(const FlatTurnedCall& c) {
+  Call x = unpacked<KW>(c.call);
+  x.a.rotary = c.rotary;
+  return x;
+}
+template <bool NT, bool ROPE, int RB, int KW, typename C>
+__global__ __launch_bounds__(64 * KW, RB > 2 ? 1 : 2) void decode_bf16_kernel(C call) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const Call from = unpacked<KW>(call);
+  const Phase2Args& a = from.a;
+  const DecodeDiv& by = from.by;
   Meeting<RB, KW>& meeting = *(Meeting<RB, KW>*)lds;
   const Geom& g = a.g;
   const int wave = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = KW == 1 ? threadIdx.x : threadIdx.x & 63;
@@ -504,7 +531,16 @@ hipError_t launch(const Phase2Args& a, hipStream_t st) {
   const Geom& g = a.g;
   const dim3 grid((unsigned)a.plan.s_total, (unsigned)g.Hkv, (unsigned)g.B);
   const DecodeDiv by = {make_div((uint32_t)a.plan.s_total * KW), make_div(g.G)};
-  decode_bf16_kernel<NT, ROPE, RB, KW><<<grid, 64 * KW, sizeof(Meeting<RB, KW>) + (ROPE ? KW * sizeof(Angles) : 0), st>>>(a, by);
+  const size_t lds = sizeof(Meeting<RB, KW>) + (ROPE ? KW * sizeof(Angles) : 0);
+  if (a.plan.flat) {
+    const FlatCall c = pack(a, RowGrid{by.steps, by.steps, by.steps, by.G});
+    if constexpr (ROPE) decode_bf16_kernel<NT, ROPE, RB, KW, FlatTurnedCall><<<grid, 64 * KW, lds, st>>>(FlatTurnedCall{c, a.rotary});
+    else decode_bf16_kernel<NT, ROPE, RB, KW, FlatCall><<<grid, 64 * KW, lds, st>>>(c);
+  } else if constexpr (!ROPE && RB == 1 && KW == 1) {
+    decode_bf16_kernel<NT, ROPE, RB, KW, Call><<<grid, 64 * KW, lds, st>>>(Call{a, by});
+  } else {
+    return hipErrorInvalidValue;      // (flat plans only)
+  }
   return hipGetLastError();
 }
 

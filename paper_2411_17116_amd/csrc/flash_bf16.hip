@@ -982,11 +982,8 @@ __global__ __launch_bounds__(64 * W * H, W * H == 4 ? 2 : 1) void phase1_bf16_pl
 // in flight (what bounds these calls is the stream of the cache); with more rows it halves
 // the per-split pairs.  The split plan chooses (rows_cost() in api.hip).  A ring of four
 // tiles with three in flight was 2.5 % slower for 256 rows: latency is not what bounds it.
-// Workgroups are numbered (kv head fastest, row tile, split, batch): with Hkv a multiple of 8 an
+// Workgroups are numbered as RowGrid says: with Hkv a multiple of 8 an
 // XCD's L2 serves one KV head, and the row tiles of a split read its keys there.
-struct RowGrid {
-  Div Hkv, tiles, splits, G;
-};
 template <int W>
 __global__ __launch_bounds__(NT, 1) void phase2_rows_bf16_kernel(Phase2Args a, RowGrid grid, int first_wg) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];

@@ -781,14 +781,31 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
 }
 
 // ------------------------------------------------------------------ phase 2
-// Workgroups are numbered (kv head fastest, row tile, split, batch).
-struct RowGrid {
-  Div Hkv, tiles, splits, G;
+// What a launch is handed: packed under a flat plan, else as it is.
+struct Call {
+  Phase2Args a;
+  RowGrid grid;
+  int first_wg;
 };
-template <int D, int NB, int KW, bool SPLIT, int P>
-__global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(Phase2Args a, RowGrid grid, int first_wg) {
+template <int ROWS>
+__device__ __forceinline__ Call unpacked(const Call& c) { return c; }
+template <int ROWS>
+__device__ __forceinline__ Call unpacked(const FlatCall& c) {
+  Call x;
+  unpack(c, 0, &x.a);
+  const Geom& g = x.a.g;
+  x.grid = RowGrid{div_of(g.Hkv, c.m[0]), div_of(((unsigned)g.G * c.q_len + ROWS - 1) / ROWS, c.m[1]), div_of(c.s_total, c.m[2]), div_of(g.G, c.m[3])};
+  x.first_wg = c.first_wg;
+  return x;
+}
+template <int D, int NB, int KW, bool SPLIT, int P, typename C>
+__global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(C call) {
   __shared__ Meet<D, NB, KW, SPLIT> x;
   constexpr int ROWS = 16 * NB;
+  const Call from = unpacked<ROWS>(call);
+  const Phase2Args& a = from.a;
+  const RowGrid& grid = from.grid;
+  const int first_wg = from.first_wg;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
   const uint32_t wg = first_wg + blockIdx.x, id = wg / P, of_head = quotient(id, grid.Hkv), of_tile = quotient(of_head, grid.tiles);
@@ -921,9 +938,21 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
   const int64_t wgs = tiles * g.B * g.Hkv * a.plan.s_total;
   if (wgs > 0x7fffffff || (int64_t)g.G * a.q_len > 0x7fffffff - 64) return hipErrorInvalidValue;
   const RowGrid grid = {make_div(g.Hkv), make_div((uint32_t)tiles), make_div(a.plan.s_total), make_div(g.G)};
-  return launch_in_pieces(wgs * P, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-    phase2_f32_kernel<D, NB, KW, SPLIT, P><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, grid, (int)first);
-  });
+  if constexpr (KW > 1) {
+    if (a.plan.flat) {
+      FlatCall call = pack(a, grid);
+      return launch_in_pieces(wgs * P, 64 * KW, [&](unsigned first, unsigned n_wgs) {
+        call.first_wg = (int)first;
+        phase2_f32_kernel<D, NB, KW, SPLIT, P, FlatCall><<<dim3(n_wgs), 64 * KW, 0, st>>>(call);
+      });
+    }
+  }
+  if constexpr (P == 1 && (KW != 4 || NB == 2)) {
+    return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
+      phase2_f32_kernel<D, NB, KW, SPLIT, P, Call><<<dim3(n_wgs), 64 * KW, 0, st>>>(Call{a, grid, (int)first});
+    });
+  }
+  return hipErrorInvalidValue;      // (flat plans only)
 }
 
 }  // namespace

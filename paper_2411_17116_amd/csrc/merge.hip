@@ -291,6 +291,23 @@ __device__ __forceinline__ float weight(float x) {
   return __builtin_ldexpf(__builtin_amdgcn_exp2f(fmaf(x, LO, fmaf(x, HI, -n))), (int)fmaxf(n, -300.f));
 }
 
+// A call of one part as a launch is handed it.
+struct FlatMerge {
+  const float *O_sub, *LSE_sub;
+  void* O;
+  float *A, *LSE;
+  int64_t batch_stride, split_stride;
+  int32_t Hq, q_len, S;
+  int16_t d, out_bf16;
+  void* Qq;
+  Rotary rotary;
+};
+static_assert(sizeof(FlatMerge) + 16 <= 112, "(and what merge_flat_rows_kernel takes besides)");
+inline FlatMerge pack(const MergeArgs& a) {
+  return FlatMerge{a.O_sub, a.LSE_sub, a.O, a.A, a.LSE, a.batch_stride, a.split_stride, a.g.Hq, a.q_len, a.plan.s_total,
+                   (int16_t)a.g.d, (int16_t)a.out_bf16, a.Qq, a.rotary};
+}
+
 // What one lane gathers: the weighted sum of its four elements of the splits' outputs, the
 // sum of weights, both relative to exp(m).  Sum is double where the splits follow blocks (MergeArgs::wide),
 // of which there may be hundreds: float sums of 64 and 128 of them were off by up to 1.3 and 1.6e-7, these round twice.
@@ -333,19 +350,18 @@ __device__ __forceinline__ void fold_splits(Fold<Sum>& f, const float (&ls)[N], 
   f.m = m;
 }
 template <typename Sum>
-__device__ __forceinline__ void store_merged(const MergeArgs& a, int beta, int h, int64_t j, int d0, const Fold<Sum>& f) {
-  const Geom& g = a.g;
+__device__ __forceinline__ void store_merged(const FlatMerge& a, int beta, int h, int64_t j, int d0, const Fold<Sum>& f) {
   const f32x4 out = f.w > 0 ? __builtin_convertvector(f.acc / f.w, f32x4) : f32x4{0.f, 0.f, 0.f, 0.f};
-  const int64_t orow = ((int64_t)beta * a.q_len + j) * g.Hq + h, arow = ((int64_t)beta * g.Hq + h) * a.q_len + j;
-  if (a.A) *(f32x4*)(a.A + arow * g.d + d0) = out;
+  const int64_t orow = ((int64_t)beta * a.q_len + j) * a.Hq + h, arow = ((int64_t)beta * a.Hq + h) * a.q_len + j;
+  if (a.A) *(f32x4*)(a.A + arow * a.d + d0) = out;
   if (a.O) {
     if (a.out_bf16) {
-      unsigned short* o = (unsigned short*)a.O + orow * g.d + d0;
+      unsigned short* o = (unsigned short*)a.O + orow * a.d + d0;
       const uint32_t lo = f32_to_bf16_rne(out[0]) | (uint32_t)f32_to_bf16_rne(out[1]) << 16;
       const uint32_t hi = f32_to_bf16_rne(out[2]) | (uint32_t)f32_to_bf16_rne(out[3]) << 16;
       *(uint2*)o = make_uint2(lo, hi);
     } else {
-      *(f32x4*)((float*)a.O + orow * g.d + d0) = out;
+      *(f32x4*)((float*)a.O + orow * a.d + d0) = out;
     }
   }
   if (a.LSE && d0 == 0) a.LSE[arow] = f.w > 0 ? f.m + logf((float)f.w) : -INFINITY;
@@ -353,8 +369,8 @@ __device__ __forceinline__ void store_merged(const MergeArgs& a, int beta, int h
 
 // A wavefront turns row (beta, h, j) of the call's queries, a lane per pair (bf16, d = 128).  Workgroups
 // behind the merge's own do this: the kernel in front has read the queries as they were.
-__device__ __forceinline__ void rotate_query(const MergeArgs& a, int beta, int h, int j, int lane) {
-  __bf16* row = (__bf16*)a.Qq + (((int64_t)beta * a.q_len + j) * a.g.Hq + h) * 128;
+__device__ __forceinline__ void rotate_query(const FlatMerge& a, int beta, int h, int j, int lane) {
+  __bf16* row = (__bf16*)a.Qq + (((int64_t)beta * a.q_len + j) * a.Hq + h) * 128;
   const float x = (float)row[lane], y = (float)row[lane + 64];
   float cs, sn;
   rotary_angle(a.rotary.pos0 + j, rotary_frequency(lane, 128, a.rotary.log2_theta), &cs, &sn);
@@ -366,15 +382,14 @@ __device__ __forceinline__ void rotate_query(const MergeArgs& a, int beta, int h
 // walk the splits, INFL in flight per lane.  grid: x = token * pieces + piece (and, behind them, a token
 // each to rotate), y = head, z = batch.
 template <int LPS, int THREADS, int INFL, typename Sum>
-__global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
+__global__ __launch_bounds__(THREADS) void merge_flat_kernel(FlatMerge a) {
   constexpr int GROUPS = THREADS / LPS, WAVES = THREADS / 64;
   __shared__ float red_m[WAVES];
   __shared__ Sum red_w[WAVES];
   __shared__ typename Fold<Sum>::Sum4 red_acc[WAVES][LPS];
-  const Geom& g = a.g;
   const int tid = threadIdx.x, li = tid % LPS, grp = tid / LPS;
-  const int h = blockIdx.y, beta = blockIdx.z, S = a.plan.s_total;
-  const int log2_pieces = __builtin_ctz(g.d / (4 * LPS)), j = blockIdx.x >> log2_pieces;      // (d is 64 or 128)
+  const int h = blockIdx.y, beta = blockIdx.z, S = a.S;
+  const int log2_pieces = __builtin_ctz(a.d / (4 * LPS)), j = blockIdx.x >> log2_pieces;      // (d is 64 or 128)
   if (j >= a.q_len) {
     if (tid < 64) rotate_query(a, beta, h, blockIdx.x - (a.q_len << log2_pieces), tid);
     return;
@@ -393,7 +408,7 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
       const int s = s0 + grp + u * GROUPS;
       const int64_t r = base + (int64_t)(s < S ? s : S - 1) * a.split_stride;
       ls[u] = a.LSE_sub[r];
-      v[u] = *(const f32x4*)(a.O_sub + r * g.d + d0);
+      v[u] = *(const f32x4*)(a.O_sub + r * a.d + d0);
       if (s >= S) ls[u] = -INFINITY;
     }
     float m = largest<INFL>(ls);
@@ -429,13 +444,10 @@ __global__ __launch_bounds__(THREADS) void merge_flat_kernel(MergeArgs a) {
 
 // Many rows of a few splits each (query encoding, pairs of other hosts): d / 4 lanes own a
 // row, INFL splits in flight, nothing crosses lanes.
-struct RowsDiv {
-  Div q_len, Hq;
-};
 template <int D, int INFL, typename Sum>
-__global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, RowsDiv by, unsigned n_rows, unsigned first_wg) {
+__global__ __launch_bounds__(256) void merge_flat_rows_kernel(FlatMerge a, uint32_t m_q_len, uint32_t m_Hq, unsigned n_rows, unsigned first_wg) {
   constexpr int LPR = D / 4;
-  const Geom& g = a.g;
+  const struct { Div q_len, Hq; } by = {div_of(a.q_len, m_q_len), div_of(a.Hq, m_Hq)};
   const unsigned n_wgs = (n_rows + 256 / LPR - 1) / (256 / LPR), wg = first_wg + blockIdx.x, tid = threadIdx.x;
   const bool turn = wg >= n_wgs;                                         // a wavefront per row to rotate
   const unsigned row = turn ? (wg - n_wgs) * 4 + tid / 64 : wg * (256 / LPR) + tid / LPR;      // (beta, h, j), j fastest
@@ -445,7 +457,7 @@ __global__ __launch_bounds__(256) void merge_flat_rows_kernel(MergeArgs a, RowsD
     rotate_query(a, (int)beta, (int)h, (int)j, tid & 63);
     return;
   }
-  const int d0 = 4 * (tid % LPR), S = a.plan.s_total;
+  const int d0 = 4 * (tid % LPR), S = a.S;
   const int64_t base = (int64_t)beta * a.batch_stride + (int64_t)h * a.q_len + j;
   Fold<Sum> f = empty_fold<Sum>();
   for (int s0 = 0; s0 < S; s0 += INFL) {
@@ -467,7 +479,7 @@ template <int LPS, int THREADS, int INFL, typename Sum>
 hipError_t launch_flat(const MergeArgs& a, hipStream_t st) {
   const int turn = a.rotary.log2_theta != 0 ? a.q_len : 0;
   const dim3 grid((unsigned)(a.q_len * (a.g.d / (4 * LPS)) + turn), (unsigned)a.g.Hq, (unsigned)a.g.B);
-  merge_flat_kernel<LPS, THREADS, INFL, Sum><<<grid, THREADS, 0, st>>>(a);
+  merge_flat_kernel<LPS, THREADS, INFL, Sum><<<grid, THREADS, 0, st>>>(pack(a));
   return hipGetLastError();
 }
 
@@ -476,13 +488,14 @@ hipError_t merge_one_part(const MergeArgs& a, int64_t rows, hipStream_t st) {
   const int S = a.plan.s_total;
   if (S <= 8 && rows >= 64) {
     const int64_t wgs = a.g.d == 64 ? (rows + 15) / 16 : (rows + 7) / 8, turn = a.rotary.log2_theta != 0 ? (rows + 3) / 4 : 0;
-    const RowsDiv by = {make_div(a.q_len), make_div(a.g.Hq)};
+    const FlatMerge c = pack(a);
+    const uint32_t m_q_len = make_div(a.q_len).m, m_Hq = make_div(a.g.Hq).m;
     return launch_in_pieces(wgs + turn, 256, [&](unsigned first, unsigned n_wgs) {
       // (a split past the last costs as much as one)
-      if (a.g.d == 64 && S <= 4) merge_flat_rows_kernel<64, 4, Sum><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
-      else if (a.g.d == 64) merge_flat_rows_kernel<64, 8, Sum><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
-      else if (S <= 4) merge_flat_rows_kernel<128, 4, Sum><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
-      else merge_flat_rows_kernel<128, 8, Sum><<<dim3(n_wgs), 256, 0, st>>>(a, by, (unsigned)rows, first);
+      if (a.g.d == 64 && S <= 4) merge_flat_rows_kernel<64, 4, Sum><<<dim3(n_wgs), 256, 0, st>>>(c, m_q_len, m_Hq, (unsigned)rows, first);
+      else if (a.g.d == 64) merge_flat_rows_kernel<64, 8, Sum><<<dim3(n_wgs), 256, 0, st>>>(c, m_q_len, m_Hq, (unsigned)rows, first);
+      else if (S <= 4) merge_flat_rows_kernel<128, 4, Sum><<<dim3(n_wgs), 256, 0, st>>>(c, m_q_len, m_Hq, (unsigned)rows, first);
+      else merge_flat_rows_kernel<128, 8, Sum><<<dim3(n_wgs), 256, 0, st>>>(c, m_q_len, m_Hq, (unsigned)rows, first);
     });
   }
   // Few rows: pieces of d, so that the row's splits are in flight at once over more

@@ -21,6 +21,14 @@ inline Div make_div(uint32_t d) {
   return x;
 }
 __device__ inline uint32_t quotient(uint32_t n, const Div& x) { return (__umulhi(n, x.m) + n) >> x.s; }
+__device__ inline Div div_of(uint32_t d, uint32_t m) { return Div{d, m, d > 1 ? 32u - (uint32_t)__builtin_clz(d - 1) : 0u}; }
+
+// What a launch costs the host grows with its arguments beyond 112 bytes (96 / 128 / 192 / 288 bytes 2.8 / 3.2 / 3.6 / 4.0 us, where the
+// host is at its slower pace; 2.3 to 2.5 at its faster one), and a wavefront waits for them at its start.  The decode, fp32 and
+// merge kernels of a call under a flat plan, two launches that a short call consists of, take theirs packed (FlatCall, FlatMerge) and
+// unpack them into what the others are handed.  Nine fp32 calls, 1024 keys: enqueueing 69 to 83 -> 62 to 65 us (54 to 56 at the faster
+// pace); one token, us, at the faster pace: fp32 on 1024 keys 6.81 -> 6.60, bf16, 32 / 8 heads, on 2000 7.52 -> 7.34, four sequences of
+// 8000 (64 / 8 heads) 28.4 -> 27.9.  (The row-tiled bf16 kernels would spill more, and their calls are longer.)
 
 // ---------------------------------------------------------------------------
 // Phase-2 split plan: every part of the cache (one per context block, plus the
@@ -127,6 +135,44 @@ __host__ __device__ inline int64_t visible_total(const Phase2Args& a) {
 }
 __host__ __device__ inline int64_t visible_limit(const Phase2Args& a, int j) {
   return a.causal ? a.cache_len + j + 1 : a.cache_len;
+}
+
+struct RowGrid {        // workgroups of the row-tiled phase-2 kernels: kv head fastest, row tile, split, batch
+  Div Hkv, tiles, splits, G;
+};
+// A phase-2 call under a flat plan.
+struct FlatCall {
+  const void *Qq, *Kn, *Vn;
+  void *Kc, *Vc;
+  float *out, *lse;      // `kind`: 0 O_sub and LSE_sub, 1 O, 2 A and LSE
+  int32_t cache_len, cap, q_len, split_len, s_total;
+  uint32_t heads;        // G << 16 | Hkv
+  float scale;
+  int16_t causal, kind;
+  uint32_t m[4];         // the divisors' (RowGrid)
+  int32_t first_wg;
+};
+static_assert(sizeof(FlatCall) <= 112, "see above");
+inline FlatCall pack(const Phase2Args& a, const RowGrid& by) {
+  const Geom& g = a.g;
+  FlatCall c = {a.Qq, a.Kn, a.Vn, a.Kc, a.Vc, nullptr, nullptr, (int32_t)a.cache_len, (int32_t)g.cap, a.q_len, (int32_t)a.plan.split_len,
+                a.plan.s_total, (uint32_t)g.G << 16 | (uint32_t)g.Hkv, g.scale, (int16_t)a.causal, 0, {by.Hkv.m, by.tiles.m, by.splits.m, by.G.m}, 0};
+  if (a.O) { c.kind = 1; c.out = (float*)a.O; }
+  else if (a.A) { c.kind = 2; c.out = a.A; c.lse = a.LSE; }
+  else { c.out = a.O_sub; c.lse = a.LSE_sub; }
+  return c;
+}
+// (B, L, b and what a plan along blocks has stay unset: no kernel asks for them under a flat plan)
+__device__ inline void unpack(const FlatCall& c, int d, Phase2Args* a) {
+  Geom& g = a->g;
+  g.G = c.heads >> 16; g.Hkv = c.heads & 0xffff; g.Hq = g.G * g.Hkv; g.d = d; g.cap = c.cap; g.scale = c.scale;
+  g.B = 0; g.L = g.b = g.a = 0;
+  a->plan = SplitPlan{c.split_len, 0, 0, 0, c.s_total, 0, 1, 0, 0};
+  a->cache_len = c.cache_len; a->q_len = c.q_len; a->causal = c.causal;
+  a->Qq = c.Qq; a->Kn = c.Kn; a->Vn = c.Vn; a->Kc = c.Kc; a->Vc = c.Vc;
+  a->O_sub = c.out; a->LSE_sub = c.lse;
+  a->O = c.kind == 1 ? c.out : nullptr; a->A = c.kind == 2 ? c.out : nullptr; a->LSE = c.kind == 2 ? c.lse : nullptr;
+  a->rotary = Rotary{0.0, 0};
 }
 
 // Split s of (batch beta, head h, token j) is row

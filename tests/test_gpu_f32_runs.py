@@ -50,3 +50,30 @@ def test_short_runs(B, Hq, Hkv, d, L, q, splits):
             bound = L + 1 + torch.arange(q, device="cuda").repeat_interleave(G)
             s.masked_fill_(torch.arange(L + q, device="cuda")[None] >= bound[:, None], -math.inf)
             assert (O[beta, :, hs].double() - (torch.softmax(s, 1) @ v).view(q, G, d)).abs().max().item() <= tol
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,d,L,q", [
+    ("fp32", 1, 65535, 1, 64, 700, 1),          # the largest group and number of KV heads a launch's arguments hold
+    ("fp32", 1, 65535, 65535, 64, 40, 2),
+    ("bf16", 1, 65535, 65535, 128, 40, 1),
+    ("fp32", 3, 255, 85, 64, 600, 7),
+])
+def test_many_heads(dtype, B, Hq, Hkv, d, L, q):
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda").to(dt)
+    shape = sa.StarShape.make(dtype, B, Hq, Hkv, d, L, L, 0, L + q)
+    Kc, Vc = new(B, Hkv, L + q, d), new(B, Hkv, L + q, d)
+    Q, K, V = new(B, q, Hq, d), new(B, q, Hkv, d), new(B, q, Hkv, d)
+    O = torch.empty_like(Q)
+    print(f"[{dtype} {B} {Hq}/{Hkv} d={d} L={L} q={q}]", flush=True)
+    sa.phase2(shape, L, Q, K, V, Kc, Vc, O, sa.alloc_workspace(shape, q))
+    torch.cuda.synchronize()
+    assert torch.equal(Kc[:, :, L:], K.transpose(1, 2)) and torch.equal(Vc[:, :, L:], V.transpose(1, 2))
+    for h in sorted({0, 1, Hq // 2, Hq - 2, Hq - 1}):
+        k, v = Kc[:, h * Hkv // Hq].double(), Vc[:, h * Hkv // Hq].double()
+        s = (Q[:, :, h].double().unsqueeze(2) * k.unsqueeze(1)).sum(-1) / d ** 0.5
+        seen = torch.arange(L + q, device="cuda") <= L + torch.arange(q, device="cuda")[:, None]
+        w = torch.softmax(s.masked_fill(~seen, -float("inf")), dim=-1)
+        want = (w.unsqueeze(-1) * v.unsqueeze(1)).sum(2)
+        assert (O[:, :, h].double() - want).abs().max().item() <= (1e-5 if dtype == "fp32" else 2e-2), h
