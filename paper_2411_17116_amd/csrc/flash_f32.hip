@@ -13,7 +13,7 @@
 //   * Rows are packed over the heads of a KV group (row = token * G + head in
 //     group), so that a K/V unit is read once for all of them.
 //   * S^T = K Q^T: lane (col = lane % 16, j4 = lane / 16) supplies K[col][16 t + 4 j4 + e]
-//     straight from a 16-byte global load (any assignment of d to (MFMA step, lane
+//     from a 16-byte global load, or from LDS (any assignment of d to (MFMA step, lane
 //     group) works as long as Q uses the same one) and receives keys 4 j4 + v of
 //     query row col.  Those are exactly the lanes that have to supply P^T in MFMA
 //     step v of O^T += V^T P^T, whose four keys are 4 j4 + v; V is loaded as
@@ -29,7 +29,7 @@
 // the caches; phase 2 reads the new tokens from the call's Kq / Vq and appends them.
 // Measured, whole calls, against a kernel of one thread per row and fp32 products throughout: 8 / 2 heads, d = 128,
 // L = 4099, b = 1024, a = 512: 3390 -> 134 -> 102.5 us (147 TFLOP/s; 174 at 8192 tokens in blocks of 2048, 129 with fp32 products;
-// a library fp32 matrix product reaches 152); 1 head, d = 64, L = 1024, b = a = 256: 274 -> 9.2 us.
+// a library fp32 matrix product reaches 152); 1 head, d = 64, L = 1024, b = a = 256: 274 -> 9.2 -> 7.6 us.
 #include "star_internal.h"
 
 namespace star {
@@ -42,6 +42,8 @@ typedef const __attribute__((address_space(1))) char* GlobalBytes;
 typedef const __attribute__((address_space(1))) f32x4* GlobalVec;
 
 constexpr int UNIT = 16;   // keys per step of a wavefront
+// How a kernel takes its products: in fp32 from K as it is loaded, in fp32 from K turned through LDS, in bf16 parts.
+enum { PLAIN, TURNED, SPLIT };
 // How far (log2 units) a score may rise above its row's reference before the reference moves.
 // O / l does not depend on the reference.  Scores of N(0, 1) inputs stay within it of the first unit's, and a
 // unit then costs no exchange between lanes and no rescaling of O.  Against moving it to every new maximum, us
@@ -137,13 +139,26 @@ __device__ __forceinline__ UnitAt unit_at(const KeySeq& seq, int u) {
 }
 
 // Rows past the range's end re-read its last row (their scores are masked).
-template <int D, int P>
+// A matrix operand has a lane per key, and four neighbouring lanes that read from four rows take four times as long as four that read
+// 64 bytes of one.  Where few wavefronts or short ranges leave nothing to hide that (TURN; the launches say where), K is loaded four
+// lanes to a row and turned through LDS (turn_k(), a wavefront's own 16 rows: no barrier).
+template <int D, bool TURN, int P>
 __device__ __forceinline__ void load_k(Unit<D, P>& r, const UnitAt& x, int lane) {
-  int i = lane & 15;
+  int i = TURN ? (lane >> 4) + (lane & 12) : lane & 15;
   if (x.n_rows < UNIT) i = i < x.n_rows ? i : x.n_rows - 1;
-  const unsigned off = (unsigned)i * x.stride + 16 * (lane >> 4);
+  const unsigned off = (unsigned)i * x.stride + 16 * (TURN ? lane & 3 : lane >> 4);
 #pragma unroll
   for (int t = 0; t < D / 16; ++t) r.k[t] = *(GlobalVec)(x.K + off + 64 * t);
+}
+// Chunk c (16 bytes) of row i sits in slot c ^ i of its row (low four bits): neither the 16 lanes of a write, four rows that differ
+// in their upper bits, nor those of a read meet in a bank.
+template <int D, int P>
+__device__ __forceinline__ void turn_k(Unit<D, P>& r, f32x4* rows, int lane) {
+  const int i = (lane >> 4) + (lane & 12), p = lane & 3, col = lane & 15, j4 = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t) rows[i * (D / 4) + ((4 * t + p) ^ i)] = r.k[t];
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t) r.k[t] = rows[col * (D / 4) + ((4 * t + j4) ^ col)];
 }
 template <int D, int P>
 __device__ __forceinline__ void load_v(Unit<D, P>& r, const UnitAt& x, int lane) {
@@ -184,10 +199,11 @@ __device__ __forceinline__ void move_references(RowState<D, NB, P>& w, const flo
 // One unit: scores, softmax, products.  MORE: K and V of unit `nxt` are requested as soon
 // as this unit's are used up -- without a branch, so that the compiler's waits for V
 // need not include them.
-template <int D, int NB, bool MORE, int P>
-__device__ __forceinline__ void attend_unit(RowState<D, NB, P>& w, Unit<D, P>& r, const UnitAt& cur, const UnitAt& nxt,
+template <int D, int NB, bool MORE, bool TURN, int P>
+__device__ __forceinline__ void attend_unit(RowState<D, NB, P>& w, Unit<D, P>& r, f32x4* rows, const UnitAt& cur, const UnitAt& nxt,
                                             const int (&row_lim)[NB], int wave_lim, int lane) {
   const int j4 = lane >> 4;
+  if (TURN) turn_k<D, P>(r, rows, lane);
   // four chains per score tile (element e of every 16-byte piece has its own; two where the
   // registers are used up): a quarter of the terms, and of the partial sums' size, per chain
   // keeps the rounding of a large logit down
@@ -206,7 +222,7 @@ __device__ __forceinline__ void attend_unit(RowState<D, NB, P>& w, Unit<D, P>& r
 #pragma unroll
         for (int k = e; k < e + 2; ++k)
           part[b][k % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.k[t][k], w.q[b][t][k], part[b][k % CH], 0, 0, 0);
-  if (MORE) load_k<D, P>(r, nxt, lane);
+  if (MORE) load_k<D, TURN, P>(r, nxt, lane);
 #pragma unroll
   for (int b = 0; b < NB; ++b)
     s[b] = CH == 2 ? part[b][0] + part[b][1] : (part[b][0] + part[b][1]) + (part[b][CH - 2] + part[b][CH - 1]);
@@ -268,21 +284,21 @@ __device__ __forceinline__ void scale_rows(RowState<D, NB, P>& w, float qk_scale
 // Attend the wavefront's rows to units first, first + step, ... of the sequence.
 //   row_lim   this lane's exclusive bound on keys of the second range, per row block
 //   wave_lim  smallest bound of the wavefront's live rows
-template <int D, int NB, int P>
-__device__ __forceinline__ void attend(RowState<D, NB, P>& w, const KeySeq& seq, int first, int step,
+template <int D, int NB, bool TURN, int P>
+__device__ __forceinline__ void attend(RowState<D, NB, P>& w, f32x4* rows, const KeySeq& seq, int first, int step,
                                        const int (&row_lim)[NB], int wave_lim, float qk_scale, int lane) {
   if (first >= seq.n_units) return;
   Unit<D, P> r;
   UnitAt cur = unit_at<UNIT>(seq, first);
-  load_k<D, P>(r, cur, lane);
+  load_k<D, TURN, P>(r, cur, lane);
   load_v<D, P>(r, cur, lane);
   scale_rows<D, NB, P>(w, qk_scale);
   for (int u = first + step; u < seq.n_units; u += step) {
     const UnitAt nxt = unit_at<UNIT>(seq, u);
-    attend_unit<D, NB, true, P>(w, r, cur, nxt, row_lim, wave_lim, lane);
+    attend_unit<D, NB, true, TURN, P>(w, r, rows, cur, nxt, row_lim, wave_lim, lane);
     cur = nxt;
   }
-  attend_unit<D, NB, false, P>(w, r, cur, cur, row_lim, wave_lim, lane);
+  attend_unit<D, NB, false, TURN, P>(w, r, rows, cur, cur, row_lim, wave_lim, lane);
 }
 
 // ------------------------------------------------------------------ split products
@@ -541,9 +557,9 @@ __device__ __forceinline__ void attend_split(RowState<D, 2>& w, SharedRows<D>* s
       cur = unit_at<SPLIT_UNIT>(seq, u);
       for (int done = 0; done < SPLIT_UNIT && cur.n_rows > 0; done += UNIT) {
         Unit<D> one;
-        load_k<D, 1>(one, cur, lane);
+        load_k<D, false, 1>(one, cur, lane);
         load_v<D, 1>(one, cur, lane);
-        attend_unit<D, 2, false, 1>(w, one, cur, cur, row_lim, wave_lim, lane);
+        attend_unit<D, 2, false, false, 1>(w, one, nullptr, cur, cur, row_lim, wave_lim, lane);
         cur.K += (size_t)UNIT * cur.stride;
         cur.V += (size_t)UNIT * cur.stride;
         cur.key0 += UNIT;
@@ -564,11 +580,13 @@ template <bool A, typename X, typename Y> struct Either { typedef X type; };
 template <typename X, typename Y> struct Either<false, X, Y> { typedef Y type; };
 // LDS in which the KW wavefronts' results of a tile meet, 64 columns of d at a time.
 // The pitch of 68 floats spreads the 16 rows of a 16-byte write over all banks.
-template <int D, int NB, int KW, bool SPLIT>
+template <int D, int NB, int KW, int HOW>
 struct Meet {
   struct None {};
   union {
-    typename Either<SPLIT && D == 128, SharedRows<D>, None>::type rows;      // split products: until the key loop ends
+    // until the key loop ends:
+    typename Either<HOW == SPLIT && D == 128, SharedRows<D>, None>::type rows;      // split products
+    typename Either<HOW == TURNED, f32x4[KW][4 * D], None>::type k;          // turn_k()
     float o[KW][16 * NB][68];
   };
   float m[KW][16 * NB], l[KW][16 * NB];
@@ -578,8 +596,8 @@ struct Meet {
 // Fold the wavefronts' partial results; `store(row, col, f32x4)` takes the normalised
 // output of tile row `row`, columns col .. col + 3, and `store_lse(row, lse)` its
 // natural-log denominator (-inf, output 0, for a row that saw no key).
-template <int D, int NB, int KW, bool SPLIT, int P, typename Store, typename StoreLse>
-__device__ __forceinline__ void meet(RowState<D, NB, P>& w, Meet<D, NB, KW, SPLIT>& x, Store store, StoreLse store_lse) {
+template <int D, int NB, int KW, int HOW, int P, typename Store, typename StoreLse>
+__device__ __forceinline__ void meet(RowState<D, NB, P>& w, Meet<D, NB, KW, HOW>& x, Store store, StoreLse store_lse) {
   constexpr int ROWS = 16 * NB, E = Piece<D, P>::E, H = Piece<D, P>::H;
   typedef typename Piece<D, P>::vec vec;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, j4 = lane >> 4;
@@ -626,14 +644,14 @@ __device__ __forceinline__ void meet(RowState<D, NB, P>& w, Meet<D, NB, KW, SPLI
 }
 
 // The key loop of wavefront `wave`.
-template <int D, int NB, int KW, bool SPLIT, int P, typename Again>
-__device__ __forceinline__ void attend_rows(RowState<D, NB, P>& w, Meet<D, NB, KW, SPLIT>& x, KeySeq& seq, int wave, const int (&row_lim)[NB],
+template <int D, int NB, int KW, int HOW, int P, typename Again>
+__device__ __forceinline__ void attend_rows(RowState<D, NB, P>& w, Meet<D, NB, KW, HOW>& x, KeySeq& seq, int wave, const int (&row_lim)[NB],
                                             int wave_lim, float qk_scale, int lane, Again again) {
-  if constexpr (SPLIT) {
+  if constexpr (HOW == SPLIT) {
     attend_split<D, KW>(w, (SharedRows<D>*)&x.rows, seq, wave, row_lim, wave_lim, qk_scale, lane, again);
   } else {
     seq.count<UNIT>();
-    attend<D, NB, P>(w, seq, wave, KW, row_lim, wave_lim, qk_scale, lane);
+    attend<D, NB, HOW == TURNED, P>(w, (f32x4*)&x.k + wave * (4 * D), seq, wave, KW, row_lim, wave_lim, qk_scale, lane);
   }
 }
 
@@ -701,9 +719,9 @@ __device__ __forceinline__ Tile tile_at(const TileOrder& p, int wg) {
   return {__builtin_amdgcn_readfirstlane(kvh), __builtin_amdgcn_readfirstlane(beta), __builtin_amdgcn_readfirstlane(i),
           __builtin_amdgcn_readfirstlane(t)};
 }
-template <int D, int NB, int KW, bool SPLIT, int P>
+template <int D, int NB, int KW, int HOW, int P>
 __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, TileOrder order, int first_wg) {
-  __shared__ Meet<D, NB, KW, SPLIT> x;
+  __shared__ Meet<D, NB, KW, HOW> x;
   constexpr int ROWS = 16 * NB;
   const Geom& g = a.g;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15, j4 = lane >> 4;
@@ -755,9 +773,9 @@ __global__ __launch_bounds__(64 * KW, 2) void phase1_f32_kernel(Phase1Args a, Ti
   seq.Kl = (GlobalBytes)Kb; seq.Vl = (GlobalBytes)(Vb + piece * C); seq.l_stride = (unsigned)stride * 4; seq.l_off = 0;
   seq.l_lo = s;
   seq.l_hi = tok0 + (int)quotient(head0 + live_rows - 1, order.G) + 1;
-  attend_rows<D, NB, KW, SPLIT, P>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
+  attend_rows<D, NB, KW, HOW, P>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
 
-  meet<D, NB, KW, SPLIT, P>(w, x,
+  meet<D, NB, KW, HOW, P>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
         const unsigned r = head0 + row, j = quotient(r, order.G);
@@ -798,9 +816,9 @@ __device__ __forceinline__ Call unpacked(const FlatCall& c) {
   x.first_wg = c.first_wg;
   return x;
 }
-template <int D, int NB, int KW, bool SPLIT, int P, typename C>
+template <int D, int NB, int KW, int HOW, int P, typename C>
 __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(C call) {
-  __shared__ Meet<D, NB, KW, SPLIT> x;
+  __shared__ Meet<D, NB, KW, HOW> x;
   constexpr int ROWS = 16 * NB;
   const Call from = unpacked<ROWS>(call);
   const Phase2Args& a = from.a;
@@ -854,10 +872,10 @@ __global__ __launch_bounds__(64 * KW, 2) void phase2_f32_kernel(C call) {
   seq.Kl = (GlobalBytes)Kl; seq.Vl = (GlobalBytes)(Vl + first_d);
   seq.l_stride = (unsigned)(fused_append ? g.Hkv * D : D) * 4;
   seq.l_off = fused_append ? cache_len : 0;
-  attend_rows<D, NB, KW, SPLIT, P>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
+  attend_rows<D, NB, KW, HOW, P>(w, x, seq, wave, row_lim, wave_lim, g.scale * LOG2E, lane, load_rows);
 
   const bool direct = a.O != nullptr || a.A != nullptr;      // one split: nothing to merge
-  meet<D, NB, KW, SPLIT, P>(w, x,
+  meet<D, NB, KW, HOW, P>(w, x,
       [&](int row, int c, f32x4 v) {
         if (row >= live_rows) return;
         const int r = r0 + row, j = quotient(r, grid.G), head = kvh * g.G + r - j * g.G;
@@ -915,7 +933,7 @@ int64_t tile_order(const Phase1Args& a, int rows, TileOrder* o) {
   return tiles;
 }
 
-template <int D, int NB, int KW, bool SPLIT, int P = 1>
+template <int D, int NB, int KW, int HOW, int P = 1>
 hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   TileOrder o;
   const int64_t tiles = tile_order(a, 16 * NB, &o);
@@ -927,11 +945,11 @@ hipError_t launch_phase1(const Phase1Args& a, hipStream_t st) {
   o.turn_from = 0x7fffffff; o.turn = 0;
   if (wgs > cus && wgs <= 2 * cus) { o.turn_from = (int)cus; o.turn = (int)(cus + wgs - 1); }
   return launch_in_pieces(wgs * P, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-    phase1_f32_kernel<D, NB, KW, SPLIT, P><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, o, (int)first);
+    phase1_f32_kernel<D, NB, KW, HOW, P><<<dim3(n_wgs), 64 * KW, 0, st>>>(a, o, (int)first);
   });
 }
 
-template <int D, int NB, int KW, bool SPLIT, int P = 1>
+template <int D, int NB, int KW, int HOW, int P = 1>
 hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
   const Geom& g = a.g;
   const int64_t tiles = ((int64_t)g.G * a.q_len + 16 * NB - 1) / (16 * NB);
@@ -943,13 +961,13 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
       FlatCall call = pack(a, grid);
       return launch_in_pieces(wgs * P, 64 * KW, [&](unsigned first, unsigned n_wgs) {
         call.first_wg = (int)first;
-        phase2_f32_kernel<D, NB, KW, SPLIT, P, FlatCall><<<dim3(n_wgs), 64 * KW, 0, st>>>(call);
+        phase2_f32_kernel<D, NB, KW, HOW, P, FlatCall><<<dim3(n_wgs), 64 * KW, 0, st>>>(call);
       });
     }
   }
   if constexpr (P == 1 && (KW != 4 || NB == 2)) {
     return launch_in_pieces(wgs, 64 * KW, [&](unsigned first, unsigned n_wgs) {
-      phase2_f32_kernel<D, NB, KW, SPLIT, P, Call><<<dim3(n_wgs), 64 * KW, 0, st>>>(Call{a, grid, (int)first});
+      phase2_f32_kernel<D, NB, KW, HOW, P, Call><<<dim3(n_wgs), 64 * KW, 0, st>>>(Call{a, grid, (int)first});
     });
   }
   return hipErrorInvalidValue;      // (flat plans only)
@@ -993,36 +1011,43 @@ Phase1Plan phase1_plan_f32(const Geom& g) {
 
 hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   const Phase1Plan p = phase1_plan_f32(a.g);
-  if (p.waves == 1) return a.g.d == 64 ? launch_phase1<64, 1, 1, false>(a, st) : launch_phase1<128, 1, 1, false>(a, st);
-  if (p.rows == 32 && a.g.d == 128) return launch_phase1<128, 2, 4, true>(a, st);
-  if (p.rows == 32) return p.split ? launch_phase1<64, 2, 4, true>(a, st) : launch_phase1<64, 2, 4, false>(a, st);
-  if (p.waves == 4) return a.g.d == 64 ? launch_phase1<64, 1, 4, false>(a, st) : launch_phase1<128, 1, 4, false>(a, st);
-  if (p.pieces == 4) return a.g.d == 64 ? launch_phase1<64, 1, 8, false, 4>(a, st) : launch_phase1<128, 1, 8, false, 4>(a, st);
-  if (p.pieces == 2) return a.g.d == 64 ? launch_phase1<64, 1, 8, false, 2>(a, st) : launch_phase1<128, 1, 8, false, 2>(a, st);
-  return a.g.d == 64 ? launch_phase1<64, 1, 8, false>(a, st) : launch_phase1<128, 1, 8, false>(a, st);
+  if (p.waves == 1) return a.g.d == 64 ? launch_phase1<64, 1, 1, PLAIN>(a, st) : launch_phase1<128, 1, 1, PLAIN>(a, st);
+  if (p.rows == 32 && a.g.d == 128) return launch_phase1<128, 2, 4, SPLIT>(a, st);
+  if (p.rows == 32) return p.split ? launch_phase1<64, 2, 4, SPLIT>(a, st) : launch_phase1<64, 2, 4, PLAIN>(a, st);
+  if (p.waves == 4) return a.g.d == 64 ? launch_phase1<64, 1, 4, PLAIN>(a, st) : launch_phase1<128, 1, 4, PLAIN>(a, st);
+  // K is turned but for long ranges at d = 64 on more than 128 tiles and where four wavefronts share a tile.  us, as loaded / turned: one
+  // head, b = a = L / 4: d = 64: 300 (quarters) 5.6 / 4.9, 1024 7.8 / 7.55, 2000 (halves) 12.8 / 12.0, 3000 (whole) 18.7 / 19.0, 4 / 2 heads,
+  // 1000, b = 250 7.7 / 7.3; d = 128: 500 9.1 / 8.3, 1000 13.4 / 11.5, 4000 42.3 / 40.2; four wavefronts: one head, 4096, d = 64 26.3 / 29.7,
+  // d = 128 28.0 / 30.3, 8 / 2 heads, 1024, d = 128 20.9 / 19.6.
+  if (p.pieces == 4) return a.g.d == 64 ? launch_phase1<64, 1, 8, TURNED, 4>(a, st) : launch_phase1<128, 1, 8, TURNED, 4>(a, st);
+  if (p.pieces == 2) return a.g.d == 64 ? launch_phase1<64, 1, 8, TURNED, 2>(a, st) : launch_phase1<128, 1, 8, TURNED, 2>(a, st);
+  if (a.g.d == 128) return launch_phase1<128, 1, 8, TURNED>(a, st);
+  return a.g.a + (a.g.b < a.g.L ? a.g.b : a.g.L) <= 512 ? launch_phase1<64, 1, 8, TURNED>(a, st) : launch_phase1<64, 1, 8, PLAIN>(a, st);
 }
 
 // Per-part outputs over short blocks make splits of at most four units: one wavefront per
 // 32-row tile.  Against four (and one thread per row), us: 114 tokens on 54 keys in blocks of
 // 2, three sequences of 120 / 6 heads 418 -> 277 (373), 395 on 600 in blocks of 40, 7 heads
 // 58.8 -> 52.1 (91.6); splits of 128 keys and more lose by it (1000 on 1000 53.8 -> 59.3).
+// 16-row tiles turn K (as in phase 1), us, as loaded / turned: 4000 keys (8 / 2 heads, d = 128) 8.5 / 8.3, 16000 11.8 / 11.5, 300 (one head, d = 64)
+// 5.5 / 5.3, 50000 10.6 / 10.7, 33 tokens on 2000 13.6 / 12.7.
 // Split products (as in phase 1), fp32 / split, us: d = 128: 100 tokens on 16000 keys (8 / 2 heads) 69.6 / 54.0, on 4000 31.1 / 26.5, 20 on
 // 4000 15.0 / 14.8; d = 64: 100 on 16000 40.1 / 33.3 (runs of 864 keys), but 40 on 16000 20.7 / 21.3 (320), 20 on 16000 16.7 / 19.0 (192).
 constexpr int SPLIT_RUN_64 = 512;       // longest splits that d = 64 takes in fp32 products in phase 2
 hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st) {
   if (a.plan.tile_rows == 32 && !a.plan.flat && a.plan.split_len <= 4 * UNIT)
-    return a.g.d == 64 ? launch_phase2<64, 2, 1, false>(a, st) : launch_phase2<128, 2, 1, false>(a, st);
-  if (a.plan.tile_rows == 32 && a.g.d == 128) return launch_phase2<128, 2, 4, true>(a, st);
-  if (a.plan.tile_rows == 32) return a.plan.split_len > SPLIT_RUN_64 ? launch_phase2<64, 2, 4, true>(a, st) : launch_phase2<64, 2, 4, false>(a, st);
-  if (a.plan.waves == 4) return a.g.d == 64 ? launch_phase2<64, 1, 4, false>(a, st) : launch_phase2<128, 1, 4, false>(a, st);
+    return a.g.d == 64 ? launch_phase2<64, 2, 1, PLAIN>(a, st) : launch_phase2<128, 2, 1, PLAIN>(a, st);
+  if (a.plan.tile_rows == 32 && a.g.d == 128) return launch_phase2<128, 2, 4, SPLIT>(a, st);
+  if (a.plan.tile_rows == 32) return a.plan.split_len > SPLIT_RUN_64 ? launch_phase2<64, 2, 4, SPLIT>(a, st) : launch_phase2<64, 2, 4, PLAIN>(a, st);
+  if (a.plan.waves == 4) return a.g.d == 64 ? launch_phase2<64, 1, 4, TURNED>(a, st) : launch_phase2<128, 1, 4, TURNED>(a, st);
   // One split: few tiles share their columns of d, as in phase 1.  us, one token, one head: d = 64: 500 keys 8.7 -> 7.5, 250 6.3 -> 5.8;
   // d = 128: 250 10.6 -> 8.1; two sequences of 20 tokens on 200 (8 / 2 heads) 11.8 -> 9.4.
   if (a.O || a.A) {
     const int64_t tiles = (int64_t)a.g.B * a.g.Hkv * (((int64_t)a.g.G * a.q_len + 15) / 16);
-    if (tiles <= 64) return a.g.d == 64 ? launch_phase2<64, 1, 8, false, 4>(a, st) : launch_phase2<128, 1, 8, false, 4>(a, st);
-    if (tiles <= 128) return a.g.d == 64 ? launch_phase2<64, 1, 8, false, 2>(a, st) : launch_phase2<128, 1, 8, false, 2>(a, st);
+    if (tiles <= 64) return a.g.d == 64 ? launch_phase2<64, 1, 8, TURNED, 4>(a, st) : launch_phase2<128, 1, 8, TURNED, 4>(a, st);
+    if (tiles <= 128) return a.g.d == 64 ? launch_phase2<64, 1, 8, TURNED, 2>(a, st) : launch_phase2<128, 1, 8, TURNED, 2>(a, st);
   }
-  return a.g.d == 64 ? launch_phase2<64, 1, 8, false>(a, st) : launch_phase2<128, 1, 8, false>(a, st);
+  return a.g.d == 64 ? launch_phase2<64, 1, 8, TURNED>(a, st) : launch_phase2<128, 1, 8, TURNED>(a, st);
 }
 
 }  // namespace star
