@@ -143,6 +143,9 @@ def test_scores_that_climb_over_large_values(step, run, d, G):
     (1, 2, 2, 64, 1025, 1025, 0, 40),       # 130 tiles: whole
     (1, 33, 1, 128, 31, 31, 0, 33),         # 64 tiles; 69 of 64 keys: halves
     (1, 16, 4, 64, 64, 64, 7, 64),          # 64 tiles, 64 tiles
+    (1, 4, 2, 64, 1001, 250, 43, 2),        # 258 tiles: whole, short ranges
+    (1, 1, 1, 64, 2501, 625, 625, 5),       # 161 tiles: whole, long ranges
+    (1, 1, 1, 128, 2099, 300, 300, 5),      # 134 tiles: whole
 ])
 def test_fp32_columns_shared_by_workgroups(B, Hq, Hkv, d, L, b, a, lq):
     """Calls of few tiles, whose columns of d are computed by two or four workgroups."""
