@@ -29,7 +29,8 @@
  *     passed as void*, NULL = the default stream) and the function returns
  *     without synchronising.  Calls on one stream run in order.
  *   - All tensors are contiguous, row-major, last index fastest.
- *   - dtype: STAR_ATTN_F32 (fp32 storage and arithmetic) or STAR_ATTN_BF16
+ *   - dtype: STAR_ATTN_F32 (fp32 storage, sums and softmax, products good to 24
+ *     bits, on the fp32 or in parts on the bf16 matrix instructions) or STAR_ATTN_BF16
  *     (bf16 storage, bf16 MFMA with fp32 accumulation and fp32 softmax).
  *     Partial outputs, LSE values and the workspace are always fp32.
  *   - Query head h reads KV head h / (n_q_heads / n_kv_heads).
@@ -396,7 +397,7 @@ const char* star_attn_status_string(int status);
 /*
  * Name of the kernel path a shape would use, for logs and benchmarks; NULL for an
  * unsupported shape.  "bf16-mfma", or "f32-valu": a label kept from the first fp32
- * kernels, since callers may compare it -- the path runs on the fp32 matrix
+ * kernels, since callers may compare it -- the path runs on the matrix
  * instructions.  Host memory, static.
  */
 const char* star_attn_kernel_path(const star_attn_shape* shape);

@@ -7,9 +7,9 @@
 // served by the same split:
 //   * A workgroup owns a tile of 16 NB query rows of one KV group, and its KW
 //     wavefronts share the tile's KEYS: wavefront w takes the 16-key units
-//     w, w + KW, ...  Nothing crosses wavefronts until the end, so there is no LDS
-//     and no barrier in the key loop, and a tile of few rows still has KW
-//     wavefronts' worth of loads and MFMAs in flight.
+//     w, w + KW, ...  Nothing crosses wavefronts until the end, so there is no
+//     barrier in the key loop (LDS only for a wavefront's own K), and a tile of few rows
+//     still has KW wavefronts' worth of loads and MFMAs in flight.
 //   * Rows are packed over the heads of a KV group (row = token * G + head in
 //     group), so that a K/V unit is read once for all of them.
 //   * S^T = K Q^T: lane (col = lane % 16, j4 = lane / 16) supplies K[col][16 t + 4 j4 + e]
