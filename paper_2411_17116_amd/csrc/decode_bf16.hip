@@ -17,8 +17,7 @@
 //     t = 0..3; V (8 KiB) as 1 KiB-contiguous bursts.  As soon as its scores are taken and its V is in
 //     LDS the next step is requested into the same registers, ahead of the softmax and the products.
 //     All waits are the compiler's (straight-line code, static register indices; steps that are not
-//     cached as a whole have a loop of their own, so that the loop over the others has no
-//     branches between loads).  Measured against batches of two steps consumed before the next two are requested
+//     cached as a whole have a loop of their own behind the others').  Measured against batches of two steps consumed before the next two are requested
 //     (the resident set-up: one step, whose V the compiler requested only once its K was there), whole
 //     calls: 131072 tokens of eight heads 84.8 -> 82.4 us, four sequences of 32768 84.5 -> 83.0, 32768 tokens 30.5 -> 29.4;
 //     two steps per batch requested early: 84.1;
@@ -37,7 +36,7 @@
 //     and transposing reads are conflict-free;
 //   * rows at or beyond cache_len are the new tokens: they are read from the
 //     call's Kq/Vq and written to the cache by the workgroup whose split holds
-//     them, so no separate append kernel runs before a decode step;
+//     them, so no separate append kernel runs before a decode step (PIPED and EARLY, in the kernel, say when);
 //   * unrotated projections of a few tokens are rotated on the way: every wavefront turns its query
 //     rows while its first step is under way, the one that files a new key its row (and the merge
 //     kernel, behind all readers, the queries in memory).  A kernel in front of this one that did it
@@ -153,8 +152,7 @@ __device__ __forceinline__ void rotate(T* x, const Angles& angles, int token, in
 
 // The same for a step that ends past `hi` or among the call's tokens.  Rows at or past `hi`
 // re-read the last valid row (they are masked in the score tile).
-template <bool ROPE>
-__device__ __forceinline__ void load_last(StepRegs& r, const Source& src, int key0, int hi, int lane, const Angles* angles) {
+__device__ __forceinline__ void load_last(StepRegs& r, const Source& src, int key0, int hi, int lane) {
   const int col = lane & 15, j4 = lane >> 4;
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt) {
@@ -163,7 +161,6 @@ __device__ __forceinline__ void load_last(StepRegs& r, const Source& src, int ke
     GlobalBytes kp = kk < src.cache_len ? src.Kb + (size_t)kk * ROWB : src.Kn + (size_t)(kk - src.cache_len) * src.new_stride;
 #pragma unroll
     for (int t = 0; t < 4; ++t) r.k[4 * kt + t] = *(GlobalVec)(kp + t * 64 + j4 * 16);
-    if (ROPE && kk >= src.cache_len) rotate(&r.k[4 * kt], *angles, kk - src.cache_len, j4);
   }
 #pragma unroll
   for (int it = 0; it < 8; ++it) {
@@ -171,6 +168,24 @@ __device__ __forceinline__ void load_last(StepRegs& r, const Source& src, int ke
     vk = vk < hi ? vk : hi - 1;
     GlobalBytes vp = vk < src.cache_len ? src.Vb + (size_t)vk * ROWB : src.Vn + (size_t)(vk - src.cache_len) * src.new_stride;
     r.v[it] = *(GlobalVec)(vp + col * 16);
+  }
+}
+// Such a step's keys that are the call's join the cache from the registers (turned, if they are unrotated).
+template <bool ROPE>
+__device__ __forceinline__ void file_last(StepRegs& r, const Source& src, char* Kc, char* Vc, int key0, int hi, int lane, const Angles* angles) {
+  const int col = lane & 15, j4 = lane >> 4;
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt) {
+    const int kk = key0 + 16 * kt + col;
+    if (kk < src.cache_len || kk >= hi) continue;
+    if (ROPE) rotate(&r.k[4 * kt], *angles, kk - src.cache_len, j4);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) *(i32x4*)(Kc + (size_t)kk * ROWB + t * 64 + j4 * 16) = r.k[4 * kt + t];
+  }
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int vk = key0 + 4 * it + j4;
+    if (vk >= src.cache_len && vk < hi) *(i32x4*)(Vc + (size_t)vk * ROWB + col * 16) = r.v[it];
   }
 }
 
@@ -413,7 +428,18 @@ __global__ __launch_bounds__(64 * KW, RB > 2 ? 1 : 2) void decode_bf16_kernel(C 
   }
   const unsigned koff = qc * ROWB + j4 * 16, voff = j4 * ROWB + qc * 16;
   StepRegs r;
-  if (n_whole > 0) load_step<NT>(r, src, base, koff, voff);
+  // The steps that hold the call's tokens are a wavefront's last, and the longest chain of a call where they are requested when the others are
+  // done.  Caches read from HBM (NT): requested like the others, the tokens filed from the registers.  us: one token on 131072 (32 / 8 heads) 82.4 ->
+  // 80.8, four sequences of 32768 (64 / 8) 82.7 -> 81.1, 300000 180.3 -> 176.8, 64 rows on 131072 90.6 -> 89.4.  Two tiles of 16 rows fill the
+  // registers, and rotated keys are worth filing from them: there a first step only is requested early (32 rows on 8191 13.4 -> 12.4,
+  // unrotated 10000 tokens (12 / 4) 10.7 -> 10.4; 32 rows on 20000 without / with the rest 19.3 / 19.9).  Other calls file the tokens from loads of their
+  // own in front of the loop: stores late in a short call are waited for at its end (600 keys 7.3 / 7.5, 3000 of sixteen heads 9.15 / 9.4).
+  constexpr bool PIPED = NT && RB != 2, EARLY = NT || ROPE || RB > 1;
+  const auto request = [&](int s) {
+    if (s < n_whole) load_step<NT>(r, src, base + s * stride, koff, voff);
+    else if (EARLY && s < nsteps) load_last(r, src, base + s * stride, hi, lane);
+  };
+  request(0);
   __builtin_amdgcn_sched_barrier(0);
   if (ROPE) {
     static_assert(!ROPE || RB == 1, "a row per column");
@@ -439,24 +465,12 @@ __global__ __launch_bounds__(64 * KW, RB > 2 ? 1 : 2) void decode_bf16_kernel(C 
 
   // Algorithm 2, append: the new tokens whose rows fall into this wavefront's steps
   // join the cache (16 lanes move one 256-byte row of K and of V).
-  if (fused_append && hi > cache_len) {
+  if (!EARLY && fused_append && hi > cache_len) {
     for (int key = cache_len + j4; key < hi; key += 4) {
       const int step = key / STEP;                          // another split's step?
       if (KW > 1 || a.plan.flat ? step - (int)quotient(step, by.steps) * all_steps != first_step : key < base) continue;
       const size_t so = (size_t)(key - cache_len) * src.new_stride, dof = cache0 + (size_t)key * ROWB + qc * 16;
-      i32x4 k = *(GlobalVec)(src.Kn + so + qc * 16);
-      const i32x4 v = *(GlobalVec)(src.Vn + so + qc * 16);
-      if (ROPE) {
-        bf16x8 own = __builtin_bit_cast(bf16x8, k), other = __builtin_bit_cast(bf16x8, *(GlobalVec)(src.Kn + so + (qc ^ 8) * 16));
-        const float* cs = &angles->cs[key - cache_len][8 * (qc & 7)];
-        const float* sn = &angles->sn[key - cache_len][8 * (qc & 7)];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x = (float)own[e], y = (float)other[e];
-          own[e] = (__bf16)(qc < 8 ? rotary_lo(x, y, cs[e], sn[e]) : rotary_hi(y, x, cs[e], sn[e]));
-        }
-        k = __builtin_bit_cast(i32x4, own);
-      }
+      const i32x4 k = *(GlobalVec)(src.Kn + so + qc * 16), v = *(GlobalVec)(src.Vn + so + qc * 16);
       *(i32x4*)((char*)a.Kc + dof) = k;
       *(i32x4*)((char*)a.Vc + dof) = v;
     }
@@ -487,7 +501,8 @@ __global__ __launch_bounds__(64 * KW, RB > 2 ? 1 : 2) void decode_bf16_kernel(C 
   for (int s = 0; s < n_whole; ++s) {
     Scores<RB> x;
     score_step(w, r, vw, x);
-    if (s + 1 < n_whole) load_step<NT>(r, src, base + (s + 1) * stride, koff, voff);
+    if (PIPED) request(s + 1);
+    else if (s + 1 < n_whole) load_step<NT>(r, src, base + (s + 1) * stride, koff, voff);
     __builtin_amdgcn_sched_barrier(0);
     attend_step(w, x, vaddr, c);
   }
@@ -499,8 +514,11 @@ __global__ __launch_bounds__(64 * KW, RB > 2 ? 1 : 2) void decode_bf16_kernel(C 
   }
   for (int s = n_whole; s < nsteps; ++s) {
     Scores<RB> x;
-    load_last<ROPE>(r, src, base + s * stride, hi, lane, angles);
+    if (!PIPED && (!EARLY || s > 0)) load_last(r, src, base + s * stride, hi, lane);
+    if (EARLY) file_last<ROPE>(r, src, (char*)a.Kc + cache0, (char*)a.Vc + cache0, base + s * stride, hi, lane, angles);
     score_step(w, r, vw, x);
+    if (PIPED) request(s + 1);
+    __builtin_amdgcn_sched_barrier(0);
     mask_step(x, base + s * stride, lim, j4);
     attend_step(w, x, vaddr, c);
   }
