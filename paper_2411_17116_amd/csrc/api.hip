@@ -447,9 +447,6 @@ static size_t plan_bytes(const star_attn_shape* s, const SplitPlan& p, int64_t q
 }
 
 static bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
-static bool overlap(const void* x, size_t nx, const void* y, size_t ny) {
-  return (uintptr_t)x < (uintptr_t)y + ny && (uintptr_t)y < (uintptr_t)x + nx;
-}
 
 // Rotary embedding requested by the *_rope entry points (theta == 0: none).
 struct Rope {

@@ -979,6 +979,13 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
 // per row), us, 8 / 8 heads: d = 64, 100000 tokens: b = 1, a = 0 4790 -> 975 (3336), b = 4, a = 0 1245 -> 274 (1000), b = 4, a = 4
 // 1379 -> 368 (1495); 50000 tokens, d = 128: b = a = 16 474 -> 251 (2262); three units and more: 146 -> 144 (b = 32, a = 0), 165 -> 169
 // (64).
+// Workgroups that share a tile's columns of d read all of its query rows and store a part of each, in any order: one workgroup
+// takes whole tiles, reading before it stores, where a call's results (`rows` rows of O or A and their LSE) lie over its queries.
+static bool over_queries(const void* O, const void* LSE, const void* Q, int64_t rows, int d) {
+  const size_t bytes = (size_t)rows * d * sizeof(float);
+  return overlap(O, bytes, Q, bytes) || overlap(LSE, (size_t)rows * sizeof(float), Q, bytes);
+}
+
 // 32-row tiles shared by four wavefronts (two workgroups per CU) from more than one such tile per CU on; down to one 16-row tile
 // per CU, 16-row tiles shared by four (three per CU); fewer rows than that are bound by the latency of a tile: eight wavefronts
 // share it, and where a tile and CUs for it are left over, two or four workgroups compute a half or a quarter of its columns of d each:
@@ -1019,8 +1026,9 @@ hipError_t launch_phase1_f32(const Phase1Args& a, hipStream_t st) {
   // head, b = a = L / 4: d = 64: 300 (quarters) 5.6 / 4.9, 1024 7.8 / 7.55, 2000 (halves) 12.8 / 12.0, 3000 (whole) 18.7 / 19.0, 4 / 2 heads,
   // 1000, b = 250 7.7 / 7.3; d = 128: 500 9.1 / 8.3, 1000 13.4 / 11.5, 4000 42.3 / 40.2; four wavefronts: one head, 4096, d = 64 26.3 / 29.7,
   // d = 128 28.0 / 30.3, 8 / 2 heads, 1024, d = 128 20.9 / 19.6.
-  if (p.pieces == 4) return a.g.d == 64 ? launch_phase1<64, 1, 8, TURNED, 4>(a, st) : launch_phase1<128, 1, 8, TURNED, 4>(a, st);
-  if (p.pieces == 2) return a.g.d == 64 ? launch_phase1<64, 1, 8, TURNED, 2>(a, st) : launch_phase1<128, 1, 8, TURNED, 2>(a, st);
+  const int pieces = over_queries(a.O, a.LSE, a.Q, (int64_t)a.g.B * a.g.L * a.g.Hq, a.g.d) ? 1 : p.pieces;
+  if (pieces == 4) return a.g.d == 64 ? launch_phase1<64, 1, 8, TURNED, 4>(a, st) : launch_phase1<128, 1, 8, TURNED, 4>(a, st);
+  if (pieces == 2) return a.g.d == 64 ? launch_phase1<64, 1, 8, TURNED, 2>(a, st) : launch_phase1<128, 1, 8, TURNED, 2>(a, st);
   if (a.g.d == 128) return launch_phase1<128, 1, 8, TURNED>(a, st);
   return a.g.a + (a.g.b < a.g.L ? a.g.b : a.g.L) <= 512 ? launch_phase1<64, 1, 8, TURNED>(a, st) : launch_phase1<64, 1, 8, PLAIN>(a, st);
 }
@@ -1042,7 +1050,7 @@ hipError_t launch_phase2_f32(const Phase2Args& a, hipStream_t st) {
   if (a.plan.waves == 4) return a.g.d == 64 ? launch_phase2<64, 1, 4, TURNED>(a, st) : launch_phase2<128, 1, 4, TURNED>(a, st);
   // One split: few tiles share their columns of d, as in phase 1.  us, one token, one head: d = 64: 500 keys 8.7 -> 7.5, 250 6.3 -> 5.8;
   // d = 128: 250 10.6 -> 8.1; two sequences of 20 tokens on 200 (8 / 2 heads) 11.8 -> 9.4.
-  if (a.O || a.A) {
+  if ((a.O || a.A) && !over_queries(a.O ? a.O : a.A, a.LSE, a.Qq, (int64_t)a.g.B * a.q_len * a.g.Hq, a.g.d)) {
     const int64_t tiles = (int64_t)a.g.B * a.g.Hkv * (((int64_t)a.g.G * a.q_len + 15) / 16);
     if (tiles <= 64) return a.g.d == 64 ? launch_phase2<64, 1, 8, TURNED, 4>(a, st) : launch_phase2<128, 1, 8, TURNED, 4>(a, st);
     if (tiles <= 128) return a.g.d == 64 ? launch_phase2<64, 1, 8, TURNED, 2>(a, st) : launch_phase2<128, 1, 8, TURNED, 2>(a, st);

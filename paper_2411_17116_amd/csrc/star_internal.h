@@ -261,13 +261,18 @@ inline hipError_t launch_in_pieces(int64_t workgroups, int threads, Launch launc
   return hipSuccess;
 }
 
+// Whether the nx bytes at x and the ny bytes at y have any in common.
+inline bool overlap(const void* x, size_t nx, const void* y, size_t ny) {
+  return (uintptr_t)x < (uintptr_t)y + ny && (uintptr_t)y < (uintptr_t)x + nx;
+}
+
 // What a phase-1 call launches: row tiles of `rows` rows shared by `waves` wavefronts, one
 // workgroup each, or (queued) drawn from the work queues.
 struct Phase1Plan {
   int32_t queued, rows, waves, group;
   int64_t tiles;
   int32_t split;       // fp32: products of bf16 parts
-  int32_t pieces;      // fp32: workgroups that share a tile's columns of d
+  int32_t pieces;      // fp32: workgroups that share a tile's columns of d (one if the results are stored over Q)
 };
 Phase1Plan phase1_plan_bf16(const Geom& g, int anchor_mode, int n_cu);
 Phase1Plan phase1_plan_f32(const Geom& g);

@@ -88,3 +88,74 @@ def test_query(Hq, Hkv, d, L, q, parts, kind):
     for h in range(Hq):
         o, _ = _attend(Q[0, :, h].double(), K[0, :, h // G].double(), V[0, :, h // G].double(), L + torch.arange(1, q + 1, device="cuda"))
         assert ((O[0, :, h].double() - o).abs().max() <= TOL * size), h
+
+
+# Two factors of a product whose sizes make up for each other: what the parts lose of the smaller one shows in results of ordinary size.
+FAR = 80.0        # nats from a heavy key to the others, whose weights are then about 2^-115
+
+
+def _uneven(kind, Q, K, V):
+    h = Q.shape[-1] // 2
+    if kind == "small queries":
+        Q[..., :h] *= 2.0 ** -122
+        K[..., :h] *= 2.0 ** 122
+    if kind == "small keys":
+        Q[..., h:] *= 2.0 ** 122
+        K[..., h:] *= 2.0 ** -122
+    if kind == "small weights":          # every sixteenth key outweighs the others, whose values are as much larger
+        Q[..., 0], K[..., 0] = 32.0, 0.0
+        K[:, ::16], V[:, ::16] = 0.0, 0.0
+        K[:, ::16, :, 0] = FAR * Q.shape[-1] ** 0.5 / 32
+        V *= 2.0 ** 96
+
+
+def _close(got, q, k, v, lim, kind):
+    want, _ = _attend(q, k, v, lim)
+    size = _attend(q, k, v.abs(), lim)[0].amax(1, keepdim=True) if kind == "small weights" else 1.0
+    # scores FAR below their reference (log2 units: 1.45 FAR): the query's scaling, the product and the difference round by 2^-24
+    # of it each
+    tol = TOL + (3 * 1.45 * FAR * 2.0 ** -24 if kind == "small weights" else 0.0)
+    return ((got.double() - want).abs() <= tol * size).all()
+
+
+KINDS = ["small queries", "small keys", "small weights"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("Hq,Hkv,d,L,b,a", [(32, 2, 128, 300, 100, 37), (40, 4, 64, 311, 290, 1)])
+def test_prefill_of_uneven_factors(Hq, Hkv, d, L, b, a, kind):
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    Q, K, V = new(1, L, Hq, d), new(1, L, Hkv, d), new(1, L, Hkv, d)
+    _uneven(kind, Q, K, V)
+    shape = sa.StarShape.make("fp32", 1, Hq, Hkv, d, L, b, a, L)
+    assert sa.phase1_plan(shape, sa.ANCHOR_FIRST).tile_rows == 32
+    O = torch.empty_like(Q)
+    print(f"{Hq}/{Hkv} d={d} L={L} {kind}", flush=True)
+    sa.phase1(shape, Q, K, V, O, *sa.alloc_cache(shape))
+    torch.cuda.synchronize()
+    for h in range(Hq):
+        k, v = K[0, :, h * Hkv // Hq].double(), V[0, :, h * Hkv // Hq].double()
+        for s in range(0, L, b):
+            e, n = min(L, s + b), a if s else 0
+            lim = n + torch.arange(1, e - s + 1, device="cuda")
+            assert _close(O[0, s:e, h], Q[0, s:e, h].double(), torch.cat([k[:n], k[s:e]]), torch.cat([v[:n], v[s:e]]), lim, kind), (h, s)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("Hq,Hkv,d,L,q", [(8, 2, 128, 4003, 60), (4, 2, 64, 30001, 100)])
+def test_query_of_uneven_factors(Hq, Hkv, d, L, q, kind):
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    Q, K, V = new(1, q, Hq, d), new(1, L + q, Hkv, d), new(1, L + q, Hkv, d)
+    _uneven(kind, Q, K, V)
+    shape = sa.StarShape.make("fp32", 1, Hq, Hkv, d, L, L // 3, 0, L + q)
+    assert sa.phase2_plan(shape, L, q).tile_rows == 32
+    O = torch.empty_like(Q)
+    print(f"{Hq}/{Hkv} d={d} L={L} q={q} {kind}", flush=True)
+    sa.phase2(shape, L, Q, K[:, L:].contiguous(), V[:, L:].contiguous(), K.transpose(1, 2).contiguous(), V.transpose(1, 2).contiguous(), O,
+              sa.alloc_workspace(shape, q))
+    torch.cuda.synchronize()
+    for h in range(Hq):
+        k, v = K[0, :, h * Hkv // Hq].double(), V[0, :, h * Hkv // Hq].double()
+        assert _close(O[0, :, h], Q[0, :, h].double(), k, v, L + torch.arange(1, q + 1, device="cuda"), kind), h

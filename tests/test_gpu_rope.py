@@ -294,3 +294,75 @@ def test_decode_on_unrotated_projections_in_shared_buffers(B, Hq, Hkv, L, q):
     sa.phase2_rope(shape, theta, L, Q3, Kc3[0, 0, L:].view(1, q, 1, 128), Vc3[0, 0, L:].view(1, q, 1, 128), Kc3, Vc3, O3, ws)
     torch.cuda.synchronize()
     assert torch.equal(O3, O) and torch.equal(Q3, Q1) and torch.equal(Kc3, Kc1) and torch.equal(Vc3, Vc1)
+
+
+@pytest.mark.parametrize("rotated", [False, True])
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,q,squeezed", [
+    (1, 4, 2, 64, 300, 3, False),         # one split, few row tiles: four workgroups would share one
+    (1, 64, 64, 64, 200, 1, False),       # 64 tiles
+    (1, 6, 2, 128, 250, 5, False),
+    (2, 33, 33, 128, 200, 5, False),      # 66 tiles: two
+    (1, 40, 8, 64, 400, 50, False),       # 128 tiles
+    (1, 2, 1, 64, 3000, 9, True),         # a workspace that holds one split
+    (3, 30, 30, 128, 2000, 2, True),
+])
+def test_fp32_results_over_their_queries(B, Hq, Hkv, d, L, q, squeezed, rotated):
+    """fp32 calls of one split: O stored over Qq (A, where its rows lie as the queries' do) gives the bits of buffers of
+    their own.  Each workgroup of a tile reads all of its query rows."""
+    gen = torch.Generator(device="cuda").manual_seed(L + q)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    shape = sa.StarShape.make("fp32", B, Hq, Hkv, d, L, max(1, L // 4), 0, L + q)
+    one = -(-B * Hq * q * (d + 1) * 4 // 256) * 256
+    ws = torch.empty(one, dtype=torch.uint8, device="cuda") if squeezed else sa.alloc_workspace(shape, q)
+    assert squeezed or sa.phase2_plan(shape, L, q).n_splits == 1
+    Kc, Vc = new(B, Hkv, L + q, d), new(B, Hkv, L + q, d)
+    Q, K, V = new(B, q, Hq, d), new(B, q, Hkv, d), new(B, q, Hkv, d)
+    print(f"[{B} {Hq}/{Hkv} d={d} L={L} q={q}]", flush=True)
+
+    def call(Qx, Kx, Vx, Ox):
+        if rotated:
+            sa.phase2_rope(shape, 500000.0, L, Qx, K, V, Kx, Vx, Ox, ws)
+        else:
+            sa.phase2(shape, L, Qx, K, V, Kx, Vx, Ox, ws)
+    Q1, K1, V1, O = Q.clone(), Kc.clone(), Vc.clone(), torch.empty_like(Q)
+    call(Q1, K1, V1, O)
+    Q2, K2, V2 = Q.clone(), Kc.clone(), Vc.clone()
+    call(Q2, K2, V2, Q2)
+    torch.cuda.synchronize()
+    assert torch.equal(Q2, O) and torch.equal(K2, K1) and torch.equal(V2, V1)
+    if q > 1 or rotated:
+        return
+    A, LSE, lse = torch.empty((B, Hq, 1, d), device="cuda"), torch.empty((B, Hq, 1), device="cuda"), torch.empty((B, Hq, 1), device="cuda")
+    sa.phase2_partial(shape, L, Q, Kc.clone(), Vc.clone(), A, LSE, ws, Kq=K, Vq=V)
+    Q3 = Q.clone()
+    sa.phase2_partial(shape, L, Q3, Kc.clone(), Vc.clone(), Q3.view(B, Hq, 1, d), lse, ws, Kq=K, Vq=V)
+    torch.cuda.synchronize()
+    assert torch.equal(Q3.view_as(A), A) and torch.equal(lse, LSE)
+
+
+@pytest.mark.parametrize("rotated", [False, True])
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,b,a", [
+    (1, 1, 1, 64, 1024, 256, 256),        # 64 tiles: four workgroups would share one
+    (1, 4, 2, 128, 300, 100, 33),
+    (1, 2, 2, 128, 600, 150, 75),         # 80 tiles: two
+    (2, 2, 1, 64, 900, 900, 0),           # 114 tiles, a range of more than 512 keys
+    (1, 8, 2, 128, 1300, 300, 200),       # 32-row tiles
+])
+def test_fp32_context_results_over_their_queries(B, Hq, Hkv, d, L, b, a, rotated):
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    new = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    shape = sa.StarShape.make("fp32", B, Hq, Hkv, d, L, b, a, L)
+    Q, K, V = new(B, L, Hq, d), new(B, L, Hkv, d), new(B, L, Hkv, d)
+    print(f"[{B} {Hq}/{Hkv} d={d} L={L}]", flush=True)
+
+    def call(Qx, Ox):
+        caches, lse = sa.alloc_cache(shape), torch.empty((B, Hq, L), device="cuda")
+        if rotated:
+            sa.phase1_rope(shape, 500000.0, Qx, K, V, Ox, *caches, LSE_ctx=lse)
+        else:
+            sa.phase1(shape, Qx, K, V, Ox, *caches, LSE_ctx=lse)
+        return [Ox, lse, *caches]
+    want, Q2 = call(Q.clone(), torch.empty_like(Q)), Q.clone()
+    got = call(Q2, Q2)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(got, want))
