@@ -30,7 +30,8 @@
  *     without synchronising.  Calls on one stream run in order.
  *   - All tensors are contiguous, row-major, last index fastest.
  *   - dtype: STAR_ATTN_F32 (fp32 storage, sums and softmax, products good to 24
- *     bits, on the fp32 or in parts on the bf16 matrix instructions) or STAR_ATTN_BF16
+ *     bits, on the fp32 or in parts on the bf16 matrix instructions; elements of V below
+ *     2^-134 in size may count as zero) or STAR_ATTN_BF16
  *     (bf16 storage, bf16 MFMA with fp32 accumulation and fp32 softmax).
  *     Partial outputs, LSE values and the workspace are always fp32.
  *   - Query head h reads KV head h / (n_q_heads / n_kv_heads).
