@@ -323,7 +323,11 @@ constexpr int SPLIT_UNIT = 32;
 //     zero, are taken in fp32 products (held()).
 //   * V is off by 2^-134: a wavefront's results below 2^-108 are taken again in fp32 products, as are those that are not finite, in
 //     which an infinite part or sum shows (unsafe()).  (Values below 2^-134 count as zero.)
-// The two checks and the weights' scale, 8 / 2 heads, d = 128, 4099 tokens: 102.65 -> 103.1 us.
+// The two checks and the weights' scale, 8 / 2 heads, d = 128, 4099 tokens: 103.2 -> 103.4 us.  What a second walk costs there, where
+// fp32 products alone took 134 us: all V, or one column of it, below 3e-33, or sums above 5e33: 224; a NaN or an infinity in V, in half of
+// the blocks 157, in the anchor 170; queries that are taken in fp32 products from the start 147.  8192 tokens (666): 1120, 650, 777 and
+// 690; d = 64 (97.5): 177, 115, 134 and 107; 100 tokens on 16000 keys (69.6): 113, 83, 77 and 75.  One look at a part of the results behind a
+// wavefront's first unit brings values that are small throughout to 160, and the ordinary call to 103.9: not kept.
 constexpr float SPLIT_HELD = 0x1p16f, Q_MOST = 0x1p88f, Q_LEAST = 0x1p-110f, O_LEAST = 0x1p-108f;
 
 struct Parts {                 // of eight elements
@@ -521,7 +525,7 @@ __device__ __forceinline__ bool unsafe(const RowState<D, 2>& w) {
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const float l = xor32_sum(w.l[b] + xor16(w.l[b]));
-      float zero = l * 0.f, least = INFINITY;
+      float most = l, least = INFINITY;
 #pragma unroll
       for (int h = 0; h < D / 64; ++h)
 #pragma unroll
@@ -529,10 +533,10 @@ __device__ __forceinline__ bool unsafe(const RowState<D, 2>& w) {
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
             const float size = fabsf(w.o[b][h][e][v]);
-            zero = fmaf(size, 0.f, zero);
+            most = __builtin_elementwise_maximum(most, size);      // (NaN if any is)
             least = fminf(least, zeros && size == 0.f ? INFINITY : size);
           }
-      any |= !(zero == 0.f) || least < O_LEAST * HELD * l;
+      any |= !(most < INFINITY) || least < O_LEAST * HELD * l;
     }
     return __builtin_amdgcn_ballot_w64(any) != 0;
   };
@@ -592,22 +596,30 @@ __device__ __forceinline__ void attend_split(RowState<D, 2>& w, SharedRows<D>* s
         for (int e = 0; e < 4; ++e) w.o[b][h][e] *= HELD / SPLIT_HELD;
     if (__builtin_expect(!unsafe<D>(w), 1)) return;
   }
-  // the same keys in fp32 products, which take every value
+  // the same keys in fp32 products, which take every value, as attend() takes them
   again();
+  cur = unit_at<SPLIT_UNIT>(seq, wave);
+  Unit<D> one;
+  load_k<D, false, 1>(one, cur, lane);
+  load_v<D, 1>(one, cur, lane);
   scale_rows<D, 2, 1>(w, qk_scale);
-  for (int u = wave; u < seq.n_units; u += KW) {
-    cur = unit_at<SPLIT_UNIT>(seq, u);
-    for (int done = 0; done < SPLIT_UNIT && cur.n_rows > 0; done += UNIT) {
-      Unit<D> one;
-      load_k<D, false, 1>(one, cur, lane);
-      load_v<D, 1>(one, cur, lane);
-      attend_unit<D, 2, false, false, 1>(w, one, nullptr, cur, cur, row_lim, wave_lim, lane);
-      cur.K += (size_t)UNIT * cur.stride;
-      cur.V += (size_t)UNIT * cur.stride;
-      cur.key0 += UNIT;
-      cur.n_rows -= UNIT;
+  for (int u = wave, half = 0;;) {
+    UnitAt nxt = cur;
+    half = half == 0 && cur.n_rows > UNIT;
+    if (half) {
+      nxt.K += (size_t)UNIT * cur.stride;
+      nxt.V += (size_t)UNIT * cur.stride;
+      nxt.key0 += UNIT;
+      nxt.n_rows -= UNIT;
+    } else {
+      u += KW;
+      if (u >= seq.n_units) break;
+      nxt = unit_at<SPLIT_UNIT>(seq, u);
     }
+    attend_unit<D, 2, true, false, 1>(w, one, nullptr, cur, nxt, row_lim, wave_lim, lane);
+    cur = nxt;
   }
+  attend_unit<D, 2, false, false, 1>(w, one, nullptr, cur, cur, row_lim, wave_lim, lane);
 }
 
 // log(l 2^m) for l > 0: the exponent of l joins m without a rounding lost, so that l may be a large sum

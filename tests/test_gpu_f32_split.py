@@ -108,18 +108,26 @@ def _uneven(kind, Q, K, V):
         V[:, torch.arange(V.shape[1], device="cuda") % 32 != 1] = 0.0
         K[:, ::16, :, 0] = FAR * Q.shape[-1] ** 0.5 / 32
         V *= 2.0 ** 96
+    if kind == "a small column":
+        V[..., 1] *= 2.0 ** -115
+    if kind == "a huge value":           # of a late key
+        V[:, 5 * V.shape[1] // 6, :, 6] = 3.4e38
 
 
 def _close(got, q, k, v, lim, kind):
     want, _ = _attend(q, k, v, lim)
-    size = _attend(q, k, v.abs(), lim)[0].amax(1, keepdim=True) if kind == "small weights" else 1.0
+    size = _attend(q, k, v.abs(), lim)[0].amax(1, keepdim=True) if kind == "small weights" else torch.ones_like(want)
+    if kind == "a small column":
+        size[:, 1] = 2.0 ** -115
+    if kind == "a huge value":
+        size[:, 6] = 3.4e38
     # scores FAR below their reference (log2 units: 1.45 FAR): the query's scaling, the product and the difference round by 2^-24
     # of it each
     tol = TOL + (3 * 1.45 * FAR * 2.0 ** -24 if kind == "small weights" else 0.0)
     return ((got.double() - want).abs() <= tol * size).all()
 
 
-KINDS = ["small queries", "small keys", "small weights"]
+KINDS = ["small queries", "small keys", "small weights", "a small column", "a huge value"]
 
 
 @pytest.mark.parametrize("kind", KINDS)
