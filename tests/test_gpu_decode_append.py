@@ -57,3 +57,48 @@ def test_last_steps_unrotated(B, Hq, Hkv, L, q):
     sa.phase2_rope(shape, 500000.0, L, Q, Kn, Vn, Kc, Vc, O, sa.alloc_workspace(shape, q), pos0=7)
     torch.cuda.synchronize()
     assert torch.equal(Kc, K) and torch.equal(Vc, V) and torch.equal(Q, Qr) and torch.equal(O, want)
+
+
+# Caches read from HBM: every step is requested while the one before it is worked on, the last ones among them
+HBM = [
+    (512, 8, 8, 90, 16),          # one wavefront to a head: two last steps behind two whole ones
+    (1100, 8, 8, 30, 16),         # two behind none
+    (1300, 8, 8, 31, 9),          # the second of eight keys
+    (512, 8, 8, 96, 8),           # one, which begins with the tokens, behind three
+    (200, 16, 8, 260, 8),         # G = 2
+]
+
+
+def _from_hbm(B, Hq, Hkv, L, q, rope):
+    shape, Q, Kn, Vn, Kc, Vc = _call(B, Hq, Hkv, L, q, L + q)
+    plan = sa.phase2_plan(shape, L, q)
+    assert plan.decode == 1 and plan.non_temporal == 1 and plan.flat == 1 and plan.n_splits == 1
+    print(f"{B} {Hq}/{Hkv} {L} {q} rope={rope}", flush=True)
+    O, ws = torch.empty_like(Q), sa.alloc_workspace(shape, q)
+    return shape, Q, Kn, Vn, Kc, Vc, O, ws
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,q", HBM)
+def test_last_steps_of_caches_from_hbm(B, Hq, Hkv, L, q):
+    shape, Q, Kn, Vn, Kc, Vc, O, ws = _from_hbm(B, Hq, Hkv, L, q, False)
+    K, V = Kc.clone(), Vc.clone()
+    K[:, :, L:L + q], V[:, :, L:L + q] = Kn.transpose(1, 2), Vn.transpose(1, 2)
+    sa.phase2(shape, L, Q, Kn, Vn, Kc, Vc, O, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(Kc, K) and torch.equal(Vc, V)
+    some = [0, 1, B // 2, B - 1]
+    want = _exact(Q[some].double().cpu(), K[some, :, :L + q].double().cpu(), V[some, :, :L + q].double().cpu(), q)
+    assert (O[some].double().cpu() - want).abs().max().item() <= ph.TOL["bf16"]["o"]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,q", [(1400, 8, 8, 28, 8), (512, 8, 8, 92, 8), (1100, 16, 8, 40, 8)])
+def test_last_steps_of_caches_from_hbm_unrotated(B, Hq, Hkv, L, q):
+    shape, Q, Kn, Vn, Kc, Vc, O, ws = _from_hbm(B, Hq, Hkv, L, q, True)
+    tokens = lambda H: sa.StarShape.make("bf16", B, H, H, 128, q, q, 0, q)
+    Qr, Kr, K, V, want = torch.empty_like(Q), torch.empty_like(Kn), Kc.clone(), Vc.clone(), torch.empty_like(Q)
+    sa.rope(tokens(Hq), Q, Qr, 500000.0, pos0=L + 7)
+    sa.rope(tokens(Hkv), Kn, Kr, 500000.0, pos0=L + 7)
+    sa.phase2(shape, L, Qr, Kr, Vn, K, V, want, ws)
+    sa.phase2_rope(shape, 500000.0, L, Q, Kn, Vn, Kc, Vc, O, ws, pos0=7)
+    torch.cuda.synchronize()
+    assert torch.equal(Kc, K) and torch.equal(Vc, V) and torch.equal(Q, Qr) and torch.equal(O, want)
