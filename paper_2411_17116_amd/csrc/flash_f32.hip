@@ -1028,10 +1028,6 @@ hipError_t launch_phase2(const Phase2Args& a, hipStream_t st) {
 
 }  // namespace
 
-// Blocks of at most two units of keys have nothing to share: one wavefront per tile.  Against the set-ups below (and one thread
-// per row), us, 8 / 8 heads: d = 64, 100000 tokens: b = 1, a = 0 4790 -> 975 (3336), b = 4, a = 0 1245 -> 274 (1000), b = 4, a = 4
-// 1379 -> 368 (1495); 50000 tokens, d = 128: b = a = 16 474 -> 251 (2262); three units and more: 146 -> 144 (b = 32, a = 0), 165 -> 169
-// (64).
 // Workgroups that share a tile's columns of d read all of its query rows and store a part of each, in any order: one workgroup
 // takes whole tiles, reading before it stores, where a call's results (`rows` rows of O or A and their LSE) lie over its queries.
 static bool over_queries(const void* O, const void* LSE, const void* Q, int64_t rows, int d) {
@@ -1039,32 +1035,46 @@ static bool over_queries(const void* O, const void* LSE, const void* Q, int64_t 
   return overlap(O, bytes, Q, bytes) || overlap(LSE, (size_t)rows * sizeof(float), Q, bytes);
 }
 
-// 32-row tiles shared by four wavefronts (two workgroups per CU) from more than one such tile per CU on; down to one 16-row tile
-// per CU, 16-row tiles shared by four (three per CU); fewer rows than that are bound by the latency of a tile: eight wavefronts
-// share it, and where a tile and CUs for it are left over, two or four workgroups compute a half or a quarter of its columns of d each:
-// every one takes all scores, but the products with V, the other half of a tile's MFMAs, are shared (one head, b = a = L / 4,
+// Blocks of at most two units of keys have nothing to share: one wavefront per tile.  Against the set-ups below (and one thread
+// per row), us, 8 / 8 heads: d = 64, 100000 tokens: b = 1, a = 0 4790 -> 975 (3336), b = 4, a = 0 1245 -> 274 (1000), b = 4, a = 4
+// 1379 -> 368 (1495); 50000 tokens, d = 128: b = a = 16 474 -> 251 (2262); three units and more: 146 -> 144 (b = 32, a = 0), 165 -> 169
+// (64).
+// 32-row tiles shared by four wavefronts (two workgroups per CU) from more than one such tile per CU on, if their rows see keys enough;
+// down to one 16-row tile per CU, 16-row tiles shared by four (three per CU); fewer rows than that are bound by the latency of a tile:
+// eight wavefronts share it, and where a tile and CUs for it are left over, two or four workgroups compute a half or a quarter of its
+// columns of d each: every one takes all scores, but the products with V, the other half of a tile's MFMAs, are shared (one head, b = a = L / 4,
 // us, whole tiles / halves / quarters: d = 64: L = 500 (32 tiles) 6.9 / 6.5 / 6.3, 1024 (64) 9.25 / 8.45 / 8.0, 1500 (96) 11.6 / 10.6
 // / 14.1; d = 128: 500 11.8 / 9.7 / 9.1, 1000 16.3 / 13.5 / 13.4, 2000 (128) 25.2 / 22.0 / 33.8; sixteen wavefronts to a tile 11.3
-// where eight take 9.25).  Measured, 16-row tiles / 32-row tiles in split products, us: d = 128: 8 / 2 heads, b = a = L / 4: L = 1060 (265 32-row tiles)
-// 25.5 / 25.4, 1150 29.2 / 26.5, 2048 62 / 44, 4000 191 / 134; one head, 8192 (256 tiles) 103 / 102, blocks as long as the
-// context 153 / 193, 9000 259 / 214.  At d = 64 a tile's start weighs more: 1060 14.1 / 16.4, 1350 (338) 19.6 / 20.1, 1500 (375) 21.5 /
-// 21.9, 2048 (512) 33.9 / 26.9, but one head, 9000 (282), b = a = 2250 79.4 / 68.2.  Eight wavefronts: one head, d = 64, L = 1024
-// (32) 10.0 (four) / 9.9, d = 64, 8 / 2 heads, 2048 37.3 / 39.4.
-// Split products against fp32 products in the same 32-row tiles, us: d = 128: 8 / 2 heads, 4099 (b = 1024, a = 512) 134 / 102.5, 8192 (b = a =
-// 2048) 668 / 496; d = 64: 98 / 78, 354 / 273; two sequences of 3000, b = a = 187 40.4 / 39.7.  Units of 32 keys for four wavefronts
-// leave some idle on short ranges, which shows at d = 64 (8 / 8 heads, 20000 tokens): b = 150, a = 75 102.8 / 111.2, b = 64, a = 32 75.6 /
-// 82.9 (d = 128: 226 / 203, 162 / 144).
-constexpr int SPLIT_KEYS_64 = 256;      // longest range that d = 64 takes in fp32 products in phase 1
+// where eight take 9.25).  Eight wavefronts: one head, d = 64, L = 1024 (32) 10.0 (four) / 9.9, d = 64, 8 / 2 heads, 2048 37.3 / 39.4.
+// What decides between the tiles is how many keys a row sees on average (`seen`; less by the square of the padding that 32 rows add to 16): a
+// 32-row tile has the longer start (the parts of its queries) and end, and units of 32 keys for four wavefronts leave some idle on short ranges.
+// 16-row tiles that all run at once (768, and some that start as the shortest end) are hard to beat; so is one round (512) of 32-row tiles that
+// 16-row ones need two for.
+// Below the lines 16-row tiles, but for more than 32768 rows of d = 64, which take 32-row tiles in fp32 products there.
+// us, 16-row tiles / 32-row tiles in fp32 products / in split products, from 350 calls drawn over 4096 to 200000 rows and 33 to 5800 keys:
+//   d = 128, up to 850 16-row tiles: seen 82 15.3 / 18.8 / 18.5, 114 16.8 / 20.6 / 18.7, 141 19.7 / - / 22.7, 185 22.0 / 25.9 / 22.4, 196 22.2 / 24.8 / 21.6, 209
+//   23.4 / - / 26.5, 244 25.9 / 28.8 / 23.9, 1366 86.4 / 114.0 / 84.7 (of 8192 rows and fewer none, 917 40.4 / 65.8 / 52.3).  960 / 496 tiles: 108 23.5 /
+//   - / 20.3.  More: 26 15.2 / 20.0 / 21.6, 73 23.2 / 26.2 / 24.7, 111 19.0 /
+//   21.4 / 19.4, 115 26.2 / 28.9 / 27.3, 125 26.6 / 29.9 / 26.5, 136 21.7 / 23.3 / 21.5, 151 33.6 / 36.8 / 34.3, 214 35.9 / 36.4 / 31.8, 1154 87.5 / 86.0 / 65.0;
+//   100000 rows: 38 111 / 131 / 143, 49 72 / 91 / 86, 100 71.3 / 79.8 / 74.6, 146 84.4 / 88.7 / 78.0, 227 162 / 136 / 126, 764 398 / 366 / 302.
+//   d = 64, up to 768 16-row tiles: 356 18.4 / 20.0 / 18.9, 410 20.8 / 25.3 / 22.4, 680 26.8 / - / 24.8, 853 33.3 / 39.1 / 31.5.  Up to 512 32-row tiles: 109 11.3 / 12.1 / 12.6,
+//   114 11.9 / 12.1 / 13.2, 234 17.4 / - / 16.4, 264 19.6 / 17.8 / 17.4.  More: 44 9.9 / 11.2 / 14.0, 154 16.9 / 17.9 / 17.2, 257 20.9 / 22.6 / 22.7, 328 26.2 /
+//   28.2 / 24.1, 771 67.4 / 67.1 / 56.6.  More than 32768 rows: 163 85.8 / 70.2 / 79.4, 200 56.5 / 52.0 / 57.4, 344 46.2 / 45.2 / 45.9, 362 - /
+//   84.1 / 79.7, 386 67.5 / 64.7 / 62.0, 802 192 / 183 / 161.
 Phase1Plan phase1_plan_f32(const Geom& g) {
-  const int64_t bmax = g.b < g.L ? g.b : g.L, rows = g.L * g.G * g.Hkv * g.B, keys = g.a + bmax;
+  const int64_t bmax = g.b < g.L ? g.b : g.L, rows = g.L * g.G * g.Hkv * g.B;
+  const int64_t full = g.L / g.b, rest = g.L - full * g.b;      // (the short last block has fewer)
+  const auto tiles = [&](int64_t r) { return (full * ((g.b * g.G + r - 1) / r) + (rest * g.G + r - 1) / r) * g.B * g.Hkv; };
+  const int64_t t16 = tiles(16), t32 = tiles(32);
+  const double pad = 2.0 * t32 / t16, seen = (double)(full * g.b * (g.b + 1) / 2 + rest * (rest + 1) / 2 + g.a * (g.L - bmax)) / g.L / (pad * pad);
+  const double line = g.d == 128 ? t16 <= 850 ? 230 : t16 > 900 && t32 <= 512 ? 100 : 120 : t16 <= 768 ? 600 : t32 <= 512 ? 200 : 280;
   Phase1Plan p = {0, 16, 8, 0, 0, 0, 1};
   if ((g.a + UNIT - 1) / UNIT + (bmax + UNIT - 1) / UNIT <= 2) p.waves = 1;
-  else if (rows > 256 * 32 && (g.d == 128 || rows > 384 * 32 || keys > 1024)) {
+  else if (rows > 256 * 32 && (seen >= line || (g.d == 64 && rows >= 1024 * 32))) {
     p.rows = 32; p.waves = 4;
-    p.split = g.d == 128 || keys > SPLIT_KEYS_64;
+    p.split = seen >= line;
   } else if (rows >= 256 * 16) p.waves = 4;
-  const int64_t full = g.L / g.b, rest = g.L - full * g.b;      // (the short last block has fewer)
-  p.tiles = (full * ((g.b * g.G + p.rows - 1) / p.rows) + (rest * g.G + p.rows - 1) / p.rows) * g.B * g.Hkv;
+  p.tiles = tiles(p.rows);
   if (p.waves == 8) p.pieces = p.tiles <= 64 ? 4 : p.tiles <= 128 ? 2 : 1;
   return p;
 }

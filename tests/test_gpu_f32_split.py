@@ -35,11 +35,11 @@ def _attend(Q, K, V, lim):
 
 @pytest.mark.parametrize("kind", ["normal", "huge", "tiny", "far"])
 @pytest.mark.parametrize("B,Hq,Hkv,d,L,b,a", [
-    (1, 32, 2, 128, 257, 257, 0),      # units of 32 keys, the last of one
-    (1, 32, 2, 128, 300, 100, 37),     # ragged anchor, wavefronts without a unit
-    (2, 6, 2, 128, 715, 143, 143),     # tiles that end between tokens (three heads), a last tile of two rows
-    (1, 40, 4, 64, 311, 290, 1),       # anchor of one key, a short last block
-    (1, 32, 1, 64, 450, 225, 200),
+    (1, 32, 2, 128, 481, 481, 0),      # units of 32 keys, the last of one
+    (1, 32, 2, 128, 440, 220, 137),    # ragged anchor, wavefronts without a unit
+    (4, 6, 2, 128, 715, 143, 143),     # tiles that end between tokens (three heads), a last tile of two rows
+    (1, 40, 4, 64, 700, 689, 1),       # anchor of one key, a short last block
+    (1, 32, 1, 64, 480, 240, 225),
 ])
 def test_prefill(B, Hq, Hkv, d, L, b, a, kind):
     gen = torch.Generator(device="cuda").manual_seed(L)
@@ -131,7 +131,7 @@ KINDS = ["small queries", "small keys", "small weights", "a small column", "a hu
 
 
 @pytest.mark.parametrize("kind", KINDS)
-@pytest.mark.parametrize("Hq,Hkv,d,L,b,a", [(32, 2, 128, 300, 100, 37), (40, 4, 64, 311, 290, 1)])
+@pytest.mark.parametrize("Hq,Hkv,d,L,b,a", [(32, 2, 128, 440, 220, 137), (40, 4, 64, 700, 689, 1)])
 def test_prefill_of_uneven_factors(Hq, Hkv, d, L, b, a, kind):
     gen = torch.Generator(device="cuda").manual_seed(L)
     new = lambda *s: torch.randn(s, generator=gen, device="cuda")
