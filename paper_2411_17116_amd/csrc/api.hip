@@ -195,14 +195,21 @@ static int64_t f32_short_runs(const Geom& g, int64_t q_len, int64_t total) {
 // about twice (a unit of 16 keys then takes half as long), 32 beyond.  Measured, us, against
 // 32-row tiles shared by eight wavefronts, one workgroup per CU (8 / 2 heads, d = 128):
 // 33 tokens on 300 keys 18.2 -> 12.6, on 4000 26.0 -> 22.9; 100 on 4000 50.0 -> 32.7, on
-// 16000 124 -> 74.
-static int f32_tile_rows(const Geom& g, int64_t q_len, int64_t total) {
+// 16000 124 -> 74.  (Of 32-row tiles in fp32 products; in split products the last two take 26.9 and 54.7.)
+// d = 128 without per-part outputs: runs of 128 keys have one unit of split products for each wavefront, whose start then counts, and
+// 16-row tiles of longer runs are faster up to 850 tiles times runs, if all of one run start at once (750 if they are few and the runs to merge many).  us, 32-row tiles in fp32
+// products / in split products / 16-row tiles: 111 tokens on 2309 keys (4 / 1 heads, 532) 22.9 / 24.9 / 15.2, 72 on 368 (three of 10 / 2, 552) 22.0 / 23.6 /
+// 13.9, 100 on 2000 (8 / 2, 850) 24.6 / 25.9 / 17.4, 4 on 13722 (20 / 4, 864) 22.8 / 21.5 / 23.4; few tiles: 11 on 7137 (16 / 4, 672) 23.2 / 24.5 / 19.1, 6 on
+// 25655 (two of 4 / 1, 804) - / 21.4 / 23.1; 336 tiles of two runs 14.0 / 15.2 / 17.4.
+static int f32_tile_rows(const Geom& g, int64_t q_len, int64_t total, bool want_parts) {
   const int64_t rows = (int64_t)g.G * q_len, tiles = (int64_t)g.B * g.Hkv * ceil_div(rows, 16);
-  return rows <= 16 || (double)tiles * ceil_div(total, F32_SPLIT_MIN) <= 512 ? 16 : 32;
+  const int64_t most = g.d == 128 && !want_parts && tiles <= 256 ? tiles < 16 ? 750 : 850 : 512;
+  return rows <= 16 || (double)tiles * ceil_div(total, F32_SPLIT_MIN) <= most ? 16 : 32;
 }
 // Up to these bytes of K and V per KV head one workgroup walks all keys of its rows and
-// there is nothing to merge: with the matrix pipe of one CU it takes 9.3 us at 250 KiB and
-// 13.9 at 530 (one row, d = 64), splits and their merge 11.7 us at either.
+// there is nothing to merge.  us from a graph, one workgroup (or the two or four that share its columns) / splits and their merge: one
+// row of one head, d = 64: 250 keys (125 KiB) 5.2 / 7.0, 487 6.7 / 6.2, 700 8.3 / 6.8, 1034 10.3 / 6.2; 32 rows on 487 7.1 / 8.2, on 1024 10.7 /
+// 7.8; 8 / 2 heads, d = 128: 250 (250 KiB) 7.5 / 9.0, 400 8.9 / 7.8.  (Enqueued one by one, splits are a launch more.)
 constexpr int64_t F32_DIRECT_BYTES = 256 << 10;
 
 // ---- bf16 row-tiled kernel: one workgroup per CU is resident, 256 on the whole chip.  (The costs
@@ -366,7 +373,7 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     return true;
   }
   if (s->dtype == STAR_ATTN_F32 && !want_parts) {
-    p->tile_rows = f32_tile_rows(g, q_len, total);
+    p->tile_rows = f32_tile_rows(g, q_len, total, want_parts);
     int64_t splits = f32_short_runs(g, q_len, total);
     p->waves = splits > 0 ? 4 : 8;
     if (splits == 0) {
@@ -394,8 +401,8 @@ static bool make_plan(const star_attn_shape* s, int64_t q_len, int64_t total, bo
     int64_t want, min_len;
     if (s->dtype == STAR_ATTN_F32) {
       // (the same splits for every length of the cache)
-      p->tile_rows = f32_tile_rows(g, q_len, total);
-      want = f32_splits_max(g, q_len, f32_tile_rows(g, q_len, g.cap));
+      p->tile_rows = f32_tile_rows(g, q_len, total, want_parts);
+      want = f32_splits_max(g, q_len, f32_tile_rows(g, q_len, g.cap, want_parts));
       min_len = F32_SPLIT_MIN;
     } else {
       const int64_t wgs = (int64_t)g.B * g.Hkv * (g.G / flash_heads_per_workgroup(g.G)) *

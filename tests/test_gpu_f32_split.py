@@ -68,7 +68,7 @@ def test_prefill(B, Hq, Hkv, d, L, b, a, kind):
 
 @pytest.mark.parametrize("kind", ["normal", "huge", "tiny", "far"])
 @pytest.mark.parametrize("parts", [False, True])
-@pytest.mark.parametrize("Hq,Hkv,d,L,q", [(8, 2, 128, 4003, 60), (12, 4, 128, 2500, 45), (4, 2, 64, 30001, 100)])
+@pytest.mark.parametrize("Hq,Hkv,d,L,q", [(8, 2, 128, 4003, 60), (12, 4, 128, 4500, 45), (4, 2, 64, 30001, 100)])
 def test_query(Hq, Hkv, d, L, q, parts, kind):
     gen = torch.Generator(device="cuda").manual_seed(L)
     new = lambda *s: torch.randn(s, generator=gen, device="cuda")
