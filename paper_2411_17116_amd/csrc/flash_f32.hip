@@ -306,7 +306,8 @@ __device__ __forceinline__ void attend(RowState<D, NB, P>& w, f32x4* rows, const
 // parts of 8 bits, x = h + m + l, and a product the sum of the six products of parts that reach its 24 bits (what is left out is
 // below 2^-24 of it), summed in fp32, 32 products at a time where an fp32 instruction adds four.  Error against 64 bits, rms over 16 seeds,
 // fp32 products / split: prefill, 8 / 2 heads, 4099 tokens: d = 128 2.75 / 1.92e-7 (log-sum-exp 1.79 / 1.64e-7), d = 64 2.79 / 2.08e-7
-// (1.81 / 1.80e-7); 100 tokens on 4000 keys 1.78 / 1.58e-7.
+// (1.81 / 1.80e-7); 100 tokens on 4000 keys 1.78 / 1.58e-7.  With queries 2 to 16 times as large, split over fp32 products (three seeds, 2099 tokens):
+// d = 128 0.91 to 0.97 (log-sum-exp 1.00 to 1.01), d = 64 0.81 to 0.88 (0.91 to 0.99).
 // What bounds this loop is the sum of 192 MFMAs (3072 cycles) and 640 VALU instructions per 32 keys and 32 rows, two thirds of them
 // to split K and V (a dot product and an MFMA do not overlap; split with shifts and subtractions, which do, they are 960, and the
 // prefill above takes 114 us); with one row block to a wavefront (16-row tiles) that outweighs what the MFMAs save.  Tiles whose

@@ -136,19 +136,25 @@ def test_scores_that_climb_over_large_values(step, run, d, G):
         cached += n
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,d,L,b,a,lq", [
-    (1, 1, 1, 64, 1024, 256, 256, 1),       # 64 tiles: quarters of d
-    (1, 3, 3, 128, 337, 100, 33, 70),       # 66 tiles (short last blocks): halves; 15 tiles of 407 keys
-    (2, 5, 1, 128, 200, 200, 0, 3),         # 126 tiles that end between tokens: halves; two tiles of 203 keys: quarters
-    (1, 2, 2, 64, 1025, 1025, 0, 40),       # 130 tiles: whole
-    (1, 33, 1, 128, 31, 31, 0, 33),         # 64 tiles; 69 of 64 keys: halves
-    (1, 16, 4, 64, 64, 64, 7, 64),          # 64 tiles, 64 tiles
-    (1, 4, 2, 64, 1001, 250, 43, 2),        # 258 tiles: whole, short ranges
-    (1, 1, 1, 64, 2501, 625, 625, 5),       # 161 tiles: whole, long ranges
-    (1, 1, 1, 128, 2099, 300, 300, 5),      # 134 tiles: whole
+# tiles: of phase 1, and of phase 2 if that is one split.  Up to 64 share quarters of d, up to 128 halves (which the plans do not say).
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,b,a,lq,tiles", [
+    (1, 1, 1, 64, 1024, 256, 256, 1, (64, None)),       # quarters of d
+    (1, 3, 3, 128, 337, 100, 33, 70, (72, None)),       # short last blocks: halves
+    (2, 5, 1, 128, 200, 200, 0, 3, (126, 2)),           # tiles that end between tokens: halves; 203 keys: quarters
+    (1, 2, 2, 64, 1025, 1025, 0, 40, (130, None)),      # whole
+    (1, 33, 1, 128, 31, 31, 16, 33, (64, 69)),          # quarters; 64 keys: halves
+    (1, 16, 4, 64, 64, 64, 7, 64, (64, 64)),
+    (1, 4, 2, 64, 1001, 250, 43, 2, (258, None)),       # whole, short ranges
+    (1, 1, 1, 64, 2501, 625, 625, 5, (161, None)),      # whole, long ranges
+    (1, 1, 1, 128, 2099, 300, 300, 5, (133, None)),     # whole
 ])
-def test_fp32_columns_shared_by_workgroups(B, Hq, Hkv, d, L, b, a, lq):
+def test_fp32_columns_shared_by_workgroups(B, Hq, Hkv, d, L, b, a, lq, tiles):
     """Calls of few tiles, whose columns of d are computed by two or four workgroups."""
+    shape = sa.StarShape.make("fp32", B, Hq, Hkv, d, L, b, a, L + lq)
+    one, two = sa.phase1_plan(shape), sa.phase2_plan(shape, L, lq)
+    assert one.tile_rows == 16 and one.wavefronts == 8 and one.n_tiles == tiles[0]
+    assert two.tile_rows == 16 and (two.n_splits == 1) == (tiles[1] is not None)
+    assert tiles[1] in (None, B * Hkv * -(-(Hq // Hkv) * lq // 16))
     cfg = workloads.StarConfig("f32pieces", "fp32", B, Hq, Hkv, d, L, b, a, lq, 1, seed=L, n_planted=2)
     print(f"[{cfg}]", flush=True)
     rep = ph.run_parity(cfg, all_rows=True)
