@@ -305,9 +305,9 @@ __device__ __forceinline__ void attend(RowState<D, NB, P>& w, f32x4* rows, const
 // 32-row tiles take both products on the bf16 matrix instructions, which do sixteen times the work: an fp32 number is three bf16
 // parts of 8 bits, x = h + m + l, and a product the sum of the six products of parts that reach its 24 bits (what is left out is
 // below 2^-24 of it), summed in fp32, 32 products at a time where an fp32 instruction adds four.  Error against 64 bits, rms over 16 seeds,
-// fp32 products / split: prefill, 8 / 2 heads, 4099 tokens: d = 128 2.75 / 1.92e-7 (log-sum-exp 1.79 / 1.64e-7), d = 64 2.79 / 2.08e-7
-// (1.81 / 1.80e-7); 100 tokens on 4000 keys 1.78 / 1.58e-7.  With queries 2 to 16 times as large, split over fp32 products (three seeds, 2099 tokens):
-// d = 128 0.91 to 0.97 (log-sum-exp 1.00 to 1.01), d = 64 0.81 to 0.88 (0.91 to 0.99).
+// fp32 products / split: prefill, 8 / 2 heads, 4099 tokens: d = 128 2.75 / 1.84e-7 (log-sum-exp 1.79 / 1.57e-7), d = 64 2.79 / 2.08e-7
+// (1.81 / 1.80e-7); 100 tokens on 4000 keys 1.78 / 1.58e-7.  With queries 4 to 16 times as large, split over fp32 products (2099 tokens):
+// d = 128 0.78 to 0.80 (log-sum-exp 0.83 to 0.87), d = 64 0.84 to 0.88 (0.91 to 0.93).
 // What bounds this loop is the sum of 192 MFMAs (3072 cycles) and 640 VALU instructions per 32 keys and 32 rows, two thirds of them
 // to split K and V (a dot product and an MFMA do not overlap; split with shifts and subtractions, which do, they are 960, and the
 // prefill above takes 114 us); with one row block to a wavefront (16-row tiles) that outweighs what the MFMAs save.  Tiles whose
@@ -401,12 +401,11 @@ __device__ __forceinline__ void attend_split_unit(RowState<D, 2>& w, const Split
   f32x4 s[2][2];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
-    // sums of their own for large and small products; d = 64 has registers for two of the large, which keeps the rounding of a
-    // large logit below the fp32 products'
-    constexpr int CH = D == 64 ? 2 : 1;
-    f32x4 sum[2][CH], small[2], least[2];
+    // sums of their own for large and small products, and two of the large, which keeps the rounding of a large logit below the fp32
+    // products' (the ratios above; with one at d = 128 0.94 to 0.98, the log-sum-exp 1.01, and 102.7 us where two take 102.9)
+    f32x4 sum[2][2], small[2], least[2];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) sum[b][0] = sum[b][CH - 1] = small[b] = least[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < 2; ++b) sum[b][0] = sum[b][1] = small[b] = least[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < D / 32; ++t) {
       Parts k;
@@ -419,7 +418,7 @@ __device__ __forceinline__ void attend_split_unit(RowState<D, 2>& w, const Split
         ql[b] = SHARED ? shared->l[b][t][lane] : q.l[b][SHARED ? 0 : t];
       }
 #pragma unroll
-      for (int b = 0; b < 2; ++b) sum[b][t % CH] = multiply(k.h, q.h[b][t], sum[b][t % CH]);
+      for (int b = 0; b < 2; ++b) sum[b][t % 2] = multiply(k.h, q.h[b][t], sum[b][t % 2]);
 #pragma unroll
       for (int b = 0; b < 2; ++b) small[b] = multiply(k.m, q.h[b][t], small[b]);
 #pragma unroll
@@ -432,7 +431,7 @@ __device__ __forceinline__ void attend_split_unit(RowState<D, 2>& w, const Split
       for (int b = 0; b < 2; ++b) least[b] = multiply(k.h, ql[b], least[b]);
     }
 #pragma unroll
-    for (int b = 0; b < 2; ++b) s[b][c] = (CH == 1 ? sum[b][0] : sum[b][0] + sum[b][CH - 1]) + (small[b] + least[b]);
+    for (int b = 0; b < 2; ++b) s[b][c] = (sum[b][0] + sum[b][1]) + (small[b] + least[b]);
     __builtin_amdgcn_sched_barrier(0);
     if (LATE) load_v<D>(r, cur, c, lane);
     else if (MORE) load_k<D>(r, nxt, c, lane);
